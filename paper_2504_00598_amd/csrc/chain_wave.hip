@@ -1,5 +1,5 @@
-// Chunk-parallel forward pass of the chain search for 32 < K <= 64 and at most
-// 12 resharding tables (Sec. 4.4, Eq. T recurrence), one wave per search.
+// Chunk-parallel forward pass of the chain search for 32 < K <= 64 (Sec. 4.4,
+// Eq. T recurrence), one wave per search.
 //
 // Parallelism over the chain.  The recurrence is a chain of N-1 dependent
 // min-plus steps per search.  Each chain is cut into P chunks that run
@@ -19,8 +19,9 @@
 //      later step of the speculative pass is exactly the true one.
 //   3. final pass, per search: sums the offsets of the chunks; if a chunk's
 //      fix-up reached its end without meeting a checkpoint (so its successor
-//      started from a wrong row), the rest of the chain is rerun sequentially
-//      from that chunk's end row, which is the true one.  Then the lowest
+//      started from a wrong row), the next chunk is rerun from that chunk's end
+//      row, which is the true one, until it meets its own speculative rows; the
+//      fix-up results of the chunks after it then count again.  Then the lowest
 //      optimal final state and the optimum.
 // The result is the sequential recurrence's bit for bit whatever the inputs;
 // only the time depends on how fast the rows converge.
@@ -44,9 +45,9 @@
 // unavailable strategy (cost CFP_COST_INF) and a padding state (s >= K) get
 // x = 2^32 - 1 and stay capped.
 //
-// Work split of a workgroup: 16 waves, each with one search of the same chunk
-// (kWG searches per wave in general), so every wave steps through the same
-// rows and the same tables.  The packed tables of four consecutive rows
+// Work split of a workgroup: 16 waves (4 for small batches), each with one
+// search of the same chunk (kWG searches per wave in general), so every wave
+// steps through the same rows and the same tables.  The packed tables of four consecutive rows
 // (4 x 16 KiB) sit in LDS and the next four are staged while these are used
 // (double buffer, one barrier per four rows); the rows are cut into blocks of
 // 12, the period of the edge map the kernels are specialised for.
@@ -61,13 +62,9 @@ namespace cfp {
 
 namespace {
 
-// Four packed words as a native vector: copies stay in registers (a struct
-// copy of the HIP vector type goes through a private-memory temporary).
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kWSpec = 0, kWFix = 1, kWRepair = 2;
+constexpr int kWSpec = 0, kWFix = 1;
 constexpr int kWU = 12;                 // rows per block (checkpoint spacing)
-constexpr int kWWaves = 16;             // waves per workgroup of the speculative pass
+constexpr int kWWaves = 16;             // waves per workgroup on large batches
 constexpr int kWG = 1;                  // searches per wave
 constexpr int kWTable16 = 64 * 64 / 4;  // 16-byte chunks of one packed table
 constexpr int kWMaxChunks = 64;         // chunks per search (the final pass reads one per lane)
@@ -129,14 +126,7 @@ __device__ __forceinline__ uint32_t wave_min64_s(uint32_t x) {
   return __builtin_amdgcn_readlane(x, 63);
 }
 
-// Four candidates of predecessors 16k + J0 .. 16k + J0 + 3 for the wave's
-// searches: acc = min(acc, C[J0 + v] + w_v) with C the row-broadcast source of
-// the search and w the four packed table words.  Written out so that every add
-// is one instruction with a DPP operand: the compiler keeps such adds fused in
-// short functions but, in the unrolled step, leaves a separate move per add.
-// The source registers come from permlane swaps; NOP = the first block after
-// them, which waits the two states a DPP read of a fresh VALU result needs.
-#define CFP_W_ADD(T, C, W, J) "v_add_u32_dpp " T ", " C ", " W " row_newbcast:" J " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+// The same for two searches that share the table words.
 template <int J0, bool NOP>
 __device__ __forceinline__ void cand4_g2(uint32_t &a0, uint32_t &a1, uint32_t c0, uint32_t c1, const u32x4 &w) {
   uint32_t t0, t1, t2, t3;
@@ -158,36 +148,6 @@ __device__ __forceinline__ void cand4_g2(uint32_t &a0, uint32_t &a1, uint32_t c0
       : [c0] "v"(c0), [c1] "v"(c1), [wx] "v"(w.x), [wy] "v"(w.y), [wz] "v"(w.z), [ww] "v"(w.w),
         [j0] "i"(J0), [j1] "i"(J0 + 1), [j2] "i"(J0 + 2), [j3] "i"(J0 + 3), [nop] "i"(NOP ? 1 : 0));
 }
-template <int J0, bool NOP>
-__device__ __forceinline__ void cand4_g1(uint32_t &a0, uint32_t c0, const u32x4 &w) {
-  uint32_t t0, t1;
-  asm(
-      ".if %[nop]\n s_nop 2\n .endif\n"
-      CFP_W_ADD("%[t0]", "%[c0]", "%[wx]", "%[j0]")
-      CFP_W_ADD("%[t1]", "%[c0]", "%[wy]", "%[j1]")
-      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
-      CFP_W_ADD("%[t0]", "%[c0]", "%[wz]", "%[j2]")
-      CFP_W_ADD("%[t1]", "%[c0]", "%[ww]", "%[j3]")
-      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
-      : [a0] "+v"(a0), [t0] "=&v"(t0), [t1] "=&v"(t1)
-      : [c0] "v"(c0), [wx] "v"(w.x), [wy] "v"(w.y), [wz] "v"(w.z), [ww] "v"(w.w),
-        [j0] "i"(J0), [j1] "i"(J0 + 1), [j2] "i"(J0 + 2), [j3] "i"(J0 + 3), [nop] "i"(NOP ? 1 : 0));
-}
-// The first four candidates of a row: a0 is set, not updated.
-__device__ __forceinline__ void cand4_g1_first(uint32_t &a0, uint32_t c0, const u32x4 &w) {
-  uint32_t t0, t1;
-  asm(
-      "s_nop 2\n"
-      CFP_W_ADD("%[t0]", "%[c0]", "%[wx]", "0")
-      CFP_W_ADD("%[t1]", "%[c0]", "%[wy]", "1")
-      "v_min_u32 %[a0], %[t0], %[t1]\n"
-      CFP_W_ADD("%[t0]", "%[c0]", "%[wz]", "2")
-      CFP_W_ADD("%[t1]", "%[c0]", "%[ww]", "3")
-      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
-      : [a0] "=&v"(a0), [t0] "=&v"(t0), [t1] "=&v"(t1)
-      : [c0] "v"(c0), [wx] "v"(w.x), [wy] "v"(w.y), [wz] "v"(w.z), [ww] "v"(w.w));
-}
-#undef CFP_W_ADD
 
 template <int NW>
 struct WaveSmem {
@@ -213,13 +173,13 @@ struct WaveChains {
 // nvalid are real.
 //   kSpec:   the start row is row 12*blk0 from its costs alone; checkpoints are
 //            written.
-//   kRepair: the start row (row 12*blk0 - 1) is start[g].
-//   kFix:    as kRepair; at every quad end the row is compared with the
-//            speculative checkpoint of the same quad.  A search that has met
-//            it stops computing (its later speculative rows are the true ones)
-//            and the workgroup stops once all of its searches have met.
+//   kFix:    the start row (row 12*blk0 - 1) is start[g]; at every quad end
+//            from quad qmin on the row is compared with the speculative
+//            checkpoint of the same quad.  A search that has met it stops
+//            computing (its later speculative rows are the true ones) and the
+//            workgroup stops once all of its searches have met.
 template <int NW, int G, int MODE, int EP>
-__device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, int blk0, int blk1,
+__device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, int blk0, int blk1, int qmin,
                                          const uint32_t *const *start, WaveSmem<NW> &sm, WaveChains<G> &ch) {
   constexpr int U = kWU, CPT = WaveSmem<NW>::CPT;
   static_assert(G == 1 || G == 2, "one or two searches per wave");
@@ -355,7 +315,11 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     }
   };
 
-  constexpr int NPRE = 4;  // table chunks of the next row read ahead
+  // Table chunks of the next row read ahead: with one wave per SIMD (NW = 4) the
+  // whole row, issued before the current row's products, since no other wave
+  // hides the LDS latency; with four waves a few, behind the products.
+  constexpr bool EARLY = NW == 4;
+  constexpr int NPRE = EARLY ? 16 : 4;
   u32x4 wpre[NPRE];
   // One row; J = row mod 12.  GUARD: the block may end before its 12th row;
   // FIRST: the run's first block, whose rows before i0 are skipped and whose
@@ -408,8 +372,8 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     // of a row; with one (sixteen waves per workgroup) it loads them in two
     // halves, and outside the first block the first half of rows 1..3 of a
     // quad is read during the previous row's normalisation (PRE).
-    constexpr int WH = (MODE == kWSpec && G == 2) ? 16 : 8;
-    constexpr bool PRE = WH < 16 && !FIRST && u != 0;
+    constexpr int WH = ((MODE == kWSpec && G == 2) || EARLY) ? 16 : 8;
+    constexpr bool PRE = (WH < 16 || EARLY) && !FIRST && u != 0;
     u32x4 w[16];
     // Candidates of every predecessor for the searches X (and Y): two
     // searches share each table chunk read.
@@ -425,6 +389,9 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     } else {                                                                               \
       _Pragma("unroll") for (int cc_ = 0; cc_ < WH; ++cc_) w[cc_] = tb[cc_ * 64 + lane];   \
     }                                                                                      \
+    if constexpr (EARLY && !FIRST && u != 3) {                                             \
+      _Pragma("unroll") for (int cc_ = 0; cc_ < NPRE; ++cc_) wpre[cc_] = tb[kWTable16 + cc_ * 64 + lane]; \
+    }                                                                                      \
     CH(__VA_ARGS__ c0, 0) CH(__VA_ARGS__ c0, 1) CH(__VA_ARGS__ c0, 2) CH(__VA_ARGS__ c0, 3) \
     CH(__VA_ARGS__ c1, 4) CH(__VA_ARGS__ c1, 5) CH(__VA_ARGS__ c1, 6) CH(__VA_ARGS__ c1, 7) \
     if constexpr (WH < 16) {                                                               \
@@ -432,7 +399,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     }                                                                                      \
     CH(__VA_ARGS__ c2, 8) CH(__VA_ARGS__ c2, 9) CH(__VA_ARGS__ c2, 10) CH(__VA_ARGS__ c2, 11) \
     CH(__VA_ARGS__ c3, 12) CH(__VA_ARGS__ c3, 13) CH(__VA_ARGS__ c3, 14) CH(__VA_ARGS__ c3, 15) \
-    if constexpr (WH < 16 && !FIRST && u != 3) {                                           \
+    if constexpr (WH < 16 && !EARLY && !FIRST && u != 3) {                                           \
       _Pragma("unroll") for (int cc_ = 0; cc_ < NPRE; ++cc_) wpre[cc_] = tb[kWTable16 + cc_ * 64 + lane]; \
     }                                                                                      \
   }
@@ -475,7 +442,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
         CFP_Q4(CFP_QSTORE)
       }
       if (MODE == kWFix) {
-        if (ch.conv[0] < 0 && __ballot(ch.qv[0] != ckv[0]) == 0) {
+        if (ch.conv[0] < 0 && (i >> 2) >= qmin && __ballot(ch.qv[0] != ckv[0]) == 0) {
           ch.conv[0] = i >> 2;
           ch.dconv[0] = ch.dsum[0];
           endr[0] = i;
@@ -529,16 +496,16 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
   if (blk < blk1 && !(MODE == kWFix && stop)) block(std::true_type{}, std::false_type{}, blk);
 }
 
-// Speculative pass, grid (ceil(B/16), P).
-template <int EP>
-__global__ __launch_bounds__(64 * kWWaves) void chain_wave_kernel(WaveArgs a) {
-  __shared__ __align__(16) WaveSmem<kWWaves> sm;
+// Speculative pass, grid (ceil(B/NW), P).
+template <int EP, int NW>
+__global__ __launch_bounds__(64 * NW) void chain_wave_kernel(WaveArgs a) {
+  __shared__ __align__(16) WaveSmem<NW> sm;
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int bw = blockIdx.x * kWWaves * kWG + wid * kWG;
+  const int bw = blockIdx.x * NW * kWG + wid * kWG;
   const int p = blockIdx.y;
   const int blk0 = p * a.CB, blk1 = min(blk0 + a.CB, a.nblk);
   WaveChains<kWG> ch;
-  wave_run<kWWaves, kWG, kWSpec, EP>(a, bw, kWG, blk0, blk1, nullptr, sm, ch);
+  wave_run<NW, kWG, kWSpec, EP>(a, bw, kWG, blk0, blk1, 0, nullptr, sm, ch);
 #pragma unroll
   for (int g = 0; g < kWG; ++g) {
     if (__ballot((int32_t)ch.cor[g] < 0)) ch.flags[g] |= 1;  // wave-uniform
@@ -547,23 +514,22 @@ __global__ __launch_bounds__(64 * kWWaves) void chain_wave_kernel(WaveArgs a) {
   }
 }
 
-// Fix-up pass, grid (ceil(B/16), P-1): the sixteen searches of a workgroup
-// rerun chunk p >= 1 from the last checkpoint row of chunk p-1 (their true row
+// Fix-up pass, grid (ceil(B/NW), P-1): the searches of a workgroup rerun chunk p >= 1 from the last checkpoint row of chunk p-1 (their true row
 // once chunk p-1 has met) until each row equals chunk p's checkpoint at a quad
-// end; the tables are staged once per quad for all sixteen, a search that has
+// end; the tables are staged once per quad for all of them, a search that has
 // met stops computing, and the workgroup stops when all have met.
-template <int EP>
-__global__ __launch_bounds__(64 * kWWaves) void chain_wave_fix_kernel(WaveArgs a) {
-  __shared__ __align__(16) WaveSmem<kWWaves> sm;
+template <int EP, int NW>
+__global__ __launch_bounds__(64 * NW) void chain_wave_fix_kernel(WaveArgs a) {
+  __shared__ __align__(16) WaveSmem<NW> sm;
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int bw = blockIdx.x * kWWaves + wid;  // one search per wave
+  const int bw = blockIdx.x * NW + wid;  // one search per wave
   const int p = blockIdx.y + 1;
   const int blk0 = p * a.CB, blk1 = min(blk0 + a.CB, a.nblk);
   const int i0 = blk0 * kWU;  // a multiple of 4
   const int b = min(bw, a.B - 1);
   const uint32_t *start[1] = {a.ckrow + ((size_t)b * a.nq + (i0 / 4 - 1)) * 64};
   WaveChains<1> ch;
-  wave_run<kWWaves, 1, kWFix, EP>(a, bw, 1, blk0, blk1, start, sm, ch);
+  wave_run<NW, 1, kWFix, EP>(a, bw, 1, blk0, blk1, 0, start, sm, ch);
   if (bw >= a.B) return;
   if (ch.conv[0] < 0) a.endrow[((size_t)bw * a.P + p) * 64 + lane] = ch.qv[0];
   if (lane == 0) {
@@ -584,53 +550,81 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
                                                                                 int64_t *__restrict__ opt,
                                                                                 int32_t *__restrict__ status) {
   __shared__ __align__(16) WaveSmem<kWFinalWaves> sm;
+  __shared__ uint32_t s_row[64];  // the true end row of the last chunk accounted
   __shared__ int s_q, s_flags;
-  __shared__ int64_t s_dtot;
+  __shared__ int64_t s_sum;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int b = blockIdx.x, P = a.P;
-
+  const int64_t *dk = a.dck + (size_t)b * a.nq;
+  const WaveRec *rec = a.rec + (size_t)b * P;
+  auto endq = [&](int p) __attribute__((always_inline)) { return (min((p + 1) * a.CB * kWU, a.N) - 1) >> 2; };
   if (wid == 0) {
-    const bool in = lane < P;
-    WaveRec r{};
-    if (in) r = a.rec[(size_t)b * P + lane];
-    const int endq = (min((lane + 1) * a.CB * kWU, a.N) - 1) >> 2;  // quad of the chunk's last row
-    const uint64_t nc = __ballot(in && lane >= 1 && r.conv < 0);
-    const int q = nc ? __ffsll((long long)nc) - 1 : P;  // first chunk whose fix-up met no checkpoint
-    int64_t delta = 0;
-    if (in && lane < q) {
-      const int64_t *dk = a.dck + (size_t)b * a.nq;
-      delta = lane == 0 ? dk[endq] : r.dfix + dk[endq] - dk[r.conv];
-    } else if (lane == q) {
-      delta = r.dfix;  // its fix-up started from the true row and ran to the end
-    }
-    int fl = in ? r.flags : 0;
+    int fl = lane < P ? rec[lane].flags : 0;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      delta += __shfl_xor(delta, off, 64);
-      fl |= __shfl_xor(fl, off, 64);
-    }
-    if (lane == 0) {
-      s_q = q;
-      s_dtot = delta;
-      s_flags = fl;
+    for (int off = 32; off >= 1; off >>= 1) fl |= __shfl_xor(fl, off, 64);
+    if (lane == 0) s_flags = fl;
+  }
+  // Chunk 0 runs from the true first row.  At the top of the loop the chunks
+  // below p are accounted in `total`; with spec_true the speculative end row of
+  // chunk p-1 is its true one (so the fix-up of chunk p is valid), otherwise
+  // s_row holds the true end row of chunk p-1.
+  int64_t total = dk[endq(0)];
+  bool spec_true = true;
+  int p = 1;
+  while (p < P) {
+    if (spec_true) {
+      // The first chunk q >= p whose fix-up met no checkpoint, and the offsets
+      // of chunks p .. q (chunk q's fix-up ran from a true row to its end).
+      if (wid == 0) {
+        const int pl = p + lane;
+        const bool in = pl < P;
+        WaveRec r{};
+        if (in) r = rec[pl];
+        const uint64_t nc = __ballot(in && r.conv < 0);
+        const int q = nc ? p + __ffsll((long long)nc) - 1 : P;
+        int64_t delta = 0;
+        if (in && pl < q) delta = r.dfix + dk[endq(pl)] - dk[r.conv];
+        else if (in && pl == q) delta = r.dfix;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) delta += __shfl_xor(delta, off, 64);
+        if (lane == 0) {
+          s_q = q;
+          s_sum = delta;
+        }
+      }
+      __syncthreads();
+      const int q = s_q;
+      total += s_sum;
+      if (q >= P) break;
+      if (wid == 0) s_row[lane] = a.endrow[((size_t)b * P + q) * 64 + lane];
+      spec_true = false;
+      p = q + 1;
+      __syncthreads();
+    } else {
+      // Rerun chunk p (wave 0; the others stage) at least over the rows its
+      // fix-up rewrote from a wrong start.
+      const uint32_t *start[1] = {s_row};
+      WaveChains<1> ch;
+      const int qmin = rec[p].conv < 0 ? endq(p) : rec[p].conv;
+      wave_run<kWFinalWaves, 1, kWFix, EP>(a, b, wid == 0 ? 1 : 0, p * a.CB, min((p + 1) * a.CB, a.nblk), qmin, start,
+                                           sm, ch);
+      __syncthreads();  // every wave has read s_row and the last tables
+      if (wid == 0) {
+        const bool met = ch.conv[0] >= 0;
+        if (lane == 0) {
+          s_q = met;
+          s_sum = met ? (int64_t)ch.dconv[0] + dk[endq(p)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
+        }
+        s_row[lane] = ch.qv[0];
+      }
+      __syncthreads();
+      total += s_sum;
+      spec_true = s_q != 0;
+      ++p;
+      __syncthreads();  // s_q is rewritten at the top of the loop
     }
   }
-  __syncthreads();
-  const int q = s_q;
-  uint64_t drep = 0;
-  uint32_t qv;
-  if (q < P - 1) {
-    // Rerun the chain after chunk q from its end row (wave 0; the others stage).
-    const uint32_t *start[1] = {a.endrow + ((size_t)b * P + q) * 64};
-    WaveChains<1> ch;
-    wave_run<kWFinalWaves, 1, kWRepair, EP>(a, b, wid == 0 ? 1 : 0, (q + 1) * a.CB, a.nblk, start, sm, ch);
-    qv = ch.qv[0];
-    drep = ch.dsum[0];
-  } else if (q == P - 1) {
-    qv = a.endrow[((size_t)b * P + q) * 64 + lane];
-  } else {
-    qv = a.ckrow[((size_t)b * a.nq + a.nq - 1) * 64 + lane];
-  }
+  const uint32_t qv = spec_true ? a.ckrow[((size_t)b * a.nq + a.nq - 1) * 64 + lane] : s_row[lane];
   if (wid != 0) return;
   // The final row has minimum 0: the lowest state at the minimum.
   const uint32_t pk = wave_min(lane < a.K ? (qv | (uint32_t)lane) : kSat);
@@ -641,7 +635,7 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
     else if (fl & 2) st = CFP_ST_INFEASIBLE;
     else if ((pk >> kWBits) != 0) st = CFP_ST_OVERFLOW;
     status[b] = st;
-    opt[b] = st == CFP_ST_OK ? s_dtot + (int64_t)drep : INT64_MAX;
+    opt[b] = st == CFP_ST_OK ? total : INT64_MAX;
     res[b].final_state = st == CFP_ST_OK ? (int32_t)(pk & 63u) : -1;
     res[b].status = st;
     res[b].final_m = 0;
@@ -650,31 +644,40 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
 
 struct WavePlan {
   int P, CB, nblk, nq;
+  int NW;  // waves (searches) per workgroup
 };
 
+// Workgroups of four waves (one search per SIMD) while the batch's chunks fit
+// the chip with them: a row then takes about 0.5 us where sixteen searches on
+// four SIMDs take 1.1 us, whether they exist or repeat the last one (1152
+// blocks, K = 64: one search 88 -> 70 us per call, 16 searches 109 -> 78 us).
+// A chain too short for two chunks goes to the register-resident kernel when
+// its tables fit there (0.32 us per row), else runs here as one chunk.
 WavePlan wave_plan(int n, int k, int e, int batch) {
-  WavePlan c{0, 0, 0, 0};
-  if (k <= 32 || k > 64 || e > kResTables) return c;
+  WavePlan c{0, 0, 0, 0, 0};
+  if (k <= 32 || k > 64) return c;
   c.nblk = (n + kWU - 1) / kWU;
   c.nq = (n + 3) / 4;
-  const int rows = (batch + kWWaves * kWG - 1) / (kWWaves * kWG);
+  c.NW = (batch + 3) / 4 * std::min(kWMaxChunks, c.nblk / kWMinBlocks) <= 256 ? 4 : kWWaves;
+  const int rows = (batch + c.NW - 1) / c.NW;
   int P = std::max(1, 256 / rows);  // one workgroup per compute unit
   P = std::min(P, std::min(kWMaxChunks, c.nblk / kWMinBlocks));
-  if (P < 2) return WavePlan{0, 0, 0, 0};
+  if (P < 2 && e <= kResTables) return WavePlan{0, 0, 0, 0, 0};
+  P = std::max(P, 1);
   c.CB = (c.nblk + P - 1) / P;
   c.P = (c.nblk + c.CB - 1) / c.CB;
   return c;
 }
 
-template <int EP>
+template <int EP, int NW>
 static void launch_wave_passes(const WaveArgs &a, const WsHeader *hdr, SearchResult *res, int64_t *opt,
                                int32_t *status, hipStream_t st) {
-  const int rows = (a.B + kWWaves * kWG - 1) / (kWWaves * kWG);
+  const int rows = (a.B + NW - 1) / NW;
   timer_begin(st);
-  timed_launch(chain_wave_kernel<EP>, dim3(rows, a.P), dim3(64 * kWWaves), 0, st, a);
+  timed_launch(chain_wave_kernel<EP, NW>, dim3(rows, a.P), dim3(64 * NW), 0, st, a);
   timer_end(st);
-  hipLaunchKernelGGL((chain_wave_fix_kernel<EP>), dim3((a.B + kWWaves - 1) / kWWaves, a.P - 1), dim3(64 * kWWaves), 0,
-                     st, a);
+  if (a.P > 1)
+    hipLaunchKernelGGL((chain_wave_fix_kernel<EP, NW>), dim3(rows, a.P - 1), dim3(64 * NW), 0, st, a);
   hipLaunchKernelGGL((chain_wave_final_kernel<EP>), dim3(a.B), dim3(64 * kWFinalWaves), 0, st, a, hdr, res, opt,
                      status);
 }
@@ -715,11 +718,11 @@ bool chain_wave_headerless(const cfp_chain_desc &d) {
   return wave_edge_period(d.redge, d.n_blocks, d.n_tables) == 12;
 }
 
-bool chain_wave_supported(int n, int k, int e, int batch) { return wave_plan(n, k, e, batch).P >= 2; }
+bool chain_wave_supported(int n, int k, int e, int batch) { return wave_plan(n, k, e, batch).P >= 1; }
 
 size_t wave_region_bytes(int n, int k, int e, int batch) {
   const WavePlan c = wave_plan(n, k, e, batch);
-  if (c.P < 2) return 0;
+  if (c.P < 1) return 0;
   size_t off = align_up((size_t)e * 64 * 64 * 4);
   off += align_up((size_t)batch * c.P * sizeof(WaveRec));
   off += align_up((size_t)batch * c.nq * 8);
@@ -758,8 +761,14 @@ hipError_t launch_chain_wave(const cfp_chain_desc &d, const int32_t *redge_dev, 
   a.seq = next_call_number();
   hipLaunchKernelGGL(wave_pack_kernel, dim3(std::min(1024, d.n_tables * 16)), dim3(256), 0, st, d.rtab, d.n_tables,
                      d.k, rpk, cfp_r_limit(CFP_V_CHAIN, d.k), const_cast<WsHeader *>(hdr), a.seq);
-  if (wave_edge_period(d.redge, d.n_blocks, d.n_tables) == 12) launch_wave_passes<12>(a, hdr, res, opt, status, st);
-  else launch_wave_passes<0>(a, hdr, res, opt, status, st);
+  const bool periodic = chain_wave_headerless(d);
+  if (c.NW == 4) {
+    if (periodic) launch_wave_passes<12, 4>(a, hdr, res, opt, status, st);
+    else launch_wave_passes<0, 4>(a, hdr, res, opt, status, st);
+  } else {
+    if (periodic) launch_wave_passes<12, kWWaves>(a, hdr, res, opt, status, st);
+    else launch_wave_passes<0, kWWaves>(a, hdr, res, opt, status, st);
+  }
   return hipGetLastError();
 }
 

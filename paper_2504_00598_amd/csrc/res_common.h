@@ -11,6 +11,10 @@ namespace cfp {
 constexpr int kResTables = 12;  // resharding tables kept in registers
 constexpr int kUnroll = 12;     // steps per unrolled group = cost rows per staging block
 
+// Four packed words as a native vector: copies stay in registers (a struct
+// copy of the HIP vector type goes through a private-memory temporary).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // DPP helpers (gfx9 encodings).
 constexpr int kQuadSwap1 = 0xB1;   // quad_perm [1,0,3,2]
 constexpr int kQuadSwap2 = 0x4E;   // quad_perm [2,3,0,1]
@@ -45,6 +49,44 @@ __device__ __forceinline__ int32_t group_min_i32(int32_t x) {
   if (N >= 8) x = dpp_min_i32<kHalfMirror>(x);
   if (N >= 16) x = dpp_min_i32<kMirror>(x);
   return x;
+}
+
+// Four candidates of predecessors 16k + J0 .. 16k + J0 + 3: acc = min(acc,
+// C[J0 + v] + w_v) with C the row-broadcast source and w the four packed table
+// words.  Written out so that every add is one instruction with a DPP operand:
+// the compiler keeps such adds fused in short functions but, in an unrolled
+// step, leaves a separate move per add.  NOP = the first block after the
+// source register was written, which waits the two states a DPP read of a
+// fresh VALU result needs.
+#define CFP_W_ADD(T, C, W, J) "v_add_u32_dpp " T ", " C ", " W " row_newbcast:" J " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+template <int J0, bool NOP>
+__device__ __forceinline__ void cand4_g1(uint32_t &a0, uint32_t c0, const u32x4 &w) {
+  uint32_t t0, t1;
+  asm(
+      ".if %[nop]\n s_nop 2\n .endif\n"
+      CFP_W_ADD("%[t0]", "%[c0]", "%[wx]", "%[j0]")
+      CFP_W_ADD("%[t1]", "%[c0]", "%[wy]", "%[j1]")
+      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
+      CFP_W_ADD("%[t0]", "%[c0]", "%[wz]", "%[j2]")
+      CFP_W_ADD("%[t1]", "%[c0]", "%[ww]", "%[j3]")
+      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
+      : [a0] "+v"(a0), [t0] "=&v"(t0), [t1] "=&v"(t1)
+      : [c0] "v"(c0), [wx] "v"(w.x), [wy] "v"(w.y), [wz] "v"(w.z), [ww] "v"(w.w),
+        [j0] "i"(J0), [j1] "i"(J0 + 1), [j2] "i"(J0 + 2), [j3] "i"(J0 + 3), [nop] "i"(NOP ? 1 : 0));
+}
+// The first four candidates of a row: a0 is set, not updated.
+__device__ __forceinline__ void cand4_g1_first(uint32_t &a0, uint32_t c0, const u32x4 &w) {
+  uint32_t t0, t1;
+  asm(
+      "s_nop 2\n"
+      CFP_W_ADD("%[t0]", "%[c0]", "%[wx]", "0")
+      CFP_W_ADD("%[t1]", "%[c0]", "%[wy]", "1")
+      "v_min_u32 %[a0], %[t0], %[t1]\n"
+      CFP_W_ADD("%[t0]", "%[c0]", "%[wz]", "2")
+      CFP_W_ADD("%[t1]", "%[c0]", "%[ww]", "3")
+      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
+      : [a0] "=&v"(a0), [t0] "=&v"(t0), [t1] "=&v"(t1)
+      : [c0] "v"(c0), [wx] "v"(w.x), [wy] "v"(w.y), [wz] "v"(w.z), [ww] "v"(w.w));
 }
 
 // Cost rows of one search staged through LDS in blocks of kUnroll rows.

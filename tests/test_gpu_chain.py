@@ -534,3 +534,31 @@ def test_chunked_k512_ties_and_statuses():
     opt, st, plan = run_chain(cost, rtab, redge)
     assert st[4] == CFP_ST_BADINPUT and opt[4] == np.iinfo(np.int64).max and (plan[4] == -1).all()
     assert st[2] != 0 and (st[[0, 1, 3]] == 0).all()
+
+
+@pytest.mark.parametrize("N,K,B,E", [(1, 40, 2, 13), (3, 64, 5, 13), (47, 64, 1, 13), (84, 50, 17, 20),
+                                     (500, 33, 17, 30), (400, 64, 70, 24)])
+def test_chunked_many_tables(N, K, B, E):
+    """More tables than the register-resident kernel holds: chains of one chunk and of
+    several, four and sixteen searches per workgroup, ragged batches and blocks."""
+    need_gpu()
+    cost, rtab, redge = rand_case([60, N, K, B, E], B, N, K, E, 0, 1_000_000, inf_frac=0.05)
+    say("chunked, many tables", N, K, B, E)
+    assert_chain_parity(cost, rtab, redge, f"many tables N={N} K={K} B={B} E={E}")
+
+
+@pytest.mark.parametrize("seed", range(3))
+def test_chunked_some_chunks_meet_small_batch(seed):
+    """Seeded patterns of chunks that do and do not meet with four searches per workgroup:
+    the final pass reruns the chunks behind those that do not, up to where they meet."""
+    need_gpu()
+    from paper_2504_00598_amd import cfp_r_limit
+    rs = np.random.default_rng([61, seed])
+    K, B, N = 64, 6, 900
+    cost = rs.integers(0, 1000, size=(B, N, K)).astype(np.int32)
+    rtab = _no_switch_tables(rs, 3, K, cfp_r_limit(0, K))
+    rtab[2] = 0
+    redge = rs.integers(0, 2, size=N).astype(np.int32)
+    redge[rs.choice(np.arange(1, N), size=int(rs.integers(2, 12)), replace=False)] = 2
+    say("chunked, partial convergence, small batch", seed)
+    assert_chain_parity(cost, rtab, redge, f"partial small seed={seed}")
