@@ -46,7 +46,10 @@ WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables) {
     L.split = off;
     off = align_up(off + split_region_bytes(k, batch));
   }
-  if (variant == CFP_V_CHAIN && chain_wave_supported(n, k, n_tables, batch)) {
+  if (variant == CFP_V_CHAIN && chain_narrow_supported(n, k, n_tables)) {
+    L.narrow = off;
+    off = align_up(off + narrow_region_bytes(n, k, n_tables, batch));
+  } else if (variant == CFP_V_CHAIN && chain_wave_supported(n, k, n_tables, batch)) {
     L.wave = off;
     off = align_up(off + wave_region_bytes(n, k, n_tables, batch));
   }
@@ -260,11 +263,25 @@ int put_header(const cfp_chain_desc *d, const WsLayout &L, uint8_t *w, hipStream
   return CFP_OK;
 }
 
+// Whether a chain forward call reads nothing of the header and the uploaded
+// edge map (the K <= 64 paths with a periodic edge map, which flag range errors
+// in R by themselves): a host-to-device copy costs several microseconds of GPU
+// time.
+bool chain_headerless(const cfp_chain_desc *d) {
+  if (chain_narrow_supported(d->n_blocks, d->k, d->n_tables)) return chain_narrow_headerless(*d);
+  return chain_wave_supported(d->n_blocks, d->k, d->n_tables, d->batch) && chain_wave_headerless(*d);
+}
+
 // The launches of a chain forward call once the header and the edge map are
-// in the workspace (or not needed: the periodic chunk-parallel K <= 64 path).
+// in the workspace (or not needed: chain_headerless).
 int dp_chain_launch(const cfp_chain_desc *d, const WsLayout &L, uint8_t *w, int64_t *opt, int32_t *status,
                     hipStream_t st) {
   WsHeader *hdr = (WsHeader *)w;
+  if (chain_narrow_supported(d->n_blocks, d->k, d->n_tables))
+    return launch_chain_narrow(*d, (const int32_t *)(w + L.redge), w + L.narrow, w + L.table,
+                               (SearchResult *)(w + L.result), opt, status, st) == hipSuccess
+               ? CFP_OK
+               : CFP_ERR_HIP;
   const bool wave = chain_wave_supported(d->n_blocks, d->k, d->n_tables, d->batch);
   const bool cw = !wave && chain_cw_supported(d->n_blocks, d->k, d->batch);
   if (!wave && !cw &&
@@ -325,12 +342,7 @@ int cfp_dp_chain(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t *op
   WsLayout L = layout(CFP_V_CHAIN, d->n_blocks, d->k, d->batch, 0, d->n_tables);
   if (!ws || ws_bytes < L.total) return CFP_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  // The chunk-parallel paths check the range of R while packing it; the K <= 64
-  // one with a periodic edge map reads nothing of the header, which is then not
-  // uploaded (a host-to-device copy costs several microseconds of GPU time).
-  const bool wave = chain_wave_supported(d->n_blocks, d->k, d->n_tables, d->batch);
-  if (!(wave && chain_wave_headerless(*d)) && (rc = upload_header(d, CFP_V_CHAIN, 0, L, ws, st)) != CFP_OK)
-    return rc;
+  if (!chain_headerless(d) && (rc = upload_header(d, CFP_V_CHAIN, 0, L, ws, st)) != CFP_OK) return rc;
   return dp_chain_launch(d, L, (uint8_t *)ws, opt, status, st);
 }
 
@@ -441,8 +453,8 @@ int cfp_search_chain_noalloc(const cfp_chain_desc *d, int64_t *opt, int32_t *sta
   if (!w) return CFP_ERR_HIP;
   hipStream_t st = (hipStream_t)stream;
   // Every region the kernels read is written earlier in the same call; the
-  // header (range flags included) is rewritten whole.
-  if ((rc = put_header(d, L, w, st)) != CFP_OK) return rc;
+  // header (range flags included), where it is read, is rewritten whole.
+  if (!chain_headerless(d) && (rc = put_header(d, L, w, st)) != CFP_OK) return rc;
   if ((rc = dp_chain_launch(d, L, w, opt, status, st)) != CFP_OK) return rc;
   const hipError_t e = launch_traceback_chain(d->n_blocks, d->k, d->batch, L.elem, w + L.table,
                                               (const SearchResult *)(w + L.result), (uint16_t *)(w + L.maps),

@@ -57,6 +57,7 @@ struct WsLayout {
   size_t bounds = 0;   // traceback chunk boundary states int32 [B][nchunks]
   size_t wide = 0;     // chain variant, K > 64: packed tables and cost-row minima
   size_t split = 0;    // chain variant, K > 64: exchange slots and flags of the split kernel
+  size_t narrow = 0;   // chain variant, K <= 32: chunk records, checkpoints
   size_t wave = 0;     // chain variant, 32 < K <= 64 on long chains: packed tables, chunk records, checkpoints
   size_t cw = 0;       // chain variant, 128 < K <= 256 on long chains: packed tables, chunk records, checkpoints
   size_t seg = 0;      // segment variant, small batches: speculative rows, running sums, chunk records
@@ -84,6 +85,13 @@ hipError_t launch_seg_fwd(const cfp_segment_desc &d, const int32_t *redge_dev, u
 hipError_t launch_chain_fwd(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table, int elem,
                             uint8_t *wide, SearchResult *res, const WsHeader *hdr, int64_t *opt,
                             int32_t *status, hipStream_t st);
+// Chain forward for K <= 32, tables in LDS; headerless: a periodic edge map
+// travels in the launch arguments, so nothing of the header is read.
+bool chain_narrow_supported(int n, int k, int n_tables);
+bool chain_narrow_headerless(const cfp_chain_desc &d);
+size_t narrow_region_bytes(int n, int k, int n_tables, int batch);
+hipError_t launch_chain_narrow(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
+                               SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
 bool chain_wave_supported(int n, int k, int n_tables, int batch);
 size_t wave_region_bytes(int n, int k, int n_tables, int batch);
 // True when the chunk-parallel K <= 64 path reads nothing of the uploaded
@@ -116,8 +124,8 @@ size_t wide_region_bytes(int n, int k, int batch, int n_tables);
 hipError_t launch_chain_fwd_wide(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
                                  SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,
                                  hipStream_t st);
-bool chain_fwd_res_supported(int k, int n_tables);
-hipError_t launch_chain_fwd_res(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table, SearchResult *res,
+bool chain_fwd_k64_supported(int k, int n_tables);
+hipError_t launch_chain_fwd_k64(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table, SearchResult *res,
                                 const WsHeader *hdr, int64_t *opt, int32_t *status, hipStream_t st);
 hipError_t launch_chain_fwd_generic(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table,
                                     SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,

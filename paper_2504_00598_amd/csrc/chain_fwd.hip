@@ -184,9 +184,9 @@ hipError_t launch_chain_fwd(const cfp_chain_desc &d, const int32_t *redge_dev, u
                             uint8_t *wide, SearchResult *res, const WsHeader *hdr, int64_t *opt,
                             int32_t *status, hipStream_t st) {
   (void)elem;
-  if (chain_fwd_res_supported(d.k, d.n_tables)) {
+  if (chain_fwd_k64_supported(d.k, d.n_tables)) {
     timer_begin(st);
-    const hipError_t e = launch_chain_fwd_res(d, redge_dev, table, res, hdr, opt, status, st);
+    const hipError_t e = launch_chain_fwd_k64(d, redge_dev, table, res, hdr, opt, status, st);
     timer_end(st);
     return e;
   }

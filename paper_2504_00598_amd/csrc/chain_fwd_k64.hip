@@ -13,8 +13,12 @@
 //   3. every lane combines the partials of the state it holds next and forms
 //      the new word of that state itself, so the row never has to be
 //      redistributed.
-// Normalisation is one step behind (see the K <= 32 kernel):
-//     Q_i[s] = min(D[i][s] - o_i, qcap) << 6,  o_i = rowmin_{i-1} + min_s c[i][s].
+// Normalisation is one step behind: the row written at step i is
+//     Q_i[s] = min(D[i][s] - o_i, qcap) << 6,  o_i = rowmin_{i-1} + min_s c[i][s],
+// which each wave can form before the minimum of row i is known.  With v the
+// cheapest strategy of block i, D[i][v] - o_i <= R_max, so the best candidate
+// of every state at step i+1 is at most 2 R_max.  In int64, opt = sum_i min_s
+// c[i][s] + sum_i (rowmin_i - o_i).
 // The adds are not saturating (DPP has no clamp form), so the value field is
 // capped at qcap = 2^25 - 1 and R < 2^24: Q + RP < 2^32 never wraps, the best
 // candidate (at most 2 R_max) is exact, and any state at the cap exceeds
@@ -176,9 +180,20 @@ static void launch_k64_ep(const cfp_chain_desc &d, const int32_t *redge_dev, uin
                      d.n_blocks, d.k, d.n_tables, table, res, hdr, opt, status);
 }
 
-void launch_chain_fwd_k64(const cfp_chain_desc &d, int period, const int32_t *redge_dev, uint8_t *table,
-                          SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status, hipStream_t st) {
-  switch (period) {
+bool chain_fwd_k64_supported(int k, int e) { return k > 32 && k <= 64 && e <= kResTables; }
+
+// Period of the edge map if redge[i] == i mod E for all i >= 1 with E
+// dividing the unroll, else 0.
+static int edge_period(const int32_t *redge, int n, int e) {
+  if (kUnroll % e != 0) return 0;
+  for (int i = 1; i < n; ++i)
+    if (redge[i] != i % e) return 0;
+  return e;
+}
+
+hipError_t launch_chain_fwd_k64(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table, SearchResult *res,
+                                const WsHeader *hdr, int64_t *opt, int32_t *status, hipStream_t st) {
+  switch (edge_period(d.redge, d.n_blocks, d.n_tables)) {
     case 1: launch_k64_ep<1>(d, redge_dev, table, res, hdr, opt, status, st); break;
     case 2: launch_k64_ep<2>(d, redge_dev, table, res, hdr, opt, status, st); break;
     case 3: launch_k64_ep<3>(d, redge_dev, table, res, hdr, opt, status, st); break;
@@ -187,6 +202,7 @@ void launch_chain_fwd_k64(const cfp_chain_desc &d, int period, const int32_t *re
     case 12: launch_k64_ep<12>(d, redge_dev, table, res, hdr, opt, status, st); break;
     default: launch_k64_ep<0>(d, redge_dev, table, res, hdr, opt, status, st); break;
   }
+  return hipGetLastError();
 }
 
 }  // namespace cfp

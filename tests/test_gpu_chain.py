@@ -562,3 +562,89 @@ def test_chunked_some_chunks_meet_small_batch(seed):
     redge[rs.choice(np.arange(1, N), size=int(rs.integers(2, 12)), replace=False)] = 2
     say("chunked, partial convergence, small batch", seed)
     assert_chain_parity(cost, rtab, redge, f"partial small seed={seed}")
+
+
+# K <= 32 runs with every table in LDS, chunk-parallel on long chains; a task (a chunk of
+# one search) takes 16 or 32 lanes of a wave.
+
+@pytest.mark.parametrize("N,K,B,E", [(1, 1, 1, 1), (2, 16, 5, 1), (3, 17, 3, 2), (5, 32, 9, 3), (47, 16, 4, 12),
+                                     (48, 16, 4, 12), (49, 15, 7, 5), (63, 32, 2, 12), (64, 32, 2, 12),
+                                     (65, 31, 1, 12), (97, 17, 33, 38), (97, 20, 3, 39), (1001, 2, 3, 4),
+                                     (1000, 32, 3, 24), (203, 16, 3, 152), (64, 9, 4100, 2)])
+@pytest.mark.parametrize("edges", ["random", "periodic"])
+def test_narrow_shapes(N, K, B, E, edges):
+    """Remainders of quads and chunks, ragged waves, tables up to and past the LDS limit
+    (38 at K > 16), four and sixteen waves per workgroup, edge maps in memory and in the
+    arguments."""
+    need_gpu()
+    cost, rtab, redge = rand_case([62, N, K, B, E], B, N, K, E, 0, 1_000_000, inf_frac=0.05)
+    if edges == "periodic":
+        redge = (np.arange(N) % E).astype(np.int32)
+    say("narrow shape", N, K, B, E, edges)
+    assert_chain_parity(cost, rtab, redge, f"narrow N={N} K={K} B={B} E={E} {edges}")
+
+
+@pytest.mark.parametrize("period", [1, 5, 24, 33, 64, 65])
+def test_narrow_edge_periods(period):
+    """Edge maps that repeat with a period up to and past the longest one carried in the
+    arguments; entry 0 (unused) breaks the pattern."""
+    need_gpu()
+    rs = np.random.default_rng([63, period])
+    N, K, E, B = 331, 12, 9, 3
+    cost, rtab, _ = rand_case([64, period], B, N, K, E, 0, 10_000)
+    redge = np.resize(rs.integers(0, E, size=period), N).astype(np.int32)
+    redge[0] = (redge[0] + 1) % E
+    say("narrow edge period", period)
+    assert_chain_parity(cost, rtab, redge, f"period {period}")
+
+
+@pytest.mark.parametrize("K,B", [(32, 3), (27, 40), (16, 5), (3, 70)])
+def test_narrow_rows_never_meet(K, B):
+    """Every chunk misses its checkpoints: the final pass reruns the chains; largest R."""
+    need_gpu()
+    from paper_2504_00598_amd import cfp_r_limit
+    rs = np.random.default_rng([65, K, B])
+    N = 600
+    cost = rs.integers(0, 50, size=(B, N, K)).astype(np.int32)
+    rtab = _no_switch_tables(rs, 12, K, cfp_r_limit(0, K))
+    redge = (np.arange(N) % 12).astype(np.int32)
+    say("narrow, no convergence", K, B)
+    assert_chain_parity(cost, rtab, redge, f"narrow never meet K={K} B={B}")
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_narrow_some_chunks_meet(seed):
+    """Zero tables on a few edges make some chunks meet and others not, in a seeded
+    pattern, with more chunks than a wave has lanes."""
+    need_gpu()
+    from paper_2504_00598_amd import cfp_r_limit
+    rs = np.random.default_rng([66, seed])
+    K, B, N = (16, 32)[seed % 2], 6, 2500
+    cost = rs.integers(0, 1000, size=(B, N, K)).astype(np.int32)
+    rtab = _no_switch_tables(rs, 3, K, cfp_r_limit(0, K))
+    rtab[2] = 0
+    redge = rs.integers(0, 2, size=N).astype(np.int32)
+    redge[rs.choice(np.arange(1, N), size=int(rs.integers(2, 30)), replace=False)] = 2
+    say("narrow, partial convergence", seed)
+    assert_chain_parity(cost, rtab, redge, f"narrow partial seed={seed}")
+
+
+@pytest.mark.parametrize("N,K", [(40, 16), (40, 32), (300, 9), (300, 30)])
+def test_narrow_ties_and_statuses(N, K):
+    """Tie-heavy values, unavailable strategies, an infeasible search, costs 0 and 2^31 - 2
+    in one row, a negative cost and an R out of range, on chains of one chunk and several."""
+    need_gpu()
+    from paper_2504_00598_amd import CFP_ST_BADINPUT, cfp_r_limit
+    cost, rtab, redge = rand_case([67, N, K], 70, N, K, 5, 0, 3, inf_frac=0.1)
+    cost[:, :, 0] = np.where(cost[:, :, 0] == INF, 1, cost[:, :, 0])
+    cost[5, N - 7, :] = INF
+    cost[6, N // 2, 1:] = 2 ** 31 - 2
+    say("narrow statuses", N, K)
+    assert_chain_parity(cost, rtab, redge, "narrow ties")
+    cost[8, N // 3, 3] = -7
+    opt, st, plan = run_chain(cost, rtab, redge)
+    assert st[8] == CFP_ST_BADINPUT and opt[8] == np.iinfo(np.int64).max and (plan[8] == -1).all()
+    assert st[5] == 1 and (np.delete(st, [5, 8]) == 0).all()
+    rtab[3, K - 1, 2] = cfp_r_limit(0, K)
+    opt, st, plan = run_chain(cost, rtab, redge)
+    assert (st == CFP_ST_BADINPUT).all() and (plan == -1).all()
