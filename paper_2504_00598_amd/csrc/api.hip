@@ -70,6 +70,23 @@ WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables) {
   return L;
 }
 
+EdgeMap edge_map(const int32_t *redge, int n) {
+  EdgeMap m{};
+  // smallest p with redge[i] == redge[i + p] for all i >= 1 (entry 0 is unused)
+  for (int p = 1; p <= kEdgePeriod; ++p) {
+    int i = 1;
+    while (i + p < n && redge[i] == redge[i + p]) ++i;
+    if (i + p < n) continue;
+    m.period = p;
+    for (int x = 0; x < p; ++x) {
+      const int row = x ? x : p;  // the first row i >= 1 of phase x
+      m.map[x] = row < n ? redge[row] : 0;
+    }
+    break;
+  }
+  return m;
+}
+
 // Benchmarking timer (cfp_timer_start / cfp_timer_stop).  Slot 2j and 2j+1
 // hold the start and stop events of the j-th timed launch.
 namespace {
@@ -263,43 +280,50 @@ int put_header(const cfp_chain_desc *d, const WsLayout &L, uint8_t *w, hipStream
   return CFP_OK;
 }
 
-// Whether a chain forward call reads nothing of the header and the uploaded
-// edge map (the K <= 64 paths with a periodic edge map, which flag range errors
-// in R by themselves): a host-to-device copy costs several microseconds of GPU
-// time.
-bool chain_headerless(const cfp_chain_desc *d) {
-  if (chain_narrow_supported(d->n_blocks, d->k, d->n_tables)) return chain_narrow_headerless(*d);
-  return chain_wave_supported(d->n_blocks, d->k, d->n_tables, d->batch) && chain_wave_headerless(*d);
+// The forms of the chain forward call (the first that supports the search runs it).
+enum { kFormNarrow, kFormWave, kFormCw, kFormSplit, kFormFwd };
+
+int chain_form(const cfp_chain_desc *d) {
+  if (chain_narrow_supported(d->n_blocks, d->k, d->n_tables)) return kFormNarrow;
+  if (chain_wave_supported(d->n_blocks, d->k, d->n_tables, d->batch)) return kFormWave;
+  if (chain_cw_supported(d->n_blocks, d->k, d->batch)) return kFormCw;
+  return chain_fwd_split_supported(d->k, d->n_tables, d->batch) ? kFormSplit : kFormFwd;
 }
 
+// Whether a call of this form reads the header or the uploaded edge map: the
+// chunk-parallel forms check R by themselves and take a periodic edge map in
+// their first launch's arguments (a host-to-device copy costs several
+// microseconds of GPU time).
+bool chain_reads_header(int form, const EdgeMap &em) { return form > kFormCw || em.period == 0; }
+
 // The launches of a chain forward call once the header and the edge map are
-// in the workspace (or not needed: chain_headerless).
-int dp_chain_launch(const cfp_chain_desc *d, const WsLayout &L, uint8_t *w, int64_t *opt, int32_t *status,
-                    hipStream_t st) {
+// in the workspace (or not needed: chain_reads_header).
+int dp_chain_launch(const cfp_chain_desc *d, int form, const EdgeMap &em, const WsLayout &L, uint8_t *w, int64_t *opt,
+                    int32_t *status, hipStream_t st) {
   WsHeader *hdr = (WsHeader *)w;
-  if (chain_narrow_supported(d->n_blocks, d->k, d->n_tables))
-    return launch_chain_narrow(*d, (const int32_t *)(w + L.redge), w + L.narrow, w + L.table,
-                               (SearchResult *)(w + L.result), opt, status, st) == hipSuccess
-               ? CFP_OK
-               : CFP_ERR_HIP;
-  const bool wave = chain_wave_supported(d->n_blocks, d->k, d->n_tables, d->batch);
-  const bool cw = !wave && chain_cw_supported(d->n_blocks, d->k, d->batch);
-  if (!wave && !cw &&
+  int32_t *redge = (int32_t *)(w + L.redge);
+  SearchResult *res = (SearchResult *)(w + L.result);
+  if (form > kFormCw &&
       launch_validate_rtab(d->rtab, d->n_tables, d->k, cfp_r_limit(CFP_V_CHAIN, d->k), hdr, st) != hipSuccess)
     return CFP_ERR_HIP;
   hipError_t e;
-  if (wave)
-    e = launch_chain_wave(*d, (const int32_t *)(w + L.redge), w + L.wave, w + L.table,
-                          (SearchResult *)(w + L.result), hdr, opt, status, st);
-  else if (cw)
-    e = launch_chain_cw(*d, (const int32_t *)(w + L.redge), w + L.cw, w + L.table, (SearchResult *)(w + L.result),
-                        hdr, opt, status, st);
-  else if (chain_fwd_split_supported(d->k, d->n_tables, d->batch))
-    e = launch_chain_fwd_split(*d, (const int32_t *)(w + L.redge), w + L.split, (uint32_t *)(w + L.wide),
-                               w + L.table, (SearchResult *)(w + L.result), hdr, opt, status, st);
-  else
-    e = launch_chain_fwd(*d, (const int32_t *)(w + L.redge), w + L.table, L.elem, w + L.wide,
-                         (SearchResult *)(w + L.result), hdr, opt, status, st);
+  switch (form) {
+    case kFormNarrow:
+      e = launch_chain_narrow(*d, redge, em, w + L.narrow, w + L.table, res, opt, status, st);
+      break;
+    case kFormWave:
+      e = launch_chain_wave(*d, redge, em, w + L.wave, w + L.table, res, opt, status, st);
+      break;
+    case kFormCw:
+      e = launch_chain_cw(*d, redge, em, w + L.cw, w + L.table, res, opt, status, st);
+      break;
+    case kFormSplit:
+      e = launch_chain_fwd_split(*d, redge, w + L.split, (uint32_t *)(w + L.wide), w + L.table, res, hdr, opt, status,
+                                 st);
+      break;
+    default:
+      e = launch_chain_fwd(*d, redge, w + L.table, L.elem, w + L.wide, res, hdr, opt, status, st);
+  }
   return e == hipSuccess ? CFP_OK : CFP_ERR_HIP;
 }
 
@@ -342,8 +366,10 @@ int cfp_dp_chain(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t *op
   WsLayout L = layout(CFP_V_CHAIN, d->n_blocks, d->k, d->batch, 0, d->n_tables);
   if (!ws || ws_bytes < L.total) return CFP_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  if (!chain_headerless(d) && (rc = upload_header(d, CFP_V_CHAIN, 0, L, ws, st)) != CFP_OK) return rc;
-  return dp_chain_launch(d, L, (uint8_t *)ws, opt, status, st);
+  const int form = chain_form(d);
+  const EdgeMap em = edge_map(d->redge, d->n_blocks);
+  if (chain_reads_header(form, em) && (rc = upload_header(d, CFP_V_CHAIN, 0, L, ws, st)) != CFP_OK) return rc;
+  return dp_chain_launch(d, form, em, L, (uint8_t *)ws, opt, status, st);
 }
 
 int cfp_dp_chain_mem(const cfp_chain_desc *d, const uint8_t *mem, int32_t n_mem, const int32_t *budget,
@@ -454,8 +480,10 @@ int cfp_search_chain_noalloc(const cfp_chain_desc *d, int64_t *opt, int32_t *sta
   hipStream_t st = (hipStream_t)stream;
   // Every region the kernels read is written earlier in the same call; the
   // header (range flags included), where it is read, is rewritten whole.
-  if (!chain_headerless(d) && (rc = put_header(d, L, w, st)) != CFP_OK) return rc;
-  if ((rc = dp_chain_launch(d, L, w, opt, status, st)) != CFP_OK) return rc;
+  const int form = chain_form(d);
+  const EdgeMap em = edge_map(d->redge, d->n_blocks);
+  if (chain_reads_header(form, em) && (rc = put_header(d, L, w, st)) != CFP_OK) return rc;
+  if ((rc = dp_chain_launch(d, form, em, L, w, opt, status, st)) != CFP_OK) return rc;
   const hipError_t e = launch_traceback_chain(d->n_blocks, d->k, d->batch, L.elem, w + L.table,
                                               (const SearchResult *)(w + L.result), (uint16_t *)(w + L.maps),
                                               (int32_t *)(w + L.bounds), L.nchunks, plan, st);

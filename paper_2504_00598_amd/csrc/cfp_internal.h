@@ -26,11 +26,7 @@ struct WsHeader {
   uint32_t magic;
   int32_t variant, n, k, batch, n_mem, elem;  // elem: bytes per argmin entry
   int32_t rflag;                               // set to 1 by the device if rtab breaks its range
-  // Paths that do not upload the header flag a range error with the number of
-  // the call instead (no reset needed: call numbers start at a random point per
-  // process and have the top bit set, so stale workspace bytes do not match).
-  uint64_t rseq;
-  int32_t pad[54];
+  int32_t pad[56];
 };
 static_assert(sizeof(WsHeader) == 256, "header is 256 bytes");
 
@@ -41,6 +37,21 @@ struct SearchResult {
   int32_t final_m;      // memory variant: budget of the search
   int32_t pad;
 };
+
+// Edge map of a call: a map that repeats with a short period travels in the
+// arguments of the call's first launch, which writes it out for the others, so
+// that nothing has to be uploaded (period 0: the map is uploaded).
+constexpr int kEdgePeriod = 64;
+struct EdgeMap {
+  int32_t period;
+  int32_t map[kEdgePeriod];   // table of the rows i = x mod period, i >= 1
+  // The n entries of the map, by all threads of a one-dimensional launch.
+  __device__ __forceinline__ void write(int32_t *redge, int n) const {
+    if (period == 0) return;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) redge[i] = map[i % period];
+  }
+};
+EdgeMap edge_map(const int32_t *redge, int n);
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
@@ -85,21 +96,17 @@ hipError_t launch_seg_fwd(const cfp_segment_desc &d, const int32_t *redge_dev, u
 hipError_t launch_chain_fwd(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table, int elem,
                             uint8_t *wide, SearchResult *res, const WsHeader *hdr, int64_t *opt,
                             int32_t *status, hipStream_t st);
-// Chain forward for K <= 32, tables in LDS; headerless: a periodic edge map
-// travels in the launch arguments, so nothing of the header is read.
+// Chain forward for K <= 32, tables in LDS.  This form and the chunk-parallel
+// ones for larger K read nothing of the header, and the uploaded edge map only
+// when it has no short period.
 bool chain_narrow_supported(int n, int k, int n_tables);
-bool chain_narrow_headerless(const cfp_chain_desc &d);
 size_t narrow_region_bytes(int n, int k, int n_tables, int batch);
-hipError_t launch_chain_narrow(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
-                               SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
+hipError_t launch_chain_narrow(const cfp_chain_desc &d, const int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
+                               uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
 bool chain_wave_supported(int n, int k, int n_tables, int batch);
 size_t wave_region_bytes(int n, int k, int n_tables, int batch);
-// True when the chunk-parallel K <= 64 path reads nothing of the uploaded
-// header (periodic edge map, range errors flagged by call number).
-bool chain_wave_headerless(const cfp_chain_desc &d);
-hipError_t launch_chain_wave(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
-                             SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,
-                             hipStream_t st);
+hipError_t launch_chain_wave(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
+                             uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
 bool chain_cw_supported(int n, int k, int batch);
 // One-launch search of small chains (forward, range checks and traceback).
 constexpr int kSmallMaxN = 512;
@@ -109,16 +116,20 @@ bool chain_small_supported(int n, int k, int n_tables, int batch);
 hipError_t launch_chain_small(const cfp_chain_desc &d, int64_t *opt, int32_t *status, int32_t *plan,
                               hipStream_t st);
 size_t cw_region_bytes(int n, int k, int n_tables, int batch);
-hipError_t launch_chain_cw(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
-                           SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status, hipStream_t st);
+hipError_t launch_chain_cw(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
+                           uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
 bool chain_fwd_split_supported(int k, int n_tables, int batch);
 size_t split_region_bytes(int k, int batch);
 hipError_t launch_chain_fwd_split(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint32_t *rpk,
                                   uint8_t *table, SearchResult *res, const WsHeader *hdr, int64_t *opt,
                                   int32_t *status, hipStream_t st);
-// Packs R as (R << lb) | t; with hdr set it also flags an R entry outside [0, limit).
-void launch_pack_rtab(const int32_t *rtab, int E, int K, int KP, int lb, uint32_t *rpk, hipStream_t st,
-                      int32_t limit = 0, WsHeader *hdr = nullptr);
+// Packs R as (R << lb) | t; with `bad` set (kPackBlocks words) it also flags R
+// entries outside [0, limit), one word per workgroup, and with a period in *em
+// writes the edge map of the n rows to redge.  Returns the workgroups.
+constexpr int kPackBlocks = 2048;
+int launch_pack_rtab(const int32_t *rtab, int E, int K, int KP, int lb, uint32_t *rpk, hipStream_t st,
+                     int32_t limit = 0, int32_t *bad = nullptr, const EdgeMap *em = nullptr,
+                     int32_t *redge = nullptr, int n = 0);
 bool chain_fwd_wide_supported(int k);
 size_t wide_region_bytes(int n, int k, int batch, int n_tables);
 hipError_t launch_chain_fwd_wide(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,

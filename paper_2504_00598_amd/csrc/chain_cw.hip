@@ -1,5 +1,5 @@
-// Chunk-parallel forward pass of the chain search for 128 < K <= 512 (Sec. 4.4,
-// Eq. T recurrence), for batches whose chains are long.
+// Chunk-parallel forward pass of the chain search for 64 < K <= 512 (Sec. 4.4,
+// Eq. T recurrence), for chains of at least two chunks.
 //
 // Parallelism over the chain: as in the K <= 64 form, every chain is cut into
 // P chunks that run at once, made exact by rank convergence (Maleki,
@@ -11,34 +11,44 @@
 //   2. fix-up pass, chunks p >= 1: start again from the last checkpoint row of
 //      chunk p-1 and recompute until the row equals chunk p's checkpoint of the
 //      same quad (from there on the speculative rows are the true ones);
-//   3. final pass: sum the chunk offsets.  The fix-up of a chunk is valid when
-//      the chunk before it ends on a true row; a chunk whose fix-up met no
-//      checkpoint has its true end row, from which the next chunk is rerun
-//      whole; the chunks after a rerun chunk whose rows met its checkpoints
-//      are valid again.  The result is the sequential recurrence's bit for bit.
+//   3. second fix-up: the chunks behind a chunk that met no checkpoint run
+//      again, all at once, from that chunk's end row.  (Left to the final pass
+//      they ran one after another: 1152 blocks, K = 256, one search, resharding
+//      never free: 1792 us per call, 316 with this pass and chunks of 32 rows
+//      instead of 20.)  With nothing to do it costs one empty launch;
+//   4. final pass: sum the chunk offsets.  The last run of a chunk counts if it
+//      started from the true end row of the chunk before; a chunk that none
+//      did is rerun from it.  The result is the sequential recurrence's bit for
+//      bit.
 //
 // One workgroup of 512 threads (8 waves) carries four chains (four searches of
 // the same chunk: every chain of a launch is at the same row, so all use the
-// same table) and all KP states, KP = 256 or 512.  Wave g works for the
+// same table) and all KP states, KP = 128, 256 or 512.  Wave g works for the
 // predecessors t = g KP/8 .. (g+1) KP/8 - 1 and lane q for the states
 // q KP/64 .. (q+1) KP/64 - 1 of every chain, so every table load of a wave
 // reads one row's KP words contiguously.  Per step a thread reads its share of
 // the packed words (R_e[t][s] << b) | t of the edge's table (each word serves
 // the four chains) in pieces of a few rows, four pieces in flight in their
-// own registers (at KP = 256 that is the whole step, loaded a step ahead), and
-// the predecessors' values from the previous rows in LDS (broadcast reads).
+// own registers (up to KP = 256 that is the whole step, loaded a step ahead),
+// and the predecessors' values from the previous rows in LDS (broadcast reads).
 // A candidate is a saturating add, and one unsigned minimum keeps the value
 // and the lowest predecessor.  The eight group minima of a state are combined
-// through LDS, after which a thread holds one state of two chains (KP = 256)
-// or of all four (KP = 512).
+// through LDS, after which a thread holds one state of one chain (KP = 128), of
+// two (256) or of all four (512).
 //
-// The table stream is what bounds a step: KP^2 words per workgroup and step
-// from the cache hierarchy (the step time does not change with the number of
-// workgroups), hence four chains per workgroup.  At KP = 512 a batch of at
-// most eight searches would leave most compute units idle; there teams of
-// four workgroups split the states of each chunk (state-split teams, below).  Chunks are at least 16 rows
-// long at KP = 256 and 64 at KP = 512, where runs take longer to become
-// parallel (tens of rows on random costs).
+// What bounds a step: at KP >= 256 the table stream, KP^2 words per workgroup
+// and step from the cache hierarchy (the step time does not change with the
+// number of workgroups), hence four chains per workgroup; at KP = 128 the
+// instructions of a wave (about 400 per row, half of them products) and the
+// two exchanges through LDS: 2.0 us per row against 4.3 us at KP = 256.  (Before
+// this form K <= 128 went through the split kernel, 1.9 us per row but one row
+// after another: 1152 blocks, K = 128: 1960 to 152 us for one search, 2237 to
+// 420 us for 128; 393 blocks, K = 81, 24 searches: 762 to 165 us.)  At KP = 512
+// a batch of at most eight searches would leave most compute units idle; there
+// teams of four workgroups split the states of each chunk (state-split teams,
+// below).  Chunks are at least 32 rows long up to KP = 256 and 64 at KP = 512:
+// runs become parallel after 14 rows on average and 38 at most at K = 128, 18
+// and about 40 at K = 256, 21 and 50 at K = 512 (uniform random costs).
 //
 // Normalisation: x[s] = (m >> b) + c[i][s]; the row is divided into the part
 // d = min_s x[s] (summed exactly, per chain) and Q[s] = min(x[s] - d, cap) << b,
@@ -68,33 +78,39 @@ constexpr int kCMaxChunks = 64;
 constexpr int kCWarm = 0;
 
 constexpr int kCG = 4;                  // chains per workgroup (searches of the same chunk)
-// Run modes: speculative; fix-up (stops once every chain met a checkpoint);
-// repair (a whole chunk from a true row, noting where it meets).
-constexpr int kCSpec = 0, kCFix = 1, kCRepair = 2;
+// Passes: speculative; fix-up (a run stops once every chain met a checkpoint);
+// second fix-up, of the chunks behind one that met none in the first.
+constexpr int kCSpec = 0, kCFix = 1, kCFix2 = 2;
 
 template <int KP>
 struct CwShape {
-  static constexpr int BITS = KP <= 256 ? 8 : 9;   // index bits of a packed word
+  static constexpr int BITS = KP <= 128 ? 7 : KP <= 256 ? 8 : 9;  // index bits of a packed word
   static constexpr int PG = KP / kCWaves;           // predecessors per wave
   static constexpr int SPL = KP / 64;               // states per lane in the products
-  static constexpr int V4 = SPL / 4;                // 4-word vectors per table row and lane
-  static constexpr int ROWS = KP <= 256 ? 8 : 2;    // table rows per piece
+  static constexpr int VW = SPL < 4 ? SPL : 4;      // words per table load
+  static constexpr int NV = SPL / VW;               // loads per table row and lane
+  static constexpr int ROWS = KP <= 128 ? 4 : KP <= 256 ? 8 : 2;  // table rows per piece
   static constexpr int PIECES = PG / ROWS;          // pieces per step
   static constexpr int NB = 4;                      // pieces held in registers
   static constexpr int TPS = kCThreads / KP;        // threads per state after the reduction
   static constexpr int CH = kCG / TPS;              // chains per thread after the reduction
+  static constexpr int WPS = KP / 64;               // waves that hold the same chains after the reduction
   static constexpr int QS = KP + KP / 8;            // LDS row stride: 4 words of padding after every 32
-  static constexpr int MINROWS = KP <= 256 ? 16 : 64;  // least rows per chunk
+  static constexpr int MINROWS = KP <= 256 ? 32 : 64;  // least rows per chunk
   static constexpr uint32_t CAP = (1u << (32 - BITS)) - 1u;
   using Arg = typename std::conditional<(KP <= 256), uint8_t, uint16_t>::type;
-  static_assert(PIECES % NB == 0 && ROWS % 2 == 0 && SPL % 4 == 0, "piece layout");
+  typedef uint32_t Vec __attribute__((ext_vector_type(VW)));
+  static_assert(PIECES % NB == 0 && ROWS % 2 == 0 && SPL % VW == 0 && TPS * CH == kCG, "piece layout");
 };
 
 struct CwRec {
   int64_t dfix;   // fix-up pass: offset sum at the meeting checkpoint, or at the chunk end
+  int64_t dfix2;  // the same of the second fix-up
   int32_t flags;  // bit 0 a negative cost, bit 1 a row with no available strategy (speculative
                   // pass); bit 2 a wait between the workgroups of a team expired
   int32_t conv;   // fix-up pass: quad of the meeting checkpoint, -1 if none
+  int32_t conv2;  // the same of the second fix-up
+  int32_t run2;   // the second fix-up ran this chunk (from the first one's end row of the chunk before)
 };
 
 struct CwArgs {
@@ -102,11 +118,13 @@ struct CwArgs {
   const uint32_t *rpk;  // packed tables [E][KP][KP]
   const int32_t *redge;
   int N, K, B, P, CL, nq;  // CL rows per chunk (a multiple of 4); nq quads of rows
-  uint8_t *table;          // argmin entries [B][N][K] (1 byte for KP = 256, 2 for 512)
+  uint8_t *table;          // argmin entries [B][N][K] (1 byte for KP <= 256, 2 for 512)
   CwRec *rec;              // [B][P]
   int64_t *dck;            // speculative offset sum at every checkpoint [B][nq]
   uint32_t *ckrow;         // speculative row at every checkpoint [B][nq][KP]
   uint32_t *endrow;        // fix-up end row of chunks that met no checkpoint [B][P][KP]
+  const int32_t *rbad;     // range flags of R, one per packing workgroup
+  int nbad;
   uint64_t *xb;            // state-split teams: exchanged rows [team][slot][chain][KP]
   int32_t *xflag;          // state-split teams: a member gave up waiting [team]
 };
@@ -115,8 +133,8 @@ template <int KP>
 struct CwSmem {
   uint32_t part[kCG][kCWaves][KP];         // partial minima [chain][predecessor group][state]
   uint32_t q[2][kCG][CwShape<KP>::QS];     // rows [buffer][chain][state, padded]
-  uint32_t wm[kCWaves][kCG];               // wave minima of the new row, per chain
-  int32_t wd[kCWaves][kCG];                // fix-up: the wave found a state off the checkpoint, per chain
+  uint32_t wm[kCWaves][CwShape<KP>::CH];   // wave minima of the new row, per chain of the wave
+  int32_t wd[kCWaves][CwShape<KP>::CH];    // fix-up: the wave found a state off the checkpoint
 };
 
 __device__ __forceinline__ int qpad(int t) { return t + (t >> 5) * 4; }
@@ -148,7 +166,7 @@ template <int KP>
 struct CwChains {
   uint32_t x[CwShape<KP>::CH];  // the thread's values of the current row, normalised and shifted
   uint64_t dsum[kCG];   // offset sums since the start row (uniform)
-  int conv[kCG];        // fix-up and repair: quad of the meeting checkpoint, -1 before
+  int conv[kCG];        // fix-up: quad of the meeting checkpoint, -1 before
   uint64_t dconv[kCG];  // fix-up: dsum at that checkpoint
   uint32_t flags[kCG];  // speculative: bit 0 a negative cost, bit 1 a row with no available strategy
 };
@@ -157,11 +175,12 @@ struct CwChains {
 // valid[c]).  Speculative: the start row is row rs <= r0 from its costs alone
 // (rows before r0 warm the run up and write nothing); argmins from row r0 and
 // checkpoints are written.  Fix-up: the start row (row r0 - 1) is start[c];
-// stops at the first quad end where every real chain has met its checkpoint.
-// Repair: like fix-up, run to r1.
+// stops at the first quad end where every real chain has met its checkpoint at
+// a quad not before qmin[c].
 template <int KP, int MODE>
 __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const bool *valid, int rs, int r0, int r1,
-                                       const uint32_t *const *start, CwSmem<KP> &sm, CwChains<KP> &ch) {
+                                       const int *qmin, const uint32_t *const *start, CwSmem<KP> &sm,
+                                       CwChains<KP> &ch) {
   using S = CwShape<KP>;
   using Arg = typename S::Arg;
   constexpr int CH = S::CH, TPS = S::TPS, BITS = S::BITS;
@@ -175,7 +194,9 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   const bool sin = ms < K;
   // element h of the thread's chains from an array indexed by chain
   auto pick = [&](const auto &arr, int h) __attribute__((always_inline)) {
-    return TPS == 1 ? arr[h] : (sub ? arr[TPS * h + 1] : arr[TPS * h]);
+    if constexpr (TPS == 1) return arr[h];
+    else if constexpr (TPS == 2) return sub ? arr[2 * h + 1] : arr[2 * h];
+    else return sub == 0 ? arr[0] : sub == 1 ? arr[1] : sub == 2 ? arr[2] : arr[3];
   };
   int hc[CH];  // chain of pair h
   bool hv[CH];
@@ -214,28 +235,28 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   // Table pieces in flight, [buffer][row in piece][vector]; word offset of the
   // thread's first word within a table.
   const uint32_t toff = (uint32_t)(S::PG * g * KP + S::SPL * qd);
-  u32x4 tb[S::NB][S::ROWS][S::V4];
+  typename S::Vec tb[S::NB][S::ROWS][S::NV];
   auto tload = [&](int buf, int piece, int row) __attribute__((always_inline)) {
     const uint32_t *tab = a.rpk + (size_t)edge(row) * KP * KP + toff + piece * S::ROWS * KP;
 #pragma unroll
     for (int j = 0; j < S::ROWS; ++j)
 #pragma unroll
-      for (int v = 0; v < S::V4; ++v) tb[buf][j][v] = *(const u32x4 *)(tab + j * KP + 4 * v);
+      for (int v = 0; v < S::NV; ++v) tb[buf][j][v] = *(const typename S::Vec *)(tab + j * KP + S::VW * v);
   };
   // Row minima of every chain from the threads' values: wave minima to LDS,
   // one barrier, then the minimum over the waves (uniform).
   auto row_min = [&](const uint32_t(&x)[CH], uint32_t(&d)[kCG]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < kCG; ++c) {
-      const uint32_t w = cw_wave_min((c % TPS) == sub ? x[c / TPS] : kCX);
-      if (lane == 0) sm.wm[wid][c] = w;
+    for (int h = 0; h < CH; ++h) {
+      const uint32_t w = cw_wave_min(x[h]);
+      if (lane == 0) sm.wm[wid][h] = w;
     }
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < kCG; ++c) {
-      uint32_t m = sm.wm[0][c];
+      uint32_t m = kCX;
 #pragma unroll
-      for (int w = 1; w < kCWaves; ++w) m = umin(m, sm.wm[w][c]);
+      for (int w = 0; w < S::WPS; ++w) m = umin(m, sm.wm[(c % TPS) * S::WPS + w][c / TPS]);
       d[c] = __builtin_amdgcn_readfirstlane(m);
     }
   };
@@ -347,15 +368,14 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 #pragma unroll
         for (int j = 0; j < S::ROWS; j += 2) {
 #pragma unroll
-          for (int vv = 0; vv < S::V4; ++vv) {
-            const u32x4 w = tb[bb][j][vv], y = tb[bb][j + 1][vv];
+          for (int vv = 0; vv < S::NV; ++vv) {
+            const typename S::Vec w = tb[bb][j][vv], y = tb[bb][j + 1][vv];
 #pragma unroll
             for (int c = 0; c < kCG; ++c) {
-              uint32_t *ac = &acc[c][4 * vv];
-              ac[0] = umin(umin(ac[0], sat_add(v[c][j], w.x)), sat_add(v[c][j + 1], y.x));
-              ac[1] = umin(umin(ac[1], sat_add(v[c][j], w.y)), sat_add(v[c][j + 1], y.y));
-              ac[2] = umin(umin(ac[2], sat_add(v[c][j], w.z)), sat_add(v[c][j + 1], y.z));
-              ac[3] = umin(umin(ac[3], sat_add(v[c][j], w.w)), sat_add(v[c][j + 1], y.w));
+              uint32_t *ac = &acc[c][S::VW * vv];
+#pragma unroll
+              for (int u = 0; u < S::VW; ++u)
+                ac[u] = umin(umin(ac[u], sat_add(v[c][j], w[u])), sat_add(v[c][j + 1], y[u]));
             }
           }
         }
@@ -369,13 +389,11 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 #pragma unroll
     for (int c = 0; c < kCG; ++c)
 #pragma unroll
-      for (int vv = 0; vv < S::V4; ++vv) {
-        u32x4 pv;
-        pv.x = acc[c][4 * vv];
-        pv.y = acc[c][4 * vv + 1];
-        pv.z = acc[c][4 * vv + 2];
-        pv.w = acc[c][4 * vv + 3];
-        *(u32x4 *)&sm.part[c][g][S::SPL * qd + 4 * vv] = pv;
+      for (int vv = 0; vv < S::NV; ++vv) {
+        typename S::Vec pv;
+#pragma unroll
+        for (int u = 0; u < S::VW; ++u) pv[u] = acc[c][S::VW * vv + u];
+        *(typename S::Vec *)&sm.part[c][g][S::SPL * qd + S::VW * vv] = pv;
       }
     __syncthreads();
     uint32_t m[CH];
@@ -436,9 +454,9 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
       }
       if (CHECK) {
 #pragma unroll
-        for (int c = 0; c < kCG; ++c) {
-          const uint64_t off = __ballot(((c % TPS) == sub) && ch.x[c / TPS] != ckv[c / TPS]);
-          if (lane == 0) sm.wd[wid][c] = off != 0;
+        for (int h = 0; h < CH; ++h) {
+          const uint64_t off = __ballot(ch.x[h] != ckv[h]);
+          if (lane == 0) sm.wd[wid][h] = off != 0;
         }
         if (i < r1) {
 #pragma unroll
@@ -454,14 +472,14 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
       for (int c = 0; c < kCG; ++c) {
         bool same = true;
 #pragma unroll
-        for (int w = 0; w < kCWaves; ++w) same = same && !sm.wd[w][c];
-        if (ch.conv[c] < 0 && same) {
+        for (int w = 0; w < S::WPS; ++w) same = same && !sm.wd[(c % TPS) * S::WPS + w][c / TPS];
+        if (ch.conv[c] < 0 && same && q >= qmin[c]) {
           ch.conv[c] = q;
           ch.dconv[c] = ch.dsum[c];
         }
         all = all && (ch.conv[c] >= 0 || !valid[c]);
       }
-      if (MODE == kCFix && all) return true;
+      if (all) return true;
     }
     return false;
   };
@@ -472,29 +490,56 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   if (MODE == kCSpec) negative_costs();
 }
 
-// Speculative (MODE kCSpec, grid (ceil(B/kCG), P)) and fix-up (kCFix, grid
-// (ceil(B/kCG), P-1)) passes.
+// Whether the second fix-up runs chunk p of a search: the fix-up of chunk p-1
+// met no checkpoint, so chunk p started from a row that is not the true one,
+// and chunk p-1 itself started from a true row as far as its neighbours tell
+// (chunk p-2 met; a run of unmet chunks is left to the final pass, as its
+// second chunk's end row changes with the first's rerun).
+__device__ __forceinline__ bool cw_second(const CwRec *rec, int p) {
+  return p >= 2 && rec[p - 1].conv < 0 && (p == 2 || rec[p - 2].conv >= 0);
+}
+
+// Quad a rerun of chunk p (last quad qe) must reach before it may stop: past
+// every row that earlier runs from other start rows rewrote.
+__device__ __forceinline__ int cw_qmin(const CwRec &r, int qe) {
+  int q = r.conv < 0 ? qe : r.conv;
+  if (r.run2) q = max(q, r.conv2 < 0 ? qe : r.conv2);
+  return q;
+}
+
+// Speculative (MODE kCSpec, grid (ceil(B/kCG), P)), fix-up (kCFix, grid
+// (ceil(B/kCG), P-1)) and second fix-up (kCFix2, grid (ceil(B/kCG), P-2))
+// passes.  A search takes part in the second one where cw_second says so.
 template <int KP, int MODE>
 __global__ __launch_bounds__(kCThreads, 1) void chain_cw_kernel(CwArgs a) {
   using S = CwShape<KP>;
   __shared__ __align__(16) CwSmem<KP> sm;
-  int bs[kCG];
+  const int p = blockIdx.y + (MODE == kCSpec ? 0 : MODE == kCFix ? 1 : 2);
+  const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
+  int bs[kCG], qmin[kCG];
   bool valid[kCG];
+  const uint32_t *start[kCG];
+  bool any = false;
 #pragma unroll
   for (int c = 0; c < kCG; ++c) {
     const int b = kCG * blockIdx.x + c;
     valid[c] = b < a.B;
     bs[c] = min(b, a.B - 1);
+    qmin[c] = 0;
+    start[c] = a.ckrow + ((size_t)bs[c] * a.nq + (r0 > 0 ? r0 / 4 - 1 : 0)) * KP;
+    if (MODE == kCFix2) {
+      const CwRec *rec = a.rec + (size_t)bs[c] * a.P;
+      valid[c] = valid[c] && cw_second(rec, p);
+      if (valid[c]) start[c] = a.endrow + ((size_t)bs[c] * a.P + p - 1) * KP;
+      qmin[c] = rec[p].conv < 0 ? r1 >> 2 : rec[p].conv;
+    }
+    any = any || valid[c];
   }
-  const int p = MODE == kCFix ? blockIdx.y + 1 : blockIdx.y;
-  const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
+  if (MODE == kCFix2 && !any) return;
   // the speculative run of a chunk after the first starts kCWarm rows early
   const int rs = (MODE == kCSpec && p > 0) ? max(r0 - kCWarm, 0) : r0;
-  const uint32_t *start[kCG];
-#pragma unroll
-  for (int c = 0; c < kCG; ++c) start[c] = a.ckrow + ((size_t)bs[c] * a.nq + (r0 > 0 ? r0 / 4 - 1 : 0)) * KP;
   CwChains<KP> ch;
-  cw_run<KP, MODE>(a, bs, valid, rs, r0, r1, start, sm, ch);
+  cw_run<KP, MODE == kCSpec ? kCSpec : kCFix>(a, bs, valid, rs, r0, r1, qmin, start, sm, ch);
   const int tid = threadIdx.x;
   const int sub = S::TPS == 1 ? 0 : tid / KP;
   const int ms = tid & (KP - 1);
@@ -504,19 +549,23 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_kernel(CwArgs a) {
       if (tid == 0 && valid[c]) a.rec[(size_t)bs[c] * a.P + p].flags = (int32_t)ch.flags[c];
   } else {
 #pragma unroll
-    for (int h = 0; h < S::CH; ++h) {
-      const int c0 = S::TPS * h;  // chain c0 + sub
-      const bool v = sub ? valid[c0 + S::TPS - 1] : valid[c0];
-      const int cv = sub ? ch.conv[c0 + S::TPS - 1] : ch.conv[c0];
-      const int bh = sub ? bs[c0 + S::TPS - 1] : bs[c0];
-      if (v && cv < 0) a.endrow[((size_t)bh * a.P + p) * KP + ms] = ch.x[h];
-    }
+    for (int c = 0; c < kCG; ++c)
+      if (c % S::TPS == sub && valid[c] && ch.conv[c] < 0)
+        a.endrow[((size_t)bs[c] * a.P + p) * KP + ms] = ch.x[c / S::TPS];
 #pragma unroll
     for (int c = 0; c < kCG; ++c) {
       if (tid != c || !valid[c]) continue;
       CwRec &r = a.rec[(size_t)bs[c] * a.P + p];
-      r.conv = ch.conv[c];
-      r.dfix = (int64_t)(ch.conv[c] >= 0 ? ch.dconv[c] : ch.dsum[c]);
+      const int64_t d = (int64_t)(ch.conv[c] >= 0 ? ch.dconv[c] : ch.dsum[c]);
+      if (MODE == kCFix) {
+        r.conv = ch.conv[c];
+        r.dfix = d;
+        r.run2 = 0;
+      } else {
+        r.conv2 = ch.conv[c];
+        r.dfix2 = d;
+        r.run2 = 1;
+      }
     }
   }
 }
@@ -531,7 +580,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_kernel(CwArgs a) {
 // exchange their new values x[s] (before normalisation) as 64-bit words
 // (tag << 32) | x through device memory, every part gathers the whole row, and
 // all parts normalise it the same way, exactly as one workgroup would.  A
-// word's tag is its row (with the top bit set in the fix-up pass), and each
+// word's tag is its row (with the top bits set in the fix-up passes), and each
 // team has two slots used in turn: a part publishes row i + 2 only after it
 // has gathered row i + 1, which every part publishes only after gathering row
 // i, so a slot is never rewritten before every part has read it.  Every
@@ -544,7 +593,8 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_kernel(CwArgs a) {
 constexpr int kXS = 4;                      // workgroups per team
 constexpr int kXW = 512 / kXS;              // states per part
 constexpr int kXSpin = 1 << 20;             // poll rounds before a part gives up
-constexpr uint32_t kXFixTag = 0x80000000u;  // tag bit of the fix-up pass
+constexpr uint32_t kXFixTag = 0x80000000u;  // tag bit of the fix-up passes
+constexpr uint32_t kXFix2Tag = 0x40000000u; // and of the second one
 constexpr int kXMaxGroups = 2;              // teams are used for at most 2 x 4 searches
 constexpr int kXQW = kXW + kXW / 8;         // padded LDS words of one part's states
 
@@ -570,8 +620,10 @@ struct CxChains {
 
 // Runs rows [r0, r1] of the team's chains in part z.  Speculative: the start
 // row r0 comes from its costs alone; argmins from row r0 + 1 and checkpoints
-// are written.  Fix-up: the start row (row r0 - 1) is start[c]; stops at the
-// first quad end where every real chain has met its checkpoint.
+// are written.  Fix-up passes: the start row (row r0 - 1) of chain c is at
+// startr; stops at the first quad end where every chain of `act` (bit cc: chain
+// cc is real and takes part) has met its checkpoint at a quad not before its
+// qmin.
 // Element idx (wave-uniform) of a four-element array, by selects rather than a
 // dynamic index (which would move the array to scratch memory).
 template <typename T>
@@ -580,20 +632,21 @@ __device__ __forceinline__ T sel4(const T (&v)[4], int idx) {
 }
 
 template <int MODE>
-__device__ __forceinline__ void cx_run(const CwArgs &a, int z, int team, int grp, int r0, int r1, CxSmem &sm,
-                                       CxChains &ch) {
+__device__ __forceinline__ void cx_run(const CwArgs &a, int z, int team, int grp, int r0, int r1, int act,
+                                       const int (&qmin)[kCG], const uint32_t *startr, CxSmem &sm, CxChains &ch) {
   constexpr int KP = 512;
   using S = CwShape<KP>;
   constexpr int BITS = S::BITS;
   constexpr uint32_t CAP = S::CAP;
   constexpr int PG = S::PG;  // predecessors per wave
-  constexpr uint32_t PASS = MODE == kCFix ? kXFixTag : 0u;
+  constexpr bool FIX = MODE != kCSpec;
+  constexpr uint32_t PASS = MODE == kCSpec ? 0u : MODE == kCFix ? kXFixTag : kXFixTag | kXFix2Tag;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = wid >> 1;          // the thread's chain after the products (uniform in the wave)
   const int sl = tid & (kXW - 1);  // the thread's state within each part
   const int N = a.N, K = a.K;
   const int b = min(kCG * grp + c, a.B - 1);  // chains past the batch repeat the last search and write nothing
-  const bool hv = kCG * grp + c < a.B;
+  const bool hv = (act >> c) & 1;
   const int s = z * kXW + sl;      // the thread's own state (computed by this part)
   const bool sin = s < K;
   const int qsl = qpad(sl);        // LDS index of state zz W + sl: zz kXQW + qsl
@@ -725,11 +778,10 @@ __device__ __forceinline__ void cx_run(const CwArgs &a, int z, int team, int grp
     }
     i0 = r0 + 1;
   } else {
-    // the start row: chunk p - 1's last checkpoint (row r0 - 1, a quad end)
-    const uint32_t *start = ckb + (size_t)(r0 / 4 - 1) * KP;
+    // the start row: an end row of chunk p - 1 (row r0 - 1, a quad end)
 #pragma unroll
     for (int zz = 0; zz < kXS; ++zz) {
-      ch.q[zz] = start[zz * kXW + sl];
+      ch.q[zz] = startr[zz * kXW + sl];
       sm.q[0][c][zz * kXQW + qsl] = ch.q[zz];
     }
     i0 = r0;
@@ -744,7 +796,7 @@ __device__ __forceinline__ void cx_run(const CwArgs &a, int z, int team, int grp
   cq[0] = cost_at((size_t)i0, coff);
   cq[1] = cost_at((size_t)min(i0 + 1, r1), coff);
 #pragma unroll
-  for (int zz = 0; zz < kXS; ++zz) ckv[zz] = MODE == kCFix ? ckb[(size_t)(i0 >> 2) * KP + zz * kXW + sl] : 0u;
+  for (int zz = 0; zz < kXS; ++zz) ckv[zz] = FIX ? ckb[(size_t)(i0 >> 2) * KP + zz * kXW + sl] : 0u;
 
   // One row i with the previous row in LDS buffer CUR; returns true when the
   // run is over (fix-up: every chain met; any mode: the team gave up).
@@ -819,17 +871,17 @@ __device__ __forceinline__ void cx_run(const CwArgs &a, int z, int team, int grp
       }
     }
     __syncthreads();
-    if (MODE == kCFix && qend) {
+    if (FIX && qend) {
       const int q = i >> 2;
       bool all = true;
 #pragma unroll
       for (int cc = 0; cc < kCG; ++cc) {
         const bool same = !sm.wd[2 * cc] && !sm.wd[2 * cc + 1];
-        if (ch.conv[cc] < 0 && same) {
+        if (ch.conv[cc] < 0 && same && q >= qmin[cc]) {
           ch.conv[cc] = q;
           ch.dconv[cc] = ch.dsum[cc];
         }
-        all = all && (ch.conv[cc] >= 0 || kCG * grp + cc >= a.B);
+        all = all && (ch.conv[cc] >= 0 || !((act >> cc) & 1));
       }
       if (all) return true;
     }
@@ -850,19 +902,39 @@ __global__ void chain_cx_init_kernel(uint64_t *xb, size_t nxb, int32_t *xflag, i
   for (size_t x = (size_t)blockIdx.x * blockDim.x + threadIdx.x; x < (size_t)nrec; x += stride) rec[x].flags = 0;
 }
 
-// Speculative (MODE kCSpec, grid (kXS, ceil(B/kCG), P)) and fix-up (kCFix,
-// grid (kXS, ceil(B/kCG), P-1)) passes of the state-split teams; part z is
-// blockIdx.x, so consecutive workgroups form a team.
+// Speculative (MODE kCSpec, grid (kXS, ceil(B/kCG), P)), fix-up (kCFix, grid
+// (kXS, ceil(B/kCG), P-1)) and second fix-up (kCFix2, P-2) passes of the
+// state-split teams; part z is blockIdx.x, so consecutive workgroups form a
+// team.  Which chains take part depends on records that the pass does not
+// write, so the parts of a team agree.
 template <int MODE>
 __global__ __launch_bounds__(kCThreads, 1) void chain_cx_kernel(CwArgs a) {
   __shared__ __align__(16) CxSmem sm;
   const int z = blockIdx.x, grp = blockIdx.y;
-  const int p = MODE == kCFix ? blockIdx.z + 1 : blockIdx.z;
+  const int p = blockIdx.z + (MODE == kCSpec ? 0 : MODE == kCFix ? 1 : 2);
   const int team = grp * a.P + p;
   const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
-  CxChains ch;
-  cx_run<MODE>(a, z, team, grp, r0, r1, sm, ch);
   const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6), c = wid >> 1, sl = tid & (kXW - 1);
+  int act = 0, qmin[kCG];
+#pragma unroll
+  for (int cc = 0; cc < kCG; ++cc) {
+    const int b = min(kCG * grp + cc, a.B - 1);
+    bool on = kCG * grp + cc < a.B;
+    qmin[cc] = 0;
+    if (MODE == kCFix2) {
+      const CwRec *rec = a.rec + (size_t)b * a.P;
+      on = on && cw_second(rec, p);
+      qmin[cc] = rec[p].conv < 0 ? r1 >> 2 : rec[p].conv;
+    }
+    act |= on ? 1 << cc : 0;
+  }
+  act = __builtin_amdgcn_readfirstlane(act);
+  if (MODE == kCFix2 && act == 0) return;
+  const int bc = min(kCG * grp + c, a.B - 1);
+  const uint32_t *startr = a.ckrow + ((size_t)bc * a.nq + (r0 > 0 ? r0 / 4 - 1 : 0)) * 512;
+  if (MODE == kCFix2 && ((act >> c) & 1)) startr = a.endrow + ((size_t)bc * a.P + p - 1) * 512;
+  CxChains ch;
+  cx_run<MODE>(a, z, team, grp, r0, r1, act, qmin, startr, sm, ch);
   // flags of the run, one word per chain, ORed over the parts
   int32_t fl[kCG];
 #pragma unroll
@@ -872,16 +944,25 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cx_kernel(CwArgs a) {
   }
 #pragma unroll
   for (int cc = 0; cc < kCG; ++cc)
-    if (tid == cc && kCG * grp + cc < a.B && fl[cc]) atomicOr(&a.rec[(size_t)(kCG * grp + cc) * a.P + p].flags, fl[cc]);
-  if (MODE == kCFix) {
-    const int s = z * kXW + sl, bc = kCG * grp + c;
-    if (bc < a.B && sel4(ch.conv, c) < 0) a.endrow[((size_t)bc * a.P + p) * 512 + s] = sel4(ch.q, z);
+    if (tid == cc && ((act >> cc) & 1) && fl[cc])
+      atomicOr(&a.rec[(size_t)(kCG * grp + cc) * a.P + p].flags, fl[cc]);
+  if (MODE != kCSpec) {
+    const int s = z * kXW + sl;
+    if (((act >> c) & 1) && sel4(ch.conv, c) < 0) a.endrow[((size_t)bc * a.P + p) * 512 + s] = sel4(ch.q, z);
 #pragma unroll
     for (int cc = 0; cc < kCG; ++cc) {
-      if (z != 0 || tid != cc || kCG * grp + cc >= a.B) continue;
+      if (z != 0 || tid != cc || !((act >> cc) & 1)) continue;
       CwRec &r = a.rec[(size_t)(kCG * grp + cc) * a.P + p];
-      r.conv = ch.conv[cc];
-      r.dfix = (int64_t)(ch.conv[cc] >= 0 ? ch.dconv[cc] : ch.dsum[cc]);
+      const int64_t d = (int64_t)(ch.conv[cc] >= 0 ? ch.dconv[cc] : ch.dsum[cc]);
+      if (MODE == kCFix) {
+        r.conv = ch.conv[cc];
+        r.dfix = d;
+        r.run2 = 0;
+      } else {
+        r.conv2 = ch.conv[cc];
+        r.dfix2 = d;
+        r.run2 = 1;
+      }
     }
   }
 }
@@ -889,8 +970,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cx_kernel(CwArgs a) {
 // Final pass, one workgroup per search: the chunk offsets, the reruns after
 // chunks whose fix-up met no checkpoint, and the lowest optimal final state.
 template <int KP>
-__global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, const WsHeader *__restrict__ hdr,
-                                                                       SearchResult *__restrict__ res,
+__global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, SearchResult *__restrict__ res,
                                                                        int64_t *__restrict__ opt,
                                                                        int32_t *__restrict__ status) {
   using S = CwShape<KP>;
@@ -907,50 +987,58 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   auto endq = [&](int p) __attribute__((always_inline)) { return (min((p + 1) * a.CL, a.N) - 1) >> 2; };
   if (wid == 0) {
     int fl = lane < P ? rec[lane].flags : 0;
+    for (int x = lane; x < a.nbad; x += 64) fl |= a.rbad[x];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) fl |= __shfl_xor(fl, off, 64);
     if (lane == 0) s_flags = fl;
   }
   // Chunk 0 runs from the true first row.  Invariant at the top of the loop:
   // chunks < p are accounted in `total`; if spec_true, the speculative end row
-  // of chunk p-1 is a true row (so the fix-up of chunk p is valid), otherwise
-  // s_row holds the true end row of chunk p-1.
+  // of chunk p-1 is a true row, otherwise s_row holds the true end row of chunk
+  // p-1.  The last run of a chunk counts if it started from the true end row of
+  // the chunk before: the fix-up from its speculative end row, the second
+  // fix-up from the end row of a fix-up that met no checkpoint.
   int64_t total = dk[endq(0)];
   bool spec_true = true;
   int p = 1;
   while (p < P) {
-    if (spec_true) {
-      // With wave 0: the first chunk q >= p whose fix-up met no checkpoint, and
-      // the offsets of chunks p .. q (chunk q's fix-up ran from a true row to its end).
+    if (spec_true && !rec[p].run2) {
+      // With wave 0: the first chunk q > p that does not count, because chunk
+      // q-1 ended on a row that no run of chunk q started from, and the offsets
+      // of chunks p .. q-1.
       if (wid == 0) {
         const int pl = p + lane;
         const bool in = pl < P;
         CwRec r{};
         if (in) r = rec[pl];
-        const uint64_t nc = __ballot(in && r.conv < 0);
-        const int q = nc ? p + __ffsll((long long)nc) - 1 : P;
+        const int conv = r.run2 ? r.conv2 : r.conv;
+        const int64_t dfix = r.run2 ? r.dfix2 : r.dfix;
+        const bool unmet = in && conv < 0;
+        const bool prev = __shfl_up((int)unmet, 1, 64) != 0 && lane > 0;
+        const uint64_t bad = __ballot(in && prev && !r.run2);
+        const int q = bad ? p + __ffsll((long long)bad) - 1 : P;
         int64_t delta = 0;
-        if (in && pl < q) delta = r.dfix + dk[endq(pl)] - dk[r.conv];
-        else if (in && pl == q) delta = r.dfix;
+        if (in && pl < q) delta = conv < 0 ? dfix : dfix + dk[endq(pl)] - dk[conv];
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) delta += __shfl_xor(delta, off, 64);
+        const bool last = __ballot(pl == q - 1 && unmet) != 0;  // chunk q-1 ended off its checkpoints
         if (lane == 0) {
-          s_q = q;
+          s_q = last ? q : -q;
           s_sum = delta;
         }
       }
       __syncthreads();
-      const int q = s_q;
+      const int sq = s_q;
       total += s_sum;
-      if (q >= P) break;
-      if (tid < KP) s_row[tid] = a.endrow[((size_t)b * P + q) * KP + tid];
-      spec_true = false;
-      p = q + 1;
+      p = abs(sq);
+      spec_true = sq < 0;
+      if (!spec_true && tid < KP) s_row[tid] = a.endrow[((size_t)b * P + p - 1) * KP + tid];
       __syncthreads();
     } else {
-      // Rerun chunk p whole from the true row in s_row; its rows are then
-      // true, and so is its speculative end row if the rerun met a checkpoint.
-      int bs[kCG];
+      // Rerun chunk p from the true row, until it meets its own checkpoints.
+      if (spec_true && tid < KP) s_row[tid] = a.ckrow[((size_t)b * a.nq + endq(p - 1)) * KP + tid];
+      __syncthreads();
+      int bs[kCG], qmin[kCG];
       bool valid[kCG];
       const uint32_t *start[kCG];
 #pragma unroll
@@ -958,12 +1046,13 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
         bs[c] = b;
         valid[c] = c == 0;  // the other chains duplicate it and are discarded
         start[c] = s_row;
+        qmin[c] = cw_qmin(rec[p], endq(p));
       }
       CwChains<KP> ch;
       const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
-      cw_run<KP, kCRepair>(a, bs, valid, r0, r0, r1, start, sm, ch);
-      total += (int64_t)ch.dsum[0];
+      cw_run<KP, kCFix>(a, bs, valid, r0, r0, r1, qmin, start, sm, ch);
       spec_true = ch.conv[0] >= 0;
+      total += spec_true ? (int64_t)ch.dconv[0] + dk[endq(p)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
       __syncthreads();  // every thread has read s_row
       if (!spec_true && tid < KP) s_row[tid] = ch.x[0];  // chain 0 of state tid is the thread's first
       __syncthreads();
@@ -981,7 +1070,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
     const int fl = s_flags;
     int st = CFP_ST_OK;
     if (fl & 4) st = CFP_ST_TIMEOUT;
-    else if ((fl & 1) || hdr->rflag) st = CFP_ST_BADINPUT;
+    else if (fl & 1) st = CFP_ST_BADINPUT;
     else if (fl & 2) st = CFP_ST_INFEASIBLE;
     else if ((fin >> S::BITS) != 0) st = CFP_ST_OVERFLOW;
     status[b] = st;
@@ -1011,22 +1100,33 @@ int cw_device_cus() {
   return cus;
 }
 
-CwPlan cw_plan(int n, int k, int batch) {
+// period: of the edge map (0 when it has none, or for the region's size).
+CwPlan cw_plan(int n, int k, int batch, int period) {
   CwPlan c{0, 0, 0, 0, 1};
-  if (k <= 128 || k > 512) return c;
-  const int kp = k <= 256 ? 256 : 512;
-  const int minrows = kp == 256 ? CwShape<256>::MINROWS : CwShape<512>::MINROWS;
-  if (n < 2 * minrows) return c;
+  if (k <= 64 || k > 512) return c;
+  const int kp = k <= 128 ? 128 : k <= 256 ? 256 : 512;
+  const int minrows = kp <= 256 ? CwShape<256>::MINROWS : CwShape<512>::MINROWS;
   const int groups = (batch + kCG - 1) / kCG;
   // K > 256 with at most two groups of four searches: state-split teams, every
   // workgroup resident on its own compute unit.
   const int cus = cw_device_cus();
   const bool team = kp == 512 && groups <= kXMaxGroups && cus / (kXS * groups) >= 2;
   int P = team ? cus / (kXS * groups) : std::max(2, (256 + groups - 1) / groups);  // about one workgroup per CU
-  P = std::min(P, std::min(kCMaxChunks, n / minrows));
-  int CL = ((n + P - 1) / P + 3) & ~3;
+  P = std::min(P, kCMaxChunks);
+  int CL = std::max(minrows, ((n + P - 1) / P + 3) & ~3);
   P = (n + CL - 1) / CL;
   if (P < 2) return c;
+  // Chunks of an even number of periods start in phase with a chain whose costs
+  // repeat with its edge map and whose rows alternate between periods; worth a
+  // sixteenth more rows per chunk.
+  int u = period;
+  while (u % 4) u += period;
+  if (period % 4 == 0) u = 2 * period;
+  const int al = period ? (CL + u - 1) / u * u : CL;
+  if (16 * al <= 17 * CL && al < n) {
+    CL = al;
+    P = (n + CL - 1) / CL;
+  }
   c.KP = kp;
   c.P = P;
   c.CL = CL;
@@ -1036,17 +1136,16 @@ CwPlan cw_plan(int n, int k, int batch) {
 }
 
 template <int KP>
-void launch_cw_kp(const CwArgs &a, int groups, const WsHeader *hdr, SearchResult *res, int64_t *opt,
-                  int32_t *status, hipStream_t st) {
+void launch_cw_kp(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
   timer_begin(st);
   timed_launch(chain_cw_kernel<KP, kCSpec>, dim3(groups, a.P), dim3(kCThreads), 0, st, a);
   timer_end(st);
   hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix>), dim3(groups, a.P - 1), dim3(kCThreads), 0, st, a);
-  hipLaunchKernelGGL(chain_cw_final_kernel<KP>, dim3(a.B), dim3(kCThreads), 0, st, a, hdr, res, opt, status);
+  if (a.P > 2) hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix2>), dim3(groups, a.P - 2), dim3(kCThreads), 0, st, a);
+  hipLaunchKernelGGL(chain_cw_final_kernel<KP>, dim3(a.B), dim3(kCThreads), 0, st, a, res, opt, status);
 }
 
-void launch_cx(const CwArgs &a, int groups, const WsHeader *hdr, SearchResult *res, int64_t *opt, int32_t *status,
-               hipStream_t st) {
+void launch_cx(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
   const int teams = groups * a.P;
   hipLaunchKernelGGL(chain_cx_init_kernel, dim3(64), dim3(256), 0, st, a.xb, (size_t)teams * 2 * kCG * 512, a.xflag,
                      teams, a.rec, a.B * a.P);
@@ -1054,18 +1153,20 @@ void launch_cx(const CwArgs &a, int groups, const WsHeader *hdr, SearchResult *r
   timed_launch(chain_cx_kernel<kCSpec>, dim3(kXS, groups, a.P), dim3(kCThreads), 0, st, a);
   timer_end(st);
   hipLaunchKernelGGL(chain_cx_kernel<kCFix>, dim3(kXS, groups, a.P - 1), dim3(kCThreads), 0, st, a);
-  hipLaunchKernelGGL(chain_cw_final_kernel<512>, dim3(a.B), dim3(kCThreads), 0, st, a, hdr, res, opt, status);
+  if (a.P > 2) hipLaunchKernelGGL(chain_cx_kernel<kCFix2>, dim3(kXS, groups, a.P - 2), dim3(kCThreads), 0, st, a);
+  hipLaunchKernelGGL(chain_cw_final_kernel<512>, dim3(a.B), dim3(kCThreads), 0, st, a, res, opt, status);
 }
 
 }  // namespace
 
-bool chain_cw_supported(int n, int k, int batch) { return cw_plan(n, k, batch).P >= 2; }
+bool chain_cw_supported(int n, int k, int batch) { return cw_plan(n, k, batch, 0).P >= 2; }
 
 size_t cw_region_bytes(int n, int k, int n_tables, int batch) {
-  const CwPlan c = cw_plan(n, k, batch);
+  const CwPlan c = cw_plan(n, k, batch, 0);  // no plan of these sizes has more chunks
   if (c.P < 2) return 0;
   const size_t kp = c.KP;
   size_t off = align_up((size_t)n_tables * kp * kp * 4);
+  off += align_up(kPackBlocks * sizeof(int32_t));
   off += align_up((size_t)batch * c.P * sizeof(CwRec));
   off += align_up((size_t)batch * c.nq * 8);
   off += align_up((size_t)batch * c.nq * kp * 4);
@@ -1078,9 +1179,9 @@ size_t cw_region_bytes(int n, int k, int n_tables, int batch) {
   return off;
 }
 
-hipError_t launch_chain_cw(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
-                           SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status, hipStream_t st) {
-  const CwPlan c = cw_plan(d.n_blocks, d.k, d.batch);
+hipError_t launch_chain_cw(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
+                           uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
+  const CwPlan c = cw_plan(d.n_blocks, d.k, d.batch, em.period);
   const size_t kp = c.KP;
   CwArgs a;
   a.cost = d.cost;
@@ -1096,6 +1197,9 @@ hipError_t launch_chain_cw(const cfp_chain_desc &d, const int32_t *redge_dev, ui
   uint32_t *rpk = (uint32_t *)(region + off);
   a.rpk = rpk;
   off += align_up((size_t)d.n_tables * kp * kp * 4);
+  int32_t *rbad = (int32_t *)(region + off);
+  a.rbad = rbad;
+  off += align_up(kPackBlocks * sizeof(int32_t));
   a.rec = (CwRec *)(region + off);
   off += align_up((size_t)d.batch * c.P * sizeof(CwRec));
   a.dck = (int64_t *)(region + off);
@@ -1112,11 +1216,13 @@ hipError_t launch_chain_cw(const cfp_chain_desc &d, const int32_t *redge_dev, ui
     off += align_up((size_t)groups * c.P * 2 * kCG * kp * 8);
     a.xflag = (int32_t *)(region + off);
   }
-  launch_pack_rtab(d.rtab, d.n_tables, d.k, (int)kp, kp == 256 ? CwShape<256>::BITS : CwShape<512>::BITS, rpk, st,
-                   cfp_r_limit(CFP_V_CHAIN, d.k), const_cast<WsHeader *>(hdr));
-  if (c.S > 1) launch_cx(a, groups, hdr, res, opt, status, st);
-  else if (kp == 256) launch_cw_kp<256>(a, groups, hdr, res, opt, status, st);
-  else launch_cw_kp<512>(a, groups, hdr, res, opt, status, st);
+  const int bits = kp == 128 ? CwShape<128>::BITS : kp == 256 ? CwShape<256>::BITS : CwShape<512>::BITS;
+  a.nbad = launch_pack_rtab(d.rtab, d.n_tables, d.k, (int)kp, bits, rpk, st, cfp_r_limit(CFP_V_CHAIN, d.k), rbad, &em,
+                            redge_dev, d.n_blocks);
+  if (c.S > 1) launch_cx(a, groups, res, opt, status, st);
+  else if (kp == 128) launch_cw_kp<128>(a, groups, res, opt, status, st);
+  else if (kp == 256) launch_cw_kp<256>(a, groups, res, opt, status, st);
+  else launch_cw_kp<512>(a, groups, res, opt, status, st);
   return hipGetLastError();
 }
 

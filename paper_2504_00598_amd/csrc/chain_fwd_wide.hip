@@ -54,11 +54,15 @@ struct WideShape {
   static constexpr int LB = Pow2Bits<TPG>::value;  // index bits within a group
 };
 
-// With hdr set, the range check of R (entries in [0, limit)) is made on the
-// way and flagged in the header.
+// With `bad` set, the range check of R (entries in [0, limit)) is made on the
+// way; every workgroup writes its own flag word, so no word needs a reset.
+// With a period in `em`, the edge map of the n rows is written out as well.
 __global__ void pack_rtab_kernel(const int32_t *__restrict__ rtab, int E, int K, int KP, int lb,
-                                 uint32_t *__restrict__ rpk, int32_t limit, WsHeader *__restrict__ hdr) {
+                                 uint32_t *__restrict__ rpk, int32_t limit, int32_t *__restrict__ bad,
+                                 EdgeMap em, int32_t *__restrict__ redge, int n) {
+  em.write(redge, n);
   const size_t total = (size_t)E * KP * KP;
+  bool off = false;
   for (size_t x = (size_t)blockIdx.x * blockDim.x + threadIdx.x; x < total; x += (size_t)gridDim.x * blockDim.x) {
     const int s = (int)(x % KP);
     const int t = (int)((x / KP) % KP);
@@ -66,10 +70,14 @@ __global__ void pack_rtab_kernel(const int32_t *__restrict__ rtab, int E, int K,
     uint32_t v = kSat;
     if (t < K && s < K) {
       const int32_t r = rtab[((size_t)e * K + t) * K + s];
-      if (hdr && (r < 0 || r >= limit)) hdr->rflag = 1;
+      off |= r < 0 || r >= limit;
       v = ((uint32_t)r << lb) | (uint32_t)(t & ((1 << lb) - 1));
     }
     rpk[x] = v;
+  }
+  if (bad) {
+    const int any = __syncthreads_or(off);
+    if (threadIdx.x == 0) bad[blockIdx.x] = any ? 1 : 0;
   }
 }
 
@@ -259,11 +267,13 @@ __global__ __launch_bounds__(kWideThreads, 1) void chain_fwd_wide_kernel(
 
 bool chain_fwd_wide_supported(int k) { return k > 64 && k <= 512; }
 
-void launch_pack_rtab(const int32_t *rtab, int E, int K, int KP, int lb, uint32_t *rpk, hipStream_t st, int32_t limit,
-                      WsHeader *hdr) {
+int launch_pack_rtab(const int32_t *rtab, int E, int K, int KP, int lb, uint32_t *rpk, hipStream_t st, int32_t limit,
+                     int32_t *bad, const EdgeMap *em, int32_t *redge, int n) {
   const size_t total = (size_t)E * KP * KP;
-  const int grid = (int)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
-  hipLaunchKernelGGL(pack_rtab_kernel, dim3(grid), dim3(256), 0, st, rtab, E, K, KP, lb, rpk, limit, hdr);
+  const int grid = (int)((total + 255) / 256 < kPackBlocks ? (total + 255) / 256 : kPackBlocks);
+  hipLaunchKernelGGL(pack_rtab_kernel, dim3(grid), dim3(256), 0, st, rtab, E, K, KP, lb, rpk, limit, bad,
+                     em ? *em : EdgeMap{}, redge, n);
+  return grid;
 }
 
 // Workspace region of the kernel: packed tables [E][KP][KP] u32, then the
@@ -283,10 +293,7 @@ static void launch_wide_kp(const cfp_chain_desc &d, const int32_t *redge_dev, ui
                            SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status, hipStream_t st) {
   uint32_t *rpk = (uint32_t *)region;
   int32_t *rowcmin = (int32_t *)(region + wide_rpk_bytes(d.k, d.n_tables));
-  const size_t total = (size_t)d.n_tables * KP * KP;
-  const int grid = (int)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
-  hipLaunchKernelGGL(pack_rtab_kernel, dim3(grid), dim3(256), 0, st, d.rtab, d.n_tables, d.k, KP,
-                     WideShape<KP>::LB, rpk, 0, (WsHeader *)nullptr);
+  launch_pack_rtab(d.rtab, d.n_tables, d.k, KP, WideShape<KP>::LB, rpk, st);
   const int rows = d.batch * d.n_blocks;
   hipLaunchKernelGGL(row_cmin_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, d.cost, rows, d.k, rowcmin);
   timer_begin(st);

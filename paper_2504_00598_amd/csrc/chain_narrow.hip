@@ -38,7 +38,6 @@ namespace {
 
 constexpr int kNSpec = 0, kNFix = 1;
 constexpr uint32_t kNX = 0xFFFFFFFFu;    // x of an unavailable or padding state
-constexpr int kNPeriod = 64;             // longest edge period carried in the arguments
 constexpr int kNRing = 8;                // rows of costs in flight
 constexpr size_t kNMaxLds = 152 * 1024;  // packed tables of a workgroup
 
@@ -71,8 +70,7 @@ struct NarrowArgs {
   SearchResult *res;
   int64_t *opt;
   int32_t *status;
-  int period;               // edge i uses table emap[i % period] (i >= 1), 0: redge
-  uint8_t emap[kNPeriod];
+  EdgeMap em;
 };
 
 // Packs the tables into LDS: word u of piece c of column s of table e is
@@ -134,7 +132,7 @@ struct NarrowRun {
 //           row is compared with the checkpoint of the same quad, and a task
 //           that has met it stops.
 template <int KP, int MODE, bool PER>
-__device__ __forceinline__ void narrow_run(const NarrowArgs &a, const u32x4 *tabs, const uint8_t *emap, int b,
+__device__ __forceinline__ void narrow_run(const NarrowArgs &a, const u32x4 *tabs, const int *emap, int b,
                                            bool valid, int r0, int iend, int qmin, NarrowRun &run) {
   using S = NarrowShape<KP>;
   constexpr int CH = S::CH;
@@ -157,10 +155,10 @@ __device__ __forceinline__ void narrow_run(const NarrowArgs &a, const u32x4 *tab
   // Periodic edge map: e1 is the table of the next row, ph the phase of the row
   // after that one.
   int ph = 0, e1 = 0;
-  auto next_phase = [&](int x) __attribute__((always_inline)) { return x + 1 == a.period ? 0 : x + 1; };
+  auto next_phase = [&](int x) __attribute__((always_inline)) { return x + 1 == a.em.period ? 0 : x + 1; };
   int e0;
   if (PER) {
-    ph = r0 % a.period;
+    ph = r0 % a.em.period;
     e0 = emap[ph];
     ph = next_phase(ph);
     e1 = emap[ph];
@@ -302,7 +300,7 @@ template <int KP, int NW, int MODE, bool PER>
 __global__ __launch_bounds__(64 * NW) void chain_narrow_kernel(NarrowArgs a) {
   using S = NarrowShape<KP>;
   extern __shared__ __align__(16) u32x4 tabs[];
-  __shared__ uint8_t emap[kNPeriod];
+  __shared__ int emap[kEdgePeriod];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, s = lane & (KP - 1);
   const int chunks = MODE == kNSpec ? a.P : a.P - 1;
   const int64_t task = ((int64_t)blockIdx.x * NW + wid) * S::TASKS + lane / KP;
@@ -313,7 +311,7 @@ __global__ __launch_bounds__(64 * NW) void chain_narrow_kernel(NarrowArgs a) {
   NarrowRun run;
   run.q = 0;
   if (MODE == kNFix) run.q = a.ckrow[((size_t)b * a.nq + (r0 / 4 - 1)) * KP + s];
-  if (PER && tid < kNPeriod) emap[tid] = a.emap[tid];
+  if (PER && tid < kEdgePeriod) emap[tid] = a.em.map[tid];
   const bool badr = narrow_stage<KP>(a, tabs, 64 * NW);
   const bool anybad = __syncthreads_or(badr);
   narrow_run<KP, MODE, PER>(a, tabs, emap, b, valid, r0, iend, 0, run);
@@ -338,7 +336,7 @@ __global__ __launch_bounds__(64 * NW) void chain_narrow_kernel(NarrowArgs a) {
 template <int KP, bool PER>
 __global__ __launch_bounds__(64) void chain_narrow_final_kernel(NarrowArgs a) {
   extern __shared__ __align__(16) u32x4 tabs[];
-  __shared__ uint8_t emap[kNPeriod];
+  __shared__ int emap[kEdgePeriod];
   const int lane = threadIdx.x, s = lane & (KP - 1);
   const int b = blockIdx.x, P = a.P;
   const int64_t *dk = a.dck + (size_t)b * a.nq;
@@ -380,7 +378,7 @@ __global__ __launch_bounds__(64) void chain_narrow_final_kernel(NarrowArgs a) {
       // Rerun chunk p (the first task of the wave) from q, at least over the
       // rows its fix-up rewrote from a wrong start.
       if (!staged) {
-        if (PER && lane < kNPeriod) emap[lane] = a.emap[lane];
+        if (PER && lane < kEdgePeriod) emap[lane] = a.em.map[lane];
         narrow_stage<KP>(a, tabs, 64);
         staged = true;
         __syncthreads();
@@ -447,16 +445,6 @@ NarrowPlan narrow_plan(int n, int k, int batch, int period) {
   return c;
 }
 
-// Smallest p <= kNPeriod with redge[i] == redge[i + p] for all i >= 1 (0 if none).
-int narrow_period(const int32_t *redge, int n) {
-  for (int p = 1; p <= kNPeriod; ++p) {
-    int i = 1;
-    while (i + p < n && redge[i] == redge[i + p]) ++i;
-    if (i + p >= n) return p;
-  }
-  return 0;
-}
-
 template <int KP, int NW, bool PER>
 hipError_t launch_narrow_passes(const NarrowArgs &a, size_t lds, hipStream_t st) {
   const int tasks = NarrowShape<KP>::TASKS * NW;
@@ -475,17 +463,15 @@ hipError_t launch_narrow_passes(const NarrowArgs &a, size_t lds, hipStream_t st)
 template <int KP>
 hipError_t launch_narrow_kp(const NarrowArgs &a, int nw, size_t lds, hipStream_t st) {
   if (nw == 4)
-    return a.period ? launch_narrow_passes<KP, 4, true>(a, lds, st) : launch_narrow_passes<KP, 4, false>(a, lds, st);
-  return a.period ? launch_narrow_passes<KP, 16, true>(a, lds, st) : launch_narrow_passes<KP, 16, false>(a, lds, st);
+    return a.em.period ? launch_narrow_passes<KP, 4, true>(a, lds, st) : launch_narrow_passes<KP, 4, false>(a, lds, st);
+  return a.em.period ? launch_narrow_passes<KP, 16, true>(a, lds, st) : launch_narrow_passes<KP, 16, false>(a, lds, st);
 }
 
 }  // namespace
 
 bool chain_narrow_supported(int n, int k, int e) {
-  return k <= 32 && n < (1 << 24) && e <= 256 && narrow_lds(k, e) <= kNMaxLds;
+  return k <= 32 && n < (1 << 24) && narrow_lds(k, e) <= kNMaxLds;
 }
-
-bool chain_narrow_headerless(const cfp_chain_desc &d) { return narrow_period(d.redge, d.n_blocks) != 0; }
 
 size_t narrow_region_bytes(int n, int k, int e, int batch) {
   if (!chain_narrow_supported(n, k, e)) return 0;
@@ -494,16 +480,11 @@ size_t narrow_region_bytes(int n, int k, int e, int batch) {
          align_up((size_t)batch * nq * kp * 4) + align_up((size_t)batch * pmax * kp * 4);
 }
 
-hipError_t launch_chain_narrow(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
-                               SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
+hipError_t launch_chain_narrow(const cfp_chain_desc &d, const int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
+                               uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
   NarrowArgs a;
-  a.period = narrow_period(d.redge, d.n_blocks);
-  // phase of row i is i mod period; entry 0 belongs to rows that are multiples of the period
-  for (int i = 0; i < kNPeriod; ++i) {
-    const int row = a.period ? (i % a.period ? i % a.period : a.period) : 0;
-    a.emap[i] = row && row < d.n_blocks ? (uint8_t)d.redge[row] : 0;
-  }
-  const NarrowPlan c = narrow_plan(d.n_blocks, d.k, d.batch, a.period);
+  a.em = em;
+  const NarrowPlan c = narrow_plan(d.n_blocks, d.k, d.batch, a.em.period);
   const size_t kp = narrow_kp(d.k);
   a.cost = d.cost;
   a.rtab = d.rtab;

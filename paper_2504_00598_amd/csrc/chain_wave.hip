@@ -52,9 +52,6 @@
 // (double buffer, one barrier per four rows); the rows are cut into blocks of
 // 12, the period of the edge map the kernels are specialised for.
 #include <algorithm>
-#include <atomic>
-#include <chrono>
-#include <random>
 
 #include "res_common.h"
 
@@ -70,6 +67,7 @@ constexpr int kWTable16 = 64 * 64 / 4;  // 16-byte chunks of one packed table
 constexpr int kWMaxChunks = 64;         // chunks per search (the final pass reads one per lane)
 constexpr int kWMinBlocks = 4;          // least blocks of 12 rows per chunk
 constexpr uint32_t kWX = 0xFFFFFFFFu;   // x of an unavailable or padding state
+constexpr int kWPackBlocks = 1024;      // most workgroups of the packing kernel
 constexpr int kWBits = 6;
 constexpr uint32_t kWQcap6 = ((1u << 25) - 1u) << kWBits;
 
@@ -89,7 +87,8 @@ struct WaveArgs {
   int64_t *dck;         // speculative offset sum (from the chunk's start row) at every checkpoint [B][nq]
   uint32_t *ckrow;      // speculative row at every checkpoint (end of a quad of rows) [B][nq][64]
   uint32_t *endrow;     // fix-up end row of chunks that met no checkpoint [B][P][64]
-  uint64_t seq;         // number of this call: a range error in R is flagged as hdr->rseq = seq
+  const int32_t *rbad;  // range flags of R, one per packing workgroup
+  int nbad;
 };
 
 // Packed tables: word u of chunk c of lane s of table e is (R_e[t][s] << 6) | t
@@ -97,17 +96,23 @@ struct WaveArgs {
 // predecessor t >= K holds a capped word, so its candidate exceeds every exact
 // one without wrapping, and a state s >= K is padding.
 // Every R entry is read here, so the range check of R (entries in [0, limit))
-// is made on the way and flagged in the header as the call's number.
+// is made on the way; every workgroup writes its own flag word, so no word
+// needs a reset.  With a period in `em`, the edge map is written out as well.
 __global__ void wave_pack_kernel(const int32_t *__restrict__ rtab, int E, int K, uint32_t *__restrict__ rpk,
-                                 int32_t limit, WsHeader *__restrict__ hdr, uint64_t seq) {
+                                 int32_t limit, int32_t *__restrict__ bad, EdgeMap em, int32_t *__restrict__ redge,
+                                 int n) {
+  em.write(redge, n);
   const size_t words = (size_t)E * 64 * 64;
+  bool off = false;
   for (size_t w = blockIdx.x * (size_t)blockDim.x + threadIdx.x; w < words; w += (size_t)gridDim.x * blockDim.x) {
     const int u = (int)(w & 3), s = (int)((w >> 2) & 63), c = (int)((w >> 8) & 15), e = (int)(w >> 12);
     const int t = 4 * c + u;
     const int32_t r = rtab[((size_t)e * K + min(t, K - 1)) * K + min(s, K - 1)];
-    if (r < 0 || r >= limit) hdr->rseq = seq;
+    off |= r < 0 || r >= limit;
     rpk[w] = ((uint32_t)r << kWBits) | (uint32_t)t;
   }
+  const int any = __syncthreads_or(off);
+  if (threadIdx.x == 0) bad[blockIdx.x] = any ? 1 : 0;
 }
 
 // Minimum over the 64 lanes of a wave as a scalar: row minima by DPP, then the
@@ -545,7 +550,6 @@ constexpr int kWFinalWaves = 4;
 
 template <int EP>
 __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(WaveArgs a,
-                                                                                const WsHeader *__restrict__ hdr,
                                                                                 SearchResult *__restrict__ res,
                                                                                 int64_t *__restrict__ opt,
                                                                                 int32_t *__restrict__ status) {
@@ -560,6 +564,7 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
   auto endq = [&](int p) __attribute__((always_inline)) { return (min((p + 1) * a.CB * kWU, a.N) - 1) >> 2; };
   if (wid == 0) {
     int fl = lane < P ? rec[lane].flags : 0;
+    for (int x = lane; x < a.nbad; x += 64) fl |= a.rbad[x];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) fl |= __shfl_xor(fl, off, 64);
     if (lane == 0) s_flags = fl;
@@ -631,7 +636,7 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
   if (lane == 0) {
     const int fl = s_flags;
     int st = CFP_ST_OK;
-    if ((fl & 1) || hdr->rseq == a.seq) st = CFP_ST_BADINPUT;
+    if (fl & 1) st = CFP_ST_BADINPUT;
     else if (fl & 2) st = CFP_ST_INFEASIBLE;
     else if ((pk >> kWBits) != 0) st = CFP_ST_OVERFLOW;
     status[b] = st;
@@ -670,53 +675,18 @@ WavePlan wave_plan(int n, int k, int e, int batch) {
 }
 
 template <int EP, int NW>
-static void launch_wave_passes(const WaveArgs &a, const WsHeader *hdr, SearchResult *res, int64_t *opt,
-                               int32_t *status, hipStream_t st) {
+static void launch_wave_passes(const WaveArgs &a, SearchResult *res, int64_t *opt, int32_t *status,
+                               hipStream_t st) {
   const int rows = (a.B + NW - 1) / NW;
   timer_begin(st);
   timed_launch(chain_wave_kernel<EP, NW>, dim3(rows, a.P), dim3(64 * NW), 0, st, a);
   timer_end(st);
   if (a.P > 1)
     hipLaunchKernelGGL((chain_wave_fix_kernel<EP, NW>), dim3(rows, a.P - 1), dim3(64 * NW), 0, st, a);
-  hipLaunchKernelGGL((chain_wave_final_kernel<EP>), dim3(a.B), dim3(64 * kWFinalWaves), 0, st, a, hdr, res, opt,
-                     status);
-}
-
-// Number of a call, stored as the range flag of a workspace whose header is
-// not uploaded.  The word starts as whatever the workspace held, so the
-// numbers must not be guessable from stale bytes: the sequence starts at a
-// random 64-bit point drawn once per process and every number has its top bit
-// set, so no zero word (what an upload writes) and no small or non-negative
-// integer left in the workspace ever equals one.
-static uint64_t next_call_number() {
-  static std::atomic<uint64_t> counter{0};
-  static const uint64_t base = [] {
-    std::random_device rd;
-    uint64_t x = ((uint64_t)rd() << 32) ^ (uint64_t)rd();
-    x ^= (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
-    // SplitMix64 finaliser (Steele, Lea and Flood, OOPSLA 2014)
-    x += 0x9E3779B97F4A7C15ull;
-    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
-    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-    return x ^ (x >> 31);
-  }();
-  return (base + counter.fetch_add(1, std::memory_order_relaxed)) | (1ull << 63);
-}
-
-// Period of the edge map if redge[i] == i mod E for all i >= 1 with E
-// dividing 12, else 0.
-static int wave_edge_period(const int32_t *redge, int n, int e) {
-  if (kWU % e != 0) return 0;
-  for (int i = 1; i < n; ++i)
-    if (redge[i] != i % e) return 0;
-  return e;
+  hipLaunchKernelGGL((chain_wave_final_kernel<EP>), dim3(a.B), dim3(64 * kWFinalWaves), 0, st, a, res, opt, status);
 }
 
 }  // namespace
-
-bool chain_wave_headerless(const cfp_chain_desc &d) {
-  return wave_edge_period(d.redge, d.n_blocks, d.n_tables) == 12;
-}
 
 bool chain_wave_supported(int n, int k, int e, int batch) { return wave_plan(n, k, e, batch).P >= 1; }
 
@@ -724,6 +694,7 @@ size_t wave_region_bytes(int n, int k, int e, int batch) {
   const WavePlan c = wave_plan(n, k, e, batch);
   if (c.P < 1) return 0;
   size_t off = align_up((size_t)e * 64 * 64 * 4);
+  off += align_up(kWPackBlocks * sizeof(int32_t));
   off += align_up((size_t)batch * c.P * sizeof(WaveRec));
   off += align_up((size_t)batch * c.nq * 8);
   off += align_up((size_t)batch * c.nq * 64 * 4);
@@ -731,9 +702,8 @@ size_t wave_region_bytes(int n, int k, int e, int batch) {
   return off;
 }
 
-hipError_t launch_chain_wave(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint8_t *table,
-                             SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,
-                             hipStream_t st) {
+hipError_t launch_chain_wave(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
+                             uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
   const WavePlan c = wave_plan(d.n_blocks, d.k, d.n_tables, d.batch);
   WaveArgs a;
   a.cost = d.cost;
@@ -751,6 +721,8 @@ hipError_t launch_chain_wave(const cfp_chain_desc &d, const int32_t *redge_dev, 
   uint32_t *rpk = (uint32_t *)(region + off);
   a.rpk = (const u32x4 *)rpk;
   off += align_up((size_t)d.n_tables * 64 * 64 * 4);
+  int32_t *rbad = (int32_t *)(region + off);
+  off += align_up(kWPackBlocks * sizeof(int32_t));
   a.rec = (WaveRec *)(region + off);
   off += align_up((size_t)d.batch * c.P * sizeof(WaveRec));
   a.dck = (int64_t *)(region + off);
@@ -758,16 +730,19 @@ hipError_t launch_chain_wave(const cfp_chain_desc &d, const int32_t *redge_dev, 
   a.ckrow = (uint32_t *)(region + off);
   off += align_up((size_t)d.batch * c.nq * 64 * 4);
   a.endrow = (uint32_t *)(region + off);
-  a.seq = next_call_number();
-  hipLaunchKernelGGL(wave_pack_kernel, dim3(std::min(1024, d.n_tables * 16)), dim3(256), 0, st, d.rtab, d.n_tables,
-                     d.k, rpk, cfp_r_limit(CFP_V_CHAIN, d.k), const_cast<WsHeader *>(hdr), a.seq);
-  const bool periodic = chain_wave_headerless(d);
+  a.rbad = rbad;
+  a.nbad = std::min(kWPackBlocks, d.n_tables * 16);
+  hipLaunchKernelGGL(wave_pack_kernel, dim3(a.nbad), dim3(256), 0, st, d.rtab, d.n_tables, d.k, rpk,
+                     cfp_r_limit(CFP_V_CHAIN, d.k), rbad, em, redge_dev, d.n_blocks);
+  // the usual period, and table i for phase i: the table index is a constant per row of a block
+  bool periodic = em.period == kWU;
+  for (int i = 0; periodic && i < kWU; ++i) periodic = em.map[i] == i;
   if (c.NW == 4) {
-    if (periodic) launch_wave_passes<12, 4>(a, hdr, res, opt, status, st);
-    else launch_wave_passes<0, 4>(a, hdr, res, opt, status, st);
+    if (periodic) launch_wave_passes<12, 4>(a, res, opt, status, st);
+    else launch_wave_passes<0, 4>(a, res, opt, status, st);
   } else {
-    if (periodic) launch_wave_passes<12, kWWaves>(a, hdr, res, opt, status, st);
-    else launch_wave_passes<0, kWWaves>(a, hdr, res, opt, status, st);
+    if (periodic) launch_wave_passes<12, kWWaves>(a, res, opt, status, st);
+    else launch_wave_passes<0, kWWaves>(a, res, opt, status, st);
   }
   return hipGetLastError();
 }

@@ -648,3 +648,68 @@ def test_narrow_ties_and_statuses(N, K):
     rtab[3, K - 1, 2] = cfp_r_limit(0, K)
     opt, st, plan = run_chain(cost, rtab, redge)
     assert (st == CFP_ST_BADINPUT).all() and (plan == -1).all()
+
+
+# 64 < K <= 128 runs chunk-parallel like the wider searches. The second fix-up reruns the
+# chunks behind an isolated one that met no checkpoint; longer runs of such chunks are left
+# to the final pass.
+
+@pytest.mark.parametrize("N,K,B,E", [(33, 65, 1, 1), (36, 128, 5, 3), (63, 128, 2, 12), (97, 100, 9, 40),
+                                     (100, 127, 130, 12), (1001, 81, 3, 16), (2100, 66, 2, 12)])
+def test_chunked_mid_shapes(N, K, B, E):
+    """Ragged batches and last chunks, K up to 128, any number of tables."""
+    need_gpu()
+    cost, rtab, redge = rand_case([70, N, K, B], B, N, K, E, 0, 1_000_000, inf_frac=0.05)
+    if N % 2:
+        redge = (np.arange(N) % E).astype(np.int32)
+    say("chunked mid shape", N, K, B, E)
+    assert_chain_parity(cost, rtab, redge, f"chunked mid N={N} K={K} B={B} E={E}")
+
+
+@pytest.mark.parametrize("K,B,N", [(100, 5, 400), (256, 3, 400), (400, 3, 600), (300, 9, 600)])
+@pytest.mark.parametrize("share", [0.0, 0.5, 0.8])
+def test_chunked_patterns_of_unmet_chunks(K, B, N, share):
+    """Zero tables near the start of a share of the chunks: isolated chunks that meet no
+    checkpoint, runs of them, and (share 0) none that meets, on every form for K > 64."""
+    need_gpu()
+    from paper_2504_00598_amd import cfp_r_limit
+    rs = np.random.default_rng([71, K, B, int(10 * share)])
+    cost = rs.integers(0, 1000, size=(B, N, K)).astype(np.int32)
+    rtab = _no_switch_tables(rs, 3, K, cfp_r_limit(0, K))
+    rtab[2] = 0
+    redge = rs.integers(0, 2, size=N).astype(np.int32)
+    for r in range(0, N, 32 if K <= 256 else 64):
+        if r and rs.random() < share:
+            redge[min(N - 1, r + int(rs.integers(1, 20)))] = 2
+    say("unmet patterns", K, B, share)
+    assert_chain_parity(cost, rtab, redge, f"unmet K={K} B={B} share={share}")
+
+
+@pytest.mark.parametrize("K", [100, 200, 300])
+def test_chunked_repeating_costs_and_range(K):
+    """Costs that repeat with the edge map, then an R out of range on a map that travels in
+    the arguments and on an uploaded one, on the same workspace as a clean call."""
+    need_gpu()
+    import torch
+    from paper_2504_00598_amd import CFP_ST_BADINPUT, cfp_r_limit, search
+    rs = np.random.default_rng([72, K])
+    N, B, E = 300, 3, 6
+    cost = np.ascontiguousarray(rs.integers(0, 10_000, size=(B, E, K)).astype(np.int32)[:, np.arange(N) % E])
+    rtab = rs.integers(0, 10_000, size=(E, K, K)).astype(np.int32)
+    periodic, other = (np.arange(N) % E).astype(np.int32), rs.integers(0, E, size=N).astype(np.int32)
+    bad = rtab.copy()
+    bad[E - 1, K - 1, 1] = cfp_r_limit(0, K)
+    say("repeating costs", K)
+    o_opt, o_plan, o_st = O.chain(cost, rtab, periodic, nthreads=oracle_threads())
+    r = search.dp_chain(dev(cost), dev(rtab), periodic)
+    torch.cuda.synchronize()
+    for _ in range(2):
+        np.testing.assert_array_equal(r.status.cpu().numpy(), o_st)
+        np.testing.assert_array_equal(r.opt.cpu().numpy(), o_opt)
+        np.testing.assert_array_equal(r.plan.cpu().numpy(), o_plan)
+        for redge in (periodic, other):
+            q = search.dp_chain(dev(cost), dev(bad), redge, ws=r.ws)
+            torch.cuda.synchronize()
+            assert (q.status.cpu().numpy() == CFP_ST_BADINPUT).all()
+        r = search.dp_chain(dev(cost), dev(rtab), periodic, ws=r.ws)
+        torch.cuda.synchronize()
