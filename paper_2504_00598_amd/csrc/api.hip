@@ -23,7 +23,7 @@ WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables) {
   L.table = off;
   size_t cells = (size_t)batch * n * k;
   if (variant == CFP_V_MEM) {
-    off = align_up(off + cells * (size_t)n_mem * L.elem);
+    off = align_up(off + cells * (size_t)mem_stride(n_mem));
     L.mem = off;
     off = align_up(off + cells);
     L.memreg = off;

@@ -58,7 +58,7 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 struct WsLayout {
   size_t redge = 0;    // int32 [N]
   size_t result = 0;   // SearchResult [B]
-  size_t table = 0;    // argmin entries [B][N][K] (chain, scan) or [B][N][K][M] (mem)
+  size_t table = 0;    // argmin entries [B][N][K] (chain, scan) or [B][N][K][M rounded up to 16] (mem)
   size_t mem = 0;      // memory variant: copy of mem [B][N][K]
   size_t memreg = 0;   // memory variant: state order, packed tables, chunk flags and halo ring
   size_t memreg_bytes = 0;
@@ -141,6 +141,7 @@ hipError_t launch_chain_fwd_k64(const cfp_chain_desc &d, const int32_t *redge_de
 hipError_t launch_chain_fwd_generic(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table,
                                     SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,
                                     hipStream_t st);
+int mem_stride(int n_mem);  // bucket stride of the memory variant's argmin table
 bool chain_mem_supported(int k, int n_tables);
 int32_t mem_r_limit(int k);
 size_t mem_region_bytes(int n, int k, int batch, int n_mem, int n_tables);

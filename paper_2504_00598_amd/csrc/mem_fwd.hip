@@ -54,6 +54,7 @@
 // o[m - dmin] + cm, and a saturated y exceeds cm by more than QCAP.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "cfp_internal.h"
 #include "common.h"
@@ -83,6 +84,8 @@ struct MemShape {
   static constexpr int THREADS = 64 * (CW + 2);    // and a loading and a storing wave
   static constexpr int SPL = KP / 4;        // states per lane
   static constexpr int TB = KP / 32;        // blocks of 32 predecessors
+  static constexpr bool HALF = KP % 32 != 0;       // and one of 16 at the end
+  static constexpr int NB = SPL % 8 ? 4 : 8;       // states per turn of phase B
   static constexpr bool RLDS = KP <= 64;    // tables staged in LDS by the loading wave
   static constexpr int SP = kMemShift + kMemChunk + 1;  // product buffer row stride (words)
   static constexpr int QS = KP + 4;         // row stride of a wave's rows (words)
@@ -91,7 +94,9 @@ struct MemShape {
   static_assert(SPL % kMemPD == 0 && SPL % 4 == 0 && SPL % 2 == 0, "items and record words per lane");
 };
 
-static int mem_kp(int k) { return k <= 32 ? 32 : k <= 64 ? 64 : k <= 96 ? 96 : k <= 128 ? 128 : k <= 192 ? 192 : 256; }
+// Padded states: multiples of 16 up to 128, where the products' K^2 cost of the
+// padding is the larger part of a step (45 states as 48 instead of 64: 57%).
+static int mem_kp(int k) { return k <= 128 ? (k + 15) / 16 * 16 : k <= 192 ? 192 : 256; }
 static int mem_bits(int k) { return k <= 32 ? 5 : k <= 64 ? 6 : k <= 128 ? 7 : 8; }
 
 // Per-(search, block) records: cost cst[s] (kSat for an unavailable or
@@ -171,7 +176,8 @@ struct MemArgs {
   MemWs w;
   int N, K, M, B;
   int b0, nb, B8;        // searches b0 .. b0+nb-1 of this launch; grid = nchunk * B8
-  uint8_t *table;        // [B][N][K][M]
+  uint8_t *table;        // [B][N][K][MS]
+  int MS;                // bucket stride of the table
   SearchResult *res;
   const WsHeader *hdr;
   int64_t *opt;
@@ -315,7 +321,6 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
   const bool consumer = j > 0;
   const size_t chunk_id = (size_t)b * W.nchunk + j;
   const size_t rowbase = (size_t)b * N;
-  const bool vec16 = (M % 16) == 0;
   if (tid == 0) s_timeout = 0;
 
 
@@ -330,7 +335,7 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
     uint64_t *my_ring = W.ring + chunk_id * kMemSlots * SW;
     const uint64_t *lo_ring = W.ring + lo_id * kMemSlots * SW;
     constexpr int HW = KP * 16 / 64;       // product words of a slot per lane
-    constexpr int HB = 8;                  // words per lane moved at once (HW is a multiple of 8)
+    constexpr int HB = HW % 8 ? 4 : 8;     // words per lane moved at once
     static_assert(HW % HB == 0, "slot words per lane in whole blocks");
     constexpr int RW = RLDS ? KP * KP / 256 : 1;  // 16-byte table pieces per lane
     bool timeout = false;
@@ -469,21 +474,14 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
         int seen = s_upcons;
         if (seen < t - kMemSlots && !spin_until(up_cons, t - kMemSlots, seen)) timeout = true;
       };
-      // Argmin bytes of step t (parity buffer t & 1) to the table, the buckets
-      // within the budget only.
+      // Argmin bytes of step t (parity buffer t & 1) to the table, the pieces of
+      // 16 buckets that reach into the budget only.
       auto flush = [&](int t) __attribute__((always_inline)) {
         for (int x = lane; x < NBK * K; x += 64) {
           const int bb = x / K, s = x % K;
-          const int lim = top + 1 - (m0 + 16 * bb);
-          if (lim <= 0) continue;
-          uint8_t *dst = a.table + ((rowbase + t) * K + s) * (size_t)M + m0 + 16 * bb;
-          const u32x4 v = *(const u32x4 *)&argb[t & 1][bb][s][0];
-          if (vec16 && lim >= 16) {
-            *(u32x4 *)dst = v;
-          } else {
-            const uint8_t *vb = (const uint8_t *)&v;
-            for (int q = 0; q < 16 && q < lim; ++q) dst[q] = vb[q];
-          }
+          if (m0 + 16 * bb > top) continue;
+          uint8_t *dst = a.table + ((rowbase + t) * K + s) * (size_t)a.MS + m0 + 16 * bb;
+          *(u32x4 *)dst = *(const u32x4 *)&argb[t & 1][bb][s][0];
         }
       };
       int published = -1;
@@ -589,6 +587,10 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
   auto item_ptr = [&](int e, int tb, int k) __attribute__((always_inline)) {
     return W.rT + ((size_t)e * KP + s0 + k) * KP + 32 * tb + l16;
   };
+  constexpr bool HALF = S::HALF;
+  constexpr int NT = TB + (HALF ? 1 : 0);  // predecessor blocks, the short one included
+  // second word of an item of block tb (the short block has none: its first again)
+  auto half2 = [&](int tb) __attribute__((always_inline)) { return HALF && tb >= TB ? 0 : 16; };
   u32x2 rr[PD];
   int e_cur = N > 1 ? redge[1] : 0;
   int e_nn = N > 2 ? redge[2] : e_cur;
@@ -596,7 +598,7 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
 #pragma unroll
     for (int x = 0; x < PD; ++x) {
       const uint32_t *p = item_ptr(e_cur, x / SPL, x % SPL);  // PD <= SPL: items of block 0
-      rr[x] = u32x2{p[0], p[16]};
+      rr[x] = u32x2{p[0], p[half2(0)]};
     }
   }
 
@@ -630,7 +632,7 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
 #pragma unroll
       for (int x = 0; x < PD; ++x) {
         const uint32_t *p = &rbuf[par][s0 + x][l16];
-        rr[x] = u32x2{p[0], p[16]};
+        rr[x] = u32x2{p[0], p[half2(0)]};
       }
     }
 
@@ -638,14 +640,17 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
     uint32_t acc[SPL];
 #pragma unroll
     for (int k = 0; k < SPL; ++k) acc[k] = kSat;
-    for (int tb = 0; tb < TB; ++tb) {
+    // One block of 32 predecessors (FULL) or the last 16.
+    auto block = [&](int tb, auto Full) __attribute__((always_inline)) {
+      constexpr bool FULL = decltype(Full)::value;
+      constexpr int NQ = FULL ? 32 : 16;
       uint32_t qb[32];
       if constexpr (ALIAS) {
 #pragma unroll
-        for (int x = 0; x < 32; ++x) qb[x] = Pb[0][32 * tb + x][col];
+        for (int x = 0; x < NQ; ++x) qb[x] = Pb[0][32 * tb + x][col];
       } else {
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
+        for (int v = 0; v < NQ / 4; ++v) {
           const u32x4 q = *(const u32x4 *)&Qw[blk][m][32 * tb + 4 * v];
           qb[4 * v] = q.x;
           qb[4 * v + 1] = q.y;
@@ -663,26 +668,30 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
           const int tn = wrap ? tb + 1 : tb;
           const int kn = wrap ? kk - SPL : kk;
           if constexpr (RLDS) {
-            if (tn < TB) {  // within the step (the next step's table is staged later)
+            if (FULL ? tn < NT : !wrap) {  // within the step (the next step's table is staged later)
               const uint32_t *p = &rbuf[par][s0 + kn][32 * tn + l16];
-              rr[(k + u) % PD] = u32x2{p[0], p[16]};
+              rr[(k + u) % PD] = u32x2{p[0], p[half2(tn)]};
             }
           } else {
-            const bool nstep = wrap && tn >= TB;
+            const bool nstep = wrap && tn >= NT;
             const uint32_t *p = item_ptr(nstep ? e_next : e_cur, nstep ? 0 : tn, kn);
-            rr[(k + u) % PD] = u32x2{p[0], p[16]};
+            rr[(k + u) % PD] = u32x2{p[0], p[half2(nstep ? 0 : tn)]};
           }
         }
         mcand4x2<0, true>(acc[k], acc[k + 1], ra.x, rb.x, qb[0], qb[1], qb[2], qb[3]);
         mcand4x2<4, false>(acc[k], acc[k + 1], ra.x, rb.x, qb[4], qb[5], qb[6], qb[7]);
         mcand4x2<8, false>(acc[k], acc[k + 1], ra.x, rb.x, qb[8], qb[9], qb[10], qb[11]);
         mcand4x2<12, false>(acc[k], acc[k + 1], ra.x, rb.x, qb[12], qb[13], qb[14], qb[15]);
-        mcand4x2<0, true>(acc[k], acc[k + 1], ra.y, rb.y, qb[16], qb[17], qb[18], qb[19]);
-        mcand4x2<4, false>(acc[k], acc[k + 1], ra.y, rb.y, qb[20], qb[21], qb[22], qb[23]);
-        mcand4x2<8, false>(acc[k], acc[k + 1], ra.y, rb.y, qb[24], qb[25], qb[26], qb[27]);
-        mcand4x2<12, false>(acc[k], acc[k + 1], ra.y, rb.y, qb[28], qb[29], qb[30], qb[31]);
+        if constexpr (FULL) {
+          mcand4x2<0, true>(acc[k], acc[k + 1], ra.y, rb.y, qb[16], qb[17], qb[18], qb[19]);
+          mcand4x2<4, false>(acc[k], acc[k + 1], ra.y, rb.y, qb[20], qb[21], qb[22], qb[23]);
+          mcand4x2<8, false>(acc[k], acc[k + 1], ra.y, rb.y, qb[24], qb[25], qb[26], qb[27]);
+          mcand4x2<12, false>(acc[k], acc[k + 1], ra.y, rb.y, qb[28], qb[29], qb[30], qb[31]);
+        }
       }
-    }
+    };
+    for (int tb = 0; tb < TB; ++tb) block(tb, std::integral_constant<bool, true>{});
+    if constexpr (HALF) block(TB, std::integral_constant<bool, false>{});
     e_cur = e_next;
 #pragma unroll
     for (int k = 0; k < SPL; ++k) Pb[pb][s0 + k][col] = acc[k];
@@ -696,10 +705,10 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
     if constexpr (ALIAS) dm = rdmin[par];
     const int64_t base = O[col - dm];
 #pragma unroll
-    for (int v0 = 0; v0 < SPL; v0 += 8) {  // eight states at a time (registers)
+    for (int v0 = 0; v0 < SPL; v0 += S::NB) {  // up to eight states at a time (registers)
       if constexpr (ALIAS) read_records(par, v0);
       constexpr int V = ALIAS ? 0 : 1;  // ALIAS: the records of states v0 .. v0+7 are in cr[0..7]
-      constexpr int NK = SPL < 8 ? SPL : 8;
+      constexpr int NK = S::NB;
       uint32_t pvs[NK];
       int64_t ods[NK];
 #pragma unroll
@@ -761,104 +770,115 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
 
 // Plan recovery for the memory variant.  The state is (s, m): the table gives
 // the predecessor strategy t = arg[i][s][m] and the budget shrinks by
-// mem[i][s].  The chase runs in windows of `win` steps: the argmin rows of the
-// window are loaded into LDS for the only buckets it can reach,
-// [m - kMemShift*(win-1), m], then one thread follows them.
-constexpr int kMemWinMax = 12;
-constexpr size_t kMemTbLds = 96 * 1024;
+// mem[i][s].  The chase runs in windows of W rows whose reachable buckets are
+// loaded into LDS, then one thread follows them.  Row k of a window that starts
+// at bucket m can only be read at m - dm k .. m, dm the search's largest shift,
+// so it takes ns(k) 16-byte pieces of each state, counted down from the piece
+// of m.  A window costs one memory latency, its bytes at the rate of one
+// compute unit and the dependent LDS reads; the packed triangle holds about
+// twice the rows of a rectangle (16 searches of 288 blocks, K = 32, shifts up
+// to 8: 28 rows per window instead of 12).
+constexpr int kMemTbThreads = 1024;
+constexpr int kMemTbWaves = kMemTbThreads / 64;
+constexpr int kMemTbLoads = 8;       // pieces in flight per lane
+constexpr int kMemTbRows = 64;       // most rows per window
+constexpr int kMemTbLds = 144 * 1024;
 
-__host__ __device__ constexpr int mem_win_width(int win) { return (kMemShift * (win - 1) + 16 + 15) / 16 * 16; }
+__device__ __forceinline__ int mem_tb_pieces(int dm, int k) { return ((dm * k + 15) >> 4) + 1; }
 
-static int mem_window(int k) {
-  int win = kMemWinMax;
-  while (win > 1 && (size_t)win * k * mem_win_width(win) + (size_t)win * k > kMemTbLds) --win;
-  return win;
-}
-
-constexpr int kMemTbThreads = 1024;  // every 16-byte piece of a window in flight at once
-constexpr int kMemTbLoads = 8;       // pieces per thread and pass
-
-__global__ __launch_bounds__(kMemTbThreads) void mem_tb_kernel(int N, int K, int M, int win,
-                                                          const uint8_t *__restrict__ table,
-                                                          const uint8_t *__restrict__ mem_copy,
-                                                          const SearchResult *__restrict__ res,
-                                                          int32_t *__restrict__ plan) {
-  // window rows are 16-byte aligned copies of [lo16, lo16 + width) of a table row
-  extern __shared__ __align__(16) uint8_t wbuf[];  // [win][K][width] then mem rows [win][K]
-  __shared__ int cur_s, cur_m;
-  const int b = blockIdx.x, tid = threadIdx.x;
+__global__ __launch_bounds__(kMemTbThreads) void mem_tb_kernel(int N, int K, int MS, const uint8_t *__restrict__ table,
+                                                               const uint8_t *__restrict__ mem_copy,
+                                                               const SearchResult *__restrict__ res,
+                                                               int32_t *__restrict__ plan) {
+  __shared__ __align__(16) uint8_t wbuf[kMemTbLds];  // mem rows [W][K], then the rows' pieces [K][ns(k)][16]
+  __shared__ int rowoff[kMemTbRows + 1];
+  __shared__ int cur_s, cur_m, s_w, s_dm;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   int32_t *pb = plan + (size_t)b * N;
   if (res[b].status != CFP_ST_OK) {
     for (int i = tid; i < N; i += blockDim.x) pb[i] = -1;
     return;
   }
-  const int width = mem_win_width(win);
-  uint8_t *mrow = wbuf + (size_t)win * K * width;
-  const bool vec = (M % 16) == 0;
+  // The search's largest shift (a few KB read once; a counter kept by the forward
+  // call's row checks cost 50 us in atomics on one word per search).
+  if (tid == 0) s_dm = 0;
+  __syncthreads();
+  {
+    const uint8_t *mb = mem_copy + (size_t)b * N * K;
+    const int count = N * K, head = min(count, (int)(-(uintptr_t)mb & 3)), words = (count - head) / 4;
+    uint32_t x = 0;
+    for (int q = tid; q < words; q += kMemTbThreads) {
+      const uint32_t v = *(const uint32_t *)(mb + head + 4 * q);
+      x = max(max(x, v & 0xFF), max(max((v >> 8) & 0xFF, (v >> 16) & 0xFF), v >> 24));
+    }
+    if (tid < head) x = max(x, (uint32_t)mb[tid]);
+    if (tid < count - head - 4 * words) x = max(x, (uint32_t)mb[head + 4 * words + tid]);
+    for (int o = 32; o >= 1; o >>= 1) x = max(x, (uint32_t)__shfl_xor((int)x, o, 64));
+    if (lane == 0) atomicMax(&s_dm, (int)x);
+  }
+  __syncthreads();
+  const int dm = s_dm;
   if (tid == 0) {
     cur_s = res[b].final_state;
     cur_m = res[b].final_m;
     pb[N - 1] = cur_s;
+    // as many rows as fit; the first always does (K <= 256: 256 + 4096 bytes)
+    int w = 0, pieces = 0;
+    while (w < kMemTbRows && w < N - 1) {
+      const int next = pieces + K * mem_tb_pieces(dm, w);
+      if (((w + 1) * K + 15) / 16 * 16 + next * 16 > kMemTbLds) break;
+      rowoff[w] = pieces;
+      pieces = next;
+      ++w;
+    }
+    s_w = w;
   }
   __syncthreads();
+  const int W = s_w;
+  uint8_t *mrow = wbuf;
+  typedef uint32_t u32x4l __attribute__((ext_vector_type(4)));  // copies stay in registers
+  u32x4l *rows = (u32x4l *)(wbuf + (W * K + 15) / 16 * 16);
   for (int i = N - 1; i >= 1;) {
-    const int steps = i < win ? i : win;
+    const int steps = min(i, W);
     const int mtop = cur_m;
-    const int lo = mtop - kMemShift * (steps - 1) > 0 ? mtop - kMemShift * (steps - 1) : 0;
-    const int lo16 = lo & ~15;
-    const int n16 = (mtop - lo16) / 16 + 1;  // 16-byte pieces covering [lo16, mtop]
-    if (vec) {
-      // all pieces of a pass are loaded before any is stored, so the window
-      // costs about one memory latency
-      const int total = steps * K * n16;
-      for (int x0 = 0; x0 < total; x0 += kMemTbLoads * kMemTbThreads) {
-        typedef uint32_t u32x4l __attribute__((ext_vector_type(4)));  // copies stay in registers
+    // One row per wave at a time, short and long rows in turn.
+    for (int r = 0; r * kMemTbWaves < steps; ++r) {
+      const int k = r * kMemTbWaves + ((r & 1) ? kMemTbWaves - 1 - wid : wid);
+      if (k >= steps) continue;
+      const int ns = mem_tb_pieces(dm, k), total = K * ns;
+      const float inv = 1.0f / (float)ns;
+      const uint8_t *src = table + ((size_t)b * N + (i - k)) * K * MS;
+      u32x4l *dst = rows + rowoff[k];
+      for (int x0 = 0; x0 < total; x0 += 64 * kMemTbLoads) {
         u32x4l v[kMemTbLoads];
 #pragma unroll
         for (int u = 0; u < kMemTbLoads; ++u) {
-          const int x = x0 + u * kMemTbThreads + tid;
-          const int k = x / (K * n16), t = (x / n16) % K, c = x % n16;
-          if (x < total)
-            v[u] = *(const u32x4l *)&table[(((size_t)b * N + (i - k)) * K + t) * M + lo16 + 16 * c];
+          const int x = min(x0 + 64 * u + lane, total - 1);
+          const int t = (int)(((float)x + 0.5f) * inv), c = x - t * ns;  // x < 2^14: exact
+          v[u] = *(const u32x4l *)(src + (size_t)t * MS + 16 * max((mtop >> 4) - c, 0));
         }
 #pragma unroll
         for (int u = 0; u < kMemTbLoads; ++u) {
-          const int x = x0 + u * kMemTbThreads + tid;
-          const int k = x / (K * n16), t = (x / n16) % K, c = x % n16;
-          if (x < total) *(u32x4l *)&wbuf[((size_t)k * K + t) * width + 16 * c] = v[u];
-        }
-      }
-    } else {
-      const int wd = mtop - lo16 + 1;
-      const int total = steps * K * wd;
-      for (int x0 = 0; x0 < total; x0 += 16 * kMemTbThreads) {
-        uint8_t v[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          const int x = x0 + u * kMemTbThreads + tid;
-          const int k = x / (K * wd), t = (x / wd) % K, c = x % wd;
-          v[u] = x < total ? table[(((size_t)b * N + (i - k)) * K + t) * M + lo16 + c] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          const int x = x0 + u * kMemTbThreads + tid;
-          const int k = x / (K * wd), t = (x / wd) % K, c = x % wd;
-          if (x < total) wbuf[((size_t)k * K + t) * width + c] = v[u];
+          const int x = x0 + 64 * u + lane;
+          if (x < total) dst[x] = v[u];
         }
       }
     }
-    for (int x = tid; x < steps * K; x += blockDim.x)
-      mrow[x] = mem_copy[((size_t)b * N + (i - x / K)) * K + x % K];
+    for (int x = tid; x < steps * K; x += kMemTbThreads) {
+      const int k = x / K;
+      mrow[x] = mem_copy[((size_t)b * N + (i - k)) * K + (x - k * K)];
+    }
     __syncthreads();
     if (tid == 0) {
       int s = cur_s, m = mtop;
       for (int k = 0; k < steps; ++k) {
-        int t = wbuf[((size_t)k * K + s) * width + (m - lo16)];
-        if (t >= K) t = K - 1;
-        m -= mrow[k * K + s];
-        if (m < lo) m = lo;  // cannot happen on a consistent table; stay inside the window
-        pb[i - k - 1] = t;
-        s = t;
+        const int ns = mem_tb_pieces(dm, k);
+        const int c = min((mtop >> 4) - (m >> 4), ns - 1);  // (the bound holds on a consistent table)
+        const int t = ((const uint8_t *)(rows + rowoff[k] + s * ns + c))[m & 15];
+        m = max(m - (int)mrow[k * K + s], 0);
+        s = min(t, K - 1);
+        pb[i - k - 1] = s;
       }
       cur_s = s;
       cur_m = m;
@@ -868,11 +888,12 @@ __global__ __launch_bounds__(kMemTbThreads) void mem_tb_kernel(int N, int K, int
   }
 }
 
+// Row stride of the argmin table along the buckets: whole 16-byte pieces.
+int mem_stride(int n_mem) { return (n_mem + 15) / 16 * 16; }
+
 hipError_t launch_traceback_mem(int n, int k, int batch, int n_mem, const uint8_t *table, const uint8_t *mem,
                                 const SearchResult *res, int32_t *plan, hipStream_t st) {
-  const int win = mem_window(k);
-  const size_t lds = (size_t)win * k * mem_win_width(win) + (size_t)win * k;
-  hipLaunchKernelGGL(mem_tb_kernel, dim3(batch), dim3(kMemTbThreads), lds, st, n, k, n_mem, win, table, mem, res,
+  hipLaunchKernelGGL(mem_tb_kernel, dim3(batch), dim3(kMemTbThreads), 0, st, n, k, mem_stride(n_mem), table, mem, res,
                      plan);
   return hipGetLastError();
 }
@@ -962,6 +983,7 @@ static hipError_t launch_mem(const cfp_chain_desc &d, const uint8_t *mem, int n_
   a.N = N;
   a.K = K;
   a.M = n_mem;
+  a.MS = mem_stride(n_mem);
   a.B = B;
   a.table = table;
   a.res = res;
@@ -993,9 +1015,13 @@ hipError_t launch_chain_mem_fwd(const cfp_chain_desc &d, const uint8_t *mem, int
   case KPV:               \
     return launch_mem<KPV>(d, mem, n_mem, budget, redge_dev, table, mem_copy, region, res, hdr, opt, status, frontier, st);
   switch (mem_kp(d.k)) {
+    CFP_MEM_CASE(16)
     CFP_MEM_CASE(32)
+    CFP_MEM_CASE(48)
     CFP_MEM_CASE(64)
+    CFP_MEM_CASE(80)
     CFP_MEM_CASE(96)
+    CFP_MEM_CASE(112)
     CFP_MEM_CASE(128)
     CFP_MEM_CASE(192)
     CFP_MEM_CASE(256)

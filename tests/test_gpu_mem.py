@@ -201,3 +201,30 @@ def test_repeat_is_bit_identical():
         again = run_mem(d["cost"], d["rtab"], d["redge"], d["mem"], d["M"], d["budget"])
         for a, b in zip(first, again):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("N,K,M", [(30, 1, 33), (30, 16, 64), (25, 17, 50), (25, 47, 130), (20, 48, 129), (20, 49, 70),
+                                   (15, 80, 90), (15, 97, 66), (12, 112, 130), (12, 128, 65)])
+def test_padded_state_counts(N, K, M):
+    """Every padded state count up to 128 (multiples of 16, odd ones with a last block of 16
+    predecessors), bucket counts that are not whole 16-byte pieces."""
+    need_gpu()
+    say("mem padded states", N, K, M)
+    cost, rtab, redge, mem = mem_case([80, N, K, M], 4, N, K, 5, 0, 1_000_000, 0, 9, M)
+    cost[np.random.default_rng([81, K]).random(cost.shape) < 0.05] = INF
+    budget = np.array([M - 1, M // 2, M // 3, 15], np.int32)
+    assert_mem_parity(cost, rtab, redge, mem, M, budget, f"N={N} K={K} M={M}")
+
+
+@pytest.mark.parametrize("N,K,mhi", [(150, 8, 1), (150, 8, 2), (90, 30, 17), (130, 5, 17), (20, 250, 17)])
+def test_traceback_windows(N, K, mhi):
+    """Windows of the plan recovery: no memory at all (64 rows each), small and the largest
+    shifts (16), whole pieces and single buckets above 0, budgets that end in every place
+    of a 16-byte piece."""
+    need_gpu()
+    say("mem traceback windows", N, K, mhi)
+    M = 16 * N // 2 + 40 if K < 100 else 200
+    M = min(M, 1500)
+    cost, rtab, redge, mem = mem_case([82, N, K, mhi], 6, N, K, 3, 0, 1000, 0, mhi, M)
+    budget = np.array([M - 1, M - 2, M - 9, M // 2, M // 2 + 16, M // 3], np.int32)
+    assert_mem_parity(cost, rtab, redge, mem, M, budget, f"windows N={N} K={K} mhi={mhi}")
