@@ -3,6 +3,7 @@
 // first HIP call, so argument errors never touch the device.
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <vector>
@@ -58,8 +59,8 @@ WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables) {
     off = align_up(off + cw_region_bytes(n, k, n_tables, batch));
   }
   if (variant == CFP_V_SEG) {
-    L.seg = off;
-    off = align_up(off + seg_region_bytes(n, k, batch));
+    L.seg = off;  // of either form
+    off = align_up(off + std::max(seg_region_bytes(n, k, batch), seg_class_bytes(n, batch)));
   }
   if (variant == CFP_V_SCAN) {
     L.scan = off;
@@ -72,16 +73,15 @@ WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables) {
 
 EdgeMap edge_map(const int32_t *redge, int n) {
   EdgeMap m{};
-  // smallest p with redge[i] == redge[i + p] for all i >= 1 (entry 0 is unused)
-  for (int p = 1; p <= kEdgePeriod; ++p) {
-    int i = 1;
-    while (i + p < n && redge[i] == redge[i + p]) ++i;
-    if (i + p < n) continue;
+  // the shortest period (entry 0 is unused), from the chain's end backwards
+  for (int p = 1; p < kEdgeWords; ++p) {
+    int i = n - 1 - p;
+    while (i >= 1 && redge[i] == redge[i + p]) --i;
+    const int head = i < 1 ? 1 : i + 1;
+    if (head + p > kEdgeWords) continue;
     m.period = p;
-    for (int x = 0; x < p; ++x) {
-      const int row = x ? x : p;  // the first row i >= 1 of phase x
-      m.map[x] = row < n ? redge[row] : 0;
-    }
+    m.head = head;
+    for (int x = 1; x < head + p && x < n; ++x) m.map[x] = redge[x];
     break;
   }
   return m;
@@ -582,6 +582,14 @@ int cfp_dp_segments(const cfp_segment_desc *d, void *ws, size_t ws_bytes, int64_
   hipStream_t st = (hipStream_t)stream;
   uint8_t *w = (uint8_t *)ws;
   const cfp_chain_desc c = as_chain(d);
+  if (seg_class_supported(*d)) {
+    const EdgeMap em = edge_map(d->redge, d->n_segments);
+    if (em.period == 0 && (rc = upload_header(&c, CFP_V_SEG, 0, L, ws, st)) != CFP_OK) return rc;
+    return launch_seg_class(*d, (const int32_t *)(w + L.redge), em, w + L.seg, (SearchResult *)(w + L.result), opt,
+                            status, st) == hipSuccess
+               ? CFP_OK
+               : CFP_ERR_HIP;
+  }
   // the search kernels check the range of rbound themselves and read the edge
   // map from the workspace only when it is too long for the kernel arguments
   if (!seg_edges_in_args(d->n_segments, d->n_tables) && (rc = upload_header(&c, CFP_V_SEG, 0, L, ws, st)) != CFP_OK)
@@ -600,6 +608,11 @@ int cfp_traceback_segments(const cfp_segment_desc *d, void *ws, size_t ws_bytes,
   WsLayout L = layout(CFP_V_SEG, d->n_segments, d->k, d->batch, 0, d->n_tables);
   if (!ws || ws_bytes < L.total) return CFP_ERR_WORKSPACE;
   uint8_t *w = (uint8_t *)ws;
+  if (seg_class_supported(*d))
+    return launch_seg_class_tb(*d, w + L.seg, (const SearchResult *)(w + L.result), plan, (hipStream_t)stream) ==
+                   hipSuccess
+               ? CFP_OK
+               : CFP_ERR_HIP;
   const hipError_t e = launch_traceback_chain(d->n_segments, d->k, d->batch, L.elem, w + L.table,
                                               (const SearchResult *)(w + L.result), (uint16_t *)(w + L.maps),
                                               (int32_t *)(w + L.bounds), L.nchunks, plan, (hipStream_t)stream);

@@ -38,17 +38,20 @@ struct SearchResult {
   int32_t pad;
 };
 
-// Edge map of a call: a map that repeats with a short period travels in the
-// arguments of the call's first launch, which writes it out for the others, so
-// that nothing has to be uploaded (period 0: the map is uploaded).
-constexpr int kEdgePeriod = 64;
+// Edge map of a call: a map that repeats with a short period after a short head
+// (a first layer of its own) travels in the arguments of the call's first
+// launch, which writes it out for the others, so that nothing has to be
+// uploaded (period 0: the map is uploaded).
+constexpr int kEdgeWords = 64;
 struct EdgeMap {
-  int32_t period;
-  int32_t map[kEdgePeriod];   // table of the rows i = x mod period, i >= 1
+  int32_t period, head;       // row i < head: map[i]; else map[head + (i - head) mod period]
+  int32_t map[kEdgeWords];    // head + period entries
+  __host__ __device__ __forceinline__ int place(int i) const { return i < head ? i : head + (i - head) % period; }
+  __host__ __device__ __forceinline__ int at(int i) const { return map[place(i)]; }
   // The n entries of the map, by all threads of a one-dimensional launch.
   __device__ __forceinline__ void write(int32_t *redge, int n) const {
     if (period == 0) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) redge[i] = map[i % period];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) redge[i] = at(i);
   }
 };
 EdgeMap edge_map(const int32_t *redge, int n);
@@ -91,6 +94,13 @@ bool seg_supported(int k, int n_last, int n_first);
 // header is read and no upload is needed).
 size_t seg_region_bytes(int n, int k, int batch);
 bool seg_edges_in_args(int n, int n_tables);
+// The class form of the segment search (one launch, its own traceback).
+bool seg_class_supported(const cfp_segment_desc &d);
+size_t seg_class_bytes(int n, int batch);
+hipError_t launch_seg_class(const cfp_segment_desc &d, const int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
+                            SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
+hipError_t launch_seg_class_tb(const cfp_segment_desc &d, const uint8_t *region, const SearchResult *res, int32_t *plan,
+                               hipStream_t st);
 hipError_t launch_seg_fwd(const cfp_segment_desc &d, const int32_t *redge_dev, uint8_t *table, uint8_t *region,
                           SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status, hipStream_t st);
 hipError_t launch_chain_fwd(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *table, int elem,

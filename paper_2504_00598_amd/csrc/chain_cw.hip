@@ -976,7 +976,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   using S = CwShape<KP>;
   __shared__ __align__(16) CwSmem<KP> sm;
   __shared__ uint32_t s_row[KP];  // a true end row of the last chunk accounted
-  __shared__ int s_q, s_flags;
+  __shared__ int s_q;
   __shared__ int64_t s_sum;
   __shared__ uint32_t s_fin[kCWaves];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -985,13 +985,9 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   const int64_t *dk = a.dck + (size_t)b * a.nq;
   const CwRec *rec = a.rec + (size_t)b * P;
   auto endq = [&](int p) __attribute__((always_inline)) { return (min((p + 1) * a.CL, a.N) - 1) >> 2; };
-  if (wid == 0) {
-    int fl = lane < P ? rec[lane].flags : 0;
-    for (int x = lane; x < a.nbad; x += 64) fl |= a.rbad[x];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) fl |= __shfl_xor(fl, off, 64);
-    if (lane == 0) s_flags = fl;
-  }
+  // flags, combined after the loop so that their loads are in flight during it
+  int fl = tid < P ? rec[tid].flags : 0;
+  for (int x = tid; x < a.nbad; x += kCThreads) fl |= a.rbad[x];
   // Chunk 0 runs from the true first row.  Invariant at the top of the loop:
   // chunks < p are accounted in `total`; if spec_true, the speculative end row
   // of chunk p-1 is a true row, otherwise s_row holds the true end row of chunk
@@ -1063,15 +1059,14 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   const uint32_t xv = spec_true ? a.ckrow[((size_t)b * a.nq + a.nq - 1) * KP + ms] : s_row[ms];
   const uint32_t pk = cw_wave_min((tid < KP && ms < a.K) ? (xv | (uint32_t)ms) : kSat);
   if (lane == 0) s_fin[wid] = pk;
-  __syncthreads();
+  const int timeout = __syncthreads_or(fl & 4), bad = __syncthreads_or(fl & 1), infeasible = __syncthreads_or(fl & 2);
   if (tid == 0) {
     uint32_t fin = s_fin[0];
     for (int w = 1; w < kCWaves; ++w) fin = umin(fin, s_fin[w]);
-    const int fl = s_flags;
     int st = CFP_ST_OK;
-    if (fl & 4) st = CFP_ST_TIMEOUT;
-    else if (fl & 1) st = CFP_ST_BADINPUT;
-    else if (fl & 2) st = CFP_ST_INFEASIBLE;
+    if (timeout) st = CFP_ST_TIMEOUT;
+    else if (bad) st = CFP_ST_BADINPUT;
+    else if (infeasible) st = CFP_ST_INFEASIBLE;
     else if ((fin >> S::BITS) != 0) st = CFP_ST_OVERFLOW;
     status[b] = st;
     opt[b] = st == CFP_ST_OK ? total : INT64_MAX;

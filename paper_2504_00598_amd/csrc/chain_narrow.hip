@@ -155,10 +155,12 @@ __device__ __forceinline__ void narrow_run(const NarrowArgs &a, const u32x4 *tab
   // Periodic edge map: e1 is the table of the next row, ph the phase of the row
   // after that one.
   int ph = 0, e1 = 0;
-  auto next_phase = [&](int x) __attribute__((always_inline)) { return x + 1 == a.em.period ? 0 : x + 1; };
+  auto next_phase = [&](int x) __attribute__((always_inline)) {
+    return x + 1 == a.em.head + a.em.period ? a.em.head : x + 1;
+  };
   int e0;
   if (PER) {
-    ph = r0 % a.em.period;
+    ph = a.em.place(r0);
     e0 = emap[ph];
     ph = next_phase(ph);
     e1 = emap[ph];
@@ -300,7 +302,7 @@ template <int KP, int NW, int MODE, bool PER>
 __global__ __launch_bounds__(64 * NW) void chain_narrow_kernel(NarrowArgs a) {
   using S = NarrowShape<KP>;
   extern __shared__ __align__(16) u32x4 tabs[];
-  __shared__ int emap[kEdgePeriod];
+  __shared__ int emap[kEdgeWords];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, s = lane & (KP - 1);
   const int chunks = MODE == kNSpec ? a.P : a.P - 1;
   const int64_t task = ((int64_t)blockIdx.x * NW + wid) * S::TASKS + lane / KP;
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(64 * NW) void chain_narrow_kernel(NarrowArgs a) {
   NarrowRun run;
   run.q = 0;
   if (MODE == kNFix) run.q = a.ckrow[((size_t)b * a.nq + (r0 / 4 - 1)) * KP + s];
-  if (PER && tid < kEdgePeriod) emap[tid] = a.em.map[tid];
+  if (PER && tid < kEdgeWords) emap[tid] = a.em.map[tid];
   const bool badr = narrow_stage<KP>(a, tabs, 64 * NW);
   const bool anybad = __syncthreads_or(badr);
   narrow_run<KP, MODE, PER>(a, tabs, emap, b, valid, r0, iend, 0, run);
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(64 * NW) void chain_narrow_kernel(NarrowArgs a) {
 template <int KP, bool PER>
 __global__ __launch_bounds__(64) void chain_narrow_final_kernel(NarrowArgs a) {
   extern __shared__ __align__(16) u32x4 tabs[];
-  __shared__ int emap[kEdgePeriod];
+  __shared__ int emap[kEdgeWords];
   const int lane = threadIdx.x, s = lane & (KP - 1);
   const int b = blockIdx.x, P = a.P;
   const int64_t *dk = a.dck + (size_t)b * a.nq;
@@ -378,7 +380,7 @@ __global__ __launch_bounds__(64) void chain_narrow_final_kernel(NarrowArgs a) {
       // Rerun chunk p (the first task of the wave) from q, at least over the
       // rows its fix-up rewrote from a wrong start.
       if (!staged) {
-        if (PER && lane < kEdgePeriod) emap[lane] = a.em.map[lane];
+        if (PER && lane < kEdgeWords) emap[lane] = a.em.map[lane];
         narrow_stage<KP>(a, tabs, 64);
         staged = true;
         __syncthreads();

@@ -555,20 +555,16 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
                                                                                 int32_t *__restrict__ status) {
   __shared__ __align__(16) WaveSmem<kWFinalWaves> sm;
   __shared__ uint32_t s_row[64];  // the true end row of the last chunk accounted
-  __shared__ int s_q, s_flags;
+  __shared__ int s_q;
   __shared__ int64_t s_sum;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int b = blockIdx.x, P = a.P;
   const int64_t *dk = a.dck + (size_t)b * a.nq;
   const WaveRec *rec = a.rec + (size_t)b * P;
   auto endq = [&](int p) __attribute__((always_inline)) { return (min((p + 1) * a.CB * kWU, a.N) - 1) >> 2; };
-  if (wid == 0) {
-    int fl = lane < P ? rec[lane].flags : 0;
-    for (int x = lane; x < a.nbad; x += 64) fl |= a.rbad[x];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) fl |= __shfl_xor(fl, off, 64);
-    if (lane == 0) s_flags = fl;
-  }
+  // flags, combined after the loop so that their loads are in flight during it
+  int fl = tid < P ? rec[tid].flags : 0;
+  for (int x = tid; x < a.nbad; x += 64 * kWFinalWaves) fl |= a.rbad[x];
   // Chunk 0 runs from the true first row.  At the top of the loop the chunks
   // below p are accounted in `total`; with spec_true the speculative end row of
   // chunk p-1 is its true one (so the fix-up of chunk p is valid), otherwise
@@ -630,14 +626,14 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
     }
   }
   const uint32_t qv = spec_true ? a.ckrow[((size_t)b * a.nq + a.nq - 1) * 64 + lane] : s_row[lane];
+  const int bad = __syncthreads_or(fl & 1), infeasible = __syncthreads_or(fl & 2);
   if (wid != 0) return;
   // The final row has minimum 0: the lowest state at the minimum.
   const uint32_t pk = wave_min(lane < a.K ? (qv | (uint32_t)lane) : kSat);
   if (lane == 0) {
-    const int fl = s_flags;
     int st = CFP_ST_OK;
-    if (fl & 1) st = CFP_ST_BADINPUT;
-    else if (fl & 2) st = CFP_ST_INFEASIBLE;
+    if (bad) st = CFP_ST_BADINPUT;
+    else if (infeasible) st = CFP_ST_INFEASIBLE;
     else if ((pk >> kWBits) != 0) st = CFP_ST_OVERFLOW;
     status[b] = st;
     opt[b] = st == CFP_ST_OK ? total : INT64_MAX;
@@ -736,7 +732,7 @@ hipError_t launch_chain_wave(const cfp_chain_desc &d, int32_t *redge_dev, const 
                      cfp_r_limit(CFP_V_CHAIN, d.k), rbad, em, redge_dev, d.n_blocks);
   // the usual period, and table i for phase i: the table index is a constant per row of a block
   bool periodic = em.period == kWU;
-  for (int i = 0; periodic && i < kWU; ++i) periodic = em.map[i] == i;
+  for (int i = 1; periodic && i < em.head + kWU; ++i) periodic = em.map[i] == i % kWU;
   if (c.NW == 4) {
     if (periodic) launch_wave_passes<12, 4>(a, res, opt, status, st);
     else launch_wave_passes<0, 4>(a, res, opt, status, st);

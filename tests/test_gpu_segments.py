@@ -207,3 +207,58 @@ def test_edge_map_in_arguments_and_in_workspace(B, N, P, S):
     say("seg edge map", B, N, P, S)
     cost, rbound, last, first, redge = seg_case([73, B, N], B, N, P, S, 5, 10_000, 10_000_000)
     assert_seg_parity(cost, rbound, last, first, redge, f"B={B} N={N} K={S ** P}")
+
+
+# Searches whose class minima fit in LDS (about 1400 segments with up to four boundary
+# strategies, 400 with more) run the recurrence over boundary classes; longer ones the
+# chunked form above.
+
+@pytest.mark.parametrize("N,K,L,F,E,B", [(1, 5, 1, 1, 1, 3), (2, 3, 8, 8, 1, 2), (3, 512, 8, 1, 2, 2),
+                                         (17, 512, 1, 8, 3, 3), (40, 100, 5, 2, 200, 2), (33, 7, 4, 4, 3, 5),
+                                         (300, 64, 3, 4, 5, 600), (1390, 9, 3, 3, 4, 2), (1450, 9, 3, 3, 4, 2),
+                                         (380, 30, 6, 7, 4, 2), (470, 30, 6, 7, 4, 2), (20, 50, 3, 3, 3000, 2)])
+def test_class_form_shapes(N, K, L, F, E, B):
+    """Arbitrary maps (empty classes, more classes than plans), unequal boundaries, many
+    tables, chains on both sides of the LDS limit; costs over the whole range in some
+    rows, plans and whole classes that are not available."""
+    need_gpu()
+    from paper_2504_00598_amd import cfp_r_limit, CFP_V_SEG
+    say("segment classes", N, K, L, F, E, B)
+    rs = np.random.default_rng([90, N, K, L, F])
+    last = rs.integers(0, L, size=K).astype(np.uint8)
+    first = rs.integers(0, F, size=K).astype(np.uint8)
+    cost = rs.integers(0, 100_000, size=(B, N, K)).astype(np.int32)
+    wide = rs.random((B, N)) < 0.1
+    cost[wide] = rs.integers(0, 2 ** 31 - 1, size=(int(wide.sum()), K))
+    gone = rs.random((B, N, F)) < 0.2                       # whole first classes
+    cost[gone[:, :, first]] = INF
+    cost[:, :, K // 2] = np.where(cost[:, :, K // 2] == INF, 77, cost[:, :, K // 2])
+    rbound = rs.integers(0, cfp_r_limit(CFP_V_SEG, K), size=(E, L, F)).astype(np.int32)
+    redge = rs.integers(0, E, size=N).astype(np.int32)
+    assert_seg_parity(cost, rbound, last, first, redge, f"classes N={N} K={K} L={L} F={F}")
+
+
+@pytest.mark.parametrize("L,F", [(3, 3), (6, 5)])
+def test_class_form_ties(L, F):
+    """Values in {0, 1}: the lowest plan over every tied class and boundary."""
+    need_gpu()
+    rs = np.random.default_rng([91, L, F])
+    B, N, K = 6, 90, 60
+    cost = rs.integers(0, 2, size=(B, N, K)).astype(np.int32)
+    rbound = rs.integers(0, 2, size=(3, L, F)).astype(np.int32)
+    last, first = rs.integers(0, L, size=K).astype(np.uint8), rs.integers(0, F, size=K).astype(np.uint8)
+    redge = np.resize(np.array([1, 2, 0, 1, 1], np.int32), N)
+    redge[:3] = [2, 2, 0]  # a head of its own before the period
+    say("segment class ties", L, F)
+    assert_seg_parity(cost, rbound, last, first, redge, f"class ties L={L} F={F}")
+
+
+@pytest.mark.parametrize("pattern", [(True,) * 8, (False, True, False, False, True, True, False, False)])
+def test_long_chains_that_meet_in_some_chunks(pattern):
+    """The chunked form, which only chains past the class form's limit take: chunks that
+    never meet and patterns of those that do."""
+    need_gpu()
+    say("long segment chunks", pattern)
+    cost, rbound, last, first, redge, P = _class_chains([92, *pattern], 4, 1600, 2, pattern)
+    assert P == 8
+    assert_seg_parity(cost, rbound, last, first, redge, f"long pattern {pattern}")
