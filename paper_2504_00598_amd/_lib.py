@@ -7,6 +7,7 @@ no other code path.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 
@@ -156,9 +157,26 @@ def _ptr(t) -> int | None:
 def _stream(stream) -> int | None:
     import torch
 
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle; building a torch.cuda.Stream object for it
+    # takes 2.9 us per call against 0.2 us (a whole small search takes 8)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
+
+
+def _host_i32(x) -> np.ndarray:
+    """x as a contiguous int32 array.  A list of plain integers goes through
+    array.array, which takes half the time of numpy's conversion (1152 entries:
+    20 against 39 us)."""
+    if type(x) is list and x:
+        try:
+            return np.frombuffer(array.array("i", x), dtype=np.int32)
+        except (TypeError, OverflowError):  # nested, or not all integers: as numpy converts them
+            pass
+    return np.ascontiguousarray(np.asarray(x, dtype=np.int32))
 
 
 class Desc:
@@ -178,13 +196,13 @@ class Desc:
         if cost.dim() != 3 or rtab.dim() != 3:
             raise ValueError("cost is [B][N][K] and rtab is [E][K][K]")
         B, N, K = cost.shape
-        self.redge = np.ascontiguousarray(np.asarray(redge, dtype=np.int32))
+        self.redge = _host_i32(redge)
         if self.redge.shape != (N,):
             raise ValueError("redge must have N entries")
         self.cost, self.rtab = cost, rtab
         self.B, self.N, self.K, self.E = int(B), int(N), int(K), int(rtab.shape[0])
         self.c = cfp_chain_desc(self.N, self.K, self.B, self.E, _ptr(cost), _ptr(rtab),
-                                self.redge.ctypes.data_as(ctypes.c_void_p).value)
+                                self.redge.ctypes.data)
 
     @property
     def ref(self):
@@ -208,14 +226,14 @@ class SegDesc:
         B, N, K = cost.shape
         if tuple(last.shape) != (K,) or tuple(first.shape) != (K,):
             raise ValueError("last and first have K entries")
-        self.redge = np.ascontiguousarray(np.asarray(redge, dtype=np.int32))
+        self.redge = _host_i32(redge)
         if self.redge.shape != (N,):
             raise ValueError("redge must have N entries")
         self.cost, self.rbound, self.last, self.first = cost, rbound, last, first
         E, Lc, Fc = rbound.shape
         self.B, self.N, self.K, self.E, self.L, self.F = int(B), int(N), int(K), int(E), int(Lc), int(Fc)
         self.c = cfp_segment_desc(self.N, self.K, self.B, self.E, self.L, self.F, _ptr(cost), _ptr(rbound),
-                                  _ptr(last), _ptr(first), self.redge.ctypes.data_as(ctypes.c_void_p).value)
+                                  _ptr(last), _ptr(first), self.redge.ctypes.data)
 
     @property
     def ref(self):
