@@ -995,10 +995,11 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   // the chunk before: the fix-up from its speculative end row, the second
   // fix-up from the end row of a fix-up that met no checkpoint.
   int64_t total = dk[endq(0)];
+  const uint32_t xlast = a.ckrow[((size_t)b * a.nq + a.nq - 1) * KP + ms];  // (in flight during the loop)
   bool spec_true = true;
   int p = 1;
   while (p < P) {
-    if (spec_true && !rec[p].run2) {
+    if (spec_true && (p == 1 || !rec[p].run2)) {  // (the second fix-up never runs chunk 1)
       // With wave 0: the first chunk q > p that does not count, because chunk
       // q-1 ended on a row that no run of chunk q started from, and the offsets
       // of chunks p .. q-1.
@@ -1056,7 +1057,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
     }
   }
   // The final row has minimum 0: the lowest state at the minimum.
-  const uint32_t xv = spec_true ? a.ckrow[((size_t)b * a.nq + a.nq - 1) * KP + ms] : s_row[ms];
+  const uint32_t xv = spec_true ? xlast : s_row[ms];
   const uint32_t pk = cw_wave_min((tid < KP && ms < a.K) ? (xv | (uint32_t)ms) : kSat);
   if (lane == 0) s_fin[wid] = pk;
   const int timeout = __syncthreads_or(fl & 4), bad = __syncthreads_or(fl & 1), infeasible = __syncthreads_or(fl & 2);
