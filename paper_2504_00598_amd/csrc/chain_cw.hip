@@ -85,17 +85,22 @@ constexpr int kCSpec = 0, kCFix = 1, kCFix2 = 2;
 template <int KP>
 struct CwShape {
   static constexpr int BITS = KP <= 128 ? 7 : KP <= 256 ? 8 : 9;  // index bits of a packed word
-  static constexpr int PG = KP / kCWaves;           // predecessors per wave
-  static constexpr int SPL = KP / 64;               // states per lane in the products
-  static constexpr int VW = SPL < 4 ? SPL : 4;      // words per table load
+  static constexpr int THREADS = KP <= 128 ? 256 : 512;
+  static constexpr int WAVES = THREADS / 64;
+  static constexpr int NH = KP <= 128 ? 2 : 1;      // table rows per load instruction of a wave
+  static constexpr int PG = KP / (WAVES * NH);      // predecessors per wave (NH = 2: per half of it)
+  static constexpr int SPL = KP * NH / 64;          // states per lane in the products
+  static constexpr int VW = 4;                      // words per table load
   static constexpr int NV = SPL / VW;               // loads per table row and lane
   static constexpr int ROWS = KP <= 128 ? 4 : KP <= 256 ? 8 : 2;  // table rows per piece
   static constexpr int PIECES = PG / ROWS;          // pieces per step
   static constexpr int NB = 4;                      // pieces held in registers
-  static constexpr int TPS = kCThreads / KP;        // threads per state after the reduction
+  static constexpr int TPS = THREADS / KP;        // threads per state after the reduction
   static constexpr int CH = kCG / TPS;              // chains per thread after the reduction
   static constexpr int WPS = KP / 64;               // waves that hold the same chains after the reduction
+  static constexpr int GROUPS = WAVES * NH;         // predecessor groups
   static constexpr int QS = KP + KP / 8;            // LDS row stride: 4 words of padding after every 32
+  static constexpr int QH = QS / NH;                // NH = 2: odd predecessors follow the even ones
   static constexpr int MINROWS = KP <= 256 ? 32 : 64;  // least rows per chunk
   static constexpr uint32_t CAP = (1u << (32 - BITS)) - 1u;
   using Arg = typename std::conditional<(KP <= 256), uint8_t, uint16_t>::type;
@@ -131,13 +136,18 @@ struct CwArgs {
 
 template <int KP>
 struct CwSmem {
-  uint32_t part[kCG][kCWaves][KP];         // partial minima [chain][predecessor group][state]
+  uint32_t part[kCG][CwShape<KP>::GROUPS][KP];         // partial minima [chain][predecessor group][state]
   uint32_t q[2][kCG][CwShape<KP>::QS];     // rows [buffer][chain][state, padded]
-  uint32_t wm[kCWaves][CwShape<KP>::CH];   // wave minima of the new row, per chain of the wave
-  int32_t wd[kCWaves][CwShape<KP>::CH];    // fix-up: the wave found a state off the checkpoint
+  uint32_t wm[CwShape<KP>::WAVES][CwShape<KP>::CH];   // wave minima of the new row, per chain of the wave
+  int32_t wd[CwShape<KP>::WAVES][CwShape<KP>::CH];    // fix-up: the wave found a state off the checkpoint
 };
 
 __device__ __forceinline__ int qpad(int t) { return t + (t >> 5) * 4; }
+// LDS position of predecessor t in a row.
+template <int KP>
+__device__ __forceinline__ int qat(int t) {
+  return CwShape<KP>::NH == 1 ? qpad(t) : (t & 1) * CwShape<KP>::QH + qpad(t >> 1);
+}
 
 // min(keep, the partner lane's send): quad_perm partners lane ^ 1 and lane ^ 2;
 // the half mirror pairs lane i with lane 7 - i of its eight.
@@ -186,7 +196,8 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   constexpr int CH = S::CH, TPS = S::TPS, BITS = S::BITS;
   constexpr bool CHECK = MODE != kCSpec;
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int qd = lane, g = wid;  // state group, predecessor group (one wave each)
+  // state group, predecessor group (one wave each; NH = 2: half a wave, rows in turn)
+  const int g = wid, hw = S::NH == 1 ? 0 : lane >> 5, qd = S::NH == 1 ? lane : lane & 31;
   const int N = a.N, K = a.K;
   // the thread's state and chains after the reduction
   const int sub = TPS == 1 ? 0 : tid / KP;
@@ -234,14 +245,14 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 
   // Table pieces in flight, [buffer][row in piece][vector]; word offset of the
   // thread's first word within a table.
-  const uint32_t toff = (uint32_t)(S::PG * g * KP + S::SPL * qd);
+  const uint32_t toff = (uint32_t)(S::PG * S::NH * g * KP + hw * KP + S::SPL * qd);
   typename S::Vec tb[S::NB][S::ROWS][S::NV];
   auto tload = [&](int buf, int piece, int row) __attribute__((always_inline)) {
-    const uint32_t *tab = a.rpk + (size_t)edge(row) * KP * KP + toff + piece * S::ROWS * KP;
+    const uint32_t *tab = a.rpk + (size_t)edge(row) * KP * KP + toff + piece * S::ROWS * S::NH * KP;
 #pragma unroll
     for (int j = 0; j < S::ROWS; ++j)
 #pragma unroll
-      for (int v = 0; v < S::NV; ++v) tb[buf][j][v] = *(const typename S::Vec *)(tab + j * KP + S::VW * v);
+      for (int v = 0; v < S::NV; ++v) tb[buf][j][v] = *(const typename S::Vec *)(tab + j * S::NH * KP + S::VW * v);
   };
   // Row minima of every chain from the threads' values: wave minima to LDS,
   // one barrier, then the minimum over the waves (uniform).
@@ -287,7 +298,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       ch.x[h] = umin(x[h] - pick(d, h), S::CAP) << BITS;
-      sm.q[0][hc[h]][qpad(ms)] = ch.x[h];
+      sm.q[0][hc[h]][qat<KP>(ms)] = ch.x[h];
     }
     if (i0 > r1) {  // a run of one row (rs = r0): the start row is its checkpoint
 #pragma unroll
@@ -301,7 +312,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       ch.x[h] = pick(start, h)[ms];
-      sm.q[0][hc[h]][qpad(ms)] = ch.x[h];
+      sm.q[0][hc[h]][qat<KP>(ms)] = ch.x[h];
       cor[h] = 0;
     }
   }
@@ -346,7 +357,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
         uint32_t v[kCG][S::ROWS];  // the predecessors' values of this piece, per chain
 #pragma unroll
         for (int c = 0; c < kCG; ++c) {
-          const uint32_t *qc = &sm.q[cur][c][qpad(S::PG * g + S::ROWS * k)];
+          const uint32_t *qc = &sm.q[cur][c][hw * S::QH + qpad(S::PG * g + S::ROWS * k)];
           if constexpr (S::ROWS % 4 == 0) {
 #pragma unroll
             for (int r4 = 0; r4 < S::ROWS / 4; ++r4) {
@@ -393,7 +404,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
         typename S::Vec pv;
 #pragma unroll
         for (int u = 0; u < S::VW; ++u) pv[u] = acc[c][S::VW * vv + u];
-        *(typename S::Vec *)&sm.part[c][g][S::SPL * qd + S::VW * vv] = pv;
+        *(typename S::Vec *)&sm.part[c][g * S::NH + hw][S::SPL * qd + S::VW * vv] = pv;
       }
     __syncthreads();
     uint32_t m[CH];
@@ -402,7 +413,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
       const int c = hc[h];
       uint32_t v = sm.part[c][0][ms];
 #pragma unroll
-      for (int w = 1; w < kCWaves; ++w) v = umin(v, sm.part[c][w][ms]);
+      for (int w = 1; w < S::GROUPS; ++w) v = umin(v, sm.part[c][w][ms]);
       m[h] = v;
     }
 
@@ -439,7 +450,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       ch.x[h] = umin(x[h] - pick(d, h), S::CAP) << BITS;
-      sm.q[nxt][hc[h]][qpad(ms)] = ch.x[h];
+      sm.q[nxt][hc[h]][qat<KP>(ms)] = ch.x[h];
     }
     const bool qend = (i & 3) == 3 || i == r1;
     if (qend) {
@@ -511,7 +522,7 @@ __device__ __forceinline__ int cw_qmin(const CwRec &r, int qe) {
 // (ceil(B/kCG), P-1)) and second fix-up (kCFix2, grid (ceil(B/kCG), P-2))
 // passes.  A search takes part in the second one where cw_second says so.
 template <int KP, int MODE>
-__global__ __launch_bounds__(kCThreads, 1) void chain_cw_kernel(CwArgs a) {
+__global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_kernel(CwArgs a) {
   using S = CwShape<KP>;
   __shared__ __align__(16) CwSmem<KP> sm;
   const int p = blockIdx.y + (MODE == kCSpec ? 0 : MODE == kCFix ? 1 : 2);
@@ -970,7 +981,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cx_kernel(CwArgs a) {
 // Final pass, one workgroup per search: the chunk offsets, the reruns after
 // chunks whose fix-up met no checkpoint, and the lowest optimal final state.
 template <int KP>
-__global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, SearchResult *__restrict__ res,
+__global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_final_kernel(CwArgs a, SearchResult *__restrict__ res,
                                                                        int64_t *__restrict__ opt,
                                                                        int32_t *__restrict__ status) {
   using S = CwShape<KP>;
@@ -978,7 +989,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   __shared__ uint32_t s_row[KP];  // a true end row of the last chunk accounted
   __shared__ int s_q;
   __shared__ int64_t s_sum;
-  __shared__ uint32_t s_fin[kCWaves];
+  __shared__ uint32_t s_fin[CwShape<KP>::WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int b = blockIdx.x, P = a.P;
   const int ms = tid & (KP - 1);
@@ -987,7 +998,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   auto endq = [&](int p) __attribute__((always_inline)) { return (min((p + 1) * a.CL, a.N) - 1) >> 2; };
   // flags, combined after the loop so that their loads are in flight during it
   int fl = tid < P ? rec[tid].flags : 0;
-  for (int x = tid; x < a.nbad; x += kCThreads) fl |= a.rbad[x];
+  for (int x = tid; x < a.nbad; x += S::THREADS) fl |= a.rbad[x];
   // Chunk 0 runs from the true first row.  Invariant at the top of the loop:
   // chunks < p are accounted in `total`; if spec_true, the speculative end row
   // of chunk p-1 is a true row, otherwise s_row holds the true end row of chunk
@@ -1063,7 +1074,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cw_final_kernel(CwArgs a, 
   const int timeout = __syncthreads_or(fl & 4), bad = __syncthreads_or(fl & 1), infeasible = __syncthreads_or(fl & 2);
   if (tid == 0) {
     uint32_t fin = s_fin[0];
-    for (int w = 1; w < kCWaves; ++w) fin = umin(fin, s_fin[w]);
+    for (int w = 1; w < S::WAVES; ++w) fin = umin(fin, s_fin[w]);
     int st = CFP_ST_OK;
     if (timeout) st = CFP_ST_TIMEOUT;
     else if (bad) st = CFP_ST_BADINPUT;
@@ -1134,11 +1145,11 @@ CwPlan cw_plan(int n, int k, int batch, int period) {
 template <int KP>
 void launch_cw_kp(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
   timer_begin(st);
-  timed_launch(chain_cw_kernel<KP, kCSpec>, dim3(groups, a.P), dim3(kCThreads), 0, st, a);
+  timed_launch(chain_cw_kernel<KP, kCSpec>, dim3(groups, a.P), dim3(CwShape<KP>::THREADS), 0, st, a);
   timer_end(st);
-  hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix>), dim3(groups, a.P - 1), dim3(kCThreads), 0, st, a);
-  if (a.P > 2) hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix2>), dim3(groups, a.P - 2), dim3(kCThreads), 0, st, a);
-  hipLaunchKernelGGL(chain_cw_final_kernel<KP>, dim3(a.B), dim3(kCThreads), 0, st, a, res, opt, status);
+  hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix>), dim3(groups, a.P - 1), dim3(CwShape<KP>::THREADS), 0, st, a);
+  if (a.P > 2) hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix2>), dim3(groups, a.P - 2), dim3(CwShape<KP>::THREADS), 0, st, a);
+  hipLaunchKernelGGL(chain_cw_final_kernel<KP>, dim3(a.B), dim3(CwShape<KP>::THREADS), 0, st, a, res, opt, status);
 }
 
 void launch_cx(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
