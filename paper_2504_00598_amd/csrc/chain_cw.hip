@@ -12,21 +12,24 @@
 //      chunk p-1 and recompute until the row equals chunk p's checkpoint of the
 //      same quad (from there on the speculative rows are the true ones);
 //   3. second fix-up: the chunks behind a chunk that met no checkpoint run
-//      again, all at once, from that chunk's end row.  (Left to the final pass
-//      they ran one after another: 1152 blocks, K = 256, one search, resharding
-//      never free: 1792 us per call, 316 with this pass and chunks of 32 rows
-//      instead of 20.)  With nothing to do it costs one empty launch;
+//      again, all at once, from that chunk's end row, which is one chunk more of
+//      history: of a run of unmet chunks it is the true row if two chunks of
+//      history are enough.  (Left to the final pass they ran one after another:
+//      1152 blocks, K = 256, one search, resharding never free: 1792 us per
+//      call, 316 with this pass and chunks of 32 rows instead of 20.)  With
+//      nothing to do it costs one empty launch;
 //   4. final pass: sum the chunk offsets.  The last run of a chunk counts if it
-//      started from the true end row of the chunk before; a chunk that none
-//      did is rerun from it.  The result is the sequential recurrence's bit for
-//      bit.
+//      started from the true end row of the chunk before (rows compared whole);
+//      a chunk that none did is rerun from it.  The result is the sequential
+//      recurrence's bit for bit.
 //
-// One workgroup of 512 threads (8 waves) carries four chains (four searches of
-// the same chunk: every chain of a launch is at the same row, so all use the
-// same table) and all KP states, KP = 128, 256 or 512.  Wave g works for the
-// predecessors t = g KP/8 .. (g+1) KP/8 - 1 and lane q for the states
-// q KP/64 .. (q+1) KP/64 - 1 of every chain, so every table load of a wave
-// reads one row's KP words contiguously.  Per step a thread reads its share of
+// One workgroup of 8 waves (4 at KP = 128) carries four chains, or two in small
+// batches (searches of the same chunk: every chain of a launch is at the same
+// row, so all use the same table) and all KP states, KP = 128, 256 or 512.
+// Wave g works for the predecessors t = g KP/8 .. (g+1) KP/8 - 1 and lane q for
+// the states q KP/64 .. (q+1) KP/64 - 1 of every chain, so every table load of a
+// wave reads one row's KP words contiguously (KP = 128: two rows, one per half
+// of the wave).  Per step a thread reads its share of
 // the packed words (R_e[t][s] << b) | t of the edge's table (each word serves
 // the four chains) in pieces of a few rows, four pieces in flight in their
 // own registers (up to KP = 256 that is the whole step, loaded a step ahead),
@@ -36,17 +39,17 @@
 // through LDS, after which a thread holds one state of one chain (KP = 128), of
 // two (256) or of all four (512).
 //
-// What bounds a step: at KP >= 256 the table stream, KP^2 words per workgroup
-// and step from the cache hierarchy (the step time does not change with the
-// number of workgroups), hence four chains per workgroup; at KP = 128 the
-// instructions of a wave (about 400 per row, half of them products) and the
-// two exchanges through LDS: 2.0 us per row against 4.3 us at KP = 256.  (Before
-// this form K <= 128 went through the split kernel, 1.9 us per row but one row
-// after another: 1152 blocks, K = 128: 1960 to 152 us for one search, 2237 to
-// 420 us for 128; 393 blocks, K = 81, 24 searches: 762 to 165 us.)  At KP = 512
-// a batch of at most eight searches would leave most compute units idle; there
-// teams of four workgroups split the states of each chunk (state-split teams,
-// below).  Chunks are at least 32 rows long up to KP = 256 and 64 at KP = 512:
+// What bounds a step: at KP = 128 the instructions of a wave alone on its SIMD
+// (1.8 us per row with four chains: products 0.8, the two exchanges through LDS
+// and the normalisation 0.75, memory 0.25, measured with parts switched off),
+// at KP = 256 both and at KP = 512 the table stream, KP^2 words per workgroup and
+// step from the cache hierarchy (16.7 us per row whatever the number of
+// workgroups).  (Before this form K <= 128 went through the split kernel, 1.9 us
+// per row but one row after another: 1152 blocks, K = 128: 1960 to 108 us for
+// one search, 2237 to 331 us for 128; 393 blocks, K = 81, 24 searches: 762 to 105
+// us.)  At KP = 512 a batch of at most eight searches would leave most compute
+// units idle; there teams of four workgroups split the states of each chunk
+// (state-split teams, below).  Chunks are at least 32 rows long up to KP = 256 and 64 at KP = 512:
 // runs become parallel after 14 rows on average and 38 at most at K = 128, 18
 // and about 40 at K = 256, 21 and 50 at K = 512 (uniform random costs).
 //
@@ -77,12 +80,12 @@ constexpr int kCMaxChunks = 64;
 // at K = 256 the rows saved there equal the rows added here (measured), so 0.
 constexpr int kCWarm = 0;
 
-constexpr int kCG = 4;                  // chains per workgroup (searches of the same chunk)
+constexpr int kCG = 4;                  // chains per workgroup (searches of the same chunk); 2 in small batches
 // Passes: speculative; fix-up (a run stops once every chain met a checkpoint);
 // second fix-up, of the chunks behind one that met none in the first.
 constexpr int kCSpec = 0, kCFix = 1, kCFix2 = 2;
 
-template <int KP>
+template <int KP, int CG>
 struct CwShape {
   static constexpr int BITS = KP <= 128 ? 7 : KP <= 256 ? 8 : 9;  // index bits of a packed word
   static constexpr int THREADS = KP <= 128 ? 256 : 512;
@@ -96,16 +99,16 @@ struct CwShape {
   static constexpr int PIECES = PG / ROWS;          // pieces per step
   static constexpr int NB = 4;                      // pieces held in registers
   static constexpr int TPS = THREADS / KP;        // threads per state after the reduction
-  static constexpr int CH = kCG / TPS;              // chains per thread after the reduction
+  static constexpr int CH = CG / TPS;              // chains per thread after the reduction
   static constexpr int WPS = KP / 64;               // waves that hold the same chains after the reduction
   static constexpr int GROUPS = WAVES * NH;         // predecessor groups
   static constexpr int QS = KP + KP / 8;            // LDS row stride: 4 words of padding after every 32
   static constexpr int QH = QS / NH;                // NH = 2: odd predecessors follow the even ones
-  static constexpr int MINROWS = KP <= 256 ? 32 : 64;  // least rows per chunk
+  static constexpr int MINROWS = KP <= 256 ? 32 : 48;            // least rows per chunk
   static constexpr uint32_t CAP = (1u << (32 - BITS)) - 1u;
   using Arg = typename std::conditional<(KP <= 256), uint8_t, uint16_t>::type;
   typedef uint32_t Vec __attribute__((ext_vector_type(VW)));
-  static_assert(PIECES % NB == 0 && ROWS % 2 == 0 && SPL % VW == 0 && TPS * CH == kCG, "piece layout");
+  static_assert(PIECES % NB == 0 && ROWS % 2 == 0 && SPL % VW == 0 && TPS * CH == CG, "piece layout");
 };
 
 struct CwRec {
@@ -116,6 +119,7 @@ struct CwRec {
   int32_t conv;   // fix-up pass: quad of the meeting checkpoint, -1 if none
   int32_t conv2;  // the same of the second fix-up
   int32_t run2;   // the second fix-up ran this chunk (from the first one's end row of the chunk before)
+  int32_t same2;  // and met no checkpoint, but ended on the first one's end row of this chunk
 };
 
 struct CwArgs {
@@ -128,25 +132,26 @@ struct CwArgs {
   int64_t *dck;            // speculative offset sum at every checkpoint [B][nq]
   uint32_t *ckrow;         // speculative row at every checkpoint [B][nq][KP]
   uint32_t *endrow;        // fix-up end row of chunks that met no checkpoint [B][P][KP]
+  uint32_t *endrow2;       // the same of the second fix-up
   const int32_t *rbad;     // range flags of R, one per packing workgroup
   int nbad;
   uint64_t *xb;            // state-split teams: exchanged rows [team][slot][chain][KP]
   int32_t *xflag;          // state-split teams: a member gave up waiting [team]
 };
 
-template <int KP>
+template <int KP, int CG>
 struct CwSmem {
-  uint32_t part[kCG][CwShape<KP>::GROUPS][KP];         // partial minima [chain][predecessor group][state]
-  uint32_t q[2][kCG][CwShape<KP>::QS];     // rows [buffer][chain][state, padded]
-  uint32_t wm[CwShape<KP>::WAVES][CwShape<KP>::CH];   // wave minima of the new row, per chain of the wave
-  int32_t wd[CwShape<KP>::WAVES][CwShape<KP>::CH];    // fix-up: the wave found a state off the checkpoint
+  uint32_t part[CG][CwShape<KP, CG>::GROUPS][KP];         // partial minima [chain][predecessor group][state]
+  uint32_t q[2][CG][CwShape<KP, CG>::QS];     // rows [buffer][chain][state, padded]
+  uint32_t wm[CwShape<KP, CG>::WAVES][CwShape<KP, CG>::CH];   // wave minima of the new row, per chain of the wave
+  int32_t wd[CwShape<KP, CG>::WAVES][CwShape<KP, CG>::CH];    // fix-up: the wave found a state off the checkpoint
 };
 
 __device__ __forceinline__ int qpad(int t) { return t + (t >> 5) * 4; }
 // LDS position of predecessor t in a row.
-template <int KP>
+template <int KP, int CG>
 __device__ __forceinline__ int qat(int t) {
-  return CwShape<KP>::NH == 1 ? qpad(t) : (t & 1) * CwShape<KP>::QH + qpad(t >> 1);
+  return CwShape<KP, CG>::NH == 1 ? qpad(t) : (t & 1) * CwShape<KP, CG>::QH + qpad(t >> 1);
 }
 
 // min(keep, the partner lane's send): quad_perm partners lane ^ 1 and lane ^ 2;
@@ -172,13 +177,13 @@ __device__ __forceinline__ uint32_t cw_wave_min(uint32_t x) {
 // State of the workgroup's chains as seen by one thread.  After the
 // reduction thread tid holds, for its state s = tid % KP, the chains
 // h TPS + tid / KP, h = 0 .. CH - 1.
-template <int KP>
+template <int KP, int CG>
 struct CwChains {
-  uint32_t x[CwShape<KP>::CH];  // the thread's values of the current row, normalised and shifted
-  uint64_t dsum[kCG];   // offset sums since the start row (uniform)
-  int conv[kCG];        // fix-up: quad of the meeting checkpoint, -1 before
-  uint64_t dconv[kCG];  // fix-up: dsum at that checkpoint
-  uint32_t flags[kCG];  // speculative: bit 0 a negative cost, bit 1 a row with no available strategy
+  uint32_t x[CwShape<KP, CG>::CH];  // the thread's values of the current row, normalised and shifted
+  uint64_t dsum[CG];   // offset sums since the start row (uniform)
+  int conv[CG];        // fix-up: quad of the meeting checkpoint, -1 before
+  uint64_t dconv[CG];  // fix-up: dsum at that checkpoint
+  uint32_t flags[CG];  // speculative: bit 0 a negative cost, bit 1 a row with no available strategy
 };
 
 // Runs rows [r0, r1] of the workgroup's chains (searches bs[c], real where
@@ -187,11 +192,11 @@ struct CwChains {
 // checkpoints are written.  Fix-up: the start row (row r0 - 1) is start[c];
 // stops at the first quad end where every real chain has met its checkpoint at
 // a quad not before qmin[c].
-template <int KP, int MODE>
+template <int KP, int CG, int MODE>
 __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const bool *valid, int rs, int r0, int r1,
-                                       const int *qmin, const uint32_t *const *start, CwSmem<KP> &sm,
-                                       CwChains<KP> &ch) {
-  using S = CwShape<KP>;
+                                       const int *qmin, const uint32_t *const *start, CwSmem<KP, CG> &sm,
+                                       CwChains<KP, CG> &ch) {
+  using S = CwShape<KP, CG>;
   using Arg = typename S::Arg;
   constexpr int CH = S::CH, TPS = S::TPS, BITS = S::BITS;
   constexpr bool CHECK = MODE != kCSpec;
@@ -256,7 +261,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   };
   // Row minima of every chain from the threads' values: wave minima to LDS,
   // one barrier, then the minimum over the waves (uniform).
-  auto row_min = [&](const uint32_t(&x)[CH], uint32_t(&d)[kCG]) __attribute__((always_inline)) {
+  auto row_min = [&](const uint32_t(&x)[CH], uint32_t(&d)[CG]) __attribute__((always_inline)) {
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       const uint32_t w = cw_wave_min(x[h]);
@@ -264,7 +269,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
     }
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < kCG; ++c) {
+    for (int c = 0; c < CG; ++c) {
       uint32_t m = kCX;
 #pragma unroll
       for (int w = 0; w < S::WPS; ++w) m = umin(m, sm.wm[(c % TPS) * S::WPS + w][c / TPS]);
@@ -274,7 +279,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 
   // Start row.
 #pragma unroll
-  for (int c = 0; c < kCG; ++c) {
+  for (int c = 0; c < CG; ++c) {
     ch.flags[c] = 0;
     ch.conv[c] = -1;
     ch.dconv[c] = 0;
@@ -282,7 +287,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   }
   uint32_t cor[CH];
   if (MODE == kCSpec) {
-    uint32_t x[CH], d[kCG];
+    uint32_t x[CH], d[CG];
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       const uint32_t cv = cost_at(h, (size_t)rs, coff);
@@ -291,34 +296,34 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
     }
     row_min(x, d);
 #pragma unroll
-    for (int c = 0; c < kCG; ++c) {
+    for (int c = 0; c < CG; ++c) {
       if (d[c] == kCX) ch.flags[c] |= 2;
       ch.dsum[c] = d[c];
     }
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       ch.x[h] = umin(x[h] - pick(d, h), S::CAP) << BITS;
-      sm.q[0][hc[h]][qat<KP>(ms)] = ch.x[h];
+      sm.q[0][hc[h]][qat<KP, CG>(ms)] = ch.x[h];
     }
     if (i0 > r1) {  // a run of one row (rs = r0): the start row is its checkpoint
 #pragma unroll
       for (int h = 0; h < CH; ++h)
         if (hv[h]) ck_at(h, (size_t)(r0 / 4)) = ch.x[h];
 #pragma unroll
-      for (int c = 0; c < kCG; ++c)
+      for (int c = 0; c < CG; ++c)
         if (tid == c && valid[c]) a.dck[(size_t)bs[c] * a.nq + r0 / 4] = (int64_t)ch.dsum[c];
     }
   } else {
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       ch.x[h] = pick(start, h)[ms];
-      sm.q[0][hc[h]][qat<KP>(ms)] = ch.x[h];
+      sm.q[0][hc[h]][qat<KP, CG>(ms)] = ch.x[h];
       cor[h] = 0;
     }
   }
   auto negative_costs = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < kCG; ++c)
+    for (int c = 0; c < CG; ++c)
       if (__syncthreads_or(((c % TPS) == sub) && (cor[c / TPS] >> 31))) ch.flags[c] |= 1;
   };
   if (i0 > r1) {
@@ -344,9 +349,9 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   // fix-up pass is done.
   auto step = [&](int i, auto Pc) __attribute__((always_inline)) -> bool {
     constexpr int cur = decltype(Pc)::value, nxt = cur ^ 1;
-    uint32_t acc[kCG][S::SPL];
+    uint32_t acc[CG][S::SPL];
 #pragma unroll
-    for (int c = 0; c < kCG; ++c)
+    for (int c = 0; c < CG; ++c)
 #pragma unroll
       for (int u = 0; u < S::SPL; ++u) acc[c][u] = kSat;
     const int inext = min(i + 1, r1);
@@ -354,9 +359,9 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 #pragma unroll
       for (int bb = 0; bb < S::NB; ++bb) {
         const int k = kk + bb;
-        uint32_t v[kCG][S::ROWS];  // the predecessors' values of this piece, per chain
+        uint32_t v[CG][S::ROWS];  // the predecessors' values of this piece, per chain
 #pragma unroll
-        for (int c = 0; c < kCG; ++c) {
+        for (int c = 0; c < CG; ++c) {
           const uint32_t *qc = &sm.q[cur][c][hw * S::QH + qpad(S::PG * g + S::ROWS * k)];
           if constexpr (S::ROWS % 4 == 0) {
 #pragma unroll
@@ -382,7 +387,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
           for (int vv = 0; vv < S::NV; ++vv) {
             const typename S::Vec w = tb[bb][j][vv], y = tb[bb][j + 1][vv];
 #pragma unroll
-            for (int c = 0; c < kCG; ++c) {
+            for (int c = 0; c < CG; ++c) {
               uint32_t *ac = &acc[c][S::VW * vv];
 #pragma unroll
               for (int u = 0; u < S::VW; ++u)
@@ -398,7 +403,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
     }
     // Minima over the eight predecessor groups (one wave each) through LDS.
 #pragma unroll
-    for (int c = 0; c < kCG; ++c)
+    for (int c = 0; c < CG; ++c)
 #pragma unroll
       for (int vv = 0; vv < S::NV; ++vv) {
         typename S::Vec pv;
@@ -440,17 +445,17 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
       asm volatile("" : "+v"(off) : "v"(x[h]));
       cq[cur][h] = cost_at(h, (size_t)min(i + 2, r1), off);
     }
-    uint32_t d[kCG];
+    uint32_t d[CG];
     row_min(x, d);
 #pragma unroll
-    for (int c = 0; c < kCG; ++c) {
+    for (int c = 0; c < CG; ++c) {
       if (MODE == kCSpec && d[c] == kCX) ch.flags[c] |= 2;
       ch.dsum[c] += d[c];
     }
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
       ch.x[h] = umin(x[h] - pick(d, h), S::CAP) << BITS;
-      sm.q[nxt][hc[h]][qat<KP>(ms)] = ch.x[h];
+      sm.q[nxt][hc[h]][qat<KP, CG>(ms)] = ch.x[h];
     }
     const bool qend = (i & 3) == 3 || i == r1;
     if (qend) {
@@ -460,7 +465,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
         for (int h = 0; h < CH; ++h)
           if (hv[h]) ck_at(h, (size_t)q) = ch.x[h];
 #pragma unroll
-        for (int c = 0; c < kCG; ++c)
+        for (int c = 0; c < CG; ++c)
           if (tid == c && valid[c]) a.dck[(size_t)bs[c] * a.nq + q] = (int64_t)ch.dsum[c];
       }
       if (CHECK) {
@@ -480,7 +485,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
       const int q = i >> 2;
       bool all = true;
 #pragma unroll
-      for (int c = 0; c < kCG; ++c) {
+      for (int c = 0; c < CG; ++c) {
         bool same = true;
 #pragma unroll
         for (int w = 0; w < S::WPS; ++w) same = same && !sm.wd[(c % TPS) * S::WPS + w][c / TPS];
@@ -502,12 +507,17 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
 }
 
 // Whether the second fix-up runs chunk p of a search: the fix-up of chunk p-1
-// met no checkpoint, so chunk p started from a row that is not the true one,
-// and chunk p-1 itself started from a true row as far as its neighbours tell
-// (chunk p-2 met; a run of unmet chunks is left to the final pass, as its
-// second chunk's end row changes with the first's rerun).
-__device__ __forceinline__ bool cw_second(const CwRec *rec, int p) {
-  return p >= 2 && rec[p - 1].conv < 0 && (p == 2 || rec[p - 2].conv >= 0);
+// met no checkpoint, so that of chunk p started from a row that is not the true
+// one.
+__device__ __forceinline__ bool cw_second(const CwRec *rec, int p) { return p >= 2 && rec[p - 1].conv < 0; }
+
+// The row that the last run of a chunk ends on: its speculative end row, the end
+// row of its fix-up (which the next chunk's second fix-up starts from), or that
+// of its second fix-up.
+enum { kEndSpec, kEnd1, kEnd2 };
+__device__ __forceinline__ int cw_end(const CwRec &r) {
+  if (r.run2) return r.conv2 >= 0 ? kEndSpec : r.same2 ? kEnd1 : kEnd2;
+  return r.conv >= 0 ? kEndSpec : kEnd1;
 }
 
 // Quad a rerun of chunk p (last quad qe) must reach before it may stop: past
@@ -518,22 +528,22 @@ __device__ __forceinline__ int cw_qmin(const CwRec &r, int qe) {
   return q;
 }
 
-// Speculative (MODE kCSpec, grid (ceil(B/kCG), P)), fix-up (kCFix, grid
-// (ceil(B/kCG), P-1)) and second fix-up (kCFix2, grid (ceil(B/kCG), P-2))
+// Speculative (MODE kCSpec, grid (ceil(B/CG), P)), fix-up (kCFix, grid
+// (ceil(B/CG), P-1)) and second fix-up (kCFix2, grid (ceil(B/CG), P-2))
 // passes.  A search takes part in the second one where cw_second says so.
-template <int KP, int MODE>
-__global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_kernel(CwArgs a) {
-  using S = CwShape<KP>;
-  __shared__ __align__(16) CwSmem<KP> sm;
+template <int KP, int CG, int MODE>
+__global__ __launch_bounds__((CwShape<KP, CG>::THREADS), 1) void chain_cw_kernel(CwArgs a) {
+  using S = CwShape<KP, CG>;
+  __shared__ __align__(16) CwSmem<KP, CG> sm;
   const int p = blockIdx.y + (MODE == kCSpec ? 0 : MODE == kCFix ? 1 : 2);
   const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
-  int bs[kCG], qmin[kCG];
-  bool valid[kCG];
-  const uint32_t *start[kCG];
+  int bs[CG], qmin[CG];
+  bool valid[CG];
+  const uint32_t *start[CG];
   bool any = false;
 #pragma unroll
-  for (int c = 0; c < kCG; ++c) {
-    const int b = kCG * blockIdx.x + c;
+  for (int c = 0; c < CG; ++c) {
+    const int b = CG * blockIdx.x + c;
     valid[c] = b < a.B;
     bs[c] = min(b, a.B - 1);
     qmin[c] = 0;
@@ -549,22 +559,33 @@ __global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_kernel(CwArg
   if (MODE == kCFix2 && !any) return;
   // the speculative run of a chunk after the first starts kCWarm rows early
   const int rs = (MODE == kCSpec && p > 0) ? max(r0 - kCWarm, 0) : r0;
-  CwChains<KP> ch;
-  cw_run<KP, MODE == kCSpec ? kCSpec : kCFix>(a, bs, valid, rs, r0, r1, qmin, start, sm, ch);
+  CwChains<KP, CG> ch;
+  cw_run<KP, CG, MODE == kCSpec ? kCSpec : kCFix>(a, bs, valid, rs, r0, r1, qmin, start, sm, ch);
   const int tid = threadIdx.x;
   const int sub = S::TPS == 1 ? 0 : tid / KP;
   const int ms = tid & (KP - 1);
   if (MODE == kCSpec) {
 #pragma unroll
-    for (int c = 0; c < kCG; ++c)
+    for (int c = 0; c < CG; ++c)
       if (tid == 0 && valid[c]) a.rec[(size_t)bs[c] * a.P + p].flags = (int32_t)ch.flags[c];
   } else {
 #pragma unroll
-    for (int c = 0; c < kCG; ++c)
+    for (int c = 0; c < CG; ++c)
       if (c % S::TPS == sub && valid[c] && ch.conv[c] < 0)
-        a.endrow[((size_t)bs[c] * a.P + p) * KP + ms] = ch.x[c / S::TPS];
+        (MODE == kCFix ? a.endrow : a.endrow2)[((size_t)bs[c] * a.P + p) * KP + ms] = ch.x[c / S::TPS];
+    bool same[CG];  // second fix-up: the end row is the first one's (which then met no checkpoint either)
 #pragma unroll
-    for (int c = 0; c < kCG; ++c) {
+    for (int c = 0; c < CG; ++c) {
+      same[c] = false;
+      if (MODE == kCFix2) {
+        const size_t at = (size_t)bs[c] * a.P + p;
+        const bool unmet = a.rec[at].conv < 0;  // uniform
+        const bool off = unmet && c % S::TPS == sub && a.endrow[at * KP + ms] != ch.x[c / S::TPS];
+        same[c] = !__syncthreads_or(off) && unmet;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < CG; ++c) {
       if (tid != c || !valid[c]) continue;
       CwRec &r = a.rec[(size_t)bs[c] * a.P + p];
       const int64_t d = (int64_t)(ch.conv[c] >= 0 ? ch.dconv[c] : ch.dsum[c]);
@@ -576,6 +597,7 @@ __global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_kernel(CwArg
         r.conv2 = ch.conv[c];
         r.dfix2 = d;
         r.run2 = 1;
+        r.same2 = same[c];
       }
     }
   }
@@ -611,7 +633,7 @@ constexpr int kXQW = kXW + kXW / 8;         // padded LDS words of one part's st
 
 struct CxSmem {
   uint32_t part[kCG][kCWaves][kXW];      // partial minima [chain][predecessor group][state of the part]
-  uint32_t q[2][kCG][CwShape<512>::QS];  // whole rows [buffer][chain][state, padded]
+  uint32_t q[2][kCG][CwShape<512, kCG>::QS];  // whole rows [buffer][chain][state, padded]
   uint32_t wm[kCWaves];                  // wave minima of the new row (waves 2c and 2c+1 hold chain c)
   int32_t wd[kCWaves];                   // fix-up: the wave found a state off the checkpoint
   int32_t abort;                         // a wait expired, or another part of the team gave up
@@ -646,7 +668,7 @@ template <int MODE>
 __device__ __forceinline__ void cx_run(const CwArgs &a, int z, int team, int grp, int r0, int r1, int act,
                                        const int (&qmin)[kCG], const uint32_t *startr, CxSmem &sm, CxChains &ch) {
   constexpr int KP = 512;
-  using S = CwShape<KP>;
+  using S = CwShape<KP, kCG>;
   constexpr int BITS = S::BITS;
   constexpr uint32_t CAP = S::CAP;
   constexpr int PG = S::PG;  // predecessors per wave
@@ -959,7 +981,21 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cx_kernel(CwArgs a) {
       atomicOr(&a.rec[(size_t)(kCG * grp + cc) * a.P + p].flags, fl[cc]);
   if (MODE != kCSpec) {
     const int s = z * kXW + sl;
-    if (((act >> c) & 1) && sel4(ch.conv, c) < 0) a.endrow[((size_t)bc * a.P + p) * 512 + s] = sel4(ch.q, z);
+    if (((act >> c) & 1) && sel4(ch.conv, c) < 0)
+      (MODE == kCFix ? a.endrow : a.endrow2)[((size_t)bc * a.P + p) * 512 + s] = sel4(ch.q, z);
+    // second fix-up: whether the end row is the first one's (every part holds the whole row)
+    bool off[kCG];
+#pragma unroll
+    for (int cc = 0; cc < kCG; ++cc) {
+      bool o = false;
+      if (MODE == kCFix2 && cc == c) {
+        const size_t at = (size_t)bc * a.P + p;
+        o = a.rec[at].conv >= 0;
+#pragma unroll
+        for (int zz = 0; zz < kXS; ++zz) o = o || a.endrow[at * 512 + zz * kXW + sl] != ch.q[zz];
+      }
+      off[cc] = MODE == kCFix2 && __syncthreads_or(o);
+    }
 #pragma unroll
     for (int cc = 0; cc < kCG; ++cc) {
       if (z != 0 || tid != cc || !((act >> cc) & 1)) continue;
@@ -973,6 +1009,7 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cx_kernel(CwArgs a) {
         r.conv2 = ch.conv[cc];
         r.dfix2 = d;
         r.run2 = 1;
+        r.same2 = !off[cc];
       }
     }
   }
@@ -980,16 +1017,16 @@ __global__ __launch_bounds__(kCThreads, 1) void chain_cx_kernel(CwArgs a) {
 
 // Final pass, one workgroup per search: the chunk offsets, the reruns after
 // chunks whose fix-up met no checkpoint, and the lowest optimal final state.
-template <int KP>
-__global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_final_kernel(CwArgs a, SearchResult *__restrict__ res,
+template <int KP, int CG>
+__global__ __launch_bounds__((CwShape<KP, CG>::THREADS), 1) void chain_cw_final_kernel(CwArgs a, SearchResult *__restrict__ res,
                                                                        int64_t *__restrict__ opt,
                                                                        int32_t *__restrict__ status) {
-  using S = CwShape<KP>;
-  __shared__ __align__(16) CwSmem<KP> sm;
+  using S = CwShape<KP, CG>;
+  __shared__ __align__(16) CwSmem<KP, CG> sm;
   __shared__ uint32_t s_row[KP];  // a true end row of the last chunk accounted
-  __shared__ int s_q;
+  __shared__ int s_q, s_end;
   __shared__ int64_t s_sum;
-  __shared__ uint32_t s_fin[CwShape<KP>::WAVES];
+  __shared__ uint32_t s_fin[CwShape<KP, CG>::WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int b = blockIdx.x, P = a.P;
   const int ms = tid & (KP - 1);
@@ -1004,16 +1041,21 @@ __global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_final_kernel
   // of chunk p-1 is a true row, otherwise s_row holds the true end row of chunk
   // p-1.  The last run of a chunk counts if it started from the true end row of
   // the chunk before: the fix-up from its speculative end row, the second
-  // fix-up from the end row of a fix-up that met no checkpoint.
+  // fix-up from the end row of its fix-up.
   int64_t total = dk[endq(0)];
   const uint32_t xlast = a.ckrow[((size_t)b * a.nq + a.nq - 1) * KP + ms];  // (in flight during the loop)
   bool spec_true = true;
   int p = 1;
   while (p < P) {
-    if (spec_true && (p == 1 || !rec[p].run2)) {  // (the second fix-up never runs chunk 1)
-      // With wave 0: the first chunk q > p that does not count, because chunk
-      // q-1 ended on a row that no run of chunk q started from, and the offsets
-      // of chunks p .. q-1.
+    bool counts = p == 1;  // the last run of chunk p counts (the second fix-up never runs chunk 1)
+    if (p > 1) {
+      counts = spec_true == !rec[p].run2;
+      if (counts && !spec_true)  // it started from the true row?
+        counts = !__syncthreads_or(tid < KP && s_row[ms] != a.endrow[((size_t)b * P + p - 1) * KP + ms]);
+    }
+    if (counts) {
+      // With wave 0: the first chunk q > p whose last run started from another
+      // row than chunk q-1's last run ends on, and the offsets of chunks p .. q-1.
       if (wid == 0) {
         const int pl = p + lane;
         const bool in = pl < P;
@@ -1021,51 +1063,50 @@ __global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_final_kernel
         if (in) r = rec[pl];
         const int conv = r.run2 ? r.conv2 : r.conv;
         const int64_t dfix = r.run2 ? r.dfix2 : r.dfix;
-        const bool unmet = in && conv < 0;
-        const bool prev = __shfl_up((int)unmet, 1, 64) != 0 && lane > 0;
-        const uint64_t bad = __ballot(in && prev && !r.run2);
+        const int end = cw_end(r), before = __shfl_up(end, 1, 64);
+        const uint64_t bad = __ballot(in && lane > 0 && before != (r.run2 ? kEnd1 : kEndSpec));
         const int q = bad ? p + __ffsll((long long)bad) - 1 : P;
         int64_t delta = 0;
         if (in && pl < q) delta = conv < 0 ? dfix : dfix + dk[endq(pl)] - dk[conv];
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) delta += __shfl_xor(delta, off, 64);
-        const bool last = __ballot(pl == q - 1 && unmet) != 0;  // chunk q-1 ended off its checkpoints
+        if (lane == q - 1 - p) s_end = end;
         if (lane == 0) {
-          s_q = last ? q : -q;
+          s_q = q;
           s_sum = delta;
         }
       }
       __syncthreads();
-      const int sq = s_q;
+      p = s_q;
       total += s_sum;
-      p = abs(sq);
-      spec_true = sq < 0;
-      if (!spec_true && tid < KP) s_row[tid] = a.endrow[((size_t)b * P + p - 1) * KP + tid];
+      const int end = s_end;
+      spec_true = end == kEndSpec;
+      if (!spec_true && tid < KP) s_row[tid] = (end == kEnd1 ? a.endrow : a.endrow2)[((size_t)b * P + p - 1) * KP + tid];
       __syncthreads();
-    } else {
-      // Rerun chunk p from the true row, until it meets its own checkpoints.
-      if (spec_true && tid < KP) s_row[tid] = a.ckrow[((size_t)b * a.nq + endq(p - 1)) * KP + tid];
-      __syncthreads();
-      int bs[kCG], qmin[kCG];
-      bool valid[kCG];
-      const uint32_t *start[kCG];
-#pragma unroll
-      for (int c = 0; c < kCG; ++c) {
-        bs[c] = b;
-        valid[c] = c == 0;  // the other chains duplicate it and are discarded
-        start[c] = s_row;
-        qmin[c] = cw_qmin(rec[p], endq(p));
-      }
-      CwChains<KP> ch;
-      const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
-      cw_run<KP, kCFix>(a, bs, valid, r0, r0, r1, qmin, start, sm, ch);
-      spec_true = ch.conv[0] >= 0;
-      total += spec_true ? (int64_t)ch.dconv[0] + dk[endq(p)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
-      __syncthreads();  // every thread has read s_row
-      if (!spec_true && tid < KP) s_row[tid] = ch.x[0];  // chain 0 of state tid is the thread's first
-      __syncthreads();
-      ++p;
+      if (p >= P) break;
     }
+    // Rerun chunk p from the true row, until it meets its own checkpoints.
+    if (spec_true && tid < KP) s_row[tid] = a.ckrow[((size_t)b * a.nq + endq(p - 1)) * KP + tid];
+    __syncthreads();
+    int bs[CG], qmin[CG];
+    bool valid[CG];
+    const uint32_t *start[CG];
+#pragma unroll
+    for (int c = 0; c < CG; ++c) {
+      bs[c] = b;
+      valid[c] = c == 0;  // the other chains duplicate it and are discarded
+      start[c] = s_row;
+      qmin[c] = cw_qmin(rec[p], endq(p));
+    }
+    CwChains<KP, CG> ch;
+    const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
+    cw_run<KP, CG, kCFix>(a, bs, valid, r0, r0, r1, qmin, start, sm, ch);
+    spec_true = ch.conv[0] >= 0;
+    total += spec_true ? (int64_t)ch.dconv[0] + dk[endq(p)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
+    __syncthreads();  // every thread has read s_row
+    if (!spec_true && tid < KP) s_row[tid] = ch.x[0];  // chain 0 of state tid is the thread's first
+    __syncthreads();
+    ++p;
   }
   // The final row has minimum 0: the lowest state at the minimum.
   const uint32_t xv = spec_true ? xlast : s_row[ms];
@@ -1090,6 +1131,7 @@ __global__ __launch_bounds__(CwShape<KP>::THREADS, 1) void chain_cw_final_kernel
 
 struct CwPlan {
   int KP, P, CL, nq;
+  int G;  // chains per workgroup: 4, or 2
   int S;  // workgroups per chunk and group of four searches: 1, or kXS for state-split teams
 };
 
@@ -1107,22 +1149,43 @@ int cw_device_cus() {
   return cus;
 }
 
+// Chunks of at least minrows rows, as many as `groups` groups of searches need
+// to fill `slots` workgroups.
+int cw_chunk_rows(int n, int groups, int slots, int minrows) {
+  const int P = std::min(kCMaxChunks, std::max(2, (slots + groups - 1) / groups));
+  return std::max(minrows, ((n + P - 1) / P + 3) & ~3);
+}
+
 // period: of the edge map (0 when it has none, or for the region's size).
 CwPlan cw_plan(int n, int k, int batch, int period) {
-  CwPlan c{0, 0, 0, 0, 1};
+  CwPlan c{0, 0, 0, 0, kCG, 1};
   if (k <= 64 || k > 512) return c;
   const int kp = k <= 128 ? 128 : k <= 256 ? 256 : 512;
-  const int minrows = kp <= 256 ? CwShape<256>::MINROWS : CwShape<512>::MINROWS;
+  const int minrows = kp <= 256 ? CwShape<256, kCG>::MINROWS : CwShape<512, kCG>::MINROWS;
   const int groups = (batch + kCG - 1) / kCG;
   // K > 256 with at most two groups of four searches: state-split teams, every
   // workgroup resident on its own compute unit.
   const int cus = cw_device_cus();
-  const bool team = kp == 512 && groups <= kXMaxGroups && cus / (kXS * groups) >= 2;
-  int P = team ? cus / (kXS * groups) : std::max(2, (256 + groups - 1) / groups);  // about one workgroup per CU
-  P = std::min(P, kCMaxChunks);
-  int CL = std::max(minrows, ((n + P - 1) / P + 3) & ~3);
-  P = (n + CL - 1) / CL;
-  if (P < 2) return c;
+  int CL;
+  if (kp == 512 && groups <= kXMaxGroups && cus / (kXS * groups) >= 2) {
+    c.S = kXS;
+    CL = cw_chunk_rows(n, groups, cus / kXS, minrows);
+  } else {
+    // Two chains per workgroup while all chunks of the least length fit the chip
+    // so: a row takes 1.1 us against 1.8 at KP = 128 (393 blocks, K = 81, 24
+    // searches: 148 -> 105 us per call) and 3.0 against 4.3 at KP = 256 (1152
+    // blocks, one search: 249 -> 184 us).  Several workgroups of KP = 128 share a
+    // compute unit (1152 blocks, K = 81, 40 searches as 720 of them 207 us, as
+    // 360 of four chains 246; 128 searches of K = 128 415 us at 256 workgroups,
+    // 331 at 512, 364 at 768); at KP = 256 a second one only adds rows (1152
+    // blocks, K = 256, 128 searches: 863 us at 256, 1026 at 512).
+    const int slots2 = kp == 128 ? 768 : 256, slots4 = kp == 128 ? 512 : 256;
+    const int half = (batch + 1) / 2, pmax = std::min(kCMaxChunks, (n + minrows - 1) / minrows);
+    c.G = (long long)half * pmax <= slots2 ? 2 : 4;
+    CL = c.G == 2 ? cw_chunk_rows(n, half, slots2, minrows) : cw_chunk_rows(n, groups, slots4, minrows);
+  }
+  int P = (n + CL - 1) / CL;
+  if (P < 2) return CwPlan{0, 0, 0, 0, kCG, 1};
   // Chunks of an even number of periods start in phase with a chain whose costs
   // repeat with its edge map and whose rows alternate between periods; worth a
   // sixteenth more rows per chunk.
@@ -1138,18 +1201,21 @@ CwPlan cw_plan(int n, int k, int batch, int period) {
   c.P = P;
   c.CL = CL;
   c.nq = (n + 3) / 4;
-  c.S = team ? kXS : 1;
   return c;
 }
 
-template <int KP>
-void launch_cw_kp(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
+template <int KP, int CG>
+void launch_cw_kp(const CwArgs &a, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
+  constexpr int FG = 2;  // the final pass reruns one chain
+  const int groups = (a.B + CG - 1) / CG;
+  const dim3 block(CwShape<KP, CG>::THREADS);
   timer_begin(st);
-  timed_launch(chain_cw_kernel<KP, kCSpec>, dim3(groups, a.P), dim3(CwShape<KP>::THREADS), 0, st, a);
+  timed_launch(chain_cw_kernel<KP, CG, kCSpec>, dim3(groups, a.P), block, 0, st, a);
   timer_end(st);
-  hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix>), dim3(groups, a.P - 1), dim3(CwShape<KP>::THREADS), 0, st, a);
-  if (a.P > 2) hipLaunchKernelGGL((chain_cw_kernel<KP, kCFix2>), dim3(groups, a.P - 2), dim3(CwShape<KP>::THREADS), 0, st, a);
-  hipLaunchKernelGGL(chain_cw_final_kernel<KP>, dim3(a.B), dim3(CwShape<KP>::THREADS), 0, st, a, res, opt, status);
+  hipLaunchKernelGGL((chain_cw_kernel<KP, CG, kCFix>), dim3(groups, a.P - 1), block, 0, st, a);
+  if (a.P > 2) hipLaunchKernelGGL((chain_cw_kernel<KP, CG, kCFix2>), dim3(groups, a.P - 2), block, 0, st, a);
+  hipLaunchKernelGGL((chain_cw_final_kernel<KP, FG>), dim3(a.B), dim3(CwShape<KP, FG>::THREADS), 0, st, a, res, opt,
+                     status);
 }
 
 void launch_cx(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
@@ -1161,7 +1227,7 @@ void launch_cx(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int
   timer_end(st);
   hipLaunchKernelGGL(chain_cx_kernel<kCFix>, dim3(kXS, groups, a.P - 1), dim3(kCThreads), 0, st, a);
   if (a.P > 2) hipLaunchKernelGGL(chain_cx_kernel<kCFix2>, dim3(kXS, groups, a.P - 2), dim3(kCThreads), 0, st, a);
-  hipLaunchKernelGGL(chain_cw_final_kernel<512>, dim3(a.B), dim3(kCThreads), 0, st, a, res, opt, status);
+  hipLaunchKernelGGL((chain_cw_final_kernel<512, 2>), dim3(a.B), dim3(kCThreads), 0, st, a, res, opt, status);
 }
 
 }  // namespace
@@ -1177,7 +1243,7 @@ size_t cw_region_bytes(int n, int k, int n_tables, int batch) {
   off += align_up((size_t)batch * c.P * sizeof(CwRec));
   off += align_up((size_t)batch * c.nq * 8);
   off += align_up((size_t)batch * c.nq * kp * 4);
-  off += align_up((size_t)batch * c.P * kp * 4);
+  off += 2 * align_up((size_t)batch * c.P * kp * 4);
   if (c.S > 1) {
     const size_t teams = (size_t)((batch + kCG - 1) / kCG) * c.P;
     off += align_up(teams * 2 * kCG * kp * 8);
@@ -1215,6 +1281,8 @@ hipError_t launch_chain_cw(const cfp_chain_desc &d, int32_t *redge_dev, const Ed
   off += align_up((size_t)d.batch * c.nq * kp * 4);
   a.endrow = (uint32_t *)(region + off);
   off += align_up((size_t)d.batch * c.P * kp * 4);
+  a.endrow2 = (uint32_t *)(region + off);
+  off += align_up((size_t)d.batch * c.P * kp * 4);
   const int groups = (d.batch + kCG - 1) / kCG;
   a.xb = nullptr;
   a.xflag = nullptr;
@@ -1223,13 +1291,16 @@ hipError_t launch_chain_cw(const cfp_chain_desc &d, int32_t *redge_dev, const Ed
     off += align_up((size_t)groups * c.P * 2 * kCG * kp * 8);
     a.xflag = (int32_t *)(region + off);
   }
-  const int bits = kp == 128 ? CwShape<128>::BITS : kp == 256 ? CwShape<256>::BITS : CwShape<512>::BITS;
+  const int bits = kp == 128 ? 7 : kp == 256 ? 8 : 9;
   a.nbad = launch_pack_rtab(d.rtab, d.n_tables, d.k, (int)kp, bits, rpk, st, cfp_r_limit(CFP_V_CHAIN, d.k), rbad, &em,
                             redge_dev, d.n_blocks);
   if (c.S > 1) launch_cx(a, groups, res, opt, status, st);
-  else if (kp == 128) launch_cw_kp<128>(a, groups, res, opt, status, st);
-  else if (kp == 256) launch_cw_kp<256>(a, groups, res, opt, status, st);
-  else launch_cw_kp<512>(a, groups, res, opt, status, st);
+  else if (kp == 128 && c.G == 2) launch_cw_kp<128, 2>(a, res, opt, status, st);
+  else if (kp == 128) launch_cw_kp<128, kCG>(a, res, opt, status, st);
+  else if (kp == 256 && c.G == 2) launch_cw_kp<256, 2>(a, res, opt, status, st);
+  else if (kp == 256) launch_cw_kp<256, kCG>(a, res, opt, status, st);
+  else if (c.G == 2) launch_cw_kp<512, 2>(a, res, opt, status, st);
+  else launch_cw_kp<512, kCG>(a, res, opt, status, st);
   return hipGetLastError();
 }
 

@@ -570,7 +570,7 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
   // chunk p-1 is its true one (so the fix-up of chunk p is valid), otherwise
   // s_row holds the true end row of chunk p-1.
   int64_t total = dk[endq(0)];
-  bool spec_true = true;
+  bool spec_true = true, reruns = false;  // reruns: the run before was a rerun that met no checkpoint
   int p = 1;
   while (p < P) {
     if (spec_true) {
@@ -603,25 +603,28 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
       __syncthreads();
     } else {
       // Rerun chunk p (wave 0; the others stage) at least over the rows its
-      // fix-up rewrote from a wrong start.
+      // fix-up rewrote from a wrong start; behind a rerun that met nothing
+      // either, the rest of the chain in one run.
       const uint32_t *start[1] = {s_row};
       WaveChains<1> ch;
-      const int qmin = rec[p].conv < 0 ? endq(p) : rec[p].conv;
-      wave_run<kWFinalWaves, 1, kWFix, EP>(a, b, wid == 0 ? 1 : 0, p * a.CB, min((p + 1) * a.CB, a.nblk), qmin, start,
-                                           sm, ch);
+      const int last = reruns ? P - 1 : p;  // last chunk of the run
+      const int qmin = reruns ? endq(P - 1) : rec[p].conv < 0 ? endq(p) : rec[p].conv;
+      wave_run<kWFinalWaves, 1, kWFix, EP>(a, b, wid == 0 ? 1 : 0, p * a.CB, min((last + 1) * a.CB, a.nblk), qmin,
+                                           start, sm, ch);
       __syncthreads();  // every wave has read s_row and the last tables
       if (wid == 0) {
         const bool met = ch.conv[0] >= 0;
         if (lane == 0) {
           s_q = met;
-          s_sum = met ? (int64_t)ch.dconv[0] + dk[endq(p)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
+          s_sum = met ? (int64_t)ch.dconv[0] + dk[endq(last)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
         }
         s_row[lane] = ch.qv[0];
       }
       __syncthreads();
       total += s_sum;
       spec_true = s_q != 0;
-      ++p;
+      reruns = !spec_true;
+      p = last + 1;
       __syncthreads();  // s_q is rewritten at the top of the loop
     }
   }

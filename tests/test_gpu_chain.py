@@ -666,7 +666,8 @@ def test_chunked_mid_shapes(N, K, B, E):
     assert_chain_parity(cost, rtab, redge, f"chunked mid N={N} K={K} B={B} E={E}")
 
 
-@pytest.mark.parametrize("K,B,N", [(100, 5, 400), (256, 3, 400), (400, 3, 600), (300, 9, 600)])
+@pytest.mark.parametrize("K,B,N", [(100, 5, 400), (100, 90, 400), (256, 3, 400), (200, 70, 400), (400, 3, 600),
+                                   (300, 9, 600), (300, 132, 200)])
 @pytest.mark.parametrize("share", [0.0, 0.5, 0.8])
 def test_chunked_patterns_of_unmet_chunks(K, B, N, share):
     """Zero tables near the start of a share of the chunks: isolated chunks that meet no
