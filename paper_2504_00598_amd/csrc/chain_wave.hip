@@ -320,11 +320,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     }
   };
 
-  // Table chunks of the next row read ahead: with one wave per SIMD (NW = 4) the
-  // whole row, issued before the current row's products, since no other wave
-  // hides the LDS latency; with four waves a few, behind the products.
-  constexpr bool EARLY = NW == 4;
-  constexpr int NPRE = EARLY ? 16 : 4;
+  constexpr int NPRE = 4;  // table chunks of the next row read ahead
   u32x4 wpre[NPRE];
   // One row; J = row mod 12.  GUARD: the block may end before its 12th row;
   // FIRST: the run's first block, whose rows before i0 are skipped and whose
@@ -377,8 +373,8 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     // of a row; with one (sixteen waves per workgroup) it loads them in two
     // halves, and outside the first block the first half of rows 1..3 of a
     // quad is read during the previous row's normalisation (PRE).
-    constexpr int WH = ((MODE == kWSpec && G == 2) || EARLY) ? 16 : 8;
-    constexpr bool PRE = (WH < 16 || EARLY) && !FIRST && u != 0;
+    constexpr int WH = (MODE == kWSpec && G == 2) ? 16 : 8;
+    constexpr bool PRE = WH < 16 && !FIRST && u != 0;
     u32x4 w[16];
     // Candidates of every predecessor for the searches X (and Y): two
     // searches share each table chunk read.
@@ -394,9 +390,6 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     } else {                                                                               \
       _Pragma("unroll") for (int cc_ = 0; cc_ < WH; ++cc_) w[cc_] = tb[cc_ * 64 + lane];   \
     }                                                                                      \
-    if constexpr (EARLY && !FIRST && u != 3) {                                             \
-      _Pragma("unroll") for (int cc_ = 0; cc_ < NPRE; ++cc_) wpre[cc_] = tb[kWTable16 + cc_ * 64 + lane]; \
-    }                                                                                      \
     CH(__VA_ARGS__ c0, 0) CH(__VA_ARGS__ c0, 1) CH(__VA_ARGS__ c0, 2) CH(__VA_ARGS__ c0, 3) \
     CH(__VA_ARGS__ c1, 4) CH(__VA_ARGS__ c1, 5) CH(__VA_ARGS__ c1, 6) CH(__VA_ARGS__ c1, 7) \
     if constexpr (WH < 16) {                                                               \
@@ -404,7 +397,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     }                                                                                      \
     CH(__VA_ARGS__ c2, 8) CH(__VA_ARGS__ c2, 9) CH(__VA_ARGS__ c2, 10) CH(__VA_ARGS__ c2, 11) \
     CH(__VA_ARGS__ c3, 12) CH(__VA_ARGS__ c3, 13) CH(__VA_ARGS__ c3, 14) CH(__VA_ARGS__ c3, 15) \
-    if constexpr (WH < 16 && !EARLY && !FIRST && u != 3) {                                           \
+    if constexpr (WH < 16 && !FIRST && u != 3) {                                           \
       _Pragma("unroll") for (int cc_ = 0; cc_ < NPRE; ++cc_) wpre[cc_] = tb[kWTable16 + cc_ * 64 + lane]; \
     }                                                                                      \
   }

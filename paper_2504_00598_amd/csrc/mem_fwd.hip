@@ -335,7 +335,7 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
     uint64_t *my_ring = W.ring + chunk_id * kMemSlots * SW;
     const uint64_t *lo_ring = W.ring + lo_id * kMemSlots * SW;
     constexpr int HW = KP * 16 / 64;       // product words of a slot per lane
-    constexpr int HB = HW % 8 ? 4 : 8;     // words per lane moved at once
+    constexpr int HB = HW <= 24 ? HW : HW % 16 ? HW / 2 : 16;  // words per lane in flight at once
     static_assert(HW % HB == 0, "slot words per lane in whole blocks");
     constexpr int RW = RLDS ? KP * KP / 256 : 1;  // 16-byte table pieces per lane
     bool timeout = false;
@@ -382,39 +382,49 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
         s_done = -1;
         s_upcons = -1;
       }
+      // Everything a step takes from memory is loaded during the step before it,
+      // so that no load's latency is part of a step: the halo slot (in its first
+      // HB words per lane; reloaded if it was not there yet), the table and the
+      // records of the next step, the progress of the chunk above.  (Loaded and
+      // used within the step they bound it where the products are short: 288
+      // blocks, K = 16, 1024 buckets, 16 searches 442 us per call, now 301; from K = 32
+      // on the products cover it.)
+      uint64_t hv[HB], ho = 0;
+      u32x4 cpc = {};  // records of the next step
+      uint32_t spc = 0;
+      int dmi = 0, upc = -1;
+      auto load_block = [&](const uint64_t *src, int u0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < HB; ++u)
+          hv[u] = __hip_atomic_load(src + lane + 64 * (u0 + u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (u0 == 0 && lane < 32)
+          ho = __hip_atomic_load(src + 16 * KP + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
+      auto prefetch = [&](int i) __attribute__((always_inline)) {  // for step i: its halo, what it stages for step i + 1
+        if (consumer) load_block(lo_ring + (size_t)(i % kMemSlots) * SW, 0);
+        if (i + 1 < N) {
+          if (RLDS) load_table(redge[i + 1]);
+          load_records(i + 1, cpc, spc);
+          dmi = dmin[rowbase + i + 1];
+        }
+        if (has_consumer) upc = __hip_atomic_load(up_cons, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
+      if (N > 1) prefetch(1);
       __syncthreads();  // step 0 of the compute waves
       for (int i = 1; i < N; ++i) {
         const int par = i & 1, pprev = par ^ 1;
         const int pb = ALIAS ? 0 : par;
         const uint64_t *src = lo_ring + (size_t)(i % kMemSlots) * SW;
-        uint64_t hv[HB];
-        uint64_t ho = (uint64_t)i << 32;
-        auto load_block = [&](int u0) __attribute__((always_inline)) {
-#pragma unroll
-          for (int u = 0; u < HB; ++u)
-            hv[u] = __hip_atomic_load(src + lane + 64 * (u0 + u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
+        if (lane >= 32) ho = (uint64_t)i << 32;
         auto block_fresh = [&]() __attribute__((always_inline)) {
           bool ok = true;
 #pragma unroll
           for (int u = 0; u < HB; ++u) ok &= (uint32_t)(hv[u] >> 32) == (uint32_t)i;
           return ok;
         };
-        if (consumer) {
-          load_block(0);
-          if (lane < 32) ho = __hip_atomic_load(src + 16 * KP + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (RLDS && i + 1 < N) load_table(redge[i + 1]);
-        u32x4 cpc = {};  // records of step i + 1
-        uint32_t spc = 0;
-        if (i + 1 < N) load_records(i + 1, cpc, spc);
-        const int dmi = i + 1 < N ? dmin[rowbase + i + 1] : 0;
-        int upc = -1;
-        if (has_consumer) upc = __hip_atomic_load(up_cons, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-
         if (consumer) {  // every word of slot i must carry the step's number (bounded reloads)
           for (int u0 = 0; u0 < HW; u0 += HB) {
-            if (u0 > 0) load_block(u0);
+            if (u0 > 0) load_block(src, u0);
             bool ok = block_fresh() && (u0 > 0 || (uint32_t)(ho >> 32) == (uint32_t)i);
             if (!__all(ok) && !timeout) {
               int spins = 0;
@@ -424,9 +434,7 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
                   break;
                 }
                 __builtin_amdgcn_s_sleep(1);
-                load_block(u0);
-                if (u0 == 0 && lane < 32)
-                  ho = __hip_atomic_load(src + 16 * KP + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                load_block(src, u0);
                 ok = block_fresh() && (u0 > 0 || (uint32_t)(ho >> 32) == (uint32_t)i);
               } while (!__all(ok));
             }
@@ -445,6 +453,7 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
         if (RLDS && i + 1 < N) store_table(par ^ 1);
         if (i + 1 < N) stage_records(i + 1, cpc, spc, dmi);
         if (lane == 0) s_upcons = upc;
+        if (i + 1 < N) prefetch(i + 1);
         __syncthreads();  // B
         if constexpr (ALIAS) __syncthreads();  // B2
       }
