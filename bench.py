@@ -47,21 +47,21 @@ KERNEL_ROLE = {
     "chain_wide_n512_k256": "speculative pass only; forward_call_frac covers the whole forward call",
     "scan_n4096_k512:chain": "speculative pass only (four workgroups per chunk, rows exchanged every step); "
                              "forward_call_frac covers the whole forward call",
-    "scan_n4096_k512": "the 12 min-plus matrix-product launches of the up-sweep",
-    "seg_gpt_n96_k81": "the forward pass in one launch (speculative, fix-up and final passes of four chunks per search)",
+    "scan_n4096_k512": "the 11 min-plus matrix-product launches of the up-sweep",
+    "seg_gpt_n96_k81": "the forward pass in one launch",
 }
 KERNELS = {
     # one launch of cfp_search_chain: forward pass and traceback
     "chain_gpt_n24_k16": ("chain_small_kernel<16>", ["chain_small.hip"]),
     # speculative pass of the chunk-parallel search: it computes every step of every chain
-    "chain_gpt_n1152_k64": ("chain_wave_kernel<12>", ["chain_wave.hip", "res_common.h"]),
+    "chain_gpt_n1152_k64": ("chain_wave_kernel<12, 16>", ["chain_wave.hip", "res_common.h"]),
     "mem_llama_n288_k32": ("mem_fwd_kernel<32>", ["mem_fwd.hip", "res_common.h"]),
     # speculative pass of the chunk-parallel search
-    "chain_wide_n512_k256": ("chain_cw_kernel<256,0>", ["chain_cw.hip", "chain_fwd_wide.hip"]),
+    "chain_wide_n512_k256": ("chain_cw_kernel<256, 4, 0>", ["chain_cw.hip", "chain_fwd_wide.hip"]),
     # the scan workload through the chain search: speculative pass of the chunk-parallel form
     "scan_n4096_k512:chain": ("chain_cx_kernel<0>", ["chain_cw.hip", "chain_fwd_wide.hip"]),
     "scan_n4096_k512": ("scan_gemm_kernel", ["scan.hip"]),
-    "seg_gpt_n96_k81": ("seg_chunk_kernel<2, 4, true>", ["seg_fwd.hip"]),
+    "seg_gpt_n96_k81": ("seg_class_kernel<4>", ["seg_class.hip"]),
 }
 COMMON_SOURCES = ["common.h", "cfp_internal.h", "../../include/cfp.h"]
 
@@ -126,8 +126,13 @@ def cells_of(cfg, data) -> int:
 
 
 def scan_gemm_cells(cfg) -> int:
-    """Cells of the scan's min-plus matrix products: N-1 products of K^3."""
-    return cfg.B * (cfg.N - 1) * cfg.K ** 3
+    """Cells of the scan's min-plus matrix products, K^3 each: every node of the
+    tree but the last of each level, which is never read."""
+    products, cnt = 0, cfg.N
+    while cnt > 1:
+        cnt = (cnt + 1) // 2
+        products += cnt - 1
+    return cfg.B * products * cfg.K ** 3
 
 
 def run_oracle(cfg, data, n=None, threads=None):
@@ -508,7 +513,7 @@ def measure(name: str, steps: int, warmup: int, cpu_s: float, frontier: bool = F
                      "step_frac": (work / (ms_per_step * 1e-3)) / PEAK_CELLS},
     }
     if cfg.form == "scan":
-        rec["roofline"]["cells_counted"] = ("min-plus matrix-product cells (N-1)*K^3 per search; value counts "
+        rec["roofline"]["cells_counted"] = ("cells of the computed min-plus matrix products, K^3 each; value counts "
                                             "K^2 per block per search")
         rec["scan_gemm_cells_per_s"] = work / (ms_per_step * 1e-3)
     if cfg.form == "seg":

@@ -6,8 +6,9 @@
 // min_t v[t] + T[t][s], and D[N-1] = 0 (x) T_0 (x) ... (x) T_{N-1}.  The
 // min-plus matrix product is associative, so:
 //   up-sweep   a tree of min-plus matrix products: level 0 holds the N
-//              blocks, level l+1 the products of adjacent pairs of level l (an
-//              unpaired last node moves up unchanged);
+//              blocks, level l+1 the products of adjacent pairs of level l.
+//              Only left children's matrices are ever read, and products for
+//              such: the last node of a level is neither, so it is not formed;
 //   down-sweep the prefix vector entering every node: the root's is 0, a
 //              left child inherits its parent's, a right child gets
 //              parent (x) left-sibling product;
@@ -24,6 +25,7 @@
 // so with R < 2^23 and finite costs of a block within 2^30 of each other no
 // entry that can matter reaches BIG and every result is exact; the second
 // condition is checked on the device (status BADINPUT otherwise).
+#include <algorithm>
 #include <type_traits>
 
 #include "cfp_internal.h"
@@ -34,9 +36,18 @@ namespace cfp {
 constexpr uint32_t kBig = 0x7FFFFFFFu;
 constexpr int kTile = 128;  // output tile of a product
 constexpr int kTk = 16;     // predecessor depth of one LDS stage
-constexpr int kMaxLevels = 40;
+constexpr int kMaxLevels = 32;
+constexpr int kScanPrepBlocks = 2048;  // most workgroups of the first launch
 
-__host__ __device__ inline int scan_kp(int k) { return (k + kTile - 1) / kTile * kTile; }
+constexpr int kTileS = 64;  // smaller tile: padding to 64, or levels with too few large tiles for the chip
+
+// Padded strategies: a multiple of the large tile, or of the small one where
+// that saves more than the small tile's products lose (about a third of their
+// rate): up to 64 (1/8 of the products), 129 .. 192 (0.42) and 257 .. 320 (0.58).
+__host__ __device__ inline int scan_kp(int k) {
+  const int big = (k + kTile - 1) / kTile * kTile, small = (k + kTileS - 1) / kTileS * kTileS;
+  return 3LL * small * small * small < 2LL * big * big * big ? small : big;
+}
 
 struct ScanLayout {
   int nlev;               // number of levels (level 0 = blocks)
@@ -46,8 +57,10 @@ struct ScanLayout {
   size_t tot[kMaxLevels]; // [B][cnt] int64
   size_t pre[kMaxLevels]; // prefix vectors entering each node: [B][cnt][KP] uint32
   size_t ptot[kMaxLevels];// [B][cnt] int64
+  size_t mn0, mn_words;   // all levels' minima, one after another
   size_t cmin;            // [B][N] int32
-  size_t flags;           // [B] int32
+  size_t flags;           // [B][N] uint8, SCANF_* of every row of costs
+  size_t rbad;            // range flags of R, one per workgroup of the first launch
   size_t bytes;
 };
 
@@ -61,12 +74,17 @@ static ScanLayout scan_layout(int n, int k, int batch) {
     ++S.nlev;
   }
   size_t off = 0;
+  S.mn0 = 0;
+  for (int l = 0; l < S.nlev; ++l) {
+    S.mn[l] = off;
+    off += (size_t)batch * S.cnt[l] * 4;
+  }
+  S.mn_words = off / 4;
+  off = align_up(off);
   for (int l = 0; l < S.nlev; ++l) {
     const size_t c = (size_t)batch * S.cnt[l];
     S.mat[l] = off;
     if (l > 0) off = align_up(off + c * KP * KP * 4);
-    S.mn[l] = off;
-    off = align_up(off + c * 4);
     S.tot[l] = off;
     off = align_up(off + c * 8);
     S.pre[l] = off;
@@ -77,7 +95,9 @@ static ScanLayout scan_layout(int n, int k, int batch) {
   S.cmin = off;
   off = align_up(off + (size_t)batch * n * 4);
   S.flags = off;
-  off = align_up(off + (size_t)batch * 4);
+  off = align_up(off + (size_t)batch * n);
+  S.rbad = off;
+  off = align_up(off + kScanPrepBlocks * 4);
   S.bytes = off;
   return S;
 }
@@ -86,36 +106,64 @@ size_t scan_region_bytes(int n, int k, int batch) { return scan_layout(n, k, bat
 
 enum { SCANF_BAD = 1, SCANF_INFEASIBLE = 2 };
 
-// cmin[b][i] = min_s c[b][i][s] over available strategies; validates the costs.
-__global__ __launch_bounds__(256) void scan_prep_kernel(const int32_t *__restrict__ cost, int N, int K, int B,
-                                                        int32_t *__restrict__ cmin, int32_t *__restrict__ flags) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+struct PrepArgs {
+  const int32_t *cost, *rtab;
+  int N, K, KP, B;
+  size_t rwords;      // entries of rtab
+  int32_t rlimit;
+  EdgeMap em;
+  int32_t *redge;
+  int32_t *cmin;
+  uint8_t *flags;
+  int32_t *rbad;
+  uint32_t *mn;       // all levels' minima
+  size_t mn_words;
+  uint32_t *pre;      // the root's prefix [B][KP] and its offsets [B]
+  int64_t *ptot;
+};
+
+// The first launch of a call: cmin[b][i] = min_s c[b][i][s] over available
+// strategies, with the checks of the costs and of R; a periodic edge map
+// written out; the products' minima and the root's prefix initialised.  (Done
+// by launches of their own, two per level, these took half of a call on a
+// small search: 1024 blocks, K = 64, 533 us.)
+__global__ __launch_bounds__(256) void scan_prep_kernel(PrepArgs a) {
   const int lane = threadIdx.x & 63;
-  if (row >= B * N) return;
-  const int32_t *c = cost + (size_t)row * K;
-  int32_t lo = CFP_COST_INF, hi = -1;
-  bool neg = false;
-  for (int s = lane; s < K; s += 64) {
-    const int32_t v = c[s];
-    neg |= v < 0;
-    if (v != CFP_COST_INF) {
-      lo = v < lo ? v : lo;
-      hi = v > hi ? v : hi;
+  const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  a.em.write(a.redge, a.N);
+  for (size_t x = first; x < a.mn_words; x += stride) a.mn[x] = kSat;
+  for (size_t x = first; x < (size_t)a.B * a.KP; x += stride) a.pre[x] = 0;
+  for (size_t x = first; x < (size_t)a.B; x += stride) a.ptot[x] = 0;
+  bool off = false;
+  for (size_t x = first; x < a.rwords; x += stride) off |= a.rtab[x] < 0 || a.rtab[x] >= a.rlimit;
+  const int any = __syncthreads_or(off);
+  if (threadIdx.x == 0) a.rbad[blockIdx.x] = any ? 1 : 0;
+  for (size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < (size_t)a.B * a.N; row += (size_t)gridDim.x * 4) {
+    const int32_t *c = a.cost + row * a.K;
+    int32_t lo = CFP_COST_INF, hi = -1;
+    bool neg = false;
+    for (int s = lane; s < a.K; s += 64) {
+      const int32_t v = c[s];
+      neg |= v < 0;
+      if (v != CFP_COST_INF) {
+        lo = v < lo ? v : lo;
+        hi = v > hi ? v : hi;
+      }
     }
-  }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const int32_t l2 = __shfl_xor(lo, off, 64), h2 = __shfl_xor(hi, off, 64);
-    lo = l2 < lo ? l2 : lo;
-    hi = h2 > hi ? h2 : hi;
-  }
-  neg = __any(neg);
-  if (lane == 0) {
-    cmin[row] = lo;
-    int f = 0;
-    if (neg || (hi >= 0 && (int64_t)hi - lo >= (1 << 30))) f |= SCANF_BAD;
-    if (lo == CFP_COST_INF) f |= SCANF_INFEASIBLE;
-    if (f) atomicOr(&flags[row / N], f);
+    for (int o = 32; o >= 1; o >>= 1) {
+      const int32_t l2 = __shfl_xor(lo, o, 64), h2 = __shfl_xor(hi, o, 64);
+      lo = l2 < lo ? l2 : lo;
+      hi = h2 > hi ? h2 : hi;
+    }
+    neg = __any(neg);
+    if (lane == 0) {
+      a.cmin[row] = lo;
+      int f = 0;
+      if (neg || (hi >= 0 && (int64_t)hi - lo >= (1 << 30))) f |= SCANF_BAD;
+      if (lo == CFP_COST_INF) f |= SCANF_INFEASIBLE;
+      a.flags[row] = (uint8_t)f;
+    }
   }
 }
 
@@ -297,50 +345,143 @@ __global__ __launch_bounds__(256) void scan_gemm_kernel(ScanArgs a) {
   if (tid == 0) atomicMin(&a.dst_mn[(size_t)b * a.cnt_dst + j], umin(umin(red[0], red[1]), umin(red[2], red[3])));
 }
 
-// Level-l nodes: tot = tot(left) + tot(right) + mn for products; an unpaired
-// last node is carried (its matrix copied, or formed from its block).
-__global__ void scan_tot_kernel(ScanArgs a, const int64_t *__restrict__ src_tot, int64_t *__restrict__ dst_tot) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= a.B * a.cnt_dst) return;
-  const int b = x / a.cnt_dst, j = x % a.cnt_dst;
+// One 64x64 tile of C = A (x) B, as above with 4 rows and 4 columns per thread:
+// a quarter of the large tile's work per workgroup, for levels that have too
+// few large tiles to fill the chip (one product of K = 256: 62 -> 17 us), and
+// for padding to 64.
+template <bool LEAF>
+__global__ __launch_bounds__(256) void scan_gemm64_kernel(ScanArgs a) {
+  __shared__ __align__(16) uint32_t As[2][kTk][kTileS];
+  __shared__ __align__(16) uint32_t Bs[2][kTk][kTileS];
+  __shared__ uint32_t red[4];
+  const int tid = threadIdx.x;
+  const int tiles = a.KP / kTileS;
+  const int tile = blockIdx.x, j = blockIdx.y, b = blockIdx.z;
+  const int tr0 = (tile / tiles) * kTileS, tc0 = (tile % tiles) * kTileS;
+  const int K = a.K, KP = a.KP;
   const int ia = 2 * j, ib = 2 * j + 1;
-  auto node_tot = [&](int i) -> int64_t {
-    if (a.l == 1) return (int64_t)a.cmin[(size_t)b * a.N + i];
-    return src_tot[(size_t)b * a.cnt_src + i];
-  };
-  if (ib < a.cnt_src)
-    dst_tot[x] = node_tot(ia) + node_tot(ib) + (int64_t)a.dst_mn[x];
-  else
-    dst_tot[x] = node_tot(ia);  // carried: tot of the single child, matrix copied with mn = the child's
-}
-
-// Copy (or form from its block) the unpaired last node of level l-1 into level l.
-__global__ void scan_carry_kernel(ScanArgs a) {
-  const int b = blockIdx.y;
-  const int j = a.cnt_dst - 1, i = a.cnt_src - 1;
-  const size_t n2 = (size_t)a.KP * a.KP;
-  uint32_t *C = a.dst + ((size_t)b * a.cnt_dst + j) * n2;
-  for (size_t x = (size_t)blockIdx.x * blockDim.x + threadIdx.x; x < n2; x += (size_t)gridDim.x * blockDim.x) {
-    const int t = (int)(x / a.KP), s = (int)(x % a.KP);
-    uint32_t v;
-    if (a.l == 1) {
-      const int32_t *c = a.cost + ((size_t)b * a.N + i) * a.K;
-      const int32_t cm = a.cmin[(size_t)b * a.N + i];
-      const uint32_t rv = i == 0 ? 0u
-                                 : (t < a.K && s < a.K) ? (uint32_t)a.rtab[(size_t)a.redge[i] * a.K * a.K + (size_t)t * a.K + s]
-                                                        : kBig;
-      v = umin(rv + cadj(c, cm, s, a.K), kBig);
-    } else {
-      v = a.src[((size_t)b * a.cnt_src + i) * n2 + x];
-    }
-    C[x] = v;
+  const int32_t *Ra = nullptr, *Rb = nullptr, *ca = nullptr, *cb = nullptr;
+  int32_t cma = 0, cmb = 0;
+  const uint32_t *Am = nullptr, *Bm = nullptr;
+  uint32_t mna = 0, mnb = 0;
+  if (LEAF) {
+    ca = a.cost + ((size_t)b * a.N + ia) * K;
+    cb = a.cost + ((size_t)b * a.N + ib) * K;
+    cma = a.cmin[(size_t)b * a.N + ia];
+    cmb = a.cmin[(size_t)b * a.N + ib];
+    Ra = ia == 0 ? nullptr : a.rtab + (size_t)a.redge[ia] * K * K;
+    Rb = a.rtab + (size_t)a.redge[ib] * K * K;
+  } else {
+    Am = a.src + ((size_t)b * a.cnt_src + ia) * KP * KP;
+    Bm = a.src + ((size_t)b * a.cnt_src + ib) * KP * KP;
+    mna = a.src_mn[(size_t)b * a.cnt_src + ia];
+    mnb = a.src_mn[(size_t)b * a.cnt_src + ib];
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    a.dst_mn[(size_t)b * a.cnt_dst + j] = a.l == 1 ? 0u : a.src_mn[(size_t)b * a.cnt_src + i];
+  // loader: A row lr, 4 predecessors from lk; B row bk, 4 columns from bc
+  const int lr = tid >> 2, lk = (tid & 3) * 4, bk = tid >> 4, bc = (tid & 15) * 4;
+  uint32_t ra[4], rb[4];
+  auto load = [&](int k0) __attribute__((always_inline)) {
+    const int t = tr0 + lr, k = k0 + bk;
+    if (LEAF) {
+      // clamped addresses, so that no load sits behind a branch
+      const int32_t *rrow = Ra ? Ra + (size_t)min(t, K - 1) * K : ca;
+      const int32_t *brow = Rb + (size_t)min(k, K - 1) * K;
+      int32_t cv[4], rv[4], bv[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        cv[q] = ca[min(k0 + lk + q, K - 1)];
+        rv[q] = rrow[min(k0 + lk + q, K - 1)];
+        bv[q] = brow[min(tc0 + bc + q, K - 1)];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool kin = k0 + lk + q < K;
+        const uint32_t c = kin && cv[q] != CFP_COST_INF ? (uint32_t)(cv[q] - cma) : kBig;
+        const uint32_t r = !Ra ? 0u : t < K && kin ? (uint32_t)rv[q] : kBig;
+        ra[q] = umin(c + r, kBig);
+        rb[q] = k < K && tc0 + bc + q < K ? (uint32_t)bv[q] : kBig;
+      }
+    } else {
+      const uint4 x = *(const uint4 *)(Am + (size_t)t * KP + k0 + lk), y = *(const uint4 *)(Bm + (size_t)k * KP + tc0 + bc);
+      ra[0] = umin(x.x - mna, kBig);
+      ra[1] = umin(x.y - mna, kBig);
+      ra[2] = umin(x.z - mna, kBig);
+      ra[3] = umin(x.w - mna, kBig);
+      rb[0] = umin(y.x - mnb, kBig);
+      rb[1] = umin(y.y - mnb, kBig);
+      rb[2] = umin(y.z - mnb, kBig);
+      rb[3] = umin(y.w - mnb, kBig);
+    }
+  };
+  auto store = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) As[buf][lk + q][lr] = ra[q];
+    *(uint4 *)&Bs[buf][bk][bc] = make_uint4(rb[0], rb[1], rb[2], rb[3]);
+  };
+  const int ty = tid >> 4, tx = tid & 15;
+  uint32_t acc[4][4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[r][c] = kSat;
+  const int nst = KP / kTk;
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int st = 0; st < nst; ++st) {
+    const int buf = st & 1;
+    if (st + 1 < nst) load((st + 1) * kTk);
+#pragma unroll 2
+    for (int kk = 0; kk < kTk; kk += 2) {
+      const uint4 x0 = *(const uint4 *)&As[buf][kk][4 * ty], x1 = *(const uint4 *)&As[buf][kk + 1][4 * ty];
+      const uint4 y0 = *(const uint4 *)&Bs[buf][kk][4 * tx], y1 = *(const uint4 *)&Bs[buf][kk + 1][4 * tx];
+      const uint32_t a0[4] = {x0.x, x0.y, x0.z, x0.w}, a1[4] = {x1.x, x1.y, x1.z, x1.w};
+      const uint32_t b0[4] = {y0.x, y0.y, y0.z, y0.w}, b1[4] = {y1.x, y1.y, y1.z, y1.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[r][c] = umin(acc[r][c], umin(a0[r] + b0[c], a1[r] + b1[c]));
+    }
+    if (st + 1 < nst) store(buf ^ 1);
+    __syncthreads();
+  }
+  uint32_t *C = a.dst + ((size_t)b * a.cnt_dst + j) * KP * KP;
+  uint32_t tmin = kSat;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int t = tr0 + 4 * ty + r;
+    uint32_t out[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      uint32_t v = acc[r][c];
+      if (LEAF) v = sat_add(v, cadj(cb, cmb, tc0 + 4 * tx + c, K));
+      out[c] = umin(v, kBig);
+      tmin = umin(tmin, out[c]);
+    }
+    *(uint4 *)&C[(size_t)t * KP + tc0 + 4 * tx] = make_uint4(out[0], out[1], out[2], out[3]);
+  }
+  tmin = wave_min(tmin);
+  if ((tid & 63) == 0) red[tid >> 6] = tmin;
+  __syncthreads();
+  if (tid == 0) atomicMin(&a.dst_mn[(size_t)b * a.cnt_dst + j], umin(umin(red[0], red[1]), umin(red[2], red[3])));
 }
 
-__global__ void scan_fill_kernel(uint32_t *p, size_t n, uint32_t v) {
-  for (size_t x = (size_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (size_t)gridDim.x * blockDim.x) p[x] = v;
+// Offsets of the products of every level, tot = tot(left) + tot(right) + mn, one
+// workgroup per search.
+__global__ __launch_bounds__(1024) void scan_tot_kernel(ScanLayout S, uint8_t *region, int N) {
+  const int b = blockIdx.x;
+  const int32_t *cmin = (const int32_t *)(region + S.cmin) + (size_t)b * N;
+  for (int l = 1; l < S.nlev; ++l) {
+    const int cnt = S.cnt[l], csrc = S.cnt[l - 1];
+    const int64_t *src = (const int64_t *)(region + S.tot[l - 1]) + (size_t)b * csrc;
+    const uint32_t *mn = (const uint32_t *)(region + S.mn[l]) + (size_t)b * cnt;
+    int64_t *dst = (int64_t *)(region + S.tot[l]) + (size_t)b * cnt;
+    for (int j = threadIdx.x; j < cnt - 1; j += blockDim.x) {
+      const int64_t x = l == 1 ? cmin[2 * j] : src[2 * j], y = l == 1 ? cmin[2 * j + 1] : src[2 * j + 1];
+      dst[j] = x + y + (int64_t)mn[j];
+    }
+    __syncthreads();
+  }
 }
 
 struct DownArgs {
@@ -360,18 +501,23 @@ constexpr int kVmRows = 16;  // matrix rows in flight per thread in vecmat
 
 // v (x) M for one vector and one matrix (a block's transfer matrix when
 // the matrices are level 0); returns the minimum of the output in `mn` and
-// writes out - mn.  256 threads, KP/256 outputs each.
+// writes out - mn.  256 threads: KP/256 outputs each, or for KP = 64 and 128
+// groups of KP threads that take a run of the rows each (the rows are read one
+// memory latency per kVmRows of them).
 template <bool TRACK>
 __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uint32_t mmn, const int32_t *R,
                        bool block0, const int32_t *crow, int32_t cm, uint32_t *out, uint32_t &mn,
                        uint32_t *args_out, uint32_t *red) {
+  __shared__ uint32_t gbest[256], garg[256];
   const int tid = threadIdx.x;
+  const int G = KP == 64 ? 4 : KP == 128 ? 2 : 1, col = G == 1 ? tid : tid & (KP - 1), grp = G == 1 ? 0 : tid / KP;
+  const int tb = grp * (KP / G), te = tb + KP / G;  // the group's rows
   uint32_t best[2] = {kSat, kSat}, arg[2] = {0, 0};
   // Rows t are taken kVmRows at a time: every load of a batch is issued
   // before any is used (one memory latency per batch rather than per row),
   // from clamped addresses, so that no load sits behind a branch; entries of
   // columns past KP (or past K for R) are never used.
-  const int c0 = tid, c1 = tid + 256;
+  const int c0 = col, c1 = tid + 256;
   auto take = [&](int t, uint32_t a0, uint32_t a1) __attribute__((always_inline)) {
     const uint32_t vt = umin(v[t], kBig);
     const uint32_t x0 = vt + a0, x1 = vt + a1;  // both below 2^32
@@ -386,7 +532,7 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
   };
   if (Mm) {
     const uint32_t *p0 = Mm + min(c0, KP - 1), *p1 = Mm + min(c1, KP - 1);
-    for (int t0 = 0; t0 < KP; t0 += kVmRows) {
+    for (int t0 = tb; t0 < te; t0 += kVmRows) {
       uint32_t m0[kVmRows], m1[kVmRows];
 #pragma unroll
       for (int u = 0; u < kVmRows; ++u) {
@@ -397,11 +543,11 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
       for (int u = 0; u < kVmRows; ++u) take(t0 + u, umin(m0[u] - mmn, kBig), umin(m1[u] - mmn, kBig));
     }
   } else if (block0) {
-    for (int t = 0; t < KP; ++t) take(t, 0u, 0u);
+    for (int t = tb; t < te; ++t) take(t, 0u, 0u);
   } else {
     const int32_t *p0 = R + min(c0, K - 1), *p1 = R + min(c1, K - 1);
     const bool k0 = c0 < K, k1 = c1 < K;
-    for (int t0 = 0; t0 < KP; t0 += kVmRows) {
+    for (int t0 = tb; t0 < te; t0 += kVmRows) {
       uint32_t m0[kVmRows], m1[kVmRows];
 #pragma unroll
       for (int u = 0; u < kVmRows; ++u) {
@@ -415,6 +561,19 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
         take(t0 + u, tin && k0 ? m0[u] : kBig, tin && k1 ? m1[u] : kBig);
       }
     }
+  }
+  if (G > 1) {  // the groups' minima, the lowest row on ties (groups in the order of their rows)
+    gbest[tid] = best[0];
+    garg[tid] = arg[0];
+    __syncthreads();
+    if (grp == 0)
+      for (int g = 1; g < G; ++g) {
+        const uint32_t o = gbest[g * KP + col];
+        if (o < best[0]) {
+          best[0] = o;
+          arg[0] = garg[g * KP + col];
+        }
+      }
   }
   uint32_t lmin = kSat;
 #pragma unroll
@@ -478,8 +637,8 @@ __global__ __launch_bounds__(256) void scan_down_kernel(DownArgs a) {
 // reports the search.
 template <typename T>
 __global__ __launch_bounds__(256) void scan_leaf_kernel(DownArgs a, T *__restrict__ table,
-                                                        const int32_t *__restrict__ flags,
-                                                        const WsHeader *__restrict__ hdr, SearchResult *__restrict__ res,
+                                                        const uint8_t *__restrict__ flags,
+                                                        const int32_t *__restrict__ rbad, int nbad, SearchResult *__restrict__ res,
                                                         int64_t *__restrict__ opt, int32_t *__restrict__ status) {
   extern __shared__ __align__(16) uint32_t sm[];
   __shared__ uint32_t red[4];
@@ -497,6 +656,10 @@ __global__ __launch_bounds__(256) void scan_leaf_kernel(DownArgs a, T *__restric
   if (i > 0)
     for (int s = tid; s < K; s += 256) table[((size_t)b * a.N + i) * K + s] = (T)args[s];
   if (i == a.N - 1) {
+    int fl = 0;
+    for (int x = tid; x < a.N; x += 256) fl |= flags[(size_t)b * a.N + x];
+    for (int x = tid; x < nbad; x += 256) fl |= rbad[x] ? SCANF_BAD : 0;
+    const int isbad = __syncthreads_or(fl & SCANF_BAD), isinf = __syncthreads_or(fl & SCANF_INFEASIBLE);
     // lowest final state of least value
     uint32_t pk = kSat;
     int ps = 0;
@@ -518,10 +681,9 @@ __global__ __launch_bounds__(256) void scan_leaf_kernel(DownArgs a, T *__restric
     if (tid == 0) {
       uint64_t k = kred[0];
       for (int w = 1; w < 4; ++w) k = kred[w] < k ? kred[w] : k;
-      const int f = flags[b];
       int st = CFP_ST_OK;
-      if ((f & SCANF_BAD) || hdr->rflag) st = CFP_ST_BADINPUT;
-      else if ((f & SCANF_INFEASIBLE) || (uint32_t)(k >> 32) >= kBig) st = CFP_ST_INFEASIBLE;
+      if (isbad) st = CFP_ST_BADINPUT;
+      else if (isinf || (uint32_t)(k >> 32) >= kBig) st = CFP_ST_INFEASIBLE;
       const int64_t total = a.ptot[(size_t)b * a.N + i] + (int64_t)cm + (int64_t)mn + (int64_t)(k >> 32);
       status[b] = st;
       opt[b] = st == CFP_ST_OK ? total : INT64_MAX;
@@ -532,18 +694,35 @@ __global__ __launch_bounds__(256) void scan_leaf_kernel(DownArgs a, T *__restric
   }
 }
 
-hipError_t launch_scan(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, size_t region_bytes,
-                       uint8_t *table, int elem, SearchResult *res, const WsHeader *hdr, int64_t *opt,
-                       int32_t *status, hipStream_t st) {
-  (void)region_bytes;
+hipError_t launch_scan(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region, uint8_t *table,
+                       int elem, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st) {
   const int N = d.n_blocks, K = d.k, B = d.batch, KP = scan_kp(K);
   const ScanLayout S = scan_layout(N, K, B);
+  const int top = S.nlev - 1;
   int32_t *cmin = (int32_t *)(region + S.cmin);
-  int32_t *flags = (int32_t *)(region + S.flags);
-  hipLaunchKernelGGL(scan_fill_kernel, dim3(1), dim3(256), 0, st, (uint32_t *)flags, (size_t)B, 0u);
-  hipLaunchKernelGGL(scan_prep_kernel, dim3((B * N + 3) / 4), dim3(256), 0, st, d.cost, N, K, B, cmin, flags);
+  PrepArgs p;
+  p.cost = d.cost;
+  p.rtab = d.rtab;
+  p.N = N;
+  p.K = K;
+  p.KP = KP;
+  p.B = B;
+  p.rwords = (size_t)d.n_tables * K * K;
+  p.rlimit = cfp_r_limit(CFP_V_SCAN, K);
+  p.em = em;
+  p.redge = redge_dev;
+  p.cmin = cmin;
+  p.flags = region + S.flags;
+  p.rbad = (int32_t *)(region + S.rbad);
+  p.mn = (uint32_t *)(region + S.mn0);
+  p.mn_words = S.mn_words;
+  p.pre = (uint32_t *)(region + S.pre[top]);  // the root's prefix is the zero vector
+  p.ptot = (int64_t *)(region + S.ptot[top]);
+  const size_t want = std::max(((size_t)B * N + 3) / 4, (p.rwords + 1023) / 1024);
+  const int blocks = (int)std::min<size_t>(std::max<size_t>(want, 1), kScanPrepBlocks);
+  hipLaunchKernelGGL(scan_prep_kernel, dim3(blocks), dim3(256), 0, st, p);
 
-  // up-sweep
+  // up-sweep: every node but the last of its level
   for (int l = 1; l < S.nlev; ++l) {
     ScanArgs a;
     a.N = N; a.K = K; a.KP = KP; a.B = B; a.l = l;
@@ -554,13 +733,19 @@ hipError_t launch_scan(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_
     a.dst_mn = (uint32_t *)(region + S.mn[l]);
     a.cnt_src = S.cnt[l - 1];
     a.cnt_dst = S.cnt[l];
-    hipLaunchKernelGGL(scan_fill_kernel, dim3(64), dim3(256), 0, st, a.dst_mn, (size_t)B * S.cnt[l], kSat);
-    const int pairs = S.cnt[l - 1] / 2;
-    if (pairs > 0) {
-      const dim3 grid((KP / kTile) * (KP / kTile), pairs, B);
+    const int pairs = S.cnt[l] - 1;
+    if (pairs < 1) continue;
+    // the small tile where the large ones do not pad to it or do not fill the chip
+    const int big = (KP / kTile) * (KP / kTile);
+    timer_begin(st);
+    if (KP % kTile || (long long)big * pairs * B < 256) {
+      const dim3 grid((KP / kTileS) * (KP / kTileS), pairs, B);
+      if (l == 1) timed_launch(scan_gemm64_kernel<true>, grid, dim3(256), 0, st, a);
+      else timed_launch(scan_gemm64_kernel<false>, grid, dim3(256), 0, st, a);
+    } else {
+      const dim3 grid(big, pairs, B);
       // vector loads need unpadded rows and 16-byte aligned inputs
       const bool full = K == KP && ((uintptr_t)d.cost % 16) == 0 && ((uintptr_t)d.rtab % 16) == 0;
-      timer_begin(st);
       if (l == 1) {
         if (full) timed_launch(scan_gemm_kernel<true, true>, grid, dim3(256), 0, st, a);
         else timed_launch(scan_gemm_kernel<true, false>, grid, dim3(256), 0, st, a);
@@ -568,23 +753,17 @@ hipError_t launch_scan(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_
         if (full) timed_launch(scan_gemm_kernel<false, true>, grid, dim3(256), 0, st, a);
         else timed_launch(scan_gemm_kernel<false, false>, grid, dim3(256), 0, st, a);
       }
-      timer_end(st);
     }
-    if (S.cnt[l - 1] & 1) hipLaunchKernelGGL(scan_carry_kernel, dim3(64, B), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(scan_tot_kernel, dim3((B * S.cnt[l] + 255) / 256), dim3(256), 0, st, a,
-                       (const int64_t *)(region + S.tot[l - 1]), (int64_t *)(region + S.tot[l]));
+    timer_end(st);
   }
+  if (S.nlev > 2) hipLaunchKernelGGL(scan_tot_kernel, dim3(B), dim3(1024), 0, st, S, region, N);
 
-  // down-sweep: the root's prefix is the zero vector
-  const int top = S.nlev - 1;
-  hipLaunchKernelGGL(scan_fill_kernel, dim3(64), dim3(256), 0, st, (uint32_t *)(region + S.pre[top]),
-                     (size_t)B * KP, 0u);
-  hipLaunchKernelGGL(scan_fill_kernel, dim3(1), dim3(256), 0, st, (uint32_t *)(region + S.ptot[top]),
-                     (size_t)B * 2, 0u);
+  // down-sweep
+  DownArgs a;
+  a.N = N; a.K = K; a.KP = KP; a.B = B;
+  a.cost = d.cost; a.rtab = d.rtab; a.redge = redge_dev; a.cmin = cmin;
   for (int l = top; l >= 1; --l) {
-    DownArgs a;
-    a.N = N; a.K = K; a.KP = KP; a.B = B; a.l = l;
-    a.cost = d.cost; a.rtab = d.rtab; a.redge = redge_dev; a.cmin = cmin;
+    a.l = l;
     a.mat = l - 1 >= 1 ? (const uint32_t *)(region + S.mat[l - 1]) : nullptr;
     a.mat_mn = (const uint32_t *)(region + S.mn[l - 1]);
     a.mat_tot = (const int64_t *)(region + S.tot[l - 1]);
@@ -596,20 +775,21 @@ hipError_t launch_scan(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_
     a.ccnt = S.cnt[l - 1];
     hipLaunchKernelGGL(scan_down_kernel, dim3(S.cnt[l], B), dim3(256), (size_t)KP * 4, st, a);
   }
-  DownArgs a;
-  a.N = N; a.K = K; a.KP = KP; a.B = B; a.l = 0;
-  a.cost = d.cost; a.rtab = d.rtab; a.redge = redge_dev; a.cmin = cmin;
+  a.l = 0;
   a.mat = nullptr; a.mat_mn = nullptr; a.mat_tot = nullptr;
   a.pre = (const uint32_t *)(region + S.pre[0]);
   a.ptot = (const int64_t *)(region + S.ptot[0]);
   a.cpre = nullptr; a.cptot = nullptr;
   a.cnt = N; a.ccnt = 0;
   const size_t lds = (size_t)3 * KP * 4;
+  const uint8_t *flags = region + S.flags;
+  const int32_t *rbad = (const int32_t *)(region + S.rbad);
   if (elem == 1)
-    hipLaunchKernelGGL(scan_leaf_kernel<uint8_t>, dim3(N, B), dim3(256), lds, st, a, table, flags, hdr, res, opt, status);
+    hipLaunchKernelGGL(scan_leaf_kernel<uint8_t>, dim3(N, B), dim3(256), lds, st, a, table, flags, rbad, blocks, res, opt,
+                       status);
   else
-    hipLaunchKernelGGL(scan_leaf_kernel<uint16_t>, dim3(N, B), dim3(256), lds, st, a, (uint16_t *)table, flags, hdr, res,
-                       opt, status);
+    hipLaunchKernelGGL(scan_leaf_kernel<uint16_t>, dim3(N, B), dim3(256), lds, st, a, (uint16_t *)table, flags, rbad,
+                       blocks, res, opt, status);
   return hipGetLastError();
 }
 
