@@ -327,6 +327,19 @@ int dp_chain_launch(const cfp_chain_desc *d, int form, const EdgeMap &em, const 
   return e == hipSuccess ? CFP_OK : CFP_ERR_HIP;
 }
 
+// The memory variant's launches; the edge map is uploaded only where it has no
+// short period (the forward kernels read nothing else of the header).
+int mem_launch(const cfp_chain_desc *d, const uint8_t *mem, int n_mem, int32_t *budget, bool fill, const WsLayout &L,
+               uint8_t *w, int64_t *opt, int32_t *status, int64_t *frontier, hipStream_t st) {
+  const EdgeMap em = edge_map(d->redge, d->n_blocks);
+  int rc;
+  if (em.period == 0 && (rc = upload_header(d, CFP_V_MEM, n_mem, L, w, st)) != CFP_OK) return rc;
+  return launch_chain_mem_fwd(*d, mem, n_mem, budget, fill, (int32_t *)(w + L.redge), em, w + L.table, w + L.mem,
+                              w + L.memreg, (SearchResult *)(w + L.result), opt, status, frontier, st) == hipSuccess
+             ? CFP_OK
+             : CFP_ERR_HIP;
+}
+
 }  // namespace
 
 #pragma GCC visibility push(default)
@@ -383,13 +396,7 @@ int cfp_dp_chain_mem(const cfp_chain_desc *d, const uint8_t *mem, int32_t n_mem,
   if (!ws || ws_bytes < L.total) return CFP_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   uint8_t *w = (uint8_t *)ws;
-  if ((rc = upload_header(d, CFP_V_MEM, n_mem, L, ws, st)) != CFP_OK) return rc;
-  WsHeader *hdr = (WsHeader *)w;
-  // the memory forward checks the range of R while packing it
-  if (launch_chain_mem_fwd(*d, mem, n_mem, budget, (const int32_t *)(w + L.redge), w + L.table, w + L.mem,
-                           w + L.memreg, (SearchResult *)(w + L.result), hdr, opt, status, nullptr, st) != hipSuccess)
-    return CFP_ERR_HIP;
-  return CFP_OK;
+  return mem_launch(d, mem, n_mem, const_cast<int32_t *>(budget), false, L, w, opt, status, nullptr, st);
 }
 
 int cfp_mem_frontier(const cfp_chain_desc *d, const uint8_t *mem, int32_t n_mem, void *ws, size_t ws_bytes,
@@ -403,16 +410,8 @@ int cfp_mem_frontier(const cfp_chain_desc *d, const uint8_t *mem, int32_t n_mem,
   if (!ws || ws_bytes < L.total) return CFP_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   uint8_t *w = (uint8_t *)ws;
-  if ((rc = upload_header(d, CFP_V_MEM, n_mem, L, ws, st)) != CFP_OK) return rc;
-  WsHeader *hdr = (WsHeader *)w;
-  int32_t *budget = (int32_t *)(w + L.fbudget);
-  if (launch_fill_i32(budget, d->batch, n_mem - 1, st) != hipSuccess) return CFP_ERR_HIP;
-  // the memory forward checks the range of R while packing it
-  if (launch_chain_mem_fwd(*d, mem, n_mem, budget, (const int32_t *)(w + L.redge), w + L.table, w + L.mem,
-                           w + L.memreg, (SearchResult *)(w + L.result), hdr, (int64_t *)(w + L.fopt), status,
-                           frontier, st) != hipSuccess)
-    return CFP_ERR_HIP;
-  return CFP_OK;
+  return mem_launch(d, mem, n_mem, (int32_t *)(w + L.fbudget), true, L, w, (int64_t *)(w + L.fopt), status, frontier,
+                    st);
 }
 
 int cfp_minplus_scan(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t *opt, int32_t *status,
@@ -424,12 +423,11 @@ int cfp_minplus_scan(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t
   if (!ws || ws_bytes < L.total) return CFP_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   uint8_t *w = (uint8_t *)ws;
-  if ((rc = upload_header(d, CFP_V_SCAN, 0, L, ws, st)) != CFP_OK) return rc;
-  WsHeader *hdr = (WsHeader *)w;
-  if (launch_validate_rtab(d->rtab, d->n_tables, d->k, cfp_r_limit(CFP_V_SCAN, d->k), hdr, st) != hipSuccess)
-    return CFP_ERR_HIP;
-  if (launch_scan(*d, (const int32_t *)(w + L.redge), w + L.scan, L.scan_bytes, w + L.table, L.elem,
-                  (SearchResult *)(w + L.result), hdr, opt, status, st) != hipSuccess)
+  // the scan checks R itself and reads nothing of the header but the edge map
+  const EdgeMap em = edge_map(d->redge, d->n_blocks);
+  if (em.period == 0 && (rc = upload_header(d, CFP_V_SCAN, 0, L, ws, st)) != CFP_OK) return rc;
+  if (launch_scan(*d, (int32_t *)(w + L.redge), em, w + L.scan, w + L.table, L.elem, (SearchResult *)(w + L.result),
+                  opt, status, st) != hipSuccess)
     return CFP_ERR_HIP;
   return CFP_OK;
 }

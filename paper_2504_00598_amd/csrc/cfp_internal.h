@@ -155,19 +155,18 @@ int mem_stride(int n_mem);  // bucket stride of the memory variant's argmin tabl
 bool chain_mem_supported(int k, int n_tables);
 int32_t mem_r_limit(int k);
 size_t mem_region_bytes(int n, int k, int batch, int n_mem, int n_tables);
-hipError_t launch_chain_mem_fwd(const cfp_chain_desc &d, const uint8_t *mem, int n_mem, const int32_t *budget,
-                                const int32_t *redge_dev, uint8_t *table, uint8_t *mem_copy, uint8_t *region,
-                                SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,
-                                int64_t *frontier, hipStream_t st);
-hipError_t launch_fill_i32(int32_t *p, int n, int32_t v, hipStream_t st);
+// fill: the budgets are written (n_mem - 1) instead of read.
+hipError_t launch_chain_mem_fwd(const cfp_chain_desc &d, const uint8_t *mem, int n_mem, int32_t *budget, bool fill,
+                                int32_t *redge_dev, const EdgeMap &em, uint8_t *table, uint8_t *mem_copy,
+                                uint8_t *region, SearchResult *res, int64_t *opt, int32_t *status, int64_t *frontier,
+                                hipStream_t st);
 hipError_t launch_traceback_chain(int n, int k, int batch, int elem, const uint8_t *table,
                                   const SearchResult *res, uint16_t *maps, int32_t *bounds, int nchunks,
                                   int32_t *plan, hipStream_t st);
 hipError_t launch_traceback_mem(int n, int k, int batch, int n_mem, const uint8_t *table, const uint8_t *mem,
                                 const SearchResult *res, int32_t *plan, hipStream_t st);
-hipError_t launch_scan(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, size_t region_bytes,
-                       uint8_t *table, int elem, SearchResult *res, const WsHeader *hdr, int64_t *opt,
-                       int32_t *status, hipStream_t st);
+hipError_t launch_scan(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region, uint8_t *table,
+                       int elem, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
 size_t scan_region_bytes(int n, int k, int batch);
 
 // Benchmarking timer: when armed, brackets each launch of a forward call's

@@ -563,6 +563,7 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
   // chunk p-1 is its true one (so the fix-up of chunk p is valid), otherwise
   // s_row holds the true end row of chunk p-1.
   int64_t total = dk[endq(0)];
+  const uint32_t qlast = a.ckrow[((size_t)b * a.nq + a.nq - 1) * 64 + lane];  // (in flight during the loop)
   bool spec_true = true, reruns = false;  // reruns: the run before was a rerun that met no checkpoint
   int p = 1;
   while (p < P) {
@@ -621,7 +622,7 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
       __syncthreads();  // s_q is rewritten at the top of the loop
     }
   }
-  const uint32_t qv = spec_true ? a.ckrow[((size_t)b * a.nq + a.nq - 1) * 64 + lane] : s_row[lane];
+  const uint32_t qv = spec_true ? qlast : s_row[lane];
   const int bad = __syncthreads_or(fl & 1), infeasible = __syncthreads_or(fl & 2);
   if (wid != 0) return;
   // The final row has minimum 0: the lowest state at the minimum.
@@ -724,11 +725,12 @@ hipError_t launch_chain_wave(const cfp_chain_desc &d, int32_t *redge_dev, const 
   a.endrow = (uint32_t *)(region + off);
   a.rbad = rbad;
   a.nbad = std::min(kWPackBlocks, d.n_tables * 16);
-  hipLaunchKernelGGL(wave_pack_kernel, dim3(a.nbad), dim3(256), 0, st, d.rtab, d.n_tables, d.k, rpk,
-                     cfp_r_limit(CFP_V_CHAIN, d.k), rbad, em, redge_dev, d.n_blocks);
-  // the usual period, and table i for phase i: the table index is a constant per row of a block
+  // the usual period, and table i for phase i: the table index is a constant per
+  // row of a block, and the map is not needed
   bool periodic = em.period == kWU;
   for (int i = 1; periodic && i < em.head + kWU; ++i) periodic = em.map[i] == i % kWU;
+  hipLaunchKernelGGL(wave_pack_kernel, dim3(a.nbad), dim3(256), 0, st, d.rtab, d.n_tables, d.k, rpk,
+                     cfp_r_limit(CFP_V_CHAIN, d.k), rbad, periodic ? EdgeMap{} : em, redge_dev, d.n_blocks);
   if (c.NW == 4) {
     if (periodic) launch_wave_passes<12, 4>(a, res, opt, status, st);
     else launch_wave_passes<0, 4>(a, res, opt, status, st);

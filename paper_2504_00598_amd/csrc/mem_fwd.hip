@@ -74,7 +74,7 @@ constexpr int mem_slot_words(int kp) { return 16 * kp + 32; }
 constexpr int64_t kOffInf = (int64_t)1 << 62;
 constexpr int kSpinLimit = 1 << 20;
 
-enum { MEMF_BAD = 1, MEMF_TIMEOUT = 2 };
+enum { MEMF_TIMEOUT = 2 };
 
 template <int KP>
 struct MemShape {
@@ -99,77 +99,109 @@ struct MemShape {
 static int mem_kp(int k) { return k <= 128 ? (k + 15) / 16 * 16 : k <= 192 ? 192 : 256; }
 static int mem_bits(int k) { return k <= 32 ? 5 : k <= 64 ? 6 : k <= 128 ? 7 : 8; }
 
-// Per-(search, block) records: cost cst[s] (kSat for an unavailable or
-// padding state), shift dsh[s], the least shift dmin over the available
-// states; a copy of mem for the traceback; validation of mem, the costs and
-// the budget.  One wave per (b, i) row.
-__global__ __launch_bounds__(256) void mem_prep_kernel(const int32_t *__restrict__ cost, const uint8_t *__restrict__ mem,
-                                                       const int32_t *__restrict__ budget, int N, int K, int KP, int M,
-                                                       int B, uint32_t *__restrict__ cst, uint8_t *__restrict__ dsh,
-                                                       int32_t *__restrict__ dmin, uint8_t *__restrict__ mem_copy,
-                                                       int32_t *__restrict__ mflags) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= B * N) return;
-  const int b = row / N;
-  const size_t base = (size_t)row * K;
-  bool bad = false;
-  int dm = kMemShift + 1;
-  for (int s = lane; s < KP; s += 64) {
-    uint32_t c = kSat;
-    int d = 0;
-    if (s < K) {
-      d = mem[base + s];
-      const int32_t cv = cost[base + s];
-      mem_copy[base + s] = (uint8_t)d;
-      bad |= d >= M || d > kMemShift || cv < 0;
-      if (d > kMemShift) d = kMemShift;
-      if (cv >= 0 && cv != CFP_COST_INF) {
-        c = (uint32_t)cv;
-        dm = min(dm, d);
-      }
-    }
-    cst[(size_t)row * KP + s] = c;
-    dsh[(size_t)row * KP + s] = (uint8_t)d;
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) dm = min(dm, __shfl_xor(dm, o, 64));
-  if (lane == 0) dmin[row] = dm > kMemShift ? 0 : dm;  // a block with no available state: every y saturates
-  if (lane == 0 && (row % N) == 0 && (budget[b] < 0 || budget[b] >= M)) bad = true;
-  if (__any(bad) && lane == 0) atomicOr(&mflags[b], MEMF_BAD);
-}
-
-// Packed tables, state-major: rT[e][s][t] = (R[e][t][s] << b) | t.  A padding
-// predecessor or state gets ((QCAP - 1) << b) | t: with the capped row value
-// QCAP its candidate is the largest value that fits, above every candidate
-// through a column's minimum state.  Every R entry is read here, so the range
-// check (entries in [0, 2^(31-b))) is made on the way and flagged in the header.
-__global__ void mem_pack_rtab_kernel(const int32_t *__restrict__ rtab, int E, int K, int KP, int bits,
-                                     uint32_t *__restrict__ rT, int32_t limit, WsHeader *__restrict__ hdr) {
-  const size_t total = (size_t)E * KP * KP;
-  const uint32_t pad = (((1u << (31 - bits)) - 1u) << bits);
-  for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < total; x += (size_t)gridDim.x * blockDim.x) {
-    const int t = (int)(x % KP), s = (int)((x / KP) % KP), e = (int)(x / ((size_t)KP * KP));
-    uint32_t v = pad | (uint32_t)t;
-    if (s < K && t < K) {
-      const int32_t r = rtab[((size_t)e * K + t) * K + s];
-      if (r < 0 || r >= limit) hdr->rflag = 1;
-      v = ((uint32_t)r << bits) | (uint32_t)t;
-    }
-    rT[x] = v;
-  }
-}
-
 struct MemWs {
   uint32_t *cst;       // [B][N][KP]
   uint8_t *dsh;        // [B][N][KP]
   int32_t *dmin;       // [B][N]
   uint32_t *rT;        // [E][KP][KP]
-  int32_t *mflags;     // [B]
+  int32_t *mflags;     // [B]: MEMF_TIMEOUT
+  uint8_t *rowbad;     // [B][N]: a value of this row is out of range (row 0: or the budget)
+  int32_t *rbad;       // range flags of R, one per workgroup of the first launch
   int32_t *cons;       // [B][nchunk] (stride kMemFlagStride): last step whose slot a chunk has consumed
   uint64_t *ring;      // [B][nchunk][kMemSlots][mem_slot_words(KP)]: word | step << 32
   int nchunk;
 };
+
+struct MemPrepArgs {
+  const int32_t *cost, *rtab;
+  const uint8_t *mem;
+  int32_t *budget;      // [B]; written (M - 1) where fill is set, else checked
+  bool fill;
+  int N, K, KP, M, B, E, bits;
+  int32_t rlimit;
+  MemWs w;
+  size_t nring;
+  int nflag;
+  uint8_t *mem_copy;
+  EdgeMap em;
+  int32_t *redge;
+};
+constexpr int kMemPrepBlocks = 1024;  // most workgroups of the first launch
+
+// The first launch of a call (three of their own, a budget fill and an upload of
+// the header took 20 us more):
+//   * stamps every ring word with an impossible step number, so that nothing a
+//     previous call left in the workspace is taken for a fresh slot, marks every
+//     slot as consumed before step 0 and clears the flags;
+//   * writes out a periodic edge map, and the budgets of a frontier call;
+//   * packs the tables, state-major: rT[e][s][t] = (R[e][t][s] << b) | t.  A
+//     padding predecessor or state gets ((QCAP - 1) << b) | t: with the capped row
+//     value QCAP its candidate is the largest value that fits, above every
+//     candidate through a column's minimum state.  Every R entry is read here, so
+//     the range check (entries in [0, 2^(31-b))) is made on the way;
+//   * per-(search, block) records, one wave per row: cost cst[s] (kSat for an
+//     unavailable or padding state), shift dsh[s], the least shift dmin over the
+//     available states; a copy of mem for the traceback; validation of mem, the
+//     costs and the budget.
+__global__ __launch_bounds__(256) void mem_prep_kernel(MemPrepArgs a) {
+  const int lane = threadIdx.x & 63, N = a.N, K = a.K, KP = a.KP;
+  const size_t stride = (size_t)gridDim.x * blockDim.x, first = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (size_t x = first; x < a.nring; x += stride) a.w.ring[x] = ~0ull;
+  for (size_t x = first; x < (size_t)a.nflag; x += stride) a.w.cons[x] = -1;
+  for (size_t x = first; x < (size_t)a.B; x += stride) {
+    a.w.mflags[x] = 0;
+    if (a.fill) a.budget[x] = a.M - 1;
+  }
+  a.em.write(a.redge, N);
+  const size_t total = (size_t)a.E * KP * KP;
+  const uint32_t pad = (((1u << (31 - a.bits)) - 1u) << a.bits);
+  bool off = false;
+  for (size_t x = first; x < total; x += stride) {
+    const int t = (int)(x % KP), s = (int)((x / KP) % KP), e = (int)(x / ((size_t)KP * KP));
+    uint32_t v = pad | (uint32_t)t;
+    if (s < K && t < K) {
+      const int32_t r = a.rtab[((size_t)e * K + t) * K + s];
+      off |= r < 0 || r >= a.rlimit;
+      v = ((uint32_t)r << a.bits) | (uint32_t)t;
+    }
+    a.w.rT[x] = v;
+  }
+  const int any = __syncthreads_or(off);
+  if (threadIdx.x == 0) a.w.rbad[blockIdx.x] = any ? 1 : 0;
+  for (size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < (size_t)a.B * N; row += (size_t)gridDim.x * 4) {
+    const size_t base = row * K;
+    bool bad = false;
+    int dm = kMemShift + 1;
+    for (int s = lane; s < KP; s += 64) {
+      uint32_t c = kSat;
+      int d = 0;
+      if (s < K) {
+        d = a.mem[base + s];
+        const int32_t cv = a.cost[base + s];
+        a.mem_copy[base + s] = (uint8_t)d;
+        bad |= d >= a.M || d > kMemShift || cv < 0;
+        if (d > kMemShift) d = kMemShift;
+        if (cv >= 0 && cv != CFP_COST_INF) {
+          c = (uint32_t)cv;
+          dm = min(dm, d);
+        }
+      }
+      a.w.cst[row * KP + s] = c;
+      a.w.dsh[row * KP + s] = (uint8_t)d;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) dm = min(dm, __shfl_xor(dm, o, 64));
+    if (!a.fill && row % N == 0) {
+      const int32_t bud = a.budget[row / N];
+      bad |= bud < 0 || bud >= a.M;
+    }
+    const bool rb = __any(bad);
+    if (lane == 0) {
+      a.w.dmin[row] = dm > kMemShift ? 0 : dm;  // a block with no available state: every y saturates
+      a.w.rowbad[row] = rb;
+    }
+  }
+}
 
 struct MemArgs {
   const int32_t *budget;
@@ -179,7 +211,7 @@ struct MemArgs {
   uint8_t *table;        // [B][N][K][MS]
   int MS;                // bucket stride of the table
   SearchResult *res;
-  const WsHeader *hdr;
+  int nbad;              // words of w.rbad
   int64_t *opt;
   int32_t *status;
   int64_t *frontier;     // [B][M] or null
@@ -303,7 +335,9 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
   const int bucket = m0 + 16 * blk + m;
   const MemWs &W = a.w;
 
-  if (W.mflags[b] & MEMF_BAD) {  // written by the prep kernel earlier in the stream
+  bool rowbad = false;  // flags of the first launch
+  for (int x = tid; x < N; x += S::THREADS) rowbad |= W.rowbad[(size_t)b * N + x] != 0;
+  if (__syncthreads_or(rowbad)) {
     if (a.frontier && !io && g == 0 && bucket < M) a.frontier[(size_t)b * M + bucket] = INT64_MAX;
     if (j == 0 && tid == 0) {
       a.status[b] = CFP_ST_BADINPUT;
@@ -760,12 +794,15 @@ __global__ __launch_bounds__(MemShape<KP>::THREADS) void mem_fwd_kernel(MemArgs 
       f = umin(f, q | (uint32_t)s);
     }
     f = wave_min(f);
+    bool rbad = false;
+    for (int x = lane; x < a.nbad; x += 64) rbad |= W.rbad[x] != 0;
+    rbad = __any(rbad);
     if (lane == 0) {
       const int64_t o = offs[fin][H + cb];
       const int sf = __hip_atomic_load(&W.mflags[b], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
       int st = CFP_ST_OK;
       if (s_timeout || (sf & MEMF_TIMEOUT)) st = CFP_ST_TIMEOUT;
-      else if (a.hdr->rflag) st = CFP_ST_BADINPUT;
+      else if (rbad) st = CFP_ST_BADINPUT;
       else if (o >= kOffInf) st = CFP_ST_INFEASIBLE;
       else if ((f >> BITS) != 0) st = CFP_ST_OVERFLOW;  // the least state of a feasible bucket is 0
       a.status[b] = st;
@@ -918,6 +955,8 @@ static MemWs carve(uint8_t *region, int n, int k, int batch, int n_mem, int n_ta
   w.dmin = (int32_t *)(region + off); off = align_up(off + (size_t)batch * n * 4);
   w.rT = (uint32_t *)(region + off); off = align_up(off + (size_t)n_tables * KP * KP * 4);
   w.mflags = (int32_t *)(region + off); off = align_up(off + (size_t)batch * 4);
+  w.rowbad = region + off; off = align_up(off + (size_t)batch * n);
+  w.rbad = (int32_t *)(region + off); off = align_up(off + kMemPrepBlocks * 4);
   w.cons = (int32_t *)(region + off); off = align_up(off + chunks * kMemFlagStride * 4);
   w.ring = (uint64_t *)(region + off); off = align_up(off + chunks * kMemSlots * mem_slot_words(KP) * 8);
   if (bytes) *bytes = off;
@@ -928,18 +967,6 @@ size_t mem_region_bytes(int n, int k, int batch, int n_mem, int n_tables) {
   size_t bytes = 0;
   (void)carve(nullptr, n, k, batch, n_mem, n_tables, &bytes);
   return bytes;
-}
-
-// Clears the flags, marks every slot as consumed before step 0 and stamps
-// every ring word with an impossible step number, so that nothing a previous
-// call left in the workspace is taken for a fresh slot.
-__global__ void mem_init_kernel(int32_t *mflags, int nb, int32_t *cons, int nflag, uint64_t *ring, size_t nring) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < (size_t)(nb + nflag); x += stride) {
-    if (x < (size_t)nb) mflags[x] = 0;
-    else cons[x - nb] = -1;
-  }
-  for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < nring; x += stride) ring[x] = ~0ull;
 }
 
 // Workgroups of one launch that the device holds at once, per XCD: the
@@ -964,22 +991,35 @@ static int mem_xcd_capacity() {
 }
 
 template <int KP>
-static hipError_t launch_mem(const cfp_chain_desc &d, const uint8_t *mem, int n_mem, const int32_t *budget,
-                             const int32_t *redge_dev, uint8_t *table, uint8_t *mem_copy, uint8_t *region,
-                             SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,
-                             int64_t *frontier, hipStream_t st) {
+static hipError_t launch_mem(const cfp_chain_desc &d, const uint8_t *mem, int n_mem, int32_t *budget, bool fill,
+                             int32_t *redge_dev, const EdgeMap &em, uint8_t *table, uint8_t *mem_copy, uint8_t *region,
+                             SearchResult *res, int64_t *opt, int32_t *status, int64_t *frontier, hipStream_t st) {
   const int N = d.n_blocks, K = d.k, B = d.batch, E = d.n_tables;
   MemWs w = carve(region, N, K, B, n_mem, E, nullptr);
-  const int nflag = B * w.nchunk * kMemFlagStride;
-  const size_t nring = (size_t)B * w.nchunk * kMemSlots * mem_slot_words(KP);
-  hipLaunchKernelGGL(mem_init_kernel, dim3((unsigned)std::min<size_t>((nring + 255) / 256, 1024)), dim3(256), 0, st,
-                     w.mflags, B, w.cons, nflag, w.ring, nring);
-  const size_t packed = (size_t)E * KP * KP;
-  hipLaunchKernelGGL(mem_pack_rtab_kernel, dim3((unsigned)std::min<size_t>((packed + 255) / 256, 2048)), dim3(256), 0,
-                     st, d.rtab, E, K, KP, MemShape<KP>::BITS, w.rT, cfp_r_limit(CFP_V_MEM, K),
-                     const_cast<WsHeader *>(hdr));
-  hipLaunchKernelGGL(mem_prep_kernel, dim3((B * N + 3) / 4), dim3(256), 0, st, d.cost, mem, budget, N, K, KP, n_mem,
-                     B, w.cst, w.dsh, w.dmin, mem_copy, w.mflags);
+  MemPrepArgs p;
+  p.cost = d.cost;
+  p.rtab = d.rtab;
+  p.mem = mem;
+  p.budget = budget;
+  p.fill = fill;
+  p.N = N;
+  p.K = K;
+  p.KP = KP;
+  p.M = n_mem;
+  p.B = B;
+  p.E = E;
+  p.bits = MemShape<KP>::BITS;
+  p.rlimit = cfp_r_limit(CFP_V_MEM, K);
+  p.w = w;
+  p.nring = (size_t)B * w.nchunk * kMemSlots * mem_slot_words(KP);
+  p.nflag = B * w.nchunk * kMemFlagStride;
+  p.mem_copy = mem_copy;
+  p.em = em;
+  p.redge = redge_dev;
+  const size_t want = std::max(std::max(((size_t)B * N + 3) / 4, (p.nring + 255) / 256),
+                               ((size_t)E * KP * KP + 255) / 256);
+  const int blocks = (int)std::min<size_t>(want, kMemPrepBlocks);
+  hipLaunchKernelGGL(mem_prep_kernel, dim3(blocks), dim3(256), 0, st, p);
   // Rounds of searches whose chunks the device holds at once: with per_xcd
   // searches on each of the 8 XCDs, a round takes 8 * per_xcd searches.
   const int cap = mem_xcd_capacity<KP>();
@@ -996,7 +1036,7 @@ static hipError_t launch_mem(const cfp_chain_desc &d, const uint8_t *mem, int n_
   a.B = B;
   a.table = table;
   a.res = res;
-  a.hdr = hdr;
+  a.nbad = blocks;
   a.opt = opt;
   a.status = status;
   a.frontier = frontier;
@@ -1005,7 +1045,7 @@ static hipError_t launch_mem(const cfp_chain_desc &d, const uint8_t *mem, int n_
     a.b0 = b0;
     a.nb = std::min(round, B - b0);
     a.B8 = (a.nb + 7) / 8 * 8;
-    timed_launch(mem_fwd_kernel<KP>, dim3(w.nchunk * a.B8), dim3(MemShape<KP>::THREADS), 0, st, a, redge_dev,
+    timed_launch(mem_fwd_kernel<KP>, dim3(w.nchunk * a.B8), dim3(MemShape<KP>::THREADS), 0, st, a, (const int32_t *)redge_dev,
                  (const int32_t *)w.dmin);
   }
   timer_end(st);
@@ -1016,13 +1056,13 @@ bool chain_mem_supported(int k, int n_tables) { return k >= 1 && k <= kMemMaxK &
 
 int32_t mem_r_limit(int k) { return k >= 1 && k <= kMemMaxK ? (int32_t)(1u << (31 - mem_bits(k))) : 0; }
 
-hipError_t launch_chain_mem_fwd(const cfp_chain_desc &d, const uint8_t *mem, int n_mem, const int32_t *budget,
-                                const int32_t *redge_dev, uint8_t *table, uint8_t *mem_copy, uint8_t *region,
-                                SearchResult *res, const WsHeader *hdr, int64_t *opt, int32_t *status,
-                                int64_t *frontier, hipStream_t st) {
+hipError_t launch_chain_mem_fwd(const cfp_chain_desc &d, const uint8_t *mem, int n_mem, int32_t *budget, bool fill,
+                                int32_t *redge_dev, const EdgeMap &em, uint8_t *table, uint8_t *mem_copy,
+                                uint8_t *region, SearchResult *res, int64_t *opt, int32_t *status, int64_t *frontier,
+                                hipStream_t st) {
 #define CFP_MEM_CASE(KPV) \
   case KPV:               \
-    return launch_mem<KPV>(d, mem, n_mem, budget, redge_dev, table, mem_copy, region, res, hdr, opt, status, frontier, st);
+    return launch_mem<KPV>(d, mem, n_mem, budget, fill, redge_dev, em, table, mem_copy, region, res, opt, status, frontier, st);
   switch (mem_kp(d.k)) {
     CFP_MEM_CASE(16)
     CFP_MEM_CASE(32)
@@ -1038,15 +1078,6 @@ hipError_t launch_chain_mem_fwd(const cfp_chain_desc &d, const uint8_t *mem, int
       return hipErrorInvalidValue;
   }
 #undef CFP_MEM_CASE
-}
-
-__global__ void fill_i32_kernel(int32_t *p, int n, int32_t v) {
-  for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) p[x] = v;
-}
-
-hipError_t launch_fill_i32(int32_t *p, int n, int32_t v, hipStream_t st) {
-  hipLaunchKernelGGL(fill_i32_kernel, dim3((n + 255) / 256 < 64 ? (n + 255) / 256 : 64), dim3(256), 0, st, p, n, v);
-  return hipGetLastError();
 }
 
 }  // namespace cfp
