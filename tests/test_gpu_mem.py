@@ -228,3 +228,18 @@ def test_traceback_windows(N, K, mhi):
     cost, rtab, redge, mem = mem_case([82, N, K, mhi], 6, N, K, 3, 0, 1000, 0, mhi, M)
     budget = np.array([M - 1, M - 2, M - 9, M // 2, M // 2 + 16, M // 3], np.int32)
     assert_mem_parity(cost, rtab, redge, mem, M, budget, f"windows N={N} K={K} mhi={mhi}")
+
+
+@pytest.mark.parametrize("head", [1, 3, 4])
+def test_edge_map_with_a_head(head):
+    """A head and a period of 61 entries: in the launch's arguments (64 entries together) or
+    uploaded."""
+    need_gpu()
+    say("mem edge map", head)
+    cost, rtab, redge, mem = mem_case([13, head], 3, 150, 12, 5, 10_000, 1_000_000, 0, 5, 70)
+    redge = np.resize(np.random.default_rng(14).integers(0, 5, size=61), 150).astype(np.int32)
+    redge[:head] = (redge[:head] + 1) % 5
+    budget = np.array([69, 66, 63], np.int32)
+    mem[:, 60:] = 0
+    mem[:, :60] //= 4
+    assert_mem_parity(cost, rtab, redge, mem, 70, budget, f"edge head {head}")

@@ -37,6 +37,29 @@ def test_shapes(N, K):
     assert_scan_parity(cost, rtab, redge, f"N={N} K={K}")
 
 
+# The padding follows K: tiles of 64 up to 64, for 129 .. 192 and for 257 .. 320, tiles of 128
+# otherwise; a level with fewer than 256 large tiles uses the small ones whatever the padding.
+# Both tiles, their first and last K, levels of one to three nodes, and edge maps that travel in
+# the launch arguments (a period behind a head, 64 entries in all) or are uploaded.
+@pytest.mark.parametrize("N,K,B", [(2, 64, 5), (3, 65, 1), (4, 128, 2), (5, 192, 1), (7, 193, 1), (3, 257, 2),
+                                   (5, 320, 1), (4, 321, 1), (530, 128, 2), (140, 130, 2), (37, 384, 3)])
+@pytest.mark.parametrize("edges", ["period 1", "head 3, period 61", "head 4, period 61", "random"])
+def test_tiles_and_edge_maps(N, K, B, edges):
+    need_gpu()
+    say("scan tiles", N, K, B, edges)
+    from paper_2504_00598_amd import cfp_r_limit
+    E = 7
+    cost, rtab, redge = case([11, N, K, B], B, N, K, E, 0, 1_000_000)
+    rtab = np.minimum(rtab, cfp_r_limit(2, K) - 1).astype(np.int32)
+    if edges == "period 1":
+        redge[:] = 5
+    elif edges != "random":
+        head = int(edges[5])
+        redge = np.resize(np.random.default_rng(12).integers(0, E, size=61), N).astype(np.int32)
+        redge[:head] = (redge[:head] + 1) % E
+    assert_scan_parity(cost, rtab, redge, f"tiles N={N} K={K} B={B} {edges}")
+
+
 @pytest.mark.parametrize("N,K", [(9, 3), (40, 16), (13, 128), (6, 200)])
 def test_heavy_ties(N, K):
     need_gpu()
