@@ -88,6 +88,8 @@ static ScanLayout scan_layout(int n, int k, int batch) {
     S.tot[l] = off;
     off = align_up(off + c * 8);
     S.pre[l] = off;
+    S.ptot[l] = off;
+    if (l == 0 && S.nlev > 1) continue;  // the leaves take level 1's
     off = align_up(off + c * KP * 4);
     S.ptot[l] = off;
     off = align_up(off + c * 8);
@@ -485,9 +487,9 @@ __global__ __launch_bounds__(1024) void scan_tot_kernel(ScanLayout S, uint8_t *r
 }
 
 struct DownArgs {
-  int N, K, KP, B, l;  // level l >= 1: children at level l-1
+  int N, K, KP, B;  // level l >= 2: children at level l-1
   const int32_t *cost, *rtab, *redge, *cmin;
-  const uint32_t *mat;     // matrices of level l-1 (l-1 >= 1)
+  const uint32_t *mat;     // matrices of level l-1
   const uint32_t *mat_mn;  // [B][cnt[l-1]]
   const int64_t *mat_tot;
   const uint32_t *pre;     // prefix vectors entering the nodes of level l
@@ -499,19 +501,23 @@ struct DownArgs {
 
 constexpr int kVmRows = 16;  // matrix rows in flight per thread in vecmat
 
-// v (x) M for one vector and one matrix (a block's transfer matrix when
-// the matrices are level 0); returns the minimum of the output in `mn` and
-// writes out - mn.  256 threads: KP/256 outputs each, or for KP = 64 and 128
-// groups of KP threads that take a run of the rows each (the rows are read one
-// memory latency per kVmRows of them).
-template <bool TRACK>
+// v (x) M for one vector and one matrix: a stored product, or with LEAF a
+// block's transfer matrix with the lowest argmins; returns the minimum of the
+// output in `mn` and writes out - mn.  256 threads: KP/256 outputs each, or with
+// SPLIT (KP = 64 and 128) groups of KP threads that take a run of the rows each
+// (the rows are read one memory latency per kVmRows of them).  Without SPLIT the
+// rows are uniform constants: kept per thread they cost a 64-bit vector add per
+// load (leaves of 4096 blocks, K = 512, 4 searches, a workgroup per block: 1032 us
+// against 792).
+template <bool LEAF, bool SPLIT>
 __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uint32_t mmn, const int32_t *R,
-                       bool block0, const int32_t *crow, int32_t cm, uint32_t *out, uint32_t &mn,
-                       uint32_t *args_out, uint32_t *red) {
-  __shared__ uint32_t gbest[256], garg[256];
+                       const int32_t *crow, int32_t cm, uint32_t *out, uint32_t &mn, uint32_t *args_out,
+                       uint32_t *red) {
+  __shared__ uint32_t gbest[SPLIT ? 256 : 1], garg[SPLIT ? 256 : 1];
   const int tid = threadIdx.x;
-  const int G = KP == 64 ? 4 : KP == 128 ? 2 : 1, col = G == 1 ? tid : tid & (KP - 1), grp = G == 1 ? 0 : tid / KP;
-  const int tb = grp * (KP / G), te = tb + KP / G;  // the group's rows
+  const int G = !SPLIT ? 1 : KP == 64 ? 4 : 2, col = SPLIT ? tid & (KP - 1) : tid;
+  const int grp = SPLIT ? __builtin_amdgcn_readfirstlane(tid / KP) : 0;  // wave-uniform: KP >= 64
+  const int tb = SPLIT ? grp * (KP / G) : 0, te = SPLIT ? tb + KP / G : KP;  // the group's rows
   uint32_t best[2] = {kSat, kSat}, arg[2] = {0, 0};
   // Rows t are taken kVmRows at a time: every load of a batch is issued
   // before any is used (one memory latency per batch rather than per row),
@@ -530,7 +536,7 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
       arg[1] = t;
     }
   };
-  if (Mm) {
+  if (!LEAF) {
     const uint32_t *p0 = Mm + min(c0, KP - 1), *p1 = Mm + min(c1, KP - 1);
     for (int t0 = tb; t0 < te; t0 += kVmRows) {
       uint32_t m0[kVmRows], m1[kVmRows];
@@ -542,7 +548,7 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
 #pragma unroll
       for (int u = 0; u < kVmRows; ++u) take(t0 + u, umin(m0[u] - mmn, kBig), umin(m1[u] - mmn, kBig));
     }
-  } else if (block0) {
+  } else if (!R) {  // block 0
     for (int t = tb; t < te; ++t) take(t, 0u, 0u);
   } else {
     const int32_t *p0 = R + min(c0, K - 1), *p1 = R + min(c1, K - 1);
@@ -562,7 +568,7 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
       }
     }
   }
-  if (G > 1) {  // the groups' minima, the lowest row on ties (groups in the order of their rows)
+  if (SPLIT) {  // the groups' minima, the lowest row on ties (groups in the order of their rows)
     gbest[tid] = best[0];
     garg[tid] = arg[0];
     __syncthreads();
@@ -581,10 +587,10 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
     const int s = tid + 256 * h;
     if (s >= KP) continue;
     uint32_t o = umin(best[h], kBig);
-    if (!Mm) o = umin(sat_add(o, cadj(crow, cm, s, K)), kBig);  // a block adds its own cost
+    if (LEAF) o = umin(sat_add(o, cadj(crow, cm, s, K)), kBig);  // a block adds its own cost
     best[h] = o;
     lmin = umin(lmin, o);
-    if (TRACK) args_out[s] = arg[h];
+    if (LEAF) args_out[s] = arg[h];
   }
   lmin = wave_min(lmin);
   if ((tid & 63) == 0) red[tid >> 6] = lmin;
@@ -598,8 +604,9 @@ __device__ void vecmat(const uint32_t *v, int KP, int K, const uint32_t *Mm, uin
   __syncthreads();
 }
 
-// Down-sweep one level: node (l, j) hands its prefix to its left child and
-// prefix (x) left-child matrix to its right child.
+// Down-sweep one level l >= 2: node (l, j) hands its prefix to its left child
+// and prefix (x) left-child matrix to its right child.
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void scan_down_kernel(DownArgs a) {
   extern __shared__ __align__(16) uint32_t sm[];
   __shared__ uint32_t red[4];
@@ -617,25 +624,18 @@ __global__ __launch_bounds__(256) void scan_down_kernel(DownArgs a) {
   if (ib >= a.ccnt) return;
   uint32_t *rv = a.cpre + ((size_t)b * a.ccnt + ib) * KP;
   uint32_t mn;
-  int64_t mtot;
-  if (a.l == 1) {
-    // left child is block ia: its transfer matrix from R and c
-    const int32_t *crow = a.cost + ((size_t)b * a.N + ia) * a.K;
-    const int32_t cm = a.cmin[(size_t)b * a.N + ia];
-    const int32_t *R = ia == 0 ? nullptr : a.rtab + (size_t)a.redge[ia] * a.K * a.K;
-    vecmat<false>(v, KP, a.K, nullptr, 0, R, ia == 0, crow, cm, rv, mn, nullptr, red);
-    mtot = cm;
-  } else {
-    const size_t mi = (size_t)b * a.ccnt + ia;
-    vecmat<false>(v, KP, a.K, a.mat + mi * KP * KP, a.mat_mn[mi], nullptr, false, nullptr, 0, rv, mn, nullptr, red);
-    mtot = a.mat_tot[mi];
-  }
-  if (tid == 0) a.cptot[(size_t)b * a.ccnt + ib] = ptot + mtot + (int64_t)mn;
+  const size_t mi = (size_t)b * a.ccnt + ia;
+  vecmat<false, SPLIT>(v, KP, a.K, a.mat + mi * KP * KP, a.mat_mn[mi], nullptr, nullptr, 0, rv, mn, nullptr, red);
+  if (tid == 0) a.cptot[(size_t)b * a.ccnt + ib] = ptot + a.mat_tot[mi] + (int64_t)mn;
 }
 
 // Leaves: D[i] = prefix(i) (x) T_i with the argmin table row i; block N-1
-// reports the search.
-template <typename T>
+// reports the search.  A workgroup takes both blocks of a level-1 node: D[i] of
+// the first is the prefix that enters the second, so the down-sweep has no step
+// for level 1, which formed the same vector in a launch of its own (4096 blocks,
+// K = 512, 4 searches: down-sweep and leaves 3.14 ms with it and rows kept per
+// thread, 2.42 now).
+template <typename T, bool SPLIT>
 __global__ __launch_bounds__(256) void scan_leaf_kernel(DownArgs a, T *__restrict__ table,
                                                         const uint8_t *__restrict__ flags,
                                                         const int32_t *__restrict__ rbad, int nbad, SearchResult *__restrict__ res,
@@ -644,18 +644,27 @@ __global__ __launch_bounds__(256) void scan_leaf_kernel(DownArgs a, T *__restric
   __shared__ uint32_t red[4];
   const int KP = a.KP, K = a.K;
   uint32_t *v = sm, *out = sm + KP, *args = sm + 2 * KP;
-  const int i = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const uint32_t *pv = a.pre + ((size_t)b * a.N + i) * KP;
+  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const uint32_t *pv = a.pre + ((size_t)b * a.cnt + j) * KP;
   for (int t = tid; t < KP; t += 256) v[t] = pv[t];
   __syncthreads();
-  const int32_t *crow = a.cost + ((size_t)b * a.N + i) * K;
-  const int32_t cm = a.cmin[(size_t)b * a.N + i];
-  const int32_t *R = i == 0 ? nullptr : a.rtab + (size_t)a.redge[i] * K * K;
-  uint32_t mn;
-  vecmat<true>(v, KP, K, nullptr, 0, R, i == 0, crow, cm, out, mn, args, red);
-  if (i > 0)
-    for (int s = tid; s < K; s += 256) table[((size_t)b * a.N + i) * K + s] = (T)args[s];
-  if (i == a.N - 1) {
+  int64_t tot = a.ptot[(size_t)b * a.cnt + j];  // offset of `out`
+  const int i1 = min(2 * j + 1, a.N - 1);
+  for (int i = 2 * j; i <= i1; ++i) {
+    const int32_t cm = a.cmin[(size_t)b * a.N + i];
+    const int32_t *R = i == 0 ? nullptr : a.rtab + (size_t)a.redge[i] * K * K;
+    uint32_t mn;
+    vecmat<true, SPLIT>(v, KP, K, nullptr, 0, R, a.cost + ((size_t)b * a.N + i) * K, cm, out, mn, args, red);
+    tot += (int64_t)cm + (int64_t)mn;
+    if (i > 0)
+      for (int s = tid; s < K; s += 256) table[((size_t)b * a.N + i) * K + s] = (T)args[s];
+    if (i < i1) {
+      uint32_t *x = v;
+      v = out;
+      out = x;
+    }
+  }
+  if (i1 == a.N - 1) {
     int fl = 0;
     for (int x = tid; x < a.N; x += 256) fl |= flags[(size_t)b * a.N + x];
     for (int x = tid; x < nbad; x += 256) fl |= rbad[x] ? SCANF_BAD : 0;
@@ -684,7 +693,7 @@ __global__ __launch_bounds__(256) void scan_leaf_kernel(DownArgs a, T *__restric
       int st = CFP_ST_OK;
       if (isbad) st = CFP_ST_BADINPUT;
       else if (isinf || (uint32_t)(k >> 32) >= kBig) st = CFP_ST_INFEASIBLE;
-      const int64_t total = a.ptot[(size_t)b * a.N + i] + (int64_t)cm + (int64_t)mn + (int64_t)(k >> 32);
+      const int64_t total = tot + (int64_t)(k >> 32);
       status[b] = st;
       opt[b] = st == CFP_ST_OK ? total : INT64_MAX;
       res[b].final_state = st == CFP_ST_OK ? (int32_t)(k & 0xFFFFFFFFu) : -1;
@@ -762,9 +771,9 @@ hipError_t launch_scan(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMa
   DownArgs a;
   a.N = N; a.K = K; a.KP = KP; a.B = B;
   a.cost = d.cost; a.rtab = d.rtab; a.redge = redge_dev; a.cmin = cmin;
-  for (int l = top; l >= 1; --l) {
-    a.l = l;
-    a.mat = l - 1 >= 1 ? (const uint32_t *)(region + S.mat[l - 1]) : nullptr;
+  const bool split = KP <= 128;
+  for (int l = top; l >= 2; --l) {
+    a.mat = (const uint32_t *)(region + S.mat[l - 1]);
     a.mat_mn = (const uint32_t *)(region + S.mn[l - 1]);
     a.mat_tot = (const int64_t *)(region + S.tot[l - 1]);
     a.pre = (const uint32_t *)(region + S.pre[l]);
@@ -773,23 +782,23 @@ hipError_t launch_scan(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMa
     a.cptot = (int64_t *)(region + S.ptot[l - 1]);
     a.cnt = S.cnt[l];
     a.ccnt = S.cnt[l - 1];
-    hipLaunchKernelGGL(scan_down_kernel, dim3(S.cnt[l], B), dim3(256), (size_t)KP * 4, st, a);
+    if (split) hipLaunchKernelGGL(scan_down_kernel<true>, dim3(S.cnt[l], B), dim3(256), (size_t)KP * 4, st, a);
+    else hipLaunchKernelGGL(scan_down_kernel<false>, dim3(S.cnt[l], B), dim3(256), (size_t)KP * 4, st, a);
   }
-  a.l = 0;
+  const int leaf = std::min(1, top);
   a.mat = nullptr; a.mat_mn = nullptr; a.mat_tot = nullptr;
-  a.pre = (const uint32_t *)(region + S.pre[0]);
-  a.ptot = (const int64_t *)(region + S.ptot[0]);
+  a.pre = (const uint32_t *)(region + S.pre[leaf]);
+  a.ptot = (const int64_t *)(region + S.ptot[leaf]);
   a.cpre = nullptr; a.cptot = nullptr;
-  a.cnt = N; a.ccnt = 0;
+  a.cnt = S.cnt[leaf]; a.ccnt = 0;
   const size_t lds = (size_t)3 * KP * 4;
   const uint8_t *flags = region + S.flags;
   const int32_t *rbad = (const int32_t *)(region + S.rbad);
-  if (elem == 1)
-    hipLaunchKernelGGL(scan_leaf_kernel<uint8_t>, dim3(N, B), dim3(256), lds, st, a, table, flags, rbad, blocks, res, opt,
-                       status);
-  else
-    hipLaunchKernelGGL(scan_leaf_kernel<uint16_t>, dim3(N, B), dim3(256), lds, st, a, (uint16_t *)table, flags, rbad,
-                       blocks, res, opt, status);
+  auto leaves = [&](auto kernel, auto *tab) {
+    hipLaunchKernelGGL(kernel, dim3(a.cnt, B), dim3(256), lds, st, a, tab, flags, rbad, blocks, res, opt, status);
+  };
+  if (elem == 1) leaves(split ? scan_leaf_kernel<uint8_t, true> : scan_leaf_kernel<uint8_t, false>, table);
+  else leaves(scan_leaf_kernel<uint16_t, false>, (uint16_t *)table);  // K > 256
   return hipGetLastError();
 }
 
