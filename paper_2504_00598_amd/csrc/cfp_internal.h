@@ -73,8 +73,8 @@ struct WsLayout {
   size_t split = 0;    // chain variant, K > 64: exchange slots and flags of the split kernel
   size_t narrow = 0;   // chain variant, K <= 32: chunk records, checkpoints
   size_t wave = 0;     // chain variant, 32 < K <= 64 on long chains: packed tables, chunk records, checkpoints
-  size_t cw = 0;       // chain variant, 128 < K <= 256 on long chains: packed tables, chunk records, checkpoints
-  size_t seg = 0;      // segment variant, small batches: speculative rows, running sums, chunk records
+  size_t cw = 0;       // chain variant, 64 < K <= 512 on long chains: packed tables, chunk records, checkpoints
+  size_t seg = 0;      // segment variant: plans and argmins of the classes, or the chunked form's rows and records
   size_t scan = 0;     // scan variant: start of its private region
   size_t scan_bytes = 0;
   size_t total = 0;

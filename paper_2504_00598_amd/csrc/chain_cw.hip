@@ -49,7 +49,7 @@
 // one search, 2237 to 331 us for 128; 393 blocks, K = 81, 24 searches: 762 to 105
 // us.)  At KP = 512 a batch of at most eight searches would leave most compute
 // units idle; there teams of four workgroups split the states of each chunk
-// (state-split teams, below).  Chunks are at least 32 rows long up to KP = 256 and 64 at KP = 512:
+// (state-split teams, below).  Chunks are at least 32 rows long up to KP = 256 and 48 at KP = 512:
 // runs become parallel after 14 rows on average and 38 at most at K = 128, 18
 // and about 40 at K = 256, 21 and 50 at K = 512 (uniform random costs).
 //

@@ -512,8 +512,9 @@ __global__ __launch_bounds__(64 * NW) void chain_wave_kernel(WaveArgs a) {
   }
 }
 
-// Fix-up pass, grid (ceil(B/NW), P-1): the searches of a workgroup rerun chunk p >= 1 from the last checkpoint row of chunk p-1 (their true row
-// once chunk p-1 has met) until each row equals chunk p's checkpoint at a quad
+// Fix-up pass, grid (ceil(B/NW), P-1): the searches of a workgroup rerun chunk
+// p >= 1 from the last checkpoint row of chunk p-1 (their true row once chunk
+// p-1 has met) until each row equals chunk p's checkpoint at a quad
 // end; the tables are staged once per quad for all of them, a search that has
 // met stops computing, and the workgroup stops when all have met.
 template <int EP, int NW>
