@@ -974,6 +974,13 @@ size_t mem_region_bytes(int n, int k, int batch, int n_mem, int n_tables) {
 // every chunk of a launch must be resident together.  Workgroup x runs on XCD
 // x mod 8, and the chunks of search b of a launch are workgroups j * B8 + b,
 // so they share one XCD and its L2 cache.
+// The hardware spreads a workgroup's waves over the four SIMDs of a compute
+// unit and does not shift the start from one workgroup to the next, so every
+// SIMD must have room for ceil(waves / 4) more: a workgroup of six waves counts
+// as one of eight.  (The query counts waves per compute unit.  Asked for six it
+// says three workgroups of 96 registers, and two fit: 64 searches of 200 or more
+// blocks with 1024 buckets then waited for chunks that could not start and ended
+// with CFP_ST_TIMEOUT.)
 template <int KP>
 static int mem_xcd_capacity() {
   static std::once_flag once;
@@ -982,8 +989,8 @@ static int mem_xcd_capacity() {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mem_fwd_kernel<KP>, MemShape<KP>::THREADS, 0) !=
-            hipSuccess)
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mem_fwd_kernel<KP>,
+                                                     (MemShape<KP>::THREADS + 255) / 256 * 256, 0) != hipSuccess)
       return;
     cap = (cus / 8) * per_cu;
   });

@@ -243,3 +243,15 @@ def test_edge_map_with_a_head(head):
     mem[:, 60:] = 0
     mem[:, :60] //= 4
     assert_mem_parity(cost, rtab, redge, mem, 70, budget, f"edge head {head}")
+
+
+@pytest.mark.parametrize("K", [4, 17])
+def test_many_searches_of_many_buckets(K):
+    """More chunks than the device holds at once, and more steps than the rings can run
+    ahead: searches wait for a round of their own, none for a chunk that cannot start."""
+    need_gpu()
+    N, M, B = 200, 1024, 64
+    say("mem residency", K)
+    cost, rtab, redge, mem = mem_case([83, K], B, N, K, 12, 10_000, 1_000_000, 0, 9, M)
+    budget = np.array([M - 1 - (M // 32) * (i % 16) for i in range(B)], np.int32)
+    assert_mem_parity(cost, rtab, redge, mem, M, budget, f"residency K={K}")
