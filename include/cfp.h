@@ -269,9 +269,12 @@ int cfp_search_chain(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t
  *   d       as for cfp_dp_chain (redge on the host)
  *   opt     device [B] int64, status device [B] int32, plan device [B][N] int32:
  *           as cfp_dp_chain and cfp_traceback write them.
- * Returns CFP_ERR_WORKSPACE when the search needs more than
- * CFP_NOALLOC_MAX_BYTES of workspace (cfp_workspace_bytes(d, CFP_V_CHAIN, 0)),
- * CFP_ERR_HIP if the array's device address cannot be obtained, otherwise as
+ * Returns CFP_ERR_WORKSPACE when the argmin entries of all searches (B N K, two
+ * bytes each for K > 256) and, for K > 64, the packed tables (E KP^2 words with
+ * KP = 128, 256 or 512) and row minima (4 B N) do not fit in
+ * CFP_NOALLOC_MAX_BYTES beside a few words per search and 64 rows (a batch whose
+ * checkpoints do not fit beside them runs in slices of searches), CFP_ERR_HIP if
+ * the array's device address cannot be obtained, otherwise as
  * cfp_dp_chain.  Every call on one GPU uses that GPU's one array: calls that
  * overlap on a GPU (different streams or threads with work in flight at the
  * same time) race and must be serialised by the caller; calls in one stream

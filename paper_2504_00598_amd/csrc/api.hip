@@ -12,7 +12,23 @@
 
 namespace cfp {
 
+ChainForm chain_form(int n, int k, int batch, int n_tables) {
+  if (chain_narrow_supported(n, k, n_tables)) return kFormNarrow;
+  if (chain_wave_supported(n, k, n_tables, batch)) return kFormWave;
+  if (chain_cw_supported(n, k, batch)) return kFormCw;
+  return chain_row_form(k, batch, n_tables);
+}
+
+ChainForm chain_row_form(int k, int batch, int n_tables) {
+  return chain_fwd_split_supported(k, n_tables, batch) ? kFormSplit : kFormFwd;
+}
+
 WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables) {
+  return layout(variant, n, k, batch, n_mem, n_tables,
+                variant == CFP_V_CHAIN ? chain_form(n, k, batch, n_tables) : kFormFwd);
+}
+
+WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables, ChainForm form) {
   WsLayout L;
   L.elem = k > 256 ? 2 : 1;
   size_t off = sizeof(WsHeader);
@@ -41,22 +57,28 @@ WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables) {
   off = align_up(off + (size_t)batch * L.nchunks * k * 2);
   L.bounds = off;
   off = align_up(off + (size_t)batch * L.nchunks * 4);
-  if (variant == CFP_V_CHAIN && chain_fwd_wide_supported(k)) {
-    L.wide = off;
-    off = align_up(off + wide_region_bytes(n, k, batch, n_tables));
-    L.split = off;
-    off = align_up(off + split_region_bytes(k, batch));
-  }
-  if (variant == CFP_V_CHAIN && chain_narrow_supported(n, k, n_tables)) {
-    L.narrow = off;
-    off = align_up(off + narrow_region_bytes(n, k, n_tables, batch));
-  } else if (variant == CFP_V_CHAIN && chain_wave_supported(n, k, n_tables, batch)) {
-    L.wave = off;
-    off = align_up(off + wave_region_bytes(n, k, n_tables, batch));
-  }
-  if (variant == CFP_V_CHAIN && chain_cw_supported(n, k, batch)) {
-    L.cw = off;
-    off = align_up(off + cw_region_bytes(n, k, n_tables, batch));
+  if (variant == CFP_V_CHAIN) {  // the region of the form that runs
+    switch (form) {
+      case kFormNarrow:
+        L.narrow = off;
+        off = align_up(off + narrow_region_bytes(n, k, n_tables, batch));
+        break;
+      case kFormWave:
+        L.wave = off;
+        off = align_up(off + wave_region_bytes(n, k, n_tables, batch));
+        break;
+      case kFormCw:
+        L.cw = off;
+        off = align_up(off + cw_region_bytes(n, k, n_tables, batch));
+        break;
+      default:  // the split kernel packs its tables into the wide kernel's region
+        if (chain_fwd_wide_supported(k)) {
+          L.wide = off;
+          off = align_up(off + wide_region_bytes(n, k, batch, n_tables));
+          L.split = off;
+          off = align_up(off + split_region_bytes(k, batch));
+        }
+    }
   }
   if (variant == CFP_V_SEG) {
     L.seg = off;  // of either form
@@ -280,25 +302,15 @@ int put_header(const cfp_chain_desc *d, const WsLayout &L, uint8_t *w, hipStream
   return CFP_OK;
 }
 
-// The forms of the chain forward call (the first that supports the search runs it).
-enum { kFormNarrow, kFormWave, kFormCw, kFormSplit, kFormFwd };
-
-int chain_form(const cfp_chain_desc *d) {
-  if (chain_narrow_supported(d->n_blocks, d->k, d->n_tables)) return kFormNarrow;
-  if (chain_wave_supported(d->n_blocks, d->k, d->n_tables, d->batch)) return kFormWave;
-  if (chain_cw_supported(d->n_blocks, d->k, d->batch)) return kFormCw;
-  return chain_fwd_split_supported(d->k, d->n_tables, d->batch) ? kFormSplit : kFormFwd;
-}
-
 // Whether a call of this form reads the header or the uploaded edge map: the
 // chunk-parallel forms check R by themselves and take a periodic edge map in
 // their first launch's arguments (a host-to-device copy costs several
 // microseconds of GPU time).
-bool chain_reads_header(int form, const EdgeMap &em) { return form > kFormCw || em.period == 0; }
+bool chain_reads_header(ChainForm form, const EdgeMap &em) { return form > kFormCw || em.period == 0; }
 
 // The launches of a chain forward call once the header and the edge map are
 // in the workspace (or not needed: chain_reads_header).
-int dp_chain_launch(const cfp_chain_desc *d, int form, const EdgeMap &em, const WsLayout &L, uint8_t *w, int64_t *opt,
+int dp_chain_launch(const cfp_chain_desc *d, ChainForm form, const EdgeMap &em, const WsLayout &L, uint8_t *w, int64_t *opt,
                     int32_t *status, hipStream_t st) {
   WsHeader *hdr = (WsHeader *)w;
   int32_t *redge = (int32_t *)(w + L.redge);
@@ -379,7 +391,7 @@ int cfp_dp_chain(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t *op
   WsLayout L = layout(CFP_V_CHAIN, d->n_blocks, d->k, d->batch, 0, d->n_tables);
   if (!ws || ws_bytes < L.total) return CFP_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  const int form = chain_form(d);
+  const ChainForm form = chain_form(d->n_blocks, d->k, d->batch, d->n_tables);
   const EdgeMap em = edge_map(d->redge, d->n_blocks);
   if (chain_reads_header(form, em) && (rc = upload_header(d, CFP_V_CHAIN, 0, L, ws, st)) != CFP_OK) return rc;
   return dp_chain_launch(d, form, em, L, (uint8_t *)ws, opt, status, st);
@@ -471,21 +483,47 @@ int cfp_search_chain_noalloc(const cfp_chain_desc *d, int64_t *opt, int32_t *sta
   int rc = check_desc(d);
   if (rc != CFP_OK) return rc;
   if (!opt || !status || !plan) return CFP_ERR_ARG;
-  const WsLayout L = layout(CFP_V_CHAIN, d->n_blocks, d->k, d->batch, 0, d->n_tables);
-  if (L.total > (size_t)CFP_NOALLOC_MAX_BYTES) return CFP_ERR_WORKSPACE;  // beyond the static scratch
+  // The array takes every batch whose argmin entries (and, for K > 64, packed
+  // tables) fit.  The chunk-parallel forms keep checkpoints beside them, up to
+  // several times as much, so the batch runs in the fewest slices of searches whose
+  // regions fit; where not even one search's do, row after row and whole.
+  const int N = d->n_blocks, K = d->k, B = d->batch, E = d->n_tables;
+  const size_t limit = CFP_NOALLOC_MAX_BYTES;
+  ChainForm form = chain_row_form(K, B, E);
+  if (layout(CFP_V_CHAIN, N, K, B, 0, E, form).total > limit) return CFP_ERR_WORKSPACE;
+  int per = B;
+  for (int slices = 1;; ++slices) {
+    const int p = (B + slices - 1) / slices;
+    const ChainForm f = chain_form(N, K, p, E);
+    if (layout(CFP_V_CHAIN, N, K, p, 0, E, f).total <= limit) {
+      form = f;
+      per = p;
+      break;
+    }
+    if (p == 1) break;
+  }
   uint8_t *w = (uint8_t *)scratch_address();
   if (!w) return CFP_ERR_HIP;
   hipStream_t st = (hipStream_t)stream;
-  // Every region the kernels read is written earlier in the same call; the
-  // header (range flags included), where it is read, is rewritten whole.
-  const int form = chain_form(d);
-  const EdgeMap em = edge_map(d->redge, d->n_blocks);
-  if (chain_reads_header(form, em) && (rc = put_header(d, L, w, st)) != CFP_OK) return rc;
-  if ((rc = dp_chain_launch(d, form, em, L, w, opt, status, st)) != CFP_OK) return rc;
-  const hipError_t e = launch_traceback_chain(d->n_blocks, d->k, d->batch, L.elem, w + L.table,
-                                              (const SearchResult *)(w + L.result), (uint16_t *)(w + L.maps),
-                                              (int32_t *)(w + L.bounds), L.nchunks, plan, st);
-  return e == hipSuccess ? CFP_OK : CFP_ERR_HIP;
+  const EdgeMap em = edge_map(d->redge, N);
+  // Slices of one size, so of one form and layout; the last one ends with the batch
+  // and runs some searches again where the size does not divide it.
+  const WsLayout L = layout(CFP_V_CHAIN, N, K, per, 0, E, form);
+  for (int done = 0; done < B; done += per) {
+    // Every region the kernels read is written earlier in the same slice; the
+    // header (range flags included), where it is read, is rewritten whole.
+    const int b0 = std::min(done, B - per);
+    cfp_chain_desc s = *d;
+    s.batch = per;
+    s.cost += (size_t)b0 * N * K;
+    if (chain_reads_header(form, em) && (rc = put_header(&s, L, w, st)) != CFP_OK) return rc;
+    if ((rc = dp_chain_launch(&s, form, em, L, w, opt + b0, status + b0, st)) != CFP_OK) return rc;
+    if (launch_traceback_chain(N, K, per, L.elem, w + L.table, (const SearchResult *)(w + L.result),
+                               (uint16_t *)(w + L.maps), (int32_t *)(w + L.bounds), L.nchunks, plan + (size_t)b0 * N,
+                               st) != hipSuccess)
+      return CFP_ERR_HIP;
+  }
+  return CFP_OK;
 }
 
 int cfp_timer_start(int32_t max_launches) {

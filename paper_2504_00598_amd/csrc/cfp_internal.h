@@ -82,7 +82,15 @@ struct WsLayout {
   int nchunks = 0;
 };
 
+// The forms of the chain forward call, the chunk-parallel ones first, and the one
+// that runs a search: the first that supports it, else one of the last two, which
+// go row after row and keep nothing but argmin entries (and packed tables).
+enum ChainForm { kFormNarrow, kFormWave, kFormCw, kFormSplit, kFormFwd };
+ChainForm chain_form(int n, int k, int batch, int n_tables);
+ChainForm chain_row_form(int k, int batch, int n_tables);
+
 WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables);
+WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables, ChainForm form);
 
 // Launchers (return hipSuccess or the launch error).
 hipError_t launch_validate_rtab(const int32_t *rtab, int e, int k, int32_t limit, WsHeader *hdr,

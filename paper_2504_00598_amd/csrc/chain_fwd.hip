@@ -193,9 +193,11 @@ hipError_t launch_chain_fwd(const cfp_chain_desc &d, const int32_t *redge_dev, u
   if (chain_fwd_wide_supported(d.k)) return launch_chain_fwd_wide(d, redge_dev, wide, table, res, hdr, opt, status, st);
   const int k = d.k;
   timer_begin(st);
-  // K <= 32 with more tables than fit in LDS (33 .. 64 always runs in one of the forms above)
+  // K <= 32 with more tables than fit in LDS; 33 .. 64 with more tables than the form
+  // above holds, where the workspace has no room for them packed
   if (k <= 16) launch_kp<16>(d, redge_dev, table, res, hdr, opt, status, st);
-  else launch_kp<32>(d, redge_dev, table, res, hdr, opt, status, st);
+  else if (k <= 32) launch_kp<32>(d, redge_dev, table, res, hdr, opt, status, st);
+  else launch_kp<64>(d, redge_dev, table, res, hdr, opt, status, st);
   timer_end(st);
   return hipGetLastError();
 }

@@ -52,6 +52,33 @@ def test_noalloc_matches_workspace_calls():
         assert (got[1] == 0).all()
 
 
+# Searches whose argmin entries fit the scratch and whose workspace with checkpoints does not:
+# slices of two and more searches (K <= 32, 64 and 128), the last one overlapping, with a periodic
+# edge map and an uploaded one; tables that leave no room for one search's checkpoints (33 .. 64
+# with more tables than registers hold, K > 64), which run row after row.
+@pytest.mark.parametrize("N,K,B,E,periodic", [(1152, 27, 512, 12, True), (1152, 8, 2049, 12, False),
+                                              (288, 32, 2048, 12, True), (1152, 81, 128, 12, True),
+                                              (300, 64, 1001, 12, False), (600, 200, 1, 127, True),
+                                              (40, 50, 2, 2100, False), (1000, 300, 1, 31, False)])
+def test_noalloc_runs_whatever_fits_without_checkpoints(N, K, B, E, periodic):
+    need_gpu()
+    from paper_2504_00598_amd import _lib as L
+
+    say("noalloc in slices", N, K, B, E)
+    rs = np.random.default_rng([92, N, K, B])
+    cost = rs.integers(0, 1_000_000, size=(B, N, K)).astype(np.int32)
+    rtab = rs.integers(0, 1_000_000, size=(E, K, K)).astype(np.int32)
+    redge = (np.arange(N) % E if periodic else rs.integers(0, E, size=N)).astype(np.int32)
+    cost[B // 2, N // 2] = L.CFP_COST_INF  # one search without a plan
+    d = L.Desc(dev(cost), dev(rtab), redge)
+    assert L.cfp_workspace_bytes(d, L.CFP_V_CHAIN) > L.CFP_NOALLOC_MAX_BYTES
+    want = _reference(cost, rtab, redge)
+    got = _noalloc(cost, rtab, redge)
+    for name, a, b in zip(("opt", "status", "plan"), got, want):
+        np.testing.assert_array_equal(a, b, err_msg=name)
+    assert got[1][B // 2] == 1 and (np.delete(got[1], B // 2) == 0).all()
+
+
 def test_noalloc_rejects_searches_beyond_the_scratch():
     need_gpu()
     from paper_2504_00598_amd import _lib as L
