@@ -598,7 +598,7 @@ def test_narrow_edge_periods(period):
     assert_chain_parity(cost, rtab, redge, f"period {period}")
 
 
-@pytest.mark.parametrize("K,B", [(32, 3), (27, 40), (16, 5), (3, 70)])
+@pytest.mark.parametrize("K,B", [(32, 3), (27, 40), (16, 5), (3, 70), (18, 900), (30, 1200)])
 def test_narrow_rows_never_meet(K, B):
     """Every chunk misses its checkpoints: the final pass reruns the chains; largest R."""
     need_gpu()
@@ -610,6 +610,23 @@ def test_narrow_rows_never_meet(K, B):
     redge = (np.arange(N) % 12).astype(np.int32)
     say("narrow, no convergence", K, B)
     assert_chain_parity(cost, rtab, redge, f"narrow never meet K={K} B={B}")
+
+
+@pytest.mark.parametrize("N,K,B", [(1152, 27, 32), (1152, 16, 32), (700, 32, 300), (640, 20, 1100), (70, 32, 5600)])
+@pytest.mark.parametrize("ratio", [1, 30])
+def test_narrow_costs_that_repeat(N, K, B, ratio):
+    """Costs that repeat with the edge map, so that all chunks of a search run alike: batches
+    with searches none of whose chunks meets (the second fix-up, then the final pass), one,
+    four and sixteen searches per workgroup of the final pass, whole and half waves per task."""
+    need_gpu()
+    from paper_2504_00598_amd import cfp_r_limit
+    rs = np.random.default_rng([68, N, K, ratio])
+    cost = rs.integers(10_000, 1_000_000, size=(B, 12, K)).astype(np.int32)[:, np.arange(N) % 12]
+    rtab = rs.integers(0, min(ratio * 1_000_000, cfp_r_limit(0, K)), size=(12, K, K)).astype(np.int32)
+    rtab[:, np.arange(K), np.arange(K)] = 0
+    redge = (np.arange(N) % 12).astype(np.int32)
+    say("narrow, repeating costs", N, K, B, ratio)
+    assert_chain_parity(np.ascontiguousarray(cost), rtab, redge, f"repeating N={N} K={K} B={B} x{ratio}")
 
 
 @pytest.mark.parametrize("seed", range(4))
