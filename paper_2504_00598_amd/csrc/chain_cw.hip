@@ -192,7 +192,8 @@ struct CwChains {
 // checkpoints are written.  Fix-up: the start row (row r0 - 1) is start[c];
 // stops at the first quad end where every real chain has met its checkpoint at
 // a quad not before qmin[c].
-template <int KP, int CG, int MODE>
+// REAL: the chains that are computed (the others' values are not meaningful).
+template <int KP, int CG, int MODE, int REAL = CG>
 __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const bool *valid, int rs, int r0, int r1,
                                        const int *qmin, const uint32_t *const *start, CwSmem<KP, CG> &sm,
                                        CwChains<KP, CG> &ch) {
@@ -361,7 +362,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
         const int k = kk + bb;
         uint32_t v[CG][S::ROWS];  // the predecessors' values of this piece, per chain
 #pragma unroll
-        for (int c = 0; c < CG; ++c) {
+        for (int c = 0; c < REAL; ++c) {
           const uint32_t *qc = &sm.q[cur][c][hw * S::QH + qpad(S::PG * g + S::ROWS * k)];
           if constexpr (S::ROWS % 4 == 0) {
 #pragma unroll
@@ -387,7 +388,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
           for (int vv = 0; vv < S::NV; ++vv) {
             const typename S::Vec w = tb[bb][j][vv], y = tb[bb][j + 1][vv];
 #pragma unroll
-            for (int c = 0; c < CG; ++c) {
+            for (int c = 0; c < REAL; ++c) {
               uint32_t *ac = &acc[c][S::VW * vv];
 #pragma unroll
               for (int u = 0; u < S::VW; ++u)
@@ -403,7 +404,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
     }
     // Minima over the eight predecessor groups (one wave each) through LDS.
 #pragma unroll
-    for (int c = 0; c < CG; ++c)
+    for (int c = 0; c < REAL; ++c)
 #pragma unroll
       for (int vv = 0; vv < S::NV; ++vv) {
         typename S::Vec pv;
@@ -1094,13 +1095,13 @@ __global__ __launch_bounds__((CwShape<KP, CG>::THREADS), 1) void chain_cw_final_
 #pragma unroll
     for (int c = 0; c < CG; ++c) {
       bs[c] = b;
-      valid[c] = c == 0;  // the other chains duplicate it and are discarded
+      valid[c] = c == 0;  // the other chain is not computed
       start[c] = s_row;
       qmin[c] = cw_qmin(rec[p], endq(p));
     }
     CwChains<KP, CG> ch;
     const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
-    cw_run<KP, CG, kCFix>(a, bs, valid, r0, r0, r1, qmin, start, sm, ch);
+    cw_run<KP, CG, kCFix, 1>(a, bs, valid, r0, r0, r1, qmin, start, sm, ch);
     spec_true = ch.conv[0] >= 0;
     total += spec_true ? (int64_t)ch.dconv[0] + dk[endq(p)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
     __syncthreads();  // every thread has read s_row
@@ -1158,19 +1159,31 @@ int cw_chunk_rows(int n, int groups, int slots, int minrows) {
 
 // period: of the edge map (0 when it has none, or for the region's size).
 CwPlan cw_plan(int n, int k, int batch, int period) {
-  CwPlan c{0, 0, 0, 0, kCG, 1};
-  if (k <= 64 || k > 512) return c;
+  const CwPlan none{0, 0, 0, 0, kCG, 1};
+  CwPlan c = none;
+  if (k <= 64 || k > 512) return none;
   const int kp = k <= 128 ? 128 : k <= 256 ? 256 : 512;
   const int minrows = kp <= 256 ? CwShape<256, kCG>::MINROWS : CwShape<512, kCG>::MINROWS;
   const int groups = (batch + kCG - 1) / kCG;
   // K > 256 with at most two groups of four searches: state-split teams, every
   // workgroup resident on its own compute unit.
+  //
+  // At K > 256 a chunk-parallel call takes about as long on any number of rows up to
+  // 512 (two or three chunks of rows, which a workgroup takes 16.7 us each and a team
+  // 6), so shorter chains go row after row: teams 390 to 560 us against 2.7 to 3.0 us
+  // per row of the split kernel (even at 144 rows), others 950 to 1150 us against the
+  // same (at most 32 searches: even at about 350) or, up to 1900 in larger batches,
+  // 9.3 us per row of the wide kernel.
+  // (Taken from 49 rows on, whatever the batch, 64 blocks, K = 400, 9 searches took
+  // 789 us instead of 206.)
   const int cus = cw_device_cus();
   int CL;
   if (kp == 512 && groups <= kXMaxGroups && cus / (kXS * groups) >= 2) {
+    if (n < 144) return none;
     c.S = kXS;
-    CL = cw_chunk_rows(n, groups, cus / kXS, minrows);
+    CL = cw_chunk_rows(n, groups, cus / (kXS * groups) * groups, minrows);  // (at most cus workgroups)
   } else {
+    if (kp == 512 && n < (chain_fwd_split_supported(k, 1, batch) ? 352 : 128)) return none;
     // Two chains per workgroup while all chunks of the least length fit the chip
     // so: a row takes 1.1 us against 1.8 at KP = 128 (393 blocks, K = 81, 24
     // searches: 148 -> 105 us per call) and 3.0 against 4.3 at KP = 256 (1152
@@ -1184,16 +1197,21 @@ CwPlan cw_plan(int n, int k, int batch, int period) {
     c.G = (long long)half * pmax <= slots2 ? 2 : 4;
     CL = c.G == 2 ? cw_chunk_rows(n, half, slots2, minrows) : cw_chunk_rows(n, groups, slots4, minrows);
   }
+  // More searches than compute units go through the wide kernel in several rounds: two
+  // halves of a shorter chain instead (32 blocks, K = 200, 1000 searches: 375 to 229 us).
+  if (kp == 256 && n >= 16 && n <= minrows && batch > cus) CL = ((n + 1) / 2 + 3) & ~3;
   int P = (n + CL - 1) / CL;
-  if (P < 2) return CwPlan{0, 0, 0, 0, kCG, 1};
+  if (P < 2) return none;
   // Chunks of an even number of periods start in phase with a chain whose costs
   // repeat with its edge map and whose rows alternate between periods; worth a
-  // sixteenth more rows per chunk.
+  // sixteenth more rows per chunk, and at K > 256 up to 64 rows in place of 48 (1152
+  // blocks, K = 512, 16 tables, 8 searches of repeating costs: 7.2 ms in chunks of 48
+  // rows, 0.6 in 64; costs of their own 0.72 and 0.79).
   int u = period;
   while (u % 4) u += period;
   if (period % 4 == 0) u = 2 * period;
   const int al = period ? (CL + u - 1) / u * u : CL;
-  if (16 * al <= 17 * CL && al < n) {
+  if ((16 * al <= 17 * CL || (kp == 512 && al <= 64)) && al < n) {
     CL = al;
     P = (n + CL - 1) / CL;
   }

@@ -343,7 +343,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
       if constexpr (u == 1) CFP_QLOAD(2)
       if constexpr (u == 2) CFP_QLOAD(3)
     }
-    if (MODE == kWFix && u == 0) {  // this quad's checkpoint (runs start at a quad)
+    if (MODE == kWFix && u == 0 && (i >> 2) >= qmin) {  // this quad's checkpoint (runs start at a quad)
 #pragma unroll
       for (int g = 0; g < G; ++g) ckv[g] = (a.ckrow + ((size_t)srch(g) * a.nq + (i >> 2)) * 64)[lane];
     }
@@ -439,8 +439,8 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
         const int qbase = (i & ~3) + 4;
         CFP_Q4(CFP_QSTORE)
       }
-      if (MODE == kWFix) {
-        if (ch.conv[0] < 0 && (i >> 2) >= qmin && __ballot(ch.qv[0] != ckv[0]) == 0) {
+      if (MODE == kWFix && (i >> 2) >= qmin) {
+        if (ch.conv[0] < 0 && __ballot(ch.qv[0] != ckv[0]) == 0) {
           ch.conv[0] = i >> 2;
           ch.dconv[0] = ch.dsum[0];
           endr[0] = i;
@@ -448,7 +448,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
         if (lane == 0) sm.wact[(i >> 2) & 1][wid] = ch.conv[0] < 0 ? 1u : 0u;
       }
       __syncthreads();
-      if (MODE == kWFix) {  // every wave reads the same flags: a uniform decision
+      if (MODE == kWFix && (i >> 2) >= qmin) {  // every wave reads the same flags: a uniform decision
         const uint32_t f = lane < NW ? sm.wact[(i >> 2) & 1][lane] : 0u;
         stop = __ballot(f != 0) == 0;
         if (stop) {

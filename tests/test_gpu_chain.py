@@ -703,6 +703,23 @@ def test_chunked_patterns_of_unmet_chunks(K, B, N, share):
     assert_chain_parity(cost, rtab, redge, f"unmet K={K} B={B} share={share}")
 
 
+# Where a chunk-parallel call takes longer than one that goes row after row, the latter runs:
+# K > 256 below 144 rows (up to 8 searches), 352 (up to 32) or 128; 16 to 32 rows of K <= 256 run
+# as two halves in batches larger than the chip. Both sides of each line, halves of odd lengths,
+# and 16 tables, whose chunks grow to an even number of periods.
+@pytest.mark.parametrize("N,K,B,E", [(143, 300, 8, 3), (144, 300, 8, 3), (351, 257, 9, 3), (352, 257, 9, 3),
+                                     (127, 260, 33, 2), (128, 260, 33, 2), (60, 400, 12, 12), (127, 512, 4, 12),
+                                     (15, 200, 300, 2), (16, 200, 300, 2), (17, 256, 257, 3), (31, 130, 270, 2),
+                                     (32, 129, 300, 2), (33, 129, 300, 2), (300, 290, 5, 16)])
+def test_lines_between_forms(N, K, B, E):
+    need_gpu()
+    cost, rtab, redge = rand_case([73, N, K, B], B, N, K, E, 0, 1_000_000, inf_frac=0.05)
+    if E == 16:
+        redge = (np.arange(N) % E).astype(np.int32)
+    say("lines between forms", N, K, B, E)
+    assert_chain_parity(cost, rtab, redge, f"lines N={N} K={K} B={B}")
+
+
 @pytest.mark.parametrize("K", [100, 200, 300])
 def test_chunked_repeating_costs_and_range(K):
     """Costs that repeat with the edge map, then an R out of range on a map that travels in
