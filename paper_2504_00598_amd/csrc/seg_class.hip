@@ -9,8 +9,13 @@
 // and the class minima, which hold all the K-sized work, do not depend on it.
 // What is left is a chain of N-1 tiny min-plus products.  One workgroup of 16
 // waves per search:
-//   1. every wave: cost rows into LDS (coalesced), class minima with one thread
-//      per (segment, class), normalised by the segment's least cost;
+//   1. every wave: cost rows into LDS (coalesced), class minima with LM^2 lanes per
+//      segment, normalised by the segment's least cost.  A lane takes a class, or,
+//      where the map gives one class so many plans that its lane would set the time,
+//      every lane an equal share of the plans in the order of their classes, combined
+//      per class by LDS minima (96 segments, 8 x 8 boundary pairs, 441 of 512 plans in
+//      one of them, 64 searches: 338 us per call with a lane per class, 50 so; even maps
+//      are 10 to 50% slower so);
 //   2. wave p runs chunk p of the chain from each of the LM unit vectors at
 //      once (LM = 4 or 8 padded classes: lane (g, j) holds value j of the run
 //      from unit vector g), i.e. it forms the chunk's transfer matrix;
@@ -68,11 +73,17 @@ struct ScArgs {
 };
 
 // LDS of a search, in words: class minima, then (one region in turn) the staged
-// cost rows / the G, M and argument rows; the boundary tables; the edge map.
+// cost rows and their class keys / the G, M and argument rows; the boundary tables;
+// the edge map.
 template <int LM>
 struct ScLds {
   static __host__ __device__ size_t cls(int n) { return (size_t)n * LM * LM; }
   static __host__ __device__ size_t rows(int n) { return (size_t)n * (2 * LM + LM / 2); }
+  // room for at least one row with its class keys of two words
+  static __host__ __device__ size_t shared(int n, int tile, int k) {
+    const size_t a = rows(n), b = (size_t)tile * k, c = (size_t)k + 1 + 2 * LM * LM;
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
+  }
   static __host__ __device__ size_t tables(int e) { return (size_t)e * LM * LM; }
   static __host__ __device__ size_t edges(int n) { return (size_t)(n + 1) / 2; }
 };
@@ -197,15 +208,17 @@ __global__ __launch_bounds__(kScThreads) void seg_class_kernel(ScArgs a) {
   __shared__ uint32_t xr[kScWaves][LM];       // row offsets relative to the least
   __shared__ int64_t xo[kScWaves];            // least row offset
   __shared__ uint16_t order[CFP_MAX_K];       // plans by class, ascending within a class
+  __shared__ uint8_t oclass[CFP_MAX_K];       // their classes
   __shared__ uint16_t wcount[CFP_MAX_K / 64][64];
   __shared__ int cstart[65];
+  __shared__ int s_most;                      // plans of the largest class
   __shared__ unsigned long long csum;         // sum of the segments' least costs
   __shared__ int64_t s_off;                   // offset of the last vector
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = blockIdx.x, N = a.N, K = a.K, L = a.L, F = a.F;
   uint32_t *C = sm;
   uint32_t *stage = C + ScLds<LM>::cls(N);    // cost rows, later G, M and the arguments of M
-  const size_t shared_words = max(ScLds<LM>::rows(N), (size_t)a.tile * K);
+  const size_t shared_words = ScLds<LM>::shared(N, a.tile, K);
   uint32_t *rT = stage + (shared_words + 3) / 4 * 4;
   uint16_t *red = (uint16_t *)(rT + ScLds<LM>::tables(a.E));
   const int32_t *cost = a.cost + (size_t)b * N * K;
@@ -258,19 +271,27 @@ __global__ __launch_bounds__(kScThreads) void seg_class_kernel(ScArgs a) {
     }
     cstart[lane + 1] = s;
     if (lane == 0) cstart[0] = 0;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) n = max(n, __shfl_xor(n, o, 64));
+    if (lane == 0) s_most = n;
   }
   __syncthreads();
   if (cl >= 0) {
     int pos = cstart[cl] + rank;
     for (int w = 0; w < wid; ++w) pos += wcount[w][cl];
     order[pos] = (uint16_t)tid;
+    oclass[pos] = (uint8_t)cl;
   }
 
   // 1b. Class minima, tile by tile.
+  const int per = (K + L2 - 1) / L2;     // plans per lane in equal shares
+  const bool share = s_most > 3 * per + 4;
+  const int tile = share ? min(a.tile, (int)((shared_words - 1) / (K + 2 * L2))) : a.tile;
+  unsigned long long *key = (unsigned long long *)(stage + (tile * K + 1) / 2 * 2);  // share: cost << 16 | plan
   bool infeasible = false;
   unsigned long long sum = 0;
-  for (int i0 = 0; i0 < N; i0 += a.tile) {
-    rows = min(a.tile, N - i0);
+  for (int i0 = 0; i0 < N; i0 += tile) {
+    rows = min(tile, N - i0);
     const int words = rows * K;
     for (int x0 = 0; x0 < words; x0 += NV * kScThreads) {
       if (i0 > 0 || x0 > 0) {
@@ -285,19 +306,58 @@ __global__ __launch_bounds__(kScThreads) void seg_class_kernel(ScArgs a) {
         if (x < words) stage[x] = (uint32_t)cv[u];
       }
     }
+    if (share)
+      for (int x = tid; x < rows * L2; x += kScThreads) key[x] = ~0ull;
     __syncthreads();  // the rows (and, the first time, the order)
+    if (share) {
+      // A thread's plans are the same in every row: eight of them at a time.
+      const int qbeg = (tid % L2) * per, qend = min(qbeg + per, K);
+      for (int q0 = qbeg; q0 < qend; q0 += 8) {
+        uint32_t o[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int q = min(q0 + u, qend - 1);
+          o[u] = (uint32_t)oclass[q] << 16 | order[q];
+        }
+        for (int r = tid / L2; r < rows; r += kScThreads / L2) {
+          uint32_t c[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) c[u] = stage[r * K + (o[u] & 0xFFFF)];
+          uint32_t best = c[0], at = o[0];
+#pragma unroll
+          for (int u = 1; u < 8; ++u) {
+            const bool next = (o[u] ^ at) >> 16 != 0;  // a new class (the last plan is repeated at the end)
+            if (next) atomicMin(&key[r * L2 + (at >> 16)], (unsigned long long)best << 16 | (at & 0xFFFF));
+            if (next || c[u] < best) {
+              best = c[u];
+              at = o[u];
+            }
+          }
+          atomicMin(&key[r * L2 + (at >> 16)], (unsigned long long)best << 16 | (at & 0xFFFF));
+        }
+      }
+      __syncthreads();  // the keys
+    }
     // whole groups of LM^2 lanes take a segment each (padding classes have no plan)
     for (int x = tid; x < rows * L2; x += kScThreads) {
       const int r = x / L2, p = x % L2;
-      const int32_t *row = (const int32_t *)stage + r * K;
       int32_t best = CFP_COST_INF;
       int at = 0;
-      for (int q = cstart[p]; q < cstart[p + 1]; ++q) {
-        const int s = order[q];
-        const int32_t c = row[s];
-        if (c < best) {
-          best = c;
-          at = s;
+      if (share) {
+        const unsigned long long k = key[x];
+        if (k != ~0ull) {
+          best = (int32_t)(k >> 16);
+          at = (int)(k & 0xFFFF);
+        }
+      } else {
+        const int32_t *row = (const int32_t *)stage + r * K;
+        for (int q = cstart[p]; q < cstart[p + 1]; ++q) {
+          const int s = order[q];
+          const int32_t c = row[s];
+          if (c < best) {
+            best = c;
+            at = s;
+          }
         }
       }
       const int32_t lo = sc_row_min<LM>(best);
@@ -309,7 +369,7 @@ __global__ __launch_bounds__(kScThreads) void seg_class_kernel(ScArgs a) {
         sum += (unsigned long long)(long long)lo;
       }
     }
-    __syncthreads();  // the staged rows are done with
+    __syncthreads();  // the staged rows and keys are done with
   }
   if (sum) atomicAdd(&csum, sum);
   int flags = __syncthreads_or(bad) ? 1 : 0;
@@ -473,7 +533,7 @@ int sc_tile(int n, int k) { return std::max(1, std::min(n, kScTileBytes / (4 * k
 
 template <int LM>
 size_t sc_lds(int n, int k, int e) {
-  const size_t shared = std::max(ScLds<LM>::rows(n), (size_t)sc_tile(n, k) * k);
+  const size_t shared = ScLds<LM>::shared(n, sc_tile(n, k), k);
   return 4 * (ScLds<LM>::cls(n) + (shared + 3) / 4 * 4 + ScLds<LM>::tables(e) + ScLds<LM>::edges(n));
 }
 

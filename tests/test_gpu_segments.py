@@ -262,3 +262,28 @@ def test_long_chains_that_meet_in_some_chunks(pattern):
     cost, rbound, last, first, redge, P = _class_chains([92, *pattern], 4, 1600, 2, pattern)
     assert P == 8
     assert_seg_parity(cost, rbound, last, first, redge, f"long pattern {pattern}")
+
+
+@pytest.mark.parametrize("N,K,L,F,B,most", [(40, 512, 8, 8, 3, 440), (40, 512, 1, 1, 3, 512), (1, 300, 1, 1, 2, 300),
+                                            (60, 130, 2, 2, 5, 100), (33, 77, 4, 3, 4, 70), (25, 512, 5, 6, 3, 60),
+                                            (200, 20, 1, 1, 3, 20), (9, 509, 8, 1, 2, 300)])
+@pytest.mark.parametrize("hi", [3, 2 ** 31 - 1])
+def test_class_form_uneven_maps(N, K, L, F, B, most, hi):
+    """One class with most of the plans, spread over the plan indices: the lanes share the
+    plans evenly; ties, unavailable strategies, the whole cost range, a negative cost."""
+    need_gpu()
+    from paper_2504_00598_amd import CFP_ST_BADINPUT
+    say("segment uneven maps", N, K, L, F, B, hi)
+    rs = np.random.default_rng([93, N, K, L, F])
+    last, first = rs.integers(0, L, size=K).astype(np.uint8), rs.integers(0, F, size=K).astype(np.uint8)
+    big = rs.choice(K, size=most, replace=False)
+    last[big], first[big] = L - 1, 0
+    cost = rs.integers(0, hi, size=(B, N, K), dtype=np.int64).astype(np.int32)
+    cost[rs.random((B, N, K)) < 0.3] = INF
+    cost[:, :, K // 3] = np.where(cost[:, :, K // 3] == INF, 1, cost[:, :, K // 3])
+    rbound = rs.integers(0, min(hi, 1000), size=(2, L, F)).astype(np.int32)
+    redge = rs.integers(0, 2, size=N).astype(np.int32)
+    assert_seg_parity(cost, rbound, last, first, redge, f"uneven N={N} K={K} L={L} F={F}")
+    cost[0, N // 2, big[0]] = -3
+    _, st, plan = run_seg(cost, rbound, last, first, redge)
+    assert st[0] == CFP_ST_BADINPUT and (plan[0] == -1).all() and (st[1:] == 0).all()
