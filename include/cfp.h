@@ -228,10 +228,12 @@ size_t cfp_segment_workspace_bytes(const cfp_segment_desc *d);
  * when K > CFP_MAX_K, L or F exceeds 8, or 8 N K exceeds 2^31 - 1 (device row
  * offsets are 32-bit).  The recurrence runs over the L F boundary classes of a
  * segment while a search's class minima fit in a workgroup's memory (about 1400
- * segments with L, F <= 4, 400 otherwise).  Longer chains run it over the plans,
- * and batches of them too small to occupy the device as chunks made exact by
- * rank convergence (the workspace then holds the speculative rows, B N K 4
- * bytes, counted by cfp_segment_workspace_bytes). */
+ * segments with L, F <= 4, 400 otherwise), in batches of up to 768 searches (more
+ * with many plans in many classes) and, with more than 24 plans per class, up to
+ * 32768 costs per search.  Other calls run it over the plans, and batches of them
+ * too small to occupy the device as chunks made exact by rank convergence (the
+ * workspace then holds the speculative rows, B N K 4 bytes, counted by
+ * cfp_segment_workspace_bytes). */
 int cfp_dp_segments(const cfp_segment_desc *d, void *ws, size_t ws_bytes, int64_t *opt, int32_t *status,
                     void *stream);
 

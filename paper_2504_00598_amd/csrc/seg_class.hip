@@ -550,11 +550,24 @@ hipError_t launch_sc(const ScArgs &a, hipStream_t st) {
 
 // The class minima and the rows of a search have to fit in LDS (about 1400
 // segments with up to four boundary strategies, 400 with more), as do the
-// boundary tables; longer chains take the chunked form.
+// boundary tables; other chains take the chunked form.  So do, as measured,
+//   * few classes of many plans on chains long enough, where the minima are the work
+//     and not the chain (more than 24 plans per class on average, 32768 costs per
+//     search: K = 512 of one class, 384 segments, one search 200 us here against 115; K
+//     = 128 of four, 1000 segments 92 against 72; K = 64 of one, 200 segments 26
+//     against 34);
+//   * batches of more than 768 searches, whose workgroups of sixteen waves run in
+//     rounds (96 segments, K = 81: 512 searches 30 us here against 41, 1000 53 against
+//     47, 4096 192 against 124), but for many plans in many classes and rows, which the
+//     other form holds in more registers (K = 512 with 8 x 8 pairs, 200 segments, 1000
+//     searches 250 us here against 480; 12 segments 51 against 49).
 bool seg_class_supported(const cfp_segment_desc &d) {
   if (d.n_segments > (1 << 16) || d.n_tables > 4096) return false;
-  const size_t lds = sc_lm(d.n_last, d.n_first) == 4 ? sc_lds<4>(d.n_segments, d.k, d.n_tables)
-                                                     : sc_lds<8>(d.n_segments, d.k, d.n_tables);
+  const int64_t costs = (int64_t)d.n_segments * d.k;
+  const int lm = sc_lm(d.n_last, d.n_first);
+  if (d.k > 24 * d.n_last * d.n_first && costs > 32768) return false;
+  if (d.batch > 768 && !(lm == 8 && d.k >= 200 && costs >= (int64_t)12 * d.batch)) return false;
+  const size_t lds = lm == 4 ? sc_lds<4>(d.n_segments, d.k, d.n_tables) : sc_lds<8>(d.n_segments, d.k, d.n_tables);
   return lds <= kScMaxLds;
 }
 

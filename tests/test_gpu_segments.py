@@ -287,3 +287,19 @@ def test_class_form_uneven_maps(N, K, L, F, B, most, hi):
     cost[0, N // 2, big[0]] = -3
     _, st, plan = run_seg(cost, rbound, last, first, redge)
     assert st[0] == CFP_ST_BADINPUT and (plan[0] == -1).all() and (st[1:] == 0).all()
+
+
+@pytest.mark.parametrize("B,N,K,L,F", [(768, 20, 30, 3, 3), (769, 20, 30, 3, 3), (800, 60, 216, 6, 6),
+                                       (800, 40, 216, 6, 6), (5, 512, 64, 1, 1), (5, 513, 64, 1, 1), (2, 140, 240, 3, 3)])
+def test_lines_between_forms(B, N, K, L, F):
+    """Both sides of the lines by batch and by plans per class."""
+    need_gpu()
+    say("segment lines", B, N, K, L, F)
+    rs = np.random.default_rng([94, B, N, K])
+    last, first = rs.integers(0, L, size=K).astype(np.uint8), rs.integers(0, F, size=K).astype(np.uint8)
+    cost = rs.integers(0, 10**6, size=(B, N, K)).astype(np.int32)
+    cost[rs.random((B, N, K)) < 0.1] = INF
+    cost[:, :, 0] = np.where(cost[:, :, 0] == INF, 9, cost[:, :, 0])
+    rbound = rs.integers(0, 10**6, size=(3, L, F)).astype(np.int32)
+    redge = rs.integers(0, 3, size=N).astype(np.int32)
+    assert_seg_parity(cost, rbound, last, first, redge, f"lines B={B} N={N} K={K}")
