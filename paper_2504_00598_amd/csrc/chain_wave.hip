@@ -87,8 +87,8 @@ struct WaveArgs {
   int64_t *dck;         // speculative offset sum (from the chunk's start row) at every checkpoint [B][nq]
   uint32_t *ckrow;      // speculative row at every checkpoint (end of a quad of rows) [B][nq][64]
   uint32_t *endrow;     // fix-up end row of chunks that met no checkpoint [B][P][64]
-  const int32_t *rbad;  // range flags of R, one per packing workgroup
-  int nbad;
+  const u32x4 *rbad;    // range flags of R, one byte per packing wave
+  int nbad;             // in pieces of 16
 };
 
 // Packed tables: word u of chunk c of lane s of table e is (R_e[t][s] << 6) | t
@@ -96,10 +96,15 @@ struct WaveArgs {
 // predecessor t >= K holds a capped word, so its candidate exceeds every exact
 // one without wrapping, and a state s >= K is padding.
 // Every R entry is read here, so the range check of R (entries in [0, limit))
-// is made on the way; every workgroup writes its own flag word, so no word
-// needs a reset.  With a period in `em`, the edge map is written out as well.
+// is made on the way; every wave writes its own flag byte, so none needs a reset
+// (and no workgroup a barrier).  With a period in `em`, the edge map is written out
+// as well.
+struct NoMap {
+  __device__ void write(int32_t *, int) const {}
+};
+template <typename Map>
 __global__ void wave_pack_kernel(const int32_t *__restrict__ rtab, int E, int K, uint32_t *__restrict__ rpk,
-                                 int32_t limit, int32_t *__restrict__ bad, EdgeMap em, int32_t *__restrict__ redge,
+                                 int32_t limit, uint8_t *__restrict__ bad, Map em, int32_t *__restrict__ redge,
                                  int n) {
   em.write(redge, n);
   const size_t words = (size_t)E * 64 * 64;
@@ -111,8 +116,8 @@ __global__ void wave_pack_kernel(const int32_t *__restrict__ rtab, int E, int K,
     off |= r < 0 || r >= limit;
     rpk[w] = ((uint32_t)r << kWBits) | (uint32_t)t;
   }
-  const int any = __syncthreads_or(off);
-  if (threadIdx.x == 0) bad[blockIdx.x] = any ? 1 : 0;
+  const bool any = __any(off);
+  if ((threadIdx.x & 63) == 0) bad[blockIdx.x * 4 + (threadIdx.x >> 6)] = any ? 1 : 0;
 }
 
 // Minimum over the 64 lanes of a wave as a scalar: row minima by DPP, then the
@@ -180,10 +185,10 @@ struct WaveChains {
 //            written.
 //   kFix:    the start row (row 12*blk0 - 1) is start[g]; at every quad end
 //            from quad qmin on the row is compared with the speculative
-//            checkpoint of the same quad.  A search that has met it stops
+//            checkpoint of the same quad (LATE: any other qmin than 0).  A search that has met it stops
 //            computing (its later speculative rows are the true ones) and the
 //            workgroup stops once all of its searches have met.
-template <int NW, int G, int MODE, int EP>
+template <int NW, int G, int MODE, int EP, bool LATE = false>
 __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, int blk0, int blk1, int qmin,
                                          const uint32_t *const *start, WaveSmem<NW> &sm, WaveChains<G> &ch) {
   constexpr int U = kWU, CPT = WaveSmem<NW>::CPT;
@@ -343,7 +348,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
       if constexpr (u == 1) CFP_QLOAD(2)
       if constexpr (u == 2) CFP_QLOAD(3)
     }
-    if (MODE == kWFix && u == 0 && (i >> 2) >= qmin) {  // this quad's checkpoint (runs start at a quad)
+    if (MODE == kWFix && u == 0 && (!LATE || (i >> 2) >= qmin)) {  // this quad's checkpoint (runs start at a quad)
 #pragma unroll
       for (int g = 0; g < G; ++g) ckv[g] = (a.ckrow + ((size_t)srch(g) * a.nq + (i >> 2)) * 64)[lane];
     }
@@ -439,7 +444,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
         const int qbase = (i & ~3) + 4;
         CFP_Q4(CFP_QSTORE)
       }
-      if (MODE == kWFix && (i >> 2) >= qmin) {
+      if (MODE == kWFix && (!LATE || (i >> 2) >= qmin)) {
         if (ch.conv[0] < 0 && __ballot(ch.qv[0] != ckv[0]) == 0) {
           ch.conv[0] = i >> 2;
           ch.dconv[0] = ch.dsum[0];
@@ -448,7 +453,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
         if (lane == 0) sm.wact[(i >> 2) & 1][wid] = ch.conv[0] < 0 ? 1u : 0u;
       }
       __syncthreads();
-      if (MODE == kWFix && (i >> 2) >= qmin) {  // every wave reads the same flags: a uniform decision
+      if (MODE == kWFix && (!LATE || (i >> 2) >= qmin)) {  // every wave reads the same flags: a uniform decision
         const uint32_t f = lane < NW ? sm.wact[(i >> 2) & 1][lane] : 0u;
         stop = __ballot(f != 0) == 0;
         if (stop) {
@@ -549,16 +554,23 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
                                                                                 int32_t *__restrict__ status) {
   __shared__ __align__(16) WaveSmem<kWFinalWaves> sm;
   __shared__ uint32_t s_row[64];  // the true end row of the last chunk accounted
-  __shared__ int s_q;
+  __shared__ int s_q, s_flags;
   __shared__ int64_t s_sum;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int b = blockIdx.x, P = a.P;
   const int64_t *dk = a.dck + (size_t)b * a.nq;
   const WaveRec *rec = a.rec + (size_t)b * P;
   auto endq = [&](int p) __attribute__((always_inline)) { return (min((p + 1) * a.CB * kWU, a.N) - 1) >> 2; };
-  // flags, combined after the loop so that their loads are in flight during it
-  int fl = tid < P ? rec[tid].flags : 0;
-  for (int x = tid; x < a.nbad; x += 64 * kWFinalWaves) fl |= a.rbad[x];
+  // flags, by wave 1 during wave 0's first sum (by all waves behind it, with two more
+  // barriers, the kernel took 1.1 us longer)
+  if (wid == 1) {
+    const int fl = lane < P ? rec[lane].flags : 0;
+    u32x4 rb = {};
+    for (int x = lane; x < a.nbad; x += 64) rb |= a.rbad[x];
+    const bool bad = __any((fl & 1) || (rb.x | rb.y | rb.z | rb.w) != 0), infeasible = __any(fl & 2);
+    if (lane == 0) s_flags = (bad ? 1 : 0) | (infeasible ? 2 : 0);
+  }
+  if (P == 1) __syncthreads();
   // Chunk 0 runs from the true first row.  At the top of the loop the chunks
   // below p are accounted in `total`; with spec_true the speculative end row of
   // chunk p-1 is its true one (so the fix-up of chunk p is valid), otherwise
@@ -604,7 +616,7 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
       WaveChains<1> ch;
       const int last = reruns ? P - 1 : p;  // last chunk of the run
       const int qmin = reruns ? endq(P - 1) : rec[p].conv < 0 ? endq(p) : rec[p].conv;
-      wave_run<kWFinalWaves, 1, kWFix, EP>(a, b, wid == 0 ? 1 : 0, p * a.CB, min((last + 1) * a.CB, a.nblk), qmin,
+      wave_run<kWFinalWaves, 1, kWFix, EP, true>(a, b, wid == 0 ? 1 : 0, p * a.CB, min((last + 1) * a.CB, a.nblk), qmin,
                                            start, sm, ch);
       __syncthreads();  // every wave has read s_row and the last tables
       if (wid == 0) {
@@ -624,14 +636,13 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
     }
   }
   const uint32_t qv = spec_true ? qlast : s_row[lane];
-  const int bad = __syncthreads_or(fl & 1), infeasible = __syncthreads_or(fl & 2);
   if (wid != 0) return;
   // The final row has minimum 0: the lowest state at the minimum.
   const uint32_t pk = wave_min(lane < a.K ? (qv | (uint32_t)lane) : kSat);
   if (lane == 0) {
     int st = CFP_ST_OK;
-    if (bad) st = CFP_ST_BADINPUT;
-    else if (infeasible) st = CFP_ST_INFEASIBLE;
+    if (s_flags & 1) st = CFP_ST_BADINPUT;
+    else if (s_flags & 2) st = CFP_ST_INFEASIBLE;
     else if ((pk >> kWBits) != 0) st = CFP_ST_OVERFLOW;
     status[b] = st;
     opt[b] = st == CFP_ST_OK ? total : INT64_MAX;
@@ -688,7 +699,7 @@ size_t wave_region_bytes(int n, int k, int e, int batch) {
   const WavePlan c = wave_plan(n, k, e, batch);
   if (c.P < 1) return 0;
   size_t off = align_up((size_t)e * 64 * 64 * 4);
-  off += align_up(kWPackBlocks * sizeof(int32_t));
+  off += align_up(kWPackBlocks * 4);
   off += align_up((size_t)batch * c.P * sizeof(WaveRec));
   off += align_up((size_t)batch * c.nq * 8);
   off += align_up((size_t)batch * c.nq * 64 * 4);
@@ -715,8 +726,8 @@ hipError_t launch_chain_wave(const cfp_chain_desc &d, int32_t *redge_dev, const 
   uint32_t *rpk = (uint32_t *)(region + off);
   a.rpk = (const u32x4 *)rpk;
   off += align_up((size_t)d.n_tables * 64 * 64 * 4);
-  int32_t *rbad = (int32_t *)(region + off);
-  off += align_up(kWPackBlocks * sizeof(int32_t));
+  uint8_t *rbad = region + off;
+  off += align_up(kWPackBlocks * 4);
   a.rec = (WaveRec *)(region + off);
   off += align_up((size_t)d.batch * c.P * sizeof(WaveRec));
   a.dck = (int64_t *)(region + off);
@@ -724,14 +735,20 @@ hipError_t launch_chain_wave(const cfp_chain_desc &d, int32_t *redge_dev, const 
   a.ckrow = (uint32_t *)(region + off);
   off += align_up((size_t)d.batch * c.nq * 64 * 4);
   a.endrow = (uint32_t *)(region + off);
-  a.rbad = rbad;
-  a.nbad = std::min(kWPackBlocks, d.n_tables * 16);
+  a.rbad = (const u32x4 *)rbad;
+  const int packs = std::min(kWPackBlocks, d.n_tables * 16);  // of four waves
+  a.nbad = packs / 4;
   // the usual period, and table i for phase i: the table index is a constant per
   // row of a block, and the map is not needed
   bool periodic = em.period == kWU;
   for (int i = 1; periodic && i < em.head + kWU; ++i) periodic = em.map[i] == i % kWU;
-  hipLaunchKernelGGL(wave_pack_kernel, dim3(a.nbad), dim3(256), 0, st, d.rtab, d.n_tables, d.k, rpk,
-                     cfp_r_limit(CFP_V_CHAIN, d.k), rbad, periodic ? EdgeMap{} : em, redge_dev, d.n_blocks);
+  const int32_t rlimit = cfp_r_limit(CFP_V_CHAIN, d.k);
+  if (periodic || em.period == 0)
+    hipLaunchKernelGGL(wave_pack_kernel<NoMap>, dim3(packs), dim3(256), 0, st, d.rtab, d.n_tables, d.k, rpk, rlimit,
+                       rbad, NoMap{}, redge_dev, d.n_blocks);
+  else
+    hipLaunchKernelGGL(wave_pack_kernel<EdgeMap>, dim3(packs), dim3(256), 0, st, d.rtab, d.n_tables, d.k, rpk, rlimit,
+                       rbad, em, redge_dev, d.n_blocks);
   if (c.NW == 4) {
     if (periodic) launch_wave_passes<12, 4>(a, res, opt, status, st);
     else launch_wave_passes<0, 4>(a, res, opt, status, st);

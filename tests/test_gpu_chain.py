@@ -547,6 +547,24 @@ def test_chunked_many_tables(N, K, B, E):
     assert_chain_parity(cost, rtab, redge, f"many tables N={N} K={K} B={B} E={E}")
 
 
+@pytest.mark.parametrize("N,E", [(1, 13), (30, 70), (300, 5)])
+def test_chunked_resharding_range_of_any_table(N, E):
+    """A bad entry in the last table, one and several chunks, more tables than one pass of
+    the packing kernel takes, on a workspace full of another call's words."""
+    need_gpu()
+    import torch
+    from paper_2504_00598_amd import CFP_ST_BADINPUT, cfp_r_limit, search
+    say("chunked, R range of any table", N, E)
+    cost, rtab, redge = rand_case([74, N, E], 3, N, 40, E, 0, 1000)
+    bad = rtab.copy()
+    bad[E - 1, 39, 39] = cfp_r_limit(0, 40)
+    ws = torch.full((64 << 20,), 255, dtype=torch.uint8, device="cuda")
+    for tab, want in ((rtab, 0), (bad, CFP_ST_BADINPUT), (rtab, 0)):
+        r = search.dp_chain(dev(cost), dev(tab), redge, ws=ws)
+        torch.cuda.synchronize()
+        assert (r.status.cpu().numpy() == want).all()
+
+
 @pytest.mark.parametrize("seed", range(3))
 def test_chunked_some_chunks_meet_small_batch(seed):
     """Seeded patterns of chunks that do and do not meet with four searches per workgroup:
