@@ -5,9 +5,10 @@
 // P chunks that run at once, made exact by rank convergence (Maleki,
 // Musuvathi and Mytkowicz, PPoPP 2014): a recurrence started from an
 // arbitrary row becomes parallel to the true one after a few steps.
-//   1. speculative pass: chunk p starts at its first row (or kCWarm rows
-//      before it) from that row's costs alone, writes its argmin rows and, at
-//      every quad end, its normalised row and running offset (a checkpoint);
+//   1. speculative pass: chunk p starts at its first row from that row's costs
+//      alone, writes its argmin rows and, at every quad end, its normalised row
+//      and running offset (a checkpoint).  (Starting rows early saves the fix-up
+//      as many rows as it adds here at K = 256: nothing gained);
 //   2. fix-up pass, chunks p >= 1: start again from the last checkpoint row of
 //      chunk p-1 and recompute until the row equals chunk p's checkpoint of the
 //      same quad (from there on the speculative rows are the true ones);
@@ -75,11 +76,6 @@ constexpr int kCThreads = 512;          // threads per workgroup
 constexpr int kCWaves = kCThreads / 64;
 constexpr uint32_t kCX = 0xFFFFFFFFu;   // x of an unavailable or padding state
 constexpr int kCMaxChunks = 64;
-// Rows a speculative run starts before its chunk.  Starting early makes the
-// run parallel to the true one sooner, so the fix-up pass stops earlier, but
-// at K = 256 the rows saved there equal the rows added here (measured), so 0.
-constexpr int kCWarm = 0;
-
 constexpr int kCG = 4;                  // chains per workgroup (searches of the same chunk); 2 in small batches
 // Passes: speculative; fix-up (a run stops once every chain met a checkpoint);
 // second fix-up, of the chunks behind one that met none in the first.
@@ -187,14 +183,13 @@ struct CwChains {
 };
 
 // Runs rows [r0, r1] of the workgroup's chains (searches bs[c], real where
-// valid[c]).  Speculative: the start row is row rs <= r0 from its costs alone
-// (rows before r0 warm the run up and write nothing); argmins from row r0 and
-// checkpoints are written.  Fix-up: the start row (row r0 - 1) is start[c];
+// valid[c]).  Speculative: the start row is row r0 from its costs alone; argmins
+// from row r0 + 1 and checkpoints are written.  Fix-up: the start row (row r0 - 1) is start[c];
 // stops at the first quad end where every real chain has met its checkpoint at
 // a quad not before qmin[c].
 // REAL: the chains that are computed (the others' values are not meaningful).
 template <int KP, int CG, int MODE, int REAL = CG>
-__device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const bool *valid, int rs, int r0, int r1,
+__device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const bool *valid, int r0, int r1,
                                        const int *qmin, const uint32_t *const *start, CwSmem<KP, CG> &sm,
                                        CwChains<KP, CG> &ch) {
   using S = CwShape<KP, CG>;
@@ -247,7 +242,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
   const __attribute__((address_space(4))) int32_t *redge_c =
       (const __attribute__((address_space(4))) int32_t *)a.redge;
   auto edge = [&](int row) __attribute__((always_inline)) { return redge_c[row]; };
-  const int i0 = MODE == kCSpec ? rs + 1 : r0;
+  const int i0 = MODE == kCSpec ? r0 + 1 : r0;
 
   // Table pieces in flight, [buffer][row in piece][vector]; word offset of the
   // thread's first word within a table.
@@ -291,7 +286,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
     uint32_t x[CH], d[CG];
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
-      const uint32_t cv = cost_at(h, (size_t)rs, coff);
+      const uint32_t cv = cost_at(h, (size_t)r0, coff);
       cor[h] = cv;
       x[h] = (sin && cv != (uint32_t)CFP_COST_INF) ? cv : kCX;
     }
@@ -306,7 +301,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
       ch.x[h] = umin(x[h] - pick(d, h), S::CAP) << BITS;
       sm.q[0][hc[h]][qat<KP, CG>(ms)] = ch.x[h];
     }
-    if (i0 > r1) {  // a run of one row (rs = r0): the start row is its checkpoint
+    if (i0 > r1) {  // a run of one row: the start row is its checkpoint
 #pragma unroll
       for (int h = 0; h < CH; ++h)
         if (hv[h]) ck_at(h, (size_t)(r0 / 4)) = ch.x[h];
@@ -433,7 +428,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
         asm volatile("" : "+v"(cor[h]));  // kept in its step (not sunk behind the argmin stores)
       }
       x[h] = (sin && cv != (uint32_t)CFP_COST_INF) ? (m[h] >> BITS) + cv : kCX;
-      if (sin && hv[h] && i >= r0)
+      if (sin && hv[h])
         *(Arg *)((char *)(tbase[h] + (size_t)i * K) + toffb) = (Arg)(m[h] & (KP - 1));
     }
     // The costs of row i + 2, into the registers just read.  The lane offset
@@ -461,7 +456,7 @@ __device__ __forceinline__ void cw_run(const CwArgs &a, const int *bs, const boo
     const bool qend = (i & 3) == 3 || i == r1;
     if (qend) {
       const int q = i >> 2;
-      if (MODE == kCSpec && i >= r0) {
+      if (MODE == kCSpec) {
 #pragma unroll
         for (int h = 0; h < CH; ++h)
           if (hv[h]) ck_at(h, (size_t)q) = ch.x[h];
@@ -558,10 +553,8 @@ __global__ __launch_bounds__((CwShape<KP, CG>::THREADS), 1) void chain_cw_kernel
     any = any || valid[c];
   }
   if (MODE == kCFix2 && !any) return;
-  // the speculative run of a chunk after the first starts kCWarm rows early
-  const int rs = (MODE == kCSpec && p > 0) ? max(r0 - kCWarm, 0) : r0;
   CwChains<KP, CG> ch;
-  cw_run<KP, CG, MODE == kCSpec ? kCSpec : kCFix>(a, bs, valid, rs, r0, r1, qmin, start, sm, ch);
+  cw_run<KP, CG, MODE == kCSpec ? kCSpec : kCFix>(a, bs, valid, r0, r1, qmin, start, sm, ch);
   const int tid = threadIdx.x;
   const int sub = S::TPS == 1 ? 0 : tid / KP;
   const int ms = tid & (KP - 1);
@@ -1101,7 +1094,7 @@ __global__ __launch_bounds__((CwShape<KP, CG>::THREADS), 1) void chain_cw_final_
     }
     CwChains<KP, CG> ch;
     const int r0 = p * a.CL, r1 = min(r0 + a.CL, a.N) - 1;
-    cw_run<KP, CG, kCFix, 1>(a, bs, valid, r0, r0, r1, qmin, start, sm, ch);
+    cw_run<KP, CG, kCFix, 1>(a, bs, valid, r0, r1, qmin, start, sm, ch);
     spec_true = ch.conv[0] >= 0;
     total += spec_true ? (int64_t)ch.dconv[0] + dk[endq(p)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
     __syncthreads();  // every thread has read s_row

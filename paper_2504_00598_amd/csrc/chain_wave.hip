@@ -46,8 +46,8 @@
 // x = 2^32 - 1 and stay capped.
 //
 // Work split of a workgroup: 16 waves (4 for small batches), each with one
-// search of the same chunk (kWG searches per wave in general), so every wave
-// steps through the same rows and the same tables.  The packed tables of four consecutive rows
+// search of the same chunk, so every wave steps through the same rows and the same
+// tables.  The packed tables of four consecutive rows
 // (4 x 16 KiB) sit in LDS and the next four are staged while these are used
 // (double buffer, one barrier per four rows); the rows are cut into blocks of
 // 12, the period of the edge map the kernels are specialised for.
@@ -62,7 +62,6 @@ namespace {
 constexpr int kWSpec = 0, kWFix = 1;
 constexpr int kWU = 12;                 // rows per block (checkpoint spacing)
 constexpr int kWWaves = 16;             // waves per workgroup on large batches
-constexpr int kWG = 1;                  // searches per wave
 constexpr int kWTable16 = 64 * 64 / 4;  // 16-byte chunks of one packed table
 constexpr int kWMaxChunks = 64;         // chunks per search (the final pass reads one per lane)
 constexpr int kWMinBlocks = 4;          // least blocks of 12 rows per chunk
@@ -136,64 +135,37 @@ __device__ __forceinline__ uint32_t wave_min64_s(uint32_t x) {
   return __builtin_amdgcn_readlane(x, 63);
 }
 
-// The same for two searches that share the table words.
-template <int J0, bool NOP>
-__device__ __forceinline__ void cand4_g2(uint32_t &a0, uint32_t &a1, uint32_t c0, uint32_t c1, const u32x4 &w) {
-  uint32_t t0, t1, t2, t3;
-  asm(
-      ".if %[nop]\n s_nop 2\n .endif\n"
-      CFP_W_ADD("%[t0]", "%[c0]", "%[wx]", "%[j0]")
-      CFP_W_ADD("%[t1]", "%[c0]", "%[wy]", "%[j1]")
-      CFP_W_ADD("%[t2]", "%[c1]", "%[wx]", "%[j0]")
-      CFP_W_ADD("%[t3]", "%[c1]", "%[wy]", "%[j1]")
-      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
-      "v_min3_u32 %[a1], %[a1], %[t2], %[t3]\n"
-      CFP_W_ADD("%[t0]", "%[c0]", "%[wz]", "%[j2]")
-      CFP_W_ADD("%[t1]", "%[c0]", "%[ww]", "%[j3]")
-      CFP_W_ADD("%[t2]", "%[c1]", "%[wz]", "%[j2]")
-      CFP_W_ADD("%[t3]", "%[c1]", "%[ww]", "%[j3]")
-      "v_min3_u32 %[a0], %[a0], %[t0], %[t1]\n"
-      "v_min3_u32 %[a1], %[a1], %[t2], %[t3]\n"
-      : [a0] "+v"(a0), [a1] "+v"(a1), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3)
-      : [c0] "v"(c0), [c1] "v"(c1), [wx] "v"(w.x), [wy] "v"(w.y), [wz] "v"(w.z), [ww] "v"(w.w),
-        [j0] "i"(J0), [j1] "i"(J0 + 1), [j2] "i"(J0 + 2), [j3] "i"(J0 + 3), [nop] "i"(NOP ? 1 : 0));
-}
-
 template <int NW>
 struct WaveSmem {
   static constexpr int CPT = kWTable16 / (64 * NW);  // 16-byte chunks per thread and table
   u32x4 tb[2][4][kWTable16];                          // packed tables of two quads of rows
-  uint8_t argb[NW][kWG][kWU][64];                     // argmin bytes of the block's rows, per wave and search
+  uint8_t argb[NW][kWU][64];                          // argmin bytes of the block's rows, per wave
   uint32_t wact[2][NW];                               // fix-up: wave still has an unmet search, by quad parity
 };
 
-// State of a wave's searches.
-template <int G>
-struct WaveChains {
-  uint32_t qv[G];      // the lane's word of the current row
-  uint64_t dsum[G];    // offset sum since the start row
-  uint32_t flags[G];   // bit 0 a negative cost, bit 1 a row with no available strategy
-  uint32_t cor[G];     // speculative pass: OR of the lane's costs (bit 31 = a negative cost)
-  int conv[G];         // fix-up: quad where the row met the checkpoint, -1 if never
-  uint64_t dconv[G];   // fix-up: offset sum at that quad
+// State of a wave's search.
+struct WaveChain {
+  uint32_t qv;         // the lane's word of the current row
+  uint64_t dsum;       // offset sum since the start row
+  uint32_t flags;      // bit 0 a negative cost, bit 1 a row with no available strategy
+  uint32_t cor;        // speculative pass: OR of the lane's costs (bit 31 = a negative cost)
+  int conv;            // fix-up: quad where the row met the checkpoint, -1 if never
+  uint64_t dconv;      // fix-up: offset sum at that quad
 };
 
-// Runs rows [12*blk0 (+1 for kSpec), min(12*blk1, N)) of the wave's G searches
-// bw .. bw+G-1, of which those below B and (for the final pass) the first
-// nvalid are real.
+// Runs rows [12*blk0 (+1 for kSpec), min(12*blk1, N)) of the wave's search bw,
+// which is real if it is below B and (in the final pass) with `real`.
 //   kSpec:   the start row is row 12*blk0 from its costs alone; checkpoints are
 //            written.
-//   kFix:    the start row (row 12*blk0 - 1) is start[g]; at every quad end
+//   kFix:    the start row (row 12*blk0 - 1) is start; at every quad end
 //            from quad qmin on the row is compared with the speculative
 //            checkpoint of the same quad (LATE: any other qmin than 0).  A search that has met it stops
 //            computing (its later speculative rows are the true ones) and the
 //            workgroup stops once all of its searches have met.
-template <int NW, int G, int MODE, int EP, bool LATE = false>
-__device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, int blk0, int blk1, int qmin,
-                                         const uint32_t *const *start, WaveSmem<NW> &sm, WaveChains<G> &ch) {
+template <int NW, int MODE, int EP, bool LATE = false>
+__device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, bool real, int blk0, int blk1, int qmin,
+                                         const uint32_t *start, WaveSmem<NW> &sm, WaveChain &ch) {
   constexpr int U = kWU, CPT = WaveSmem<NW>::CPT;
-  static_assert(G == 1 || G == 2, "one or two searches per wave");
-  static_assert(MODE != kWFix || G == 1, "the fix-up carries one search per wave");
   static_assert(CPT == 1 || CPT == 2 || CPT == 4, "1, 2 or 4 chunks per thread and table");
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = a.N, K = a.K;
@@ -201,15 +173,13 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
   const int ilast = min(blk1 * U, N) - 1;              // last row of the run
   const int sl = min(lane, K - 1);
 
-  auto valid = [&](int g) __attribute__((always_inline)) { return g < nvalid && bw + g < a.B; };
-  auto srch = [&](int g) __attribute__((always_inline)) { return min(bw + g, a.B - 1); };
+  const bool valid = real && bw < a.B;
+  const int b = min(bw, a.B - 1);
   auto edge = [&](int row) __attribute__((always_inline)) { return EP ? row % (EP ? EP : 1) : a.redge[row]; };
-  // cost rows of the two searches (wave-uniform bases; a row adds row * K and
-  // the lane its state, so the loads take a scalar base and a lane offset)
-  const int32_t *cb0 = a.cost + (size_t)srch(0) * N * K;
-  const int32_t *cb1 = a.cost + (size_t)srch(G - 1) * N * K;
-  uint8_t *tb0 = a.table + (size_t)srch(0) * N * K;
-  uint8_t *tb1 = a.table + (size_t)srch(G - 1) * N * K;
+  // the search's rows (wave-uniform bases; a row adds row * K and the lane its
+  // state, so the loads take a scalar base and a lane offset)
+  const int32_t *cb = a.cost + (size_t)b * N * K;
+  uint8_t *tb = a.table + (size_t)b * N * K;
 
   // Memory schedule.  The tables of the next quad are loaded during the first
   // three rows of a quad of four and the costs of the quad after the next in
@@ -217,10 +187,10 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
   // every outstanding load, so a load consumed earlier would stall the row.)
   // Array indices are literals only, so every array stays in registers.
   u32x4 sq[4][4];           // next quad's tables: [row in quad][chunk of this thread]
-  // Costs of three consecutive quads, [quad mod 3][row in quad][search]: quad
+  // Costs of three consecutive quads, [quad mod 3][row in quad]: quad
   // q reads set q mod 3 while set (q+2) mod 3 is loaded.  A block of 12 rows
   // starts at a quad that is 0 mod 3, so every index is a constant.
-  uint32_t cs[3][4][2] = {};
+  uint32_t cs[3][4] = {};
 #define CFP_QLOAD(V)                                                               \
   {                                                                                \
     const int row = min(qbase + (V), ilast); /* past the end: any in-range row */  \
@@ -235,8 +205,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
 #define CFP_CLOAD(V, DST)                                                          \
   {                                                                                \
     const int row = min(cbase + (V), ilast);                                       \
-    DST[V][0] = (uint32_t)(cb0 + (size_t)row * K)[sl];                             \
-    if constexpr (G == 2) DST[V][1] = (uint32_t)(cb1 + (size_t)row * K)[sl];       \
+    DST[V] = (uint32_t)(cb + (size_t)row * K)[sl];                                 \
   }
 #define CFP_QSTORE(V)                                                              \
   {                                                                                \
@@ -273,33 +242,28 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
   }
 
   // Start row.
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    ch.flags[g] = 0;
-    if (MODE == kWSpec) {
-      const uint32_t cv = (uint32_t)((g == 0 ? cb0 : cb1) + (size_t)blk0 * U * K)[sl];
-      const bool avail = lane < K && cv != (uint32_t)CFP_COST_INF;
-      ch.cor[g] = cv;
-      const uint32_t x = avail ? cv : kWX;
-      const uint32_t d = wave_min64_s(x);
-      if (d == kWX) ch.flags[g] |= 2;
-      ch.qv[g] = umin(x - d, kWQcap6 >> kWBits) << kWBits;
-      ch.dsum[g] = d;
-      if (i0 > ilast && valid(g)) {  // a run of one row: the start row is its checkpoint
-        a.ckrow[((size_t)(bw + g) * a.nq + (i0 - 1) / 4) * 64 + lane] = ch.qv[g];
-        if (lane == 0) a.dck[(size_t)(bw + g) * a.nq + (i0 - 1) / 4] = (int64_t)ch.dsum[g];
-      }
-    } else {
-      ch.qv[g] = start[g][lane];
-      ch.dsum[g] = 0;
+  ch.flags = 0;
+  if (MODE == kWSpec) {
+    const uint32_t cv = (uint32_t)(cb + (size_t)blk0 * U * K)[sl];
+    const bool avail = lane < K && cv != (uint32_t)CFP_COST_INF;
+    ch.cor = cv;
+    const uint32_t x = avail ? cv : kWX;
+    const uint32_t d = wave_min64_s(x);
+    if (d == kWX) ch.flags |= 2;
+    ch.qv = umin(x - d, kWQcap6 >> kWBits) << kWBits;
+    ch.dsum = d;
+    if (i0 > ilast && valid) {  // a run of one row: the start row is its checkpoint
+      a.ckrow[((size_t)b * a.nq + (i0 - 1) / 4) * 64 + lane] = ch.qv;
+      if (lane == 0) a.dck[(size_t)b * a.nq + (i0 - 1) / 4] = (int64_t)ch.dsum;
     }
-    ch.conv[g] = valid(g) ? -1 : 0;  // a missing search counts as met
-    ch.dconv[g] = 0;
+  } else {
+    ch.qv = start[lane];
+    ch.dsum = 0;
   }
-  int endr[G];  // last row whose argmin bytes are written back
-  uint32_t ckv[G] = {};  // fix-up: checkpoint of the current quad
-#pragma unroll
-  for (int g = 0; g < G; ++g) endr[g] = ilast;
+  ch.conv = valid ? -1 : 0;  // a missing search counts as met
+  ch.dconv = 0;
+  int endr = ilast;   // last row whose argmin bytes are written back
+  uint32_t ckv = 0;   // fix-up: checkpoint of the current quad
   bool stop = false;
   __syncthreads();  // the first quad's tables
 
@@ -307,20 +271,17 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
   // LDS to the table: a row of one search is 64 bytes, four 16-byte pieces.
   auto flush = [&](int blk, int nr) __attribute__((always_inline)) {
     const int r0 = (MODE == kWSpec && blk == blk0) ? 1 : 0;  // the start row has no argmin
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      if (!valid(g)) continue;
-      uint8_t *dst = (g == 0 ? tb0 : tb1) + (size_t)blk * U * K;
-      const int nrg = MODE == kWFix ? min(nr, endr[g] - blk * U + 1) : nr;
-      for (int x = lane + 4 * r0; x < 4 * nrg; x += 64) {  // piece x: row x / 4, bytes 16 (x % 4) ..
-        const int r = x >> 2, c = (x & 3) * 16;
-        const u32x4 v = *(const u32x4 *)&sm.argb[wid][g][r][c];
-        if (K == 64) {
-          *(u32x4 *)(dst + (size_t)r * K + c) = v;
-        } else {
-          const uint8_t *vb = (const uint8_t *)&v;
-          for (int q = 0; q < 16 && c + q < K; ++q) dst[(size_t)r * K + c + q] = vb[q];
-        }
+    if (!valid) return;
+    uint8_t *dst = tb + (size_t)blk * U * K;
+    const int nrg = MODE == kWFix ? min(nr, endr - blk * U + 1) : nr;
+    for (int x = lane + 4 * r0; x < 4 * nrg; x += 64) {  // piece x: row x / 4, bytes 16 (x % 4) ..
+      const int r = x >> 2, c = (x & 3) * 16;
+      const u32x4 v = *(const u32x4 *)&sm.argb[wid][r][c];
+      if (K == 64) {
+        *(u32x4 *)(dst + (size_t)r * K + c) = v;
+      } else {
+        const uint8_t *vb = (const uint8_t *)&v;
+        for (int q = 0; q < 16 && c + q < K; ++q) dst[(size_t)r * K + c + q] = vb[q];
       }
     }
   };
@@ -349,8 +310,7 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
       if constexpr (u == 2) CFP_QLOAD(3)
     }
     if (MODE == kWFix && u == 0 && (!LATE || (i >> 2) >= qmin)) {  // this quad's checkpoint (runs start at a quad)
-#pragma unroll
-      for (int g = 0; g < G; ++g) ckv[g] = (a.ckrow + ((size_t)srch(g) * a.nq + (i >> 2)) * 64)[lane];
+      ckv = (a.ckrow + ((size_t)b * a.nq + (i >> 2)) * 64)[lane];
     }
     if (u == 3 && (!FIRST || i >= (i0 & ~3) + 4)) {  // costs two quads ahead, after this quad's table loads
       const int cbase = (i & ~3) + 8;
@@ -361,76 +321,61 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
     }
 
     // Row-broadcast sources: C_k has row k of the wave in every row.
-    uint32_t c0[G], c1[G], c2[G], c3[G], acc[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const auto p = __builtin_amdgcn_permlane16_swap(ch.qv[g], ch.qv[g], false, false);
-      const auto lo = __builtin_amdgcn_permlane32_swap(p[0], p[0], false, false);
-      const auto hi = __builtin_amdgcn_permlane32_swap(p[1], p[1], false, false);
-      c0[g] = lo[0];
-      c2[g] = lo[1];
-      c1[g] = hi[0];
-      c3[g] = hi[1];
-      acc[g] = kSat;
-    }
-    const u32x4 *tb = sm.tb[(i >> 2) & 1][u];
-    // With two searches a wave has the registers for all sixteen table chunks
-    // of a row; with one (sixteen waves per workgroup) it loads them in two
-    // halves, and outside the first block the first half of rows 1..3 of a
-    // quad is read during the previous row's normalisation (PRE).
-    constexpr int WH = (MODE == kWSpec && G == 2) ? 16 : 8;
-    constexpr bool PRE = WH < 16 && !FIRST && u != 0;
+    const auto p = __builtin_amdgcn_permlane16_swap(ch.qv, ch.qv, false, false);
+    const auto lo = __builtin_amdgcn_permlane32_swap(p[0], p[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(p[1], p[1], false, false);
+    const uint32_t c0 = lo[0], c1 = hi[0], c2 = lo[1], c3 = hi[1];
+    uint32_t acc = kSat;
+    const u32x4 *rows = sm.tb[(i >> 2) & 1][u];
+    // The row's sixteen table chunks in two halves; outside the first block the
+    // first NPRE of rows 1..3 of a quad are read during the previous row's
+    // normalisation (PRE).
+    constexpr int WH = 8;
+    constexpr bool PRE = !FIRST && u != 0;
     u32x4 w[16];
-    // Candidates of every predecessor for the searches X (and Y): two
-    // searches share each table chunk read.
-#define CFP_CH2(C, cc_) cand4_g2<4 * ((cc_) & 3), ((cc_) & 3) == 0>(acc[0], acc[G - 1], C[0], C[G - 1], w[cc_]);
-#define CFP_CH1(X, C, cc_)                                                  \
-  if constexpr ((cc_) == 0) cand4_g1_first(acc[X], C[X], w[0]);             \
-  else cand4_g1<4 * ((cc_) & 3), ((cc_) & 3) == 0>(acc[X], C[X], w[cc_]);
-#define CFP_ROW(CH, ...)                                                                   \
-  {                                                                                        \
-    if constexpr (PRE) {                                                                   \
-      _Pragma("unroll") for (int cc_ = 0; cc_ < NPRE; ++cc_) w[cc_] = wpre[cc_];           \
-      _Pragma("unroll") for (int cc_ = NPRE; cc_ < WH; ++cc_) w[cc_] = tb[cc_ * 64 + lane]; \
-    } else {                                                                               \
-      _Pragma("unroll") for (int cc_ = 0; cc_ < WH; ++cc_) w[cc_] = tb[cc_ * 64 + lane];   \
-    }                                                                                      \
-    CH(__VA_ARGS__ c0, 0) CH(__VA_ARGS__ c0, 1) CH(__VA_ARGS__ c0, 2) CH(__VA_ARGS__ c0, 3) \
-    CH(__VA_ARGS__ c1, 4) CH(__VA_ARGS__ c1, 5) CH(__VA_ARGS__ c1, 6) CH(__VA_ARGS__ c1, 7) \
-    if constexpr (WH < 16) {                                                               \
-      _Pragma("unroll") for (int cc_ = 8; cc_ < 16; ++cc_) w[cc_] = tb[cc_ * 64 + lane];   \
-    }                                                                                      \
-    CH(__VA_ARGS__ c2, 8) CH(__VA_ARGS__ c2, 9) CH(__VA_ARGS__ c2, 10) CH(__VA_ARGS__ c2, 11) \
-    CH(__VA_ARGS__ c3, 12) CH(__VA_ARGS__ c3, 13) CH(__VA_ARGS__ c3, 14) CH(__VA_ARGS__ c3, 15) \
-    if constexpr (WH < 16 && !FIRST && u != 3) {                                           \
-      _Pragma("unroll") for (int cc_ = 0; cc_ < NPRE; ++cc_) wpre[cc_] = tb[kWTable16 + cc_ * 64 + lane]; \
-    }                                                                                      \
-  }
-    const bool live = MODE != kWFix || ch.conv[0] < 0;  // (one search per wave in the fix-up)
-    if constexpr (G == 2) CFP_ROW(CFP_CH2)
-    else if (live) CFP_ROW(CFP_CH1, 0,)
-#undef CFP_ROW
-#undef CFP_CH1
-#undef CFP_CH2
+    const bool live = MODE != kWFix || ch.conv < 0;
+#define CFP_CH(C, cc_)                                          \
+  if constexpr ((cc_) == 0) cand4_g1_first(acc, C, w[0]);       \
+  else cand4_g1<4 * ((cc_) & 3), ((cc_) & 3) == 0>(acc, C, w[cc_]);
+    if (live) {
+      if constexpr (PRE) {
+#pragma unroll
+        for (int cc_ = 0; cc_ < NPRE; ++cc_) w[cc_] = wpre[cc_];
+#pragma unroll
+        for (int cc_ = NPRE; cc_ < WH; ++cc_) w[cc_] = rows[cc_ * 64 + lane];
+      } else {
+#pragma unroll
+        for (int cc_ = 0; cc_ < WH; ++cc_) w[cc_] = rows[cc_ * 64 + lane];
+      }
+      CFP_CH(c0, 0) CFP_CH(c0, 1) CFP_CH(c0, 2) CFP_CH(c0, 3)
+      CFP_CH(c1, 4) CFP_CH(c1, 5) CFP_CH(c1, 6) CFP_CH(c1, 7)
+#pragma unroll
+      for (int cc_ = WH; cc_ < 16; ++cc_) w[cc_] = rows[cc_ * 64 + lane];
+      CFP_CH(c2, 8) CFP_CH(c2, 9) CFP_CH(c2, 10) CFP_CH(c2, 11)
+      CFP_CH(c3, 12) CFP_CH(c3, 13) CFP_CH(c3, 14) CFP_CH(c3, 15)
+      if constexpr (!FIRST && u != 3) {
+#pragma unroll
+        for (int cc_ = 0; cc_ < NPRE; ++cc_) wpre[cc_] = rows[kWTable16 + cc_ * 64 + lane];
+      }
+    }
+#undef CFP_CH
 
     // New row: add the cost, normalise by the row minimum, record the argmin.
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      if (MODE == kWFix && !live) continue;
-      const uint32_t cv = cs[(J / 4) % 3][u][g];
+    if (live) {
+      const uint32_t cv = cs[(J / 4) % 3][u];
       const bool avail = lane < K && cv != (uint32_t)CFP_COST_INF;
       if (MODE == kWSpec) {
-        ch.cor[g] |= cv;
+        ch.cor |= cv;
         // kept in its row: sunk to the end of a block, the OR waits for the
         // latest cost loads behind the block's argmin stores
-        asm volatile("" : "+v"(ch.cor[g]));
+        asm volatile("" : "+v"(ch.cor));
       }
-      const uint32_t x = avail ? (acc[g] >> kWBits) + cv : kWX;
+      const uint32_t x = avail ? (acc >> kWBits) + cv : kWX;
       const uint32_t d = wave_min64_s(x);
-      if (MODE == kWSpec && d == kWX) ch.flags[g] |= 2;
-      ch.qv[g] = umin(x - d, kWQcap6 >> kWBits) << kWBits;
-      ch.dsum[g] += d;
-      sm.argb[wid][g][J][lane] = (uint8_t)acc[g];
+      if (MODE == kWSpec && d == kWX) ch.flags |= 2;
+      ch.qv = umin(x - d, kWQcap6 >> kWBits) << kWBits;
+      ch.dsum += d;
+      sm.argb[wid][J][lane] = (uint8_t)acc;
     }
 
     // End of a quad: the next quad's tables in place and one barrier, then the
@@ -445,12 +390,12 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
         CFP_Q4(CFP_QSTORE)
       }
       if (MODE == kWFix && (!LATE || (i >> 2) >= qmin)) {
-        if (ch.conv[0] < 0 && __ballot(ch.qv[0] != ckv[0]) == 0) {
-          ch.conv[0] = i >> 2;
-          ch.dconv[0] = ch.dsum[0];
-          endr[0] = i;
+        if (ch.conv < 0 && __ballot(ch.qv != ckv) == 0) {
+          ch.conv = i >> 2;
+          ch.dconv = ch.dsum;
+          endr = i;
         }
-        if (lane == 0) sm.wact[(i >> 2) & 1][wid] = ch.conv[0] < 0 ? 1u : 0u;
+        if (lane == 0) sm.wact[(i >> 2) & 1][wid] = ch.conv < 0 ? 1u : 0u;
       }
       __syncthreads();
       if (MODE == kWFix && (!LATE || (i >> 2) >= qmin)) {  // every wave reads the same flags: a uniform decision
@@ -463,11 +408,9 @@ __device__ __forceinline__ void wave_run(const WaveArgs &a, int bw, int nvalid, 
       }
       if (MODE == kWSpec) {
         const int q = i >> 2;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          if (!valid(g)) continue;
-          (a.ckrow + ((size_t)(bw + g) * a.nq + q) * 64)[lane] = ch.qv[g];
-          if (lane == 0) a.dck[(size_t)(bw + g) * a.nq + q] = (int64_t)ch.dsum[g];
+        if (valid) {
+          (a.ckrow + ((size_t)b * a.nq + q) * 64)[lane] = ch.qv;
+          if (lane == 0) a.dck[(size_t)b * a.nq + q] = (int64_t)ch.dsum;
         }
       }
       if (J == U - 1 || (GUARD && i == ilast)) flush(blk, J + 1);
@@ -504,17 +447,13 @@ template <int EP, int NW>
 __global__ __launch_bounds__(64 * NW) void chain_wave_kernel(WaveArgs a) {
   __shared__ __align__(16) WaveSmem<NW> sm;
   const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int bw = blockIdx.x * NW * kWG + wid * kWG;
+  const int bw = blockIdx.x * NW + wid;  // one search per wave
   const int p = blockIdx.y;
   const int blk0 = p * a.CB, blk1 = min(blk0 + a.CB, a.nblk);
-  WaveChains<kWG> ch;
-  wave_run<NW, kWG, kWSpec, EP>(a, bw, kWG, blk0, blk1, 0, nullptr, sm, ch);
-#pragma unroll
-  for (int g = 0; g < kWG; ++g) {
-    if (__ballot((int32_t)ch.cor[g] < 0)) ch.flags[g] |= 1;  // wave-uniform
-    if (bw + g >= a.B) continue;
-    if (lane == 0) a.rec[(size_t)(bw + g) * a.P + p].flags = (int32_t)ch.flags[g];
-  }
+  WaveChain ch;
+  wave_run<NW, kWSpec, EP>(a, bw, true, blk0, blk1, 0, nullptr, sm, ch);
+  if (__ballot((int32_t)ch.cor < 0)) ch.flags |= 1;  // wave-uniform
+  if (bw < a.B && lane == 0) a.rec[(size_t)bw * a.P + p].flags = (int32_t)ch.flags;
 }
 
 // Fix-up pass, grid (ceil(B/NW), P-1): the searches of a workgroup rerun chunk
@@ -531,15 +470,14 @@ __global__ __launch_bounds__(64 * NW) void chain_wave_fix_kernel(WaveArgs a) {
   const int blk0 = p * a.CB, blk1 = min(blk0 + a.CB, a.nblk);
   const int i0 = blk0 * kWU;  // a multiple of 4
   const int b = min(bw, a.B - 1);
-  const uint32_t *start[1] = {a.ckrow + ((size_t)b * a.nq + (i0 / 4 - 1)) * 64};
-  WaveChains<1> ch;
-  wave_run<NW, 1, kWFix, EP>(a, bw, 1, blk0, blk1, 0, start, sm, ch);
+  WaveChain ch;
+  wave_run<NW, kWFix, EP>(a, bw, true, blk0, blk1, 0, a.ckrow + ((size_t)b * a.nq + (i0 / 4 - 1)) * 64, sm, ch);
   if (bw >= a.B) return;
-  if (ch.conv[0] < 0) a.endrow[((size_t)bw * a.P + p) * 64 + lane] = ch.qv[0];
+  if (ch.conv < 0) a.endrow[((size_t)bw * a.P + p) * 64 + lane] = ch.qv;
   if (lane == 0) {
     WaveRec &r = a.rec[(size_t)bw * a.P + p];
-    r.conv = ch.conv[0];
-    r.dfix = (int64_t)(ch.conv[0] >= 0 ? ch.dconv[0] : ch.dsum[0]);
+    r.conv = ch.conv;
+    r.dfix = (int64_t)(ch.conv >= 0 ? ch.dconv : ch.dsum);
   }
 }
 
@@ -612,20 +550,19 @@ __global__ __launch_bounds__(64 * kWFinalWaves, 1) void chain_wave_final_kernel(
       // Rerun chunk p (wave 0; the others stage) at least over the rows its
       // fix-up rewrote from a wrong start; behind a rerun that met nothing
       // either, the rest of the chain in one run.
-      const uint32_t *start[1] = {s_row};
-      WaveChains<1> ch;
+      WaveChain ch;
       const int last = reruns ? P - 1 : p;  // last chunk of the run
       const int qmin = reruns ? endq(P - 1) : rec[p].conv < 0 ? endq(p) : rec[p].conv;
-      wave_run<kWFinalWaves, 1, kWFix, EP, true>(a, b, wid == 0 ? 1 : 0, p * a.CB, min((last + 1) * a.CB, a.nblk), qmin,
-                                           start, sm, ch);
+      wave_run<kWFinalWaves, kWFix, EP, true>(a, b, wid == 0, p * a.CB, min((last + 1) * a.CB, a.nblk), qmin, s_row, sm,
+                                              ch);
       __syncthreads();  // every wave has read s_row and the last tables
       if (wid == 0) {
-        const bool met = ch.conv[0] >= 0;
+        const bool met = ch.conv >= 0;
         if (lane == 0) {
           s_q = met;
-          s_sum = met ? (int64_t)ch.dconv[0] + dk[endq(last)] - dk[ch.conv[0]] : (int64_t)ch.dsum[0];
+          s_sum = met ? (int64_t)ch.dconv + dk[endq(last)] - dk[ch.conv] : (int64_t)ch.dsum;
         }
-        s_row[lane] = ch.qv[0];
+        s_row[lane] = ch.qv;
       }
       __syncthreads();
       total += s_sum;
