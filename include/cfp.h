@@ -284,6 +284,25 @@ int cfp_search_chain(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t
 #define CFP_NOALLOC_MAX_BYTES (32u << 20)
 int cfp_search_chain_noalloc(const cfp_chain_desc *d, int64_t *opt, int32_t *status, int32_t *plan, void *stream);
 
+/* Which kernels a call with these sizes runs (not needed for searching; results
+ * do not depend on it).  Host only: no device pointer is read, and the pointers of
+ * the descriptor may be NULL.  A CFP_FORM_* value, 0 for sizes that are refused.
+ * cfp_chain_form answers for cfp_dp_chain, cfp_segment_form for cfp_dp_segments. */
+enum {
+  CFP_FORM_NARROW = 1,        /* K <= 32, tables in LDS */
+  CFP_FORM_WAVE = 2,          /* 32 < K <= 64, one wave per search or chunk */
+  CFP_FORM_CHUNKS = 3,        /* K > 64, chunk-parallel, 2 or 4 searches per workgroup */
+  CFP_FORM_TEAMS = 4,         /* K > 256, chunk-parallel, four workgroups per chunk */
+  CFP_FORM_SPLIT = 5,         /* K > 64, several workgroups per search, tables in registers */
+  CFP_FORM_SPLIT_STREAM = 6,  /* the same, tables streamed */
+  CFP_FORM_ROWS = 7,          /* one workgroup per search, row after row */
+  CFP_FORM_SEG_CLASS = 16,    /* segments: over boundary classes */
+  CFP_FORM_SEG_CHUNKS = 17,   /* segments: over plans, chunk-parallel */
+  CFP_FORM_SEG_ROWS = 18      /* segments: over plans, one wave per search */
+};
+int cfp_chain_form(const cfp_chain_desc *d);
+int cfp_segment_form(const cfp_segment_desc *d);
+
 /* Benchmarking aid (not needed for searching).  cfp_timer_start creates
  * max_launches pairs of HIP events (1 <= max_launches <= 2^20) and arms
  * recording: from then on every launch of a forward call's main kernel (the

@@ -32,13 +32,16 @@ CFP_V_CHAIN = 0
 CFP_V_MEM = 1
 CFP_V_SCAN = 2
 CFP_V_SEG = 3
+CFP_FORM_NARROW, CFP_FORM_WAVE, CFP_FORM_CHUNKS, CFP_FORM_TEAMS = 1, 2, 3, 4
+CFP_FORM_SPLIT, CFP_FORM_SPLIT_STREAM, CFP_FORM_ROWS = 5, 6, 7
+CFP_FORM_SEG_CLASS, CFP_FORM_SEG_CHUNKS, CFP_FORM_SEG_ROWS = 16, 17, 18
 CFP_COST_INF = 0x7FFFFFFF
 CFP_MAX_K = 512
 
 EXPORTED = ("cfp_r_limit", "cfp_workspace_bytes", "cfp_dp_chain", "cfp_dp_chain_mem", "cfp_mem_frontier",
             "cfp_minplus_scan", "cfp_traceback", "cfp_segment_workspace_bytes", "cfp_dp_segments",
             "cfp_traceback_segments", "cfp_status_string", "cfp_timer_start", "cfp_timer_stop",
-            "cfp_search_chain", "cfp_search_chain_noalloc")
+            "cfp_search_chain", "cfp_search_chain_noalloc", "cfp_chain_form", "cfp_segment_form")
 
 
 class CfpError(RuntimeError):
@@ -112,6 +115,10 @@ def lib() -> ctypes.CDLL:
         L.cfp_search_chain.restype = ctypes.c_int
         L.cfp_search_chain_noalloc.argtypes = [D, P, P, P, P]
         L.cfp_search_chain_noalloc.restype = ctypes.c_int
+        L.cfp_chain_form.argtypes = [D]
+        L.cfp_chain_form.restype = ctypes.c_int
+        L.cfp_segment_form.argtypes = [SD]
+        L.cfp_segment_form.restype = ctypes.c_int
         L.cfp_timer_start.argtypes = [I32]
         L.cfp_timer_start.restype = ctypes.c_int
         L.cfp_timer_stop.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(I32)]
@@ -128,6 +135,17 @@ def status_string(code: int) -> str:
 
 def cfp_r_limit(variant: int, k: int) -> int:
     return int(lib().cfp_r_limit(variant, k))
+
+
+def cfp_chain_form(N: int, K: int, B: int, E: int) -> int:
+    """The CFP_FORM_* a chain search of these sizes runs."""
+    return int(lib().cfp_chain_form(ctypes.byref(cfp_chain_desc(N, K, B, E, None, None, None))))
+
+
+def cfp_segment_form(N: int, K: int, B: int, E: int, n_last: int, n_first: int) -> int:
+    """The CFP_FORM_SEG_* a segment search of these sizes runs."""
+    d = cfp_segment_desc(N, K, B, E, n_last, n_first, None, None, None, None, None)
+    return int(lib().cfp_segment_form(ctypes.byref(d)))
 
 
 def cfp_timer_start(max_launches: int) -> None:

@@ -93,6 +93,18 @@ WsLayout layout(int variant, int n, int k, int batch, int n_mem, int n_tables, C
   return L;
 }
 
+int device_cus() {
+  static int cus = -1;
+  if (cus < 0) {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+      n = 256;
+    cus = n;
+  }
+  return cus;
+}
+
 EdgeMap edge_map(const int32_t *redge, int n) {
   EdgeMap m{};
   // the shortest period (entry 0 is unused), from the chain's end backwards
@@ -653,6 +665,26 @@ int cfp_traceback_segments(const cfp_segment_desc *d, void *ws, size_t ws_bytes,
                                               (const SearchResult *)(w + L.result), (uint16_t *)(w + L.maps),
                                               (int32_t *)(w + L.bounds), L.nchunks, plan, (hipStream_t)stream);
   return e == hipSuccess ? CFP_OK : CFP_ERR_HIP;
+}
+
+int cfp_chain_form(const cfp_chain_desc *d) {
+  if (!d || d->n_blocks < 1 || d->k < 1 || d->k > CFP_MAX_K || d->batch < 1 || d->n_tables < 1) return 0;
+  switch (chain_form(d->n_blocks, d->k, d->batch, d->n_tables)) {
+    case kFormNarrow: return CFP_FORM_NARROW;
+    case kFormWave: return CFP_FORM_WAVE;
+    case kFormCw: return chain_cw_teams(d->n_blocks, d->k, d->batch) ? CFP_FORM_TEAMS : CFP_FORM_CHUNKS;
+    case kFormSplit:
+      return chain_fwd_split_streams(d->k, d->n_tables, d->batch) ? CFP_FORM_SPLIT_STREAM : CFP_FORM_SPLIT;
+    default: return CFP_FORM_ROWS;
+  }
+}
+
+int cfp_segment_form(const cfp_segment_desc *d) {
+  if (!d || d->n_segments < 1 || d->batch < 1 || d->n_tables < 1 || !seg_supported(d->k, d->n_last, d->n_first) ||
+      (size_t)d->n_segments * d->k * 8 > (size_t)INT32_MAX)
+    return 0;
+  if (seg_class_supported(*d)) return CFP_FORM_SEG_CLASS;
+  return seg_chunks(d->n_segments, d->batch) >= 2 ? CFP_FORM_SEG_CHUNKS : CFP_FORM_SEG_ROWS;
 }
 
 const char *cfp_status_string(int code) {

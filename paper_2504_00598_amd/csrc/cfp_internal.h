@@ -82,6 +82,10 @@ struct WsLayout {
   int nchunks = 0;
 };
 
+// Compute units of the current device (256 if the query fails, as on a host
+// without one, so that forms and workspace sizes are the same there).
+int device_cus();
+
 // The forms of the chain forward call, the chunk-parallel ones first, and the one
 // that runs a search: the first that supports it, else one of the last two, which
 // go row after row and keep nothing but argmin entries (and packed tables).
@@ -102,6 +106,7 @@ bool seg_supported(int k, int n_last, int n_first);
 // header is read and no upload is needed).
 size_t seg_region_bytes(int n, int k, int batch);
 bool seg_edges_in_args(int n, int n_tables);
+int seg_chunks(int n, int batch);
 // The class form of the segment search (one launch, its own traceback).
 bool seg_class_supported(const cfp_segment_desc &d);
 size_t seg_class_bytes(int n, int batch);
@@ -126,6 +131,7 @@ size_t wave_region_bytes(int n, int k, int n_tables, int batch);
 hipError_t launch_chain_wave(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
                              uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
 bool chain_cw_supported(int n, int k, int batch);
+bool chain_cw_teams(int n, int k, int batch);
 // One-launch search of small chains (forward, range checks and traceback).
 constexpr int kSmallMaxN = 512;
 constexpr int kSmallMaxBatch = 256;
@@ -137,6 +143,7 @@ size_t cw_region_bytes(int n, int k, int n_tables, int batch);
 hipError_t launch_chain_cw(const cfp_chain_desc &d, int32_t *redge_dev, const EdgeMap &em, uint8_t *region,
                            uint8_t *table, SearchResult *res, int64_t *opt, int32_t *status, hipStream_t st);
 bool chain_fwd_split_supported(int k, int n_tables, int batch);
+bool chain_fwd_split_streams(int k, int n_tables, int batch);
 size_t split_region_bytes(int k, int batch);
 hipError_t launch_chain_fwd_split(const cfp_chain_desc &d, const int32_t *redge_dev, uint8_t *region, uint32_t *rpk,
                                   uint8_t *table, SearchResult *res, const WsHeader *hdr, int64_t *opt,

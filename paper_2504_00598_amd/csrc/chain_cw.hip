@@ -1129,20 +1129,6 @@ struct CwPlan {
   int S;  // workgroups per chunk and group of four searches: 1, or kXS for state-split teams
 };
 
-// Compute units of the current device (256 if the query fails, as on a host
-// without one, so that workspace sizes do not depend on it there).
-int cw_device_cus() {
-  static int cus = -1;
-  if (cus < 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-      n = 256;
-    cus = n;
-  }
-  return cus;
-}
-
 // Chunks of at least minrows rows, as many as `groups` groups of searches need
 // to fill `slots` workgroups.
 int cw_chunk_rows(int n, int groups, int slots, int minrows) {
@@ -1169,7 +1155,7 @@ CwPlan cw_plan(int n, int k, int batch, int period) {
   // 9.3 us per row of the wide kernel.
   // (Taken from 49 rows on, whatever the batch, 64 blocks, K = 400, 9 searches took
   // 789 us instead of 206.)
-  const int cus = cw_device_cus();
+  const int cus = device_cus();
   int CL;
   if (kp == 512 && groups <= kXMaxGroups && cus / (kXS * groups) >= 2) {
     if (n < 144) return none;
@@ -1244,6 +1230,8 @@ void launch_cx(const CwArgs &a, int groups, SearchResult *res, int64_t *opt, int
 }  // namespace
 
 bool chain_cw_supported(int n, int k, int batch) { return cw_plan(n, k, batch, 0).P >= 2; }
+
+bool chain_cw_teams(int n, int k, int batch) { return cw_plan(n, k, batch, 0).S > 1; }
 
 size_t cw_region_bytes(int n, int k, int n_tables, int batch) {
   const CwPlan c = cw_plan(n, k, batch, 0);  // no plan of these sizes has more chunks

@@ -406,20 +406,6 @@ __global__ __launch_bounds__(kSplitWThreads, 1) void chain_fwd_splitw_kernel(
 
 static int split_kp(int k) { return k <= 128 ? 128 : k <= 256 ? 256 : 512; }
 
-// The workgroups of every search of one launch must be resident together:
-// at most one per compute unit, with the tables held in registers.
-static int device_cus() {
-  static int cus = -1;
-  if (cus < 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      n = 0;
-    cus = n;
-  }
-  return cus;
-}
-
 // Which split form fits: 1 = tables in registers, 2 = streamed slices, 0 = none.
 static int split_form(int k, int n_tables, int batch) {
   if (k <= 64 || k > 512) return 0;
@@ -432,6 +418,8 @@ static int split_form(int k, int n_tables, int batch) {
 // The workgroups of every search of one launch must be resident together:
 // at most one per compute unit.
 bool chain_fwd_split_supported(int k, int n_tables, int batch) { return split_form(k, n_tables, batch) != 0; }
+
+bool chain_fwd_split_streams(int k, int n_tables, int batch) { return split_form(k, n_tables, batch) == 2; }
 
 size_t split_region_bytes(int k, int batch) {
   const size_t kp = split_kp(k);

@@ -683,6 +683,8 @@ size_t seg_region_bytes(int n, int k, int batch) {
   return off;
 }
 
+int seg_chunks(int n, int batch) { return seg_plan(n, batch).P; }
+
 bool seg_edges_in_args(int n, int n_tables) { return n <= kSegArgN && n_tables <= 65536; }
 
 hipError_t launch_seg_fwd(const cfp_segment_desc &d, const int32_t *redge_dev, uint8_t *table, uint8_t *region,

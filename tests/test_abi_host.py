@@ -36,6 +36,29 @@ def test_only_the_abi_is_exported():
     assert names == set(L.EXPORTED)
 
 
+def test_forms_follow_the_sizes():
+    """The form a call runs, on both sides of the lines between them (256 compute units)."""
+    f = {v: k[9:] for k, v in vars(L).items() if k.startswith("CFP_FORM_")}
+    chain = lambda *a: f.get(L.cfp_chain_form(*a))  # noqa: E731
+    assert [chain(1152, 27, 32, 12), chain(1, 32, 1, 38), chain(60, 16, 3, 160)] == ["NARROW", "NARROW", "ROWS"]
+    assert [chain(84, 64, 3, 12), chain(96, 64, 3, 12), chain(1, 40, 1, 13)] == ["ROWS", "WAVE", "WAVE"]
+    assert [chain(33, 65, 4, 12), chain(32, 65, 64, 12), chain(32, 65, 65, 12), chain(32, 65, 4, 13),
+            chain(32, 65, 129, 12)] == ["CHUNKS", "SPLIT", "SPLIT_STREAM", "SPLIT_STREAM", "ROWS"]
+    assert [chain(32, 256, 16, 12), chain(32, 256, 64, 12), chain(32, 256, 65, 12), chain(32, 256, 257, 12),
+            chain(15, 256, 257, 12)] == ["SPLIT", "SPLIT_STREAM", "ROWS", "CHUNKS", "ROWS"]
+    assert [chain(143, 300, 4, 12), chain(143, 300, 8, 12), chain(144, 300, 8, 12)] == ["SPLIT", "SPLIT_STREAM", "TEAMS"]
+    assert [chain(351, 300, 32, 12), chain(352, 300, 32, 12), chain(127, 512, 33, 12),
+            chain(128, 512, 33, 12)] == ["SPLIT_STREAM", "CHUNKS", "ROWS", "CHUNKS"]
+    seg = lambda *a: f.get(L.cfp_segment_form(*a))  # noqa: E731
+    assert [seg(96, 81, 256, 2, 3, 3), seg(96, 81, 768, 2, 3, 3), seg(96, 81, 769, 2, 3, 3)] == [
+        "SEG_CLASS", "SEG_CLASS", "SEG_ROWS"]
+    assert [seg(64, 512, 3, 2, 2, 2), seg(65, 512, 3, 2, 2, 2), seg(1600, 9, 3, 2, 3, 3)] == [
+        "SEG_CLASS", "SEG_CHUNKS", "SEG_CHUNKS"]
+    assert [chain(0, 4, 1, 1), chain(4, 513, 1, 1), chain(4, 4, 0, 1), chain(4, 4, 1, 0)] == [None] * 4
+    assert [seg(4, 513, 1, 1, 3, 3), seg(4, 9, 1, 1, 9, 3), seg(4, 9, 1, 1, 3, 0), seg(2 ** 28, 8, 1, 1, 3, 3)] == [None] * 4
+    assert L.lib().cfp_chain_form(None) == 0 and L.lib().cfp_segment_form(None) == 0
+
+
 def test_r_limit_values():
     # packed (value, index) words: b = max(4, ceil(log2 K)) index bits
     assert L.cfp_r_limit(L.CFP_V_CHAIN, 16) == 2 ** 26
