@@ -34,6 +34,12 @@ def say(*args):
     sys.stdout.flush()
 
 
+def assert_form(form, N, K, B, E):
+    """A chain search of these sizes runs the kernels the test is about (a CFP_FORM_* name)."""
+    from paper_2504_00598_amd import _lib as L
+    assert L.cfp_chain_form(N, K, B, E) == getattr(L, "CFP_FORM_" + form), (form, N, K, B, E)
+
+
 def run_chain(cost, rtab, redge):
     import torch
     from paper_2504_00598_amd import search

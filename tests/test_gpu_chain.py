@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from oracle import oracle as O
-from tests.gpu_util import assert_chain_parity, dev, need_gpu, oracle_threads, run_chain, say
+from tests.gpu_util import assert_chain_parity, assert_form, dev, need_gpu, oracle_threads, run_chain, say
 from workloads import configs, gen
 
 pytestmark = pytest.mark.gpu
@@ -140,11 +140,14 @@ def test_traceback_lds_and_memory_paths(N, K, B):
 # The chunk-parallel paths check the range of R while packing it (the other
 # paths in a separate pass): an entry at cfp_r_limit or below 0 marks every
 # search of the call as bad input.
-@pytest.mark.parametrize("N,K,B,bad", [(400, 64, 70, "limit"), (400, 64, 70, "negative"),
-                                       (200, 256, 9, "limit"), (200, 256, 9, "negative"),
-                                       (20, 16, 3, "limit")])
-def test_resharding_range_checked_on_every_path(N, K, B, bad):
+@pytest.mark.parametrize("N,K,B,bad,form", [
+    (400, 64, 70, "limit", "WAVE"), (400, 64, 70, "negative", "WAVE"), (200, 256, 9, "limit", "CHUNKS"),
+    (200, 256, 9, "negative", "CHUNKS"), (20, 16, 3, "limit", "NARROW"), (200, 300, 3, "negative", "TEAMS"),
+    (30, 100, 3, "limit", "SPLIT"), (30, 100, 70, "negative", "SPLIT_STREAM"), (30, 100, 130, "limit", "ROWS"),
+    (30, 64, 3, "negative", "ROWS")])
+def test_resharding_range_checked_on_every_path(N, K, B, bad, form):
     need_gpu()
+    assert_form(form, N, K, B, 12)
     from paper_2504_00598_amd import CFP_ST_BADINPUT, cfp_r_limit
     say("R range", N, K, B, bad)
     cost, rtab, redge = rand_case([48, N, K], B, N, K, 12, 0, 1000)
@@ -156,35 +159,48 @@ def test_resharding_range_checked_on_every_path(N, K, B, bad):
     assert (st == CFP_ST_BADINPUT).all() and (opt == np.iinfo(np.int64).max).all() and (plan == -1).all()
 
 
-# K > 64 runs on one of two kernels: the split kernel (each search over P = K_P^2 / 4096
-# workgroups, K_P the padded K, tables in registers) when all B * P workgroups fit the
-# device's 256 compute units and there are at most 12 tables, else the wide kernel (one
-# workgroup per search streaming its tables).  Both must give the oracle's answer.
+# Chains of K > 64 too short to be cut into chunks (up to 32 rows of K <= 256, and those of
+# K > 256 that take less time row after row) run on three kernels.  Two split a search over
+# several workgroups that must all fit the device's 256 compute units: K_P^2 / 4096 of them
+# with the tables in registers (K_P the padded K, at most 12 tables), or K_P / 64 that stream
+# the tables.  The third is the wide kernel, one workgroup per search.
 
-@pytest.mark.parametrize("K,B", [(100, 65), (200, 17), (300, 5), (512, 5)])
-def test_wide_path_batches(K, B):
-    """Batches too large for the split kernel: the wide kernel."""
+@pytest.mark.parametrize("N,K,B,E", [(30, 100, 129, 12), (32, 65, 300, 12), (32, 128, 140, 12), (1, 100, 200, 3),
+                                     (31, 200, 65, 12), (15, 256, 300, 12), (2, 130, 90, 17), (40, 300, 33, 12),
+                                     (127, 512, 40, 12), (9, 257, 50, 17)])
+def test_wide_path_batches(N, K, B, E):
+    """Batches too large for the split kernels: the wide kernel."""
     need_gpu()
     from paper_2504_00598_amd import cfp_r_limit
-    say("wide path", K, B)
+    assert_form("ROWS", N, K, B, E)
+    say("wide path", N, K, B)
     rhi = min(10_000_000, cfp_r_limit(0, K))
-    cost, rtab, redge = rand_case([3, K, B], B, 40, K, 12, 10_000, 10_000_000, rlo=10_000, rhi=rhi)
-    assert_chain_parity(cost, rtab, redge, f"wide K={K} B={B}")
+    cost, rtab, redge = rand_case([3, K, B], B, N, K, E, 10_000, 10_000_000, rlo=10_000, rhi=rhi)
+    assert_chain_parity(cost, rtab, redge, f"wide N={N} K={K} B={B}")
 
 
-def test_wide_path_many_tables():
-    """More than 12 tables: the wide kernel even for a single search."""
-    need_gpu()
-    cost, rtab, redge = rand_case([4], 2, 60, 150, 17, 0, 10**6)
-    assert_chain_parity(cost, rtab, redge, "wide E=17")
-
-
-@pytest.mark.parametrize("N,K,B", [(300, 65, 4), (500, 128, 60), (31, 256, 16), (120, 257, 4), (127, 512, 4)])
-def test_split_path_long_chains(N, K, B):
-    """Few chains spread over many workgroups (B * P = 256 at the largest); the
-    chains with K > 128 are too short for the chunk-parallel form."""
+@pytest.mark.parametrize("N,K,B,E", [(32, 65, 65, 12), (32, 128, 128, 12), (20, 100, 2, 17), (2, 100, 5, 13),
+                                     (30, 200, 17, 12), (32, 256, 64, 12), (31, 150, 2, 17), (40, 300, 5, 12),
+                                     (143, 512, 8, 12), (351, 400, 32, 12), (60, 257, 1, 17)])
+def test_split_path_streamed_tables(N, K, B, E):
+    """Batches or tables too many for the registers: slices of the tables streamed."""
     need_gpu()
     from paper_2504_00598_amd import cfp_r_limit
+    assert_form("SPLIT_STREAM", N, K, B, E)
+    say("split path, streamed", N, K, B, E)
+    rhi = min(1_000_000, cfp_r_limit(0, K))
+    cost, rtab, redge = rand_case([6, N, K, B], B, N, K, E, 10_000, 1_000_000, rlo=10_000, rhi=rhi, inf_frac=0.02)
+    assert_chain_parity(cost, rtab, redge, f"split, streamed N={N} K={K} B={B} E={E}")
+
+
+@pytest.mark.parametrize("N,K,B", [(32, 65, 4), (30, 128, 64), (2, 100, 3), (31, 256, 16), (17, 130, 5), (120, 257, 4),
+                                   (127, 512, 4), (143, 400, 3)])
+def test_split_path_long_chains(N, K, B):
+    """Few chains spread over many workgroups (B * P = 256 at the largest), of up to the
+    most rows that go row after row."""
+    need_gpu()
+    from paper_2504_00598_amd import cfp_r_limit
+    assert_form("SPLIT", N, K, B, 12)
     say("split path", N, K, B)
     rhi = min(1_000_000, cfp_r_limit(0, K))
     cost, rtab, redge = rand_case([5, N, K, B], B, N, K, 12, 10_000, 1_000_000, rlo=10_000, rhi=rhi)
@@ -195,14 +211,15 @@ def test_long_chain_workload():
     """The 4096-block K=512 workload of the scan through the chain search (64
     chunks of 64 rows)."""
     need_gpu()
+    assert_form("TEAMS", 4096, 512, 4, 12)
     say("config scan_n4096_k512 through cfp_dp_chain")
     d = configs.make("scan_n4096_k512")
     assert_chain_parity(d["cost"], d["rtab"], d["redge"], "long chain K=512")
 
 
-# 32 < K <= 64 on long chains (at least 8 blocks of 12 rows) with at most 12 tables runs
-# chunk-parallel: the chains are cut into chunks that are searched concurrently from
-# arbitrary start rows and then repaired until their rows meet the speculative ones; a
+# 32 < K <= 64 on long chains (at least 8 blocks of 12 rows), and with more than 12 tables on
+# any, runs chunk-parallel: the chains are cut into chunks that are searched concurrently
+# from arbitrary start rows and then repaired until their rows meet the speculative ones; a
 # chain whose rows never meet is finished sequentially.  Whatever happens inside, the
 # answer must be the oracle's.
 
@@ -254,6 +271,7 @@ def test_chunked_shapes(N, K, B):
     blocks, K below 64 and chunk counts from 2 to 64."""
     need_gpu()
     from paper_2504_00598_amd import cfp_r_limit
+    assert_form("WAVE", N, K, B, 12)
     rhi = min(10_000_000, cfp_r_limit(0, K))
     cost, rtab, redge = rand_case([42, N, K, B], B, N, K, 12, 10_000, 10_000_000, rlo=10_000, rhi=rhi)
     if N % 2:
@@ -275,16 +293,17 @@ def test_chunked_ties_and_statuses():
     assert st[5] != 0 and (st[np.r_[0:5, 6:9, 10:70]] == 0).all()
 
 
-# 128 < K <= 256 on long chains (at least 32 blocks) runs chunk-parallel as well, with two
-# chains per workgroup sharing each streamed table word.  Same requirement: the oracle's
-# answer whatever the rows do.
+# 128 < K <= 256 on chains of more than 32 blocks runs chunk-parallel as well, with two or
+# four chains per workgroup sharing each streamed table word.  Same requirement: the
+# oracle's answer whatever the rows do.
 
-@pytest.mark.parametrize("N,K,B", [(32, 256, 1), (33, 129, 2), (100, 200, 3), (513, 256, 64), (1000, 255, 5),
+@pytest.mark.parametrize("N,K,B", [(36, 256, 1), (33, 129, 2), (100, 200, 3), (513, 256, 64), (1000, 255, 5),
                                    (257, 160, 64), (64, 256, 129), (81, 256, 2)])
 def test_chunked_wide_shapes(N, K, B):
     """Ragged batches (an odd last search), ragged last chunks, K below 256, one-row chunks."""
     need_gpu()
     from paper_2504_00598_amd import cfp_r_limit
+    assert_form("CHUNKS", N, K, B, 12)
     rhi = min(10_000_000, cfp_r_limit(0, K))
     cost, rtab, redge = rand_case([44, N, K, B], B, N, K, 12, 10_000, 10_000_000, rlo=10_000, rhi=rhi)
     if N % 2:
@@ -426,19 +445,20 @@ def test_range_flag_ignores_stale_workspace_bytes():
         np.testing.assert_array_equal(r.plan.cpu().numpy(), o_plan, err_msg=f"plan, stale word {v}")
 
 
-# 256 < K <= 512 on chains of at least 128 blocks runs chunk-parallel with chunks of at
-# least 64 rows (runs take tens of rows to become parallel at this width).  The final
-# pass reruns, whole, each chunk that follows one whose fix-up met no checkpoint.
-# Batches of at most 8 searches run in state-split teams (four workgroups per chunk,
-# rows exchanged every step); larger batches carry four searches per workgroup.
+# 256 < K <= 512 runs chunk-parallel with chunks of at least 48 rows (runs take tens of
+# rows to become parallel at this width): batches of at most 8 searches from 144 blocks on
+# in state-split teams (four workgroups per chunk, rows exchanged every step), larger ones
+# with two or four searches per workgroup from 352 blocks on, or 128 if no split kernel
+# takes them.  The final pass reruns, whole, each chunk whose start row was not the true one.
 
-@pytest.mark.parametrize("N,K,B", [(128, 512, 1), (300, 400, 5), (1000, 512, 3), (640, 300, 8), (129, 257, 2),
-                                   (4096, 512, 1), (700, 512, 12), (300, 300, 9), (1200, 511, 7)])
+@pytest.mark.parametrize("N,K,B", [(144, 512, 1), (300, 400, 5), (1000, 512, 3), (640, 300, 8), (145, 257, 2),
+                                   (4096, 512, 1), (700, 512, 12), (352, 300, 9), (1200, 511, 7), (130, 260, 50)])
 def test_chunked_k512_shapes(N, K, B):
-    """Two chunks of 64 rows, ragged K and batches, ragged last chunks, 64 chunks;
-    teams of one and two groups of searches, and four searches per workgroup."""
+    """Three chunks of 48 rows, ragged K and batches, ragged last chunks, 64 chunks;
+    teams of one and two groups of searches, and several searches per workgroup."""
     need_gpu()
     from paper_2504_00598_amd import cfp_r_limit
+    assert_form("TEAMS" if B <= 8 else "CHUNKS", N, K, B, 12)
     rhi = min(1_000_000, cfp_r_limit(0, K))
     cost, rtab, redge = rand_case([48, N, K, B], B, N, K, 12, 10_000, 1_000_000, rlo=10_000, rhi=rhi)
     if N % 2 == 0:
@@ -447,12 +467,13 @@ def test_chunked_k512_shapes(N, K, B):
     assert_chain_parity(cost, rtab, redge, f"chunked K>256 N={N} K={K} B={B}")
 
 
-@pytest.mark.parametrize("N,K,B", [(1089, 512, 1), (1090, 400, 5), (1091, 512, 3)])
+@pytest.mark.parametrize("N,K,B", [(1105, 512, 1), (1106, 400, 5), (1107, 512, 3)])
 def test_chunked_k512_short_last_chunk(N, K, B):
-    """17 chunks of 68 rows and a last chunk of 1, 2 or 3 rows (a run of one
+    """23 chunks of 48 rows and a last chunk of 1, 2 or 3 rows (a run of one
     row is its own checkpoint), in state-split teams of one and two groups."""
     need_gpu()
     from paper_2504_00598_amd import cfp_r_limit
+    assert_form("TEAMS", N, K, B, 12)
     rhi = min(1_000_000, cfp_r_limit(0, K))
     cost, rtab, redge = rand_case([52, N, K, B], B, N, K, 12, 10_000, 1_000_000, rlo=10_000, rhi=rhi)
     say("chunked K>256, short last chunk", N, K, B)
@@ -466,6 +487,7 @@ def test_chunked_k512_rows_never_meet(K, B):
     from paper_2504_00598_amd import cfp_r_limit
     rs = np.random.default_rng([49, K, B])
     N = 400
+    assert_form("TEAMS", N, K, B, 12)
     cost = rs.integers(0, 50, size=(B, N, K)).astype(np.int32)
     rtab = _no_switch_tables(rs, 12, K, cfp_r_limit(0, K))
     redge = (np.arange(N) % 12).astype(np.int32)
@@ -542,6 +564,7 @@ def test_chunked_many_tables(N, K, B, E):
     """More tables than the register-resident kernel holds: chains of one chunk and of
     several, four and sixteen searches per workgroup, ragged batches and blocks."""
     need_gpu()
+    assert_form("WAVE", N, K, B, E)
     cost, rtab, redge = rand_case([60, N, K, B, E], B, N, K, E, 0, 1_000_000, inf_frac=0.05)
     say("chunked, many tables", N, K, B, E)
     assert_chain_parity(cost, rtab, redge, f"many tables N={N} K={K} B={B} E={E}")
@@ -595,6 +618,7 @@ def test_narrow_shapes(N, K, B, E, edges):
     (38 at K > 16), four and sixteen waves per workgroup, edge maps in memory and in the
     arguments."""
     need_gpu()
+    assert_form("ROWS" if (K, E) == (20, 39) else "NARROW", N, K, B, E)
     cost, rtab, redge = rand_case([62, N, K, B, E], B, N, K, E, 0, 1_000_000, inf_frac=0.05)
     if edges == "periodic":
         redge = (np.arange(N) % E).astype(np.int32)
@@ -685,15 +709,16 @@ def test_narrow_ties_and_statuses(N, K):
     assert (st == CFP_ST_BADINPUT).all() and (plan == -1).all()
 
 
-# 64 < K <= 128 runs chunk-parallel like the wider searches. The second fix-up reruns the
-# chunks behind an isolated one that met no checkpoint; longer runs of such chunks are left
-# to the final pass.
+# 64 < K <= 128 runs chunk-parallel like the wider searches, on chains of more than 32 blocks.
+# The second fix-up reruns every chunk behind one that met no checkpoint, from that one's end
+# row; what still started from a wrong row then is left to the final pass.
 
 @pytest.mark.parametrize("N,K,B,E", [(33, 65, 1, 1), (36, 128, 5, 3), (63, 128, 2, 12), (97, 100, 9, 40),
                                      (100, 127, 130, 12), (1001, 81, 3, 16), (2100, 66, 2, 12)])
 def test_chunked_mid_shapes(N, K, B, E):
     """Ragged batches and last chunks, K up to 128, any number of tables."""
     need_gpu()
+    assert_form("CHUNKS", N, K, B, E)
     cost, rtab, redge = rand_case([70, N, K, B], B, N, K, E, 0, 1_000_000, inf_frac=0.05)
     if N % 2:
         redge = (np.arange(N) % E).astype(np.int32)
@@ -706,9 +731,11 @@ def test_chunked_mid_shapes(N, K, B, E):
 @pytest.mark.parametrize("share", [0.0, 0.5, 0.8])
 def test_chunked_patterns_of_unmet_chunks(K, B, N, share):
     """Zero tables near the start of a share of the chunks: isolated chunks that meet no
-    checkpoint, runs of them, and (share 0) none that meets, on every form for K > 64."""
+    checkpoint, runs of them, and (share 0) none that meets, on every chunk-parallel form
+    for K > 64."""
     need_gpu()
     from paper_2504_00598_amd import cfp_r_limit
+    assert_form("TEAMS" if (K, B) == (400, 3) else "CHUNKS", N, K, B, 3)
     rs = np.random.default_rng([71, K, B, int(10 * share)])
     cost = rs.integers(0, 1000, size=(B, N, K)).astype(np.int32)
     rtab = _no_switch_tables(rs, 3, K, cfp_r_limit(0, K))

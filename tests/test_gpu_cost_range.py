@@ -6,10 +6,11 @@ draw costs uniformly from [0, 2^31 - 1) and put 0 and 2^31 - 2 into every
 cost row, so that states far above a row's minimum (where the kernels cap
 their normalised values) are reached by finite costs and not only by
 unavailable strategies and padding.  Each shape is chosen to land on one
-kernel family of the chain search (register-resident K <= 32 and K <= 64,
-chunk-parallel K <= 64, K <= 256 and K <= 512, split, split with streamed tables, wide,
-the generic kernel for many tables), and the memory, frontier, scan and
-segment entry points get the same treatment.  The bar is the oracle's answer
+kernel family of the chain search (K <= 32 with tables in LDS, register-resident
+K <= 64, chunk-parallel K <= 64, K <= 256 and K <= 512, state-split teams, split, split
+with streamed tables, wide, the generic kernel for more tables than LDS holds), which
+is checked, and the memory, frontier, scan and segment entry points get the same
+treatment.  The bar is the oracle's answer
 bit for bit: optimum, status and every plan entry (Sec. 4.4, Eq. T and Eq. M).
 """
 from __future__ import annotations
@@ -18,8 +19,8 @@ import numpy as np
 import pytest
 
 from oracle import oracle as O
-from tests.gpu_util import (assert_chain_parity, assert_frontier_parity, assert_mem_parity, assert_scan_parity,
-                            dev, need_gpu, oracle_threads, run_scan, say)
+from tests.gpu_util import (assert_chain_parity, assert_form, assert_frontier_parity, assert_mem_parity,
+                            assert_scan_parity, dev, need_gpu, oracle_threads, run_scan, say)
 from workloads import gen
 
 pytestmark = pytest.mark.gpu
@@ -48,30 +49,39 @@ def wide_tables(rs, E, K, limit, zero_diag=False):
     return rtab
 
 
-# (N, K, B, E, periodic edge map, kernel family the shape lands on)
+# (N, K, B, E, periodic edge map, form, kernel family the shape lands on)
 CHAIN_CASES = [
-    (50, 16, 3, 5, False, "register-resident K<=16"),
-    (60, 32, 3, 12, True, "register-resident K<=32"),
-    (40, 64, 3, 12, False, "register-resident K<=64, short chain"),
-    (400, 64, 70, 12, True, "chunk-parallel K<=64, periodic tables (headerless)"),
-    (300, 48, 20, 12, False, "chunk-parallel K<=64"),
-    (200, 256, 9, 12, True, "chunk-parallel K<=256"),
-    (100, 200, 3, 5, False, "chunk-parallel K<=256, ragged K"),
-    (200, 512, 4, 12, True, "chunk-parallel K<=512, state-split teams"),
-    (130, 300, 3, 7, False, "chunk-parallel K<=512, ragged K, state-split teams"),
-    (200, 400, 12, 12, False, "chunk-parallel K<=512, four searches per workgroup"),
-    (100, 100, 4, 12, False, "split, tables in registers"),
-    (30, 512, 2, 12, False, "split K=512"),
-    (60, 100, 8, 17, False, "split, streamed tables"),
-    (20, 100, 130, 3, False, "wide"),
-    (50, 40, 3, 13, False, "generic K<=64, more than 12 tables"),
+    (50, 16, 3, 5, False, "NARROW", "tables in LDS, K<=16"),
+    (60, 32, 3, 12, True, "NARROW", "tables in LDS, K<=32"),
+    (40, 64, 3, 12, False, "ROWS", "register-resident K<=64, short chain"),
+    (400, 64, 70, 12, True, "WAVE", "chunk-parallel K<=64, periodic tables (headerless)"),
+    (300, 48, 20, 12, False, "WAVE", "chunk-parallel K<=64"),
+    (50, 40, 3, 13, False, "WAVE", "one chunk K<=64, more than 12 tables"),
+    (100, 100, 4, 12, False, "CHUNKS", "chunk-parallel K<=128"),
+    (60, 100, 8, 17, False, "CHUNKS", "chunk-parallel K<=128, two chunks, more than 12 tables"),
+    (200, 256, 9, 12, True, "CHUNKS", "chunk-parallel K<=256"),
+    (100, 200, 3, 5, False, "CHUNKS", "chunk-parallel K<=256, ragged K"),
+    (200, 512, 4, 12, True, "TEAMS", "chunk-parallel K<=512, state-split teams"),
+    (150, 300, 3, 7, False, "TEAMS", "chunk-parallel K<=512, ragged K, state-split teams"),
+    (360, 400, 12, 12, False, "CHUNKS", "chunk-parallel K<=512, several searches per workgroup"),
+    (30, 100, 4, 12, False, "SPLIT", "split, tables in registers"),
+    (130, 300, 3, 7, False, "SPLIT", "split, tables in registers, ragged K"),
+    (30, 512, 2, 12, False, "SPLIT", "split K=512"),
+    (30, 100, 8, 17, False, "SPLIT_STREAM", "split, streamed tables"),
+    (200, 400, 12, 12, False, "SPLIT_STREAM", "split, streamed tables, K<=512"),
+    (20, 100, 130, 3, False, "ROWS", "wide"),
+    (15, 200, 66, 3, False, "ROWS", "wide K<=256"),
+    (20, 300, 34, 3, False, "ROWS", "wide K<=512"),
+    (50, 12, 3, 160, False, "ROWS", "generic K<=16"),
+    (50, 30, 3, 40, False, "ROWS", "generic K<=32"),
 ]
 
 
-@pytest.mark.parametrize("N,K,B,E,periodic,family", CHAIN_CASES, ids=[c[5] for c in CHAIN_CASES])
+@pytest.mark.parametrize("N,K,B,E,periodic,form,family", CHAIN_CASES, ids=[c[6] for c in CHAIN_CASES])
 @pytest.mark.parametrize("rvals", ["full", "small"])
-def test_chain_full_int32_costs(N, K, B, E, periodic, family, rvals):
+def test_chain_full_int32_costs(N, K, B, E, periodic, form, family, rvals):
     need_gpu()
+    assert_form(form, N, K, B, E)
     from paper_2504_00598_amd import cfp_r_limit
     say("cost range chain", family, N, K, B, E, rvals)
     rs = np.random.default_rng([70, N, K, B, E, rvals == "full"])
@@ -166,14 +176,17 @@ def test_mem_full_int32_costs(K, M):
     assert_frontier_parity(cost, rtab, redge, mem, M, f"frontier K={K}")
 
 
-def test_segments_full_int32_costs():
+@pytest.mark.parametrize("B,N,form", [(5, 80, "SEG_CLASS"), (5, 1500, "SEG_CHUNKS"), (800, 40, "SEG_ROWS")])
+def test_segments_full_int32_costs(B, N, form):
     need_gpu()
     import torch
+    from paper_2504_00598_amd import _lib as L
     from paper_2504_00598_amd import cfp_r_limit, search
     from oracle import oracle as OR
-    say("cost range segments")
+    say("cost range segments", form)
     rs = np.random.default_rng(74)
-    B, N, K, Lc, Fc, E = 5, 80, 81, 3, 3, 2
+    K, Lc, Fc, E = 81, 3, 3, 2
+    assert L.cfp_segment_form(N, K, B, E, Lc, Fc) == getattr(L, "CFP_FORM_" + form)
     cost = wide_costs(rs, B, N, K, inf_frac=0.02)
     rbound = rs.integers(0, cfp_r_limit(3, K), size=(E, Lc, Fc), dtype=np.int64).astype(np.int32)
     last = (np.arange(K) // 27).astype(np.uint8)
