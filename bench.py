@@ -74,17 +74,17 @@ COMMON_SOURCES = ["common.h", "cfp_internal.h", "../../include/cfp.h"]
 # changed and the figure is withheld.
 FETCH_SCALE, WRITE_SCALE = 524288.0 / 262166.9, 524288.0 / 524288.0
 TRAFFIC = {
-    "chain_gpt_n24_k16": {"fetch_kib": 12.7, "write_kib": 0.2, "sources": "52818aaa4e4934d4"},
-    "chain_gpt_n1152_k64": {"fetch_kib": 37976.1, "write_kib": 37516.8, "sources": "7611dbd3b031e2fb"},
-    "mem_llama_n288_k32": {"fetch_kib": 127247.8, "write_kib": 338789.8, "sources": "800a6f06f2b6bf9f"},
-    "chain_wide_n512_k256": {"fetch_kib": 45109.3, "write_kib": 16423.7, "sources": "fabd52fde0631d42"},
-    # mean over the 12 matrix-product launches of one forward call
-    "scan_n4096_k512": {"fetch_kib": 3034309.5, "write_kib": 1398442.5, "sources": "2746a9b212acf5ef"},
-    "seg_gpt_n96_k81": {"fetch_kib": 6338.9, "write_kib": 10137.1, "sources": "1d03d894fb522632"},
+    "chain_gpt_n24_k16": {"fetch_kib": 12.7, "write_kib": 0.2, "sources": "23e947f283582335"},
+    "chain_gpt_n1152_k64": {"fetch_kib": 37971.9, "write_kib": 37523.5, "sources": "f5e0cceff0824dc8"},
+    "mem_llama_n288_k32": {"fetch_kib": 121735.2, "write_kib": 338591.1, "sources": "03988ca230c02cf3"},
+    "chain_wide_n512_k256": {"fetch_kib": 45498.9, "write_kib": 16450.3, "sources": "c30606387f882b89"},
+    # mean over the 11 matrix-product launches of one forward call
+    "scan_n4096_k512": {"fetch_kib": 3301009.2, "write_kib": 1521105.3, "sources": "3b5b202461cc07d9"},
+    "seg_gpt_n96_k81": {"fetch_kib": 4005.3, "write_kib": 984.0, "sources": "d21b8296ed3f2b29"},
     # the memory workload run as a budget frontier (every chunk of every search active)
-    "mem_llama_n288_k32:frontier": {"fetch_kib": 166120.7, "write_kib": 442222.8, "sources": "800a6f06f2b6bf9f"},
+    "mem_llama_n288_k32:frontier": {"fetch_kib": 158395.8, "write_kib": 441977.8, "sources": "03988ca230c02cf3"},
     # the scan workload through the chain search (speculative pass)
-    "scan_n4096_k512:chain": {"fetch_kib": 290919.0, "write_kib": 89986.2, "sources": "fabd52fde0631d42"},
+    "scan_n4096_k512:chain": {"fetch_kib": 292692.2, "write_kib": 89984.0, "sources": "c30606387f882b89"},
 }
 
 

@@ -148,7 +148,9 @@ int cfp_dp_chain(const cfp_chain_desc *d, void *ws, size_t ws_bytes, int64_t *op
  * the exact optimum (CFP_ST_OVERFLOW is not reachable).  The buckets of a
  * search are cut into chunks of 64 that run as a pipeline of workgroups;
  * searches are launched in rounds small enough that every chunk of a round
- * is resident at once.  A chunk that waits too long for the chunk below it
+ * is resident at once.  (A search's chunks share one of the device's eight
+ * dies, which holds 32 of them for K > 48: there n_mem > 2048 returns
+ * CFP_ERR_HIP.)  A chunk that waits too long for the chunk below it
  * (which cannot happen when the GPU is not shared) ends its search with
  * CFP_ST_TIMEOUT.  ws must hold cfp_workspace_bytes(d, CFP_V_MEM, n_mem)
  * bytes. */

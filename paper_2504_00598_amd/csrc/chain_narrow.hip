@@ -18,7 +18,8 @@
 // searches in a thousand), which the second fix-up resolves for three in four;
 // where resharding dominates, no chunk meets and the final pass runs the chain.
 // There one chunk takes all lanes of a wave (narrow_solo).  Per call with its
-// traceback, 1152 blocks, K = 27, 32 searches: 52 us on costs of their own; 48 to 55
+// traceback, 1152 blocks, K = 27, 32 searches, through the Python binding one after
+// another (40 us of 52 on the device): 52 us on costs of their own; 48 to 55
 // on repeated ones, 66 where a search leaves its chunks unmet (366 when the final
 // pass reran them with one of two half-wave tasks and without a second fix-up); 95
 // with resharding 30 times the costs (187); 265 where no chunk ever meets (367; a
@@ -650,8 +651,8 @@ size_t narrow_lds(int k, int e) {
 }
 
 // Least rows per chunk: rows on uniform costs become parallel after 6 (K = 8)
-// to 9 (K = 27) rows on average and under 30 at most, and a chunk shorter than
-// that would have to be rerun in turn.
+// to 9 (K = 27) rows on average and under 30 at most; shorter chunks would leave
+// more of them unmet, for the second fix-up and the final pass to rerun.
 int narrow_min_rows(int k) { return k <= 16 ? 24 : 32; }
 
 struct NarrowPlan {
